@@ -123,7 +123,8 @@ cbinfer_state *cbinfer_create(const cbinfer_network *net, float threshold);
  * Errors (NULL returned, message in cbinfer_last_error): everything cbinfer_create rejects;
  * CBINFER_ENOMEM if the network needs more than CBINFER_STATIC_WORKSPACE_BYTES
  * (cbinfer_workspace_bytes tells how much it needs; the 320x240 scene-labeling network fits, the
- * 1280x720 and 64-stream workloads do not); CBINFER_ESTATE while another state created by this
+ * 1280x720 and 64-stream workloads do not; a network a little too large runs with half or a quarter
+ * of the workgroups per launch, whose partial sums then take that much less); CBINFER_ESTATE while another state created by this
  * call is still alive on the same device: there is one array per device, so at most one such
  * state per device may exist at a time, and two processes' worth of frames must not be
  * interleaved through it.  The array keeps the previous state's contents; this call clears the

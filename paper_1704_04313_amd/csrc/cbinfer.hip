@@ -68,7 +68,7 @@ struct Plan {
     size_t set_bytes = 0;      // its size; with `pipeline` a second set follows directly behind it
     size_t o_flags = 0;        // the byte change maps of all layers behind the first, contiguous
     long long flag_words = 0;  // their total size in 64-bit words
-    int compute_units = 256; // sizes the GEMM grids; the device's count replaces it in cbinfer_create
+    int compute_units = 256; // sizes the GEMM grids; the device's count replaces it in cbinfer_create if that is smaller
     int iota_len = 0;
     size_t bytes = 0;
 };
@@ -83,9 +83,21 @@ struct Carver {
     }
 };
 
-// Validates the description and lays out the workspace.  Touches no device.
-int make_plan(const cbinfer_network *net, float threshold, bool need_threshold, Plan &P)
+// Workgroups of op's multiplication on a device of that many compute units.
+int gemm_grid_of(const Op &op, int streams, int dtype, int compute_units)
 {
+    cbk::GemmArgs a{};
+    a.dtype = dtype;
+    a.M = op.M; a.Mpad = op.Mpad; a.Kpad = op.Kpad;
+    a.max_pixels = streams * op.Ho * op.Wo;
+    return cbk::gemm_grid(a, compute_units);
+}
+
+// Validates the description and lays out the workspace for launches of at most max_grid workgroups.
+// Touches no device.
+int make_plan(const cbinfer_network *net, float threshold, bool need_threshold, Plan &P, int max_grid = kMaxGemmGrid)
+{
+    P.compute_units = max_grid;
     if (!net) return fail(CBINFER_EINVAL, "network description is NULL");
     if (net->n_layers <= 0 || !net->layers) return fail(CBINFER_EINVAL, "network has no layers");
     if (net->in_c <= 0 || net->in_h <= 0 || net->in_w <= 0)
@@ -197,7 +209,7 @@ int make_plan(const cbinfer_network *net, float threshold, bool need_threshold, 
             // or to run densely: their previous input is the stored output of the op before them.
             if (l == 0 || ((P.hold || op.dense) && !op.propagate)) op.o_ref = cv.take(in_px * op.pix_words * 4 + 16);
             if (l == 0 && P.hold) op.o_cur = cv.take(in_px * op.pix_words * 4 + 16);
-            op.o_wt = cv.take((size_t)op.Mpad * op.Kpad * esz);
+            op.o_wt = cv.take(cbk::gemm_filter_bytes(P.dtype, op.Mpad, op.Kpad));
             op.o_bias = cv.take((size_t)op.Mpad * 4);
             op.o_taps = cv.take((size_t)op.Kpad / eu * sizeof(int2));
         }
@@ -242,10 +254,11 @@ int make_plan(const cbinfer_network *net, float threshold, bool need_threshold, 
                         words_for((long long)P.S * op.Ho * op.Wo) <= cbk::gemm_select_max_words() &&
                         words_for((long long)P.S * op.H * op.W) <= cbk::gemm_select_max_words();
     {
-        // sized for the largest grid the GEMM may use (its cap), whatever the device turns out to be
+        // sized for the largest grid the GEMM may use, whatever the device turns out to be
         size_t pb = 0;
         for (const Op &op : P.ops)
-            if (op.kind == CBINFER_OP_CONV) pb = std::max(pb, cbk::gemm_partial_bytes(op.M, kMaxGemmGrid));
+            if (op.kind == CBINFER_OP_CONV)
+                pb = std::max(pb, cbk::gemm_partial_bytes(op.M, gemm_grid_of(op, P.S, P.dtype, max_grid)));
         P.o_partial = cv.take(pb);
         P.o_tickets = cv.take(cbk::gemm_ticket_bytes(kMaxGemmGrid));
     }
@@ -350,24 +363,67 @@ int collect_profile(cbinfer_state *s)
     return CBINFER_OK;
 }
 
-// Filter matrix K (Section 3) re-laid-out for the gather: row o, column k = (j*kw + i)*Cs + c,
-// as float32 or bfloat16 (round to nearest even) bytes.
+// The bfloat16 parts of n float32 weights, rounded to nearest even: the first alone (bfloat16 storage), or
+// three that add up to the weight exactly.  A finite weight next to the largest float32 must not round to
+// infinity then (its first part is cut off instead); of one that is not finite only the first part
+// is kept.  Without branches, for the sake of the compiler's vectors: a network has millions of weights.
+void bf16_parts(const float *x, int n, int parts, unsigned short *p0, unsigned short *p1, unsigned short *p2)
+{
+    auto bits = [](float f) { unsigned u; memcpy(&u, &f, 4); return u; };
+    auto value = [](unsigned u) { u <<= 16; float f; memcpy(&f, &u, 4); return f; };
+    auto rounded = [](unsigned u) { return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16; };
+    for (int i = 0; i < n; ++i) {
+        const unsigned u = bits(x[i]), a = u & 0x7fffffffu;
+        p0[i] = (unsigned short)(a > 0x7f800000u ? (u >> 16) | 0x0040u : rounded(u)); // NaN stays a (quiet) NaN
+    }
+    if (parts < 3) return;
+    for (int i = 0; i < n; ++i) {
+        const unsigned u = bits(x[i]), a = u & 0x7fffffffu, finite = a < 0x7f800000u ? ~0u : 0u;
+        const unsigned h = p0[i] - (finite & ((p0[i] & 0x7fffu) == 0x7f80u ? 1u : 0u));
+        const float r = x[i] - value(h);
+        const unsigned m = rounded(bits(r));
+        const float q = r - value(m);
+        p0[i] = (unsigned short)h;
+        p1[i] = (unsigned short)(m & finite);
+        p2[i] = (unsigned short)(rounded(bits(q)) & finite);
+    }
+}
+
+// Filter matrix K (Section 3) re-laid-out for the gather: row o, column k = (j*kw + i)*Cs + c, as
+// float32 or bfloat16 (round to nearest even), row by row or in fragments.
 void build_filter_matrix(const Op &op, int dtype, const float *w, std::vector<unsigned char> &bytes)
 {
-    std::vector<float> wt((size_t)op.Mpad * op.Kpad, 0.0f);
-    for (int o = 0; o < op.M; ++o)
+    bytes.assign(cbk::gemm_filter_bytes(dtype, op.Mpad, op.Kpad), 0);
+    const bool fragments = cbk::gemm_filter_in_fragments(dtype, op.Mpad, op.Kpad);
+    unsigned short *b = reinterpret_cast<unsigned short *>(bytes.data());
+    float *f = reinterpret_cast<float *>(bytes.data());
+    const int area = op.kh * op.kw, eu = cbk::elems_per_unit(dtype), parts = dtype == cbk::kF32 ? 3 : 1;
+    std::vector<float> row(op.Kpad, 0.0f);
+    std::vector<unsigned short> part((size_t)op.Kpad * 3, 0);
+    std::vector<size_t> place(fragments ? op.Kpad / eu : 0); // of a row's units, from where the row begins
+    for (size_t v = 0; v < place.size(); ++v)
+        place[v] = cbk::gemm_filter_fragment(dtype, op.Mpad, op.Kpad, 0, (int)v * eu);
+    for (int o = 0; o < op.M; ++o) {
         for (int c = 0; c < op.C; ++c)
-            for (int j = 0; j < op.kh; ++j)
-                for (int i = 0; i < op.kw; ++i)
-                    wt[(size_t)o * op.Kpad + (size_t)(j * op.kw + i) * op.Cs + c] =
-                        w[(((size_t)o * op.C + c) * op.kh + j) * op.kw + i];
-    if (dtype == cbk::kBF16) {
-        bytes.resize(wt.size() * 2);
-        unsigned short *b = reinterpret_cast<unsigned short *>(bytes.data());
-        for (size_t i = 0; i < wt.size(); ++i) b[i] = cbk::bf16_bits(wt[i]);
-    } else {
-        bytes.resize(wt.size() * 4);
-        memcpy(bytes.data(), wt.data(), bytes.size());
+            for (int t = 0; t < area; ++t) row[(size_t)t * op.Cs + c] = w[((size_t)o * op.C + c) * area + t];
+        if (!fragments && dtype == cbk::kF32) {
+            memcpy(f + (size_t)o * op.Kpad, row.data(), (size_t)op.Kpad * 4);
+            continue;
+        }
+        bf16_parts(row.data(), op.Kpad, fragments ? parts : 1, part.data(), part.data() + op.Kpad, part.data() + 2 * (size_t)op.Kpad);
+        if (!fragments) {
+            memcpy(b + (size_t)o * op.Kpad, part.data(), (size_t)op.Kpad * 2);
+            continue;
+        }
+        unsigned short *dst = b + cbk::gemm_filter_fragment(dtype, op.Mpad, op.Kpad, o, 0);
+        for (size_t v = 0; v < place.size(); ++v) // a unit's values stay together
+            for (int q = 0; q < parts; ++q) {
+                const unsigned short *src = part.data() + (size_t)q * op.Kpad + v * eu;
+                if (eu == 4)
+                    memcpy(dst + place[v] + q * cbk::kFilterPartStride, src, 8);
+                else
+                    memcpy(dst + place[v] + q * cbk::kFilterPartStride, src, 16);
+            }
     }
 }
 
@@ -729,16 +785,10 @@ static cbinfer_state *create_state(const cbinfer_network *net, const Plan &P, ch
         int dev = 0, cus = 0;
         if (hipGetDevice(&dev) == hipSuccess &&
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
-            s->plan.compute_units = cus < kMaxGemmGrid ? cus : kMaxGemmGrid;
+            s->plan.compute_units = cus < P.compute_units ? cus : P.compute_units;
     }
-    for (Op &op : s->plan.ops) {
-        if (op.kind != CBINFER_OP_CONV) continue;
-        cbk::GemmArgs a{};
-        a.dtype = P.dtype;
-        a.M = op.M; a.Mpad = op.Mpad; a.Kpad = op.Kpad;
-        a.max_pixels = P.S * op.Ho * op.Wo;
-        op.gemm_grid = cbk::gemm_grid(a, s->plan.compute_units);
-    }
+    for (Op &op : s->plan.ops)
+        if (op.kind == CBINFER_OP_CONV) op.gemm_grid = gemm_grid_of(op, P.S, P.dtype, s->plan.compute_units);
     s->prof_ms.assign(P.ops.size() * CBINFER_STEP_COUNT, 0.0);
     s->prof_n.assign(P.ops.size() * CBINFER_STEP_COUNT, 0);
 
@@ -831,6 +881,12 @@ cbinfer_state *cbinfer_create_static(const cbinfer_network *net, float threshold
 {
     Plan P;
     if (make_plan(net, threshold, true, P) != CBINFER_OK) return nullptr;
+    // Partial sums take 64 KiB to 128 KiB per workgroup, a third to a half of what fits: a network of large filter
+    // matrices runs with fewer workgroups rather than not at all.
+    for (int grid = kMaxGemmGrid / 2; P.bytes > (size_t)CBINFER_STATIC_WORKSPACE_BYTES && grid >= kMaxGemmGrid / 4; grid /= 2) {
+        Plan Q;
+        if (make_plan(net, threshold, true, Q, grid) == CBINFER_OK && Q.bytes <= (size_t)CBINFER_STATIC_WORKSPACE_BYTES) P = Q;
+    }
     if (P.bytes > (size_t)CBINFER_STATIC_WORKSPACE_BYTES) {
         fail(CBINFER_ENOMEM,
              "this network needs %zu bytes of state and scratch; the static workspace holds %zu "

@@ -182,7 +182,8 @@ hipError_t compact(hipStream_t st, const CompactJob *jobs, int njobs, bool group
 struct GemmArgs {
     int dtype;          // kF32 or kBF16: storage of x, wt and out
     const void *x;      // input map, pix_words 4-byte words per pixel, followed by at least 16 bytes of zeros
-    const void *wt;     // filter matrix, [Mpad][Kpad], k = (j*kw + i)*Cs + c, zero padded
+    const void *wt;     // filter matrix, rows o < Mpad, columns k = (j*kw + i)*Cs + c < Kpad, zero padded: [Mpad][Kpad],
+                        // or in fragments (gemm_filter_in_fragments)
     const float *bias;  // [Mpad] float32
     const int2 *taps;   // one entry per 16-byte unit of a filter-matrix row:
                         //   .x = offset of that unit, in 4-byte words, from the window origin in the input map,
@@ -233,6 +234,15 @@ int gemm_channel_tile(int M);   // channel tile BM used for M output channels (M
 int gemm_k_multiple(int dtype); // Kpad must be a multiple of this many elements (128 bytes)
 int gemm_grid(const GemmArgs &a, int compute_units); // needs M, Mpad, Kpad, max_pixels
 int gemm_select_max_words(void);
+// How the filter matrix lies in memory.  Layers of the kernel for short filter rows: [Mpad][Kpad] in the
+// storage type.  All others: in the order in which the multiplication reads it, as bfloat16 fragments of
+// 16 rows x 32 k (512 values, lane by lane, eight each); a float32 value as the sum of three bfloat16
+// (largest first), whose fragments follow one another.  gemm_filter_fragment: where value (row, k) lies, in
+// bfloat16 values from the matrix' start; float32: its first part, the others kFilterPartStride further on each.
+bool gemm_filter_in_fragments(int dtype, int Mpad, int Kpad);
+size_t gemm_filter_bytes(int dtype, int Mpad, int Kpad);
+size_t gemm_filter_fragment(int dtype, int Mpad, int Kpad, int row, int k);
+constexpr int kFilterPartStride = 512;
 size_t gemm_partial_bytes(int M, int grid);
 size_t gemm_ticket_bytes(int grid);
 hipError_t gemm_prepare(void);  // one-time function attributes (dynamic LDS size)

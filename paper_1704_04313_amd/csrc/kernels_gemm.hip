@@ -15,13 +15,26 @@
 // of Section 3.1 without launches of their own.
 //
 // The workgroup has twelve waves with two roles.  The last four ("producers") compute gather
-// addresses, load the next K slices of both operands from global memory and store them to LDS;
-// the first eight ("consumers") only read LDS fragments and issue MFMAs (v_mfma_f32_16x16x4_f32
-// for float32 storage, v_mfma_f32_16x16x32_bf16 for bfloat16; float32 accumulation either way).
-// One producer and two consumer waves share each SIMD, so address arithmetic, global-load latency
-// and LDS stores overlap the matrix pipeline instead of draining it once per slice, and while one
-// consumer wave waits for its fragments the other keeps the pipeline fed (measured +2.5 % over
-// one consumer wave per SIMD).
+// addresses and issue the loads that bring the next K slices of both operands from global memory
+// straight into LDS; the first eight ("consumers") only read LDS fragments and issue MFMAs
+// (v_mfma_f32_16x16x32_bf16, float32 accumulation).  One producer and two consumer waves share each
+// SIMD, so address arithmetic and global-load latency overlap the matrix pipeline instead of draining
+// it once per slice, and while one consumer wave waits for its fragments the other keeps the pipeline
+// fed (measured +2.5 % over one consumer wave per SIMD).
+//
+// float32 storage multiplies in bfloat16 parts.  A float32 is the exact sum of three bfloat16 (8 bits of
+// its 24 each); of the nine products of parts the six down to 2^-24 of the leading one are formed, the
+// leading one and the corrections in accumulators of their own.  The matrix unit takes 16 cycles for 32 k
+// of a 16 x 16 tile in bfloat16 and 256 in float32, so six products cost 96: the float32 instruction bounded
+// these layers at 151 TFLOP/s (measured for a plain product), 64->256 7x7 on 320x180 ran at 126 and
+// runs at 209 TFLOP/s (736 -> 443 us), 16->64 7x7 on 640x360 at 105 and 163 (220 -> 142 us).  What bounds
+// them now is the bfloat16 matrix rate that the card sustains on such data: 209 x 6 = 1 254 TFLOP/s, the
+// plain library product of 8192 and 16384 rows reaches 1 120 to 1 340.  The sums are
+// more exact than before: 2.8e-7 against 7.1e-7 (2-norm, K = 3 136, against 64 bits), because 32 products
+// enter the leading accumulator with one rounding instead of eight; with one accumulator for all
+// six the error would be 8.1e-7.  The filter matrix is split once, when the state is created, and lies
+// in memory in the order in which it is read; pixels are split in registers (3.5 instructions per
+// value) in the shadow of the MFMAs.
 //
 // Work distribution: one workgroup per compute unit.  Output tiles are dealt out whole as long
 // as every workgroup gets one; the (tiles mod workgroups) left over are cut along K into
@@ -65,35 +78,44 @@ static constexpr int LDK = BK;      // LDS row pitch in 4-byte words: 128 bytes,
                                     // (16 rows, one or two neighbouring units) and of a ds_write_b128 (two rows,
                                     // all units) each cover all 64 banks once
 static constexpr int kConsWaves = 8;              // consumer waves per workgroup (two per SIMD)
-static constexpr int NPROD = 64 * 4;              // producer threads (one wave per SIMD)
+static constexpr int kProdWaves = 4;              // producer waves (one per SIMD)
+static constexpr int NPROD = 64 * kProdWaves;     // producer threads
 static constexpr int kRP = NPROD / 8;             // tile rows staged per pass: eight threads (units) per row
 static constexpr int NCONS = 64 * kConsWaves;     // consumer threads: waves 0 .. kConsWaves-1
 static constexpr int NT = NCONS + NPROD;          // threads per workgroup
-static constexpr int kStagedRing = 3; // K slices resident in LDS when the producers stage them through registers
-static constexpr int kThreeSetsUnits = 6; // (register staging) tiles whose producer threads load at most this many 16-byte
-                                          // units per slice keep three register sets of loads in flight, the others two
 static constexpr int kEpiChunk = 4;       // accumulators whose replaced values are loaded together in the output update
 static constexpr int kMinIters = 8;       // shortest K range worth giving to a workgroup
 static constexpr int kMaxGrid = 1024;
-static constexpr int kSmallTileFactor = 2; // big tiles are used from (workgroups / this) big tiles on
+// Big tiles are used from (workgroups / this) of them on.  Their K range is cut for the others then, so
+// 128 channels of float32 split further: the small tile reads LDS for longer than it multiplies
+// (64->256 7x7, 4 800 positions: 60 us with 64-pixel tiles, 56 us with 128; the 256->64 1x1, eight slices
+// long, 9.1 with the small ones and 11.5 with the big).
+template <int DT, int BM>
+static constexpr int kSmallTileFactor = DT == kF32 && BM == 128 ? 4 : 2;
 
 static constexpr int kSelMaxWords = 2048; // largest selection map ranked in-kernel (131072 pixels)
 static constexpr int kSelWordsPerThread = (kSelMaxWords + NT - 1) / NT;
-static constexpr int kSelSlots = kSelWordsPerThread * NT; // LDS words per ranking array (>= kSelMaxWords)
+static constexpr int kSelSlots = kSelMaxWords + kSelWordsPerThread; // LDS words per ranking array
+
+// 16-byte-per-lane fragments that one slice of 16 filter rows consists of: bfloat16 storage two (the two
+// halves of a slice's 64 k), float32 three (the bfloat16 parts of 32 k, see split_fragment).
+template <int DT>
+static constexpr int kFilterParts = DT == kBF16 ? 2 : 3;
+static constexpr int kFragBytes = 1024; // one fragment: 64 lanes x 16 bytes
 
 // LDS of one tile shape: a ring of STAGES K slices of both operands, then the tile's pixel list,
 // the ticket and two ints for the tile selection.
-template <int BM, int BN, int STAGES>
+template <int DT, int BM, int BN, int STAGES>
 struct TileSmem {
     static constexpr int a_floats = BN * LDK;
-    static constexpr int b_floats = BM * LDK;
+    static constexpr int b_floats = BM / 16 * kFilterParts<DT> * kFragBytes / 4;
     static constexpr int tile_bytes = STAGES * (a_floats + b_floats) * 4 + BN * 4 + 16;
 };
 // LDS of a kernel instantiation (a big and a small tile shape share it): behind the larger of the
 // two tiles the selection map's words, their exclusive ranks, and the wave totals of the scan.
-template <int BM, int BNB, int SB, int BNS, int SS>
+template <int DT, int BM, int BNB, int SB, int BNS, int SS>
 struct KernelSmem {
-    static constexpr int tb = TileSmem<BM, BNB, SB>::tile_bytes, ts = TileSmem<BM, BNS, SS>::tile_bytes;
+    static constexpr int tb = TileSmem<DT, BM, BNB, SB>::tile_bytes, ts = TileSmem<DT, BM, BNS, SS>::tile_bytes;
     static constexpr int sel_offset = ((tb > ts ? tb : ts) + 15) / 16 * 16;
     static constexpr int bytes = sel_offset + kSelSlots * 12 + 64;
     static_assert(bytes <= 160 * 1024, "a workgroup has 160 KiB of LDS");
@@ -296,7 +318,8 @@ __device__ __forceinline__ int rank_selection(const GemmArgs &a, uint64_t *sW, i
     }
     __syncthreads(); // every thread has read its words before they are rewritten below
 #pragma unroll
-    for (int j = 0; j < kSelWordsPerThread; ++j) sW[kSelWordsPerThread * tid + j] = w[j]; // zero beyond the map
+    for (int j = 0; j < kSelWordsPerThread; ++j)
+        if (kSelWordsPerThread * tid + j < kSelSlots) sW[kSelWordsPerThread * tid + j] = w[j]; // zero beyond the map
     int c[kSelWordsPerThread], sum = 0;
 #pragma unroll
     for (int j = 0; j < kSelWordsPerThread; ++j) {
@@ -316,7 +339,7 @@ __device__ __forceinline__ int rank_selection(const GemmArgs &a, uint64_t *sW, i
     int e = before + incl - sum;
 #pragma unroll
     for (int j = 0; j < kSelWordsPerThread; ++j) {
-        sRank[kSelWordsPerThread * tid + j] = e;
+        if (kSelWordsPerThread * tid + j < kSelSlots) sRank[kSelWordsPerThread * tid + j] = e;
         e += c[j];
     }
     __syncthreads();
@@ -335,6 +358,7 @@ __device__ __forceinline__ void select_tile(const Selection &sel, int n, int r0,
 #pragma unroll
     for (int j = 0; j < kSelWordsPerThread; ++j) {
         const int i = kSelWordsPerThread * tid + j;
+        if (i >= kSelSlots) break;
         const int e = sel.rank[i], c = __popcll(sel.words[i]);
         if (e <= r0 && r0 < e + c) sRange[0] = i;
         if (e <= r1 && r1 < e + c) sRange[1] = i;
@@ -406,54 +430,7 @@ __device__ __forceinline__ int share_owner(const Schedule &s, int it)
     return w;
 }
 
-// Image-matrix rows gathered by one producer thread for one K slice: PA rows (32 apart), one
-// 16-byte unit each.  tp is the slice's tap descriptor for this thread's unit column.
-template <int PA>
-__device__ __forceinline__ void gather_rows(const GemmArgs &a, const int2 tp, const int (&iy0)[PA],
-                                            const int (&ix0)[PA], const int (&base)[PA], floatx4 (&ra)[PA])
-{
-    const float *x = static_cast<const float *>(a.x); // 4-byte words, whatever the storage type
-    const int tj = tp.y & 0xff, ti = (tp.y >> 8) & 0xff;
-    const bool tv = (tp.y >> 16) != 0;
-#pragma unroll
-    for (int ps = 0; ps < PA; ++ps) {
-        const bool ok = tv && (unsigned)(iy0[ps] + tj) < (unsigned)a.H && (unsigned)(ix0[ps] + ti) < (unsigned)a.W;
-        // outside the image (or no pixel in this row): the zero unit kept behind the map, so that the
-        // load needs no predication and the registers no clearing
-        const unsigned idx = ok ? (unsigned)(base[ps] + tp.x) : (unsigned)a.zero_word;
-        ra[ps] = *reinterpret_cast<const floatx4_a4 *>(x + idx);
-    }
-}
-
-// wrow: this thread's unit column in its first filter-matrix row; krow = units per row.
-template <int BM, int PB>
-__device__ __forceinline__ void load_filter_rows(const floatx4 *wrow, int krow, int kc, int r0, floatx4 (&rb)[PB])
-{
-    if constexpr (BM >= kRP) {
-#pragma unroll
-        for (int ps = 0; ps < PB; ++ps) rb[ps] = wrow[(size_t)(kRP * ps) * krow + kc * KU];
-    } else {
-        if (r0 < BM) rb[0] = wrow[kc * KU];
-    }
-}
-
 __device__ __forceinline__ int lds_swizzle(int row) { return (row >> 1) & 7; }
-
-// v: this thread's slot in the row, i.e. its unit column already permuted for row r0 (rows 32 apart
-// share the permutation).
-template <int BM, int PA, int PB>
-__device__ __forceinline__ void stage_rows(float *A, float *B, int r0, int v, const floatx4 (&ra)[PA],
-                                           const floatx4 (&rb)[PB])
-{
-#pragma unroll
-    for (int ps = 0; ps < PA; ++ps) *reinterpret_cast<floatx4 *>(A + (r0 + kRP * ps) * LDK + v * 4) = ra[ps];
-    if constexpr (BM >= kRP) {
-#pragma unroll
-        for (int ps = 0; ps < PB; ++ps) *reinterpret_cast<floatx4 *>(B + (r0 + kRP * ps) * LDK + v * 4) = rb[ps];
-    } else {
-        if (r0 < BM) *reinterpret_cast<floatx4 *>(B + r0 * LDK + v * 4) = rb[0];
-    }
-}
 
 // s_waitcnt vmcnt(N), everything else unconstrained (gfx9 encoding: vmcnt in bits 3:0 and 15:14).
 template <int N>
@@ -493,29 +470,27 @@ typedef __attribute__((address_space(3))) void *LdsPtr;
 // producer wave on that SIMD gets issued about once per MFMA (measured: 40 cycles per instruction),
 // so the producers' instruction count per slice, not the memory system, is what can hold up the loop.
 // Hence: everything wave-uniform is computed on the scalar unit (the ring slot and the LDS
-// destinations; with UT also the filter tap of the slice), filter rows are addressed as a uniform
-// base plus a per-lane 32-bit offset that never changes, and what is left per image-matrix row is
-// the bounds test of its tap and the choice between the pixel's address and the zero unit.
+// destinations; with UT also the filter tap of the slice), filter fragments are addressed as a uniform
+// base plus 16 bytes per lane, and what is left per image-matrix row is the bounds test of its tap and
+// the choice between the pixel's address and the zero unit.
 // UT ("uniform tap"): the units per pixel are a multiple of the eight units of a slice, so a slice
 // lies inside one filter tap and the tap is the same for all lanes; base[] then already contains
 // the lane's own unit offset.
 template <int DT, int BM, int BN, int STAGES, int PA, bool UT>
 __device__ __forceinline__ void direct_producer(const GemmArgs &a, float *As, float *Bs, int kc0, int kc1, int mt,
-                                                int krow, int pw_, int r0, int vf, const int (&iy0)[PA],
+                                                int nk, int pw_, int vf, const int (&iy0)[PA],
                                                 const int (&ix0)[PA], const int (&base)[PA])
 {
-    constexpr int PB = (BM + kRP - 1) / kRP; // filter-row passes (a tile of 16 channels: two waves repeat the others' rows)
-    constexpr int PS = PA + PB;              // instructions per slice and wave
-    constexpr int ASZ = BN * LDK, BSZ = BM * LDK;
+    constexpr int FB = BM / 16 * kFilterParts<DT>;      // filter fragments per slice
+    constexpr int PB = (FB + kProdWaves - 1) / kProdWaves; // ... per wave (the last ones repeat others' when FB does not divide)
+    constexpr int PS = PA + PB;                         // instructions per slice and wave
+    constexpr int ASZ = BN * LDK, BSZ = FB * kFragBytes / 4;
     static_assert((STAGES - 3) * PS < 64, "outstanding loads must fit the counter");
     const int pw = __builtin_amdgcn_readfirstlane(pw_); // the wave's number among the producers, as a scalar
     const float *x = static_cast<const float *>(a.x);
-    // this channel tile's rows of the filter matrix; the lane's rows and unit as byte offsets from there
-    // (below 4 GiB: the host checks BM * Kpad)
-    const char *wtile = reinterpret_cast<const char *>(static_cast<const floatx4 *>(a.wt) + (size_t)mt * BM * krow);
-    unsigned wofs[PB];
-#pragma unroll
-    for (int ps = 0; ps < PB; ++ps) wofs[ps] = (unsigned)((r0 % BM + kRP * ps) * krow + vf) * 16u;
+    // this channel tile's slices of the filter matrix, one behind the other as they lie in LDS
+    const char *wtile = static_cast<const char *>(a.wt) + (size_t)mt * nk * (FB * kFragBytes);
+    const unsigned lofs = (threadIdx.x & 63) * 16u;
     auto issue = [&](int kc, int slot) {
         // tap of this lane's unit in slice kc: unit index -> (filter tap, channel unit) -> (j, i)
         const int q = kc * KU + (UT ? 0 : vf);
@@ -523,7 +498,7 @@ __device__ __forceinline__ void direct_producer(const GemmArgs &a, float *As, fl
         const int tj = fast_div(tap, a.dKw), ti = tap - tj * a.kw;
         const bool tv = tj < a.kh;
         const int off = (tj * a.W + ti) * a.pix_words + cu * 4;
-        float *A = As + slot * ASZ + pw * 8 * LDK, *B = Bs + slot * BSZ + (pw * 8 % BM) * LDK;
+        float *A = As + slot * ASZ + pw * 8 * LDK, *B = Bs + slot * BSZ;
 #pragma unroll
         for (int ps = 0; ps < PA; ++ps) {
             const bool ok = tv && (unsigned)(iy0[ps] + tj) < (unsigned)a.H && (unsigned)(ix0[ps] + ti) < (unsigned)a.W;
@@ -532,10 +507,13 @@ __device__ __forceinline__ void direct_producer(const GemmArgs &a, float *As, fl
             const unsigned idx = ok ? (unsigned)(base[ps] + off) : (unsigned)a.zero_word;
             __builtin_amdgcn_global_load_lds((GlobalPtr)(x + idx), (LdsPtr)(A + kRP * ps * LDK), 16, 0, 0);
         }
-        const char *wslice = wtile + (size_t)kc * (KU * 16);
+        const char *wslice = wtile + (size_t)kc * (FB * kFragBytes);
 #pragma unroll
-        for (int ps = 0; ps < PB; ++ps)
-            __builtin_amdgcn_global_load_lds((GlobalPtr)(wslice + wofs[ps]), (LdsPtr)(B + kRP * ps * LDK), 16, 0, 0);
+        for (int ps = 0; ps < PB; ++ps) {
+            const int f = (pw + kProdWaves * ps) % FB;
+            __builtin_amdgcn_global_load_lds((GlobalPtr)(wslice + f * kFragBytes + lofs), (LdsPtr)(B + f * (kFragBytes / 4)), 16,
+                                             0, 0);
+        }
     };
     // Nothing of this wave is in flight here; saying so keeps the compiler, which tracks loads into
     // registers along every path through the kernel, from waiting for imagined ones inside the loop.
@@ -562,31 +540,115 @@ __device__ __forceinline__ void direct_producer(const GemmArgs &a, float *As, fl
     }
 }
 
+// A float32 as the sum of three bfloat16: hi = x rounded to 8 significant bits, mid = the rest rounded
+// likewise, lo = what is left; 24 bits need no fourth.  Both differences are exact (the rest of a
+// rounding to nearest has at most 16 significant bits, the next one at most 8), so hi + mid + lo is x
+// itself.  Eight consecutive values of a lane become one 16-byte fragment of each part.
+struct Parts {
+    uintx4 hi, mid, lo;
+};
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ unsigned bf16_pair(float a, float b)
+{
+    const bf16x2 v = {(__bf16)a, (__bf16)b};
+    return __builtin_bit_cast(unsigned, v);
+}
+__device__ __forceinline__ float minus_part(float x, unsigned pair, unsigned which)
+{
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, which), __builtin_bit_cast(bf16x2, pair), x, false);
+}
+__device__ __forceinline__ Parts split_fragment(const floatx4 x0, const floatx4 x1)
+{
+    // (-1, 0) and (0, -1) in scalar registers: as an inline constant the compiler writes the first as the
+    // float -1, whose bits the instruction reads as (0, -1)
+    unsigned first = 0x0000bf80u, second = 0xbf800000u;
+    asm("" : "+s"(first));
+    asm("" : "+s"(second));
+    Parts p;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float a = i < 2 ? x0[2 * i] : x1[2 * i - 4], b = i < 2 ? x0[2 * i + 1] : x1[2 * i - 3];
+        const unsigned h = bf16_pair(a, b);
+        // a - hi(a): the two-element dot product with (-1, 0) and the float added takes a packed part as it is
+        const float ra = minus_part(a, h, first), rb = minus_part(b, h, second);
+        const unsigned m = bf16_pair(ra, rb);
+        p.hi[i] = h;
+        p.mid[i] = m;
+        p.lo[i] = bf16_pair(minus_part(ra, m, first), minus_part(rb, m, second));
+    }
+    return p;
+}
+
+// Where value (row, k) of a filter matrix in fragments lies, in bfloat16 values from its start; float32:
+// its first part.
+template <int DT>
+__host__ __device__ inline size_t filter_fragment(int bm, int nk, int row, int k)
+{
+    constexpr int KS = DT == kBF16 ? 64 : 32; // k per slice
+    const int mt = row / bm, ct = row % bm / 16, kc = k / KS, kk = k % KS;
+    // float32: a lane's eight k are two units of four, 16 k apart; bfloat16: one unit of eight
+    const int lk = DT == kF32 ? kk % 16 / 4 : kk / 8 % 4, e = DT == kF32 ? kk / 16 * 4 + kk % 4 : kk % 8;
+    const int part = DT == kF32 ? 0 : kk / 32;
+    return ((((size_t)mt * nk + kc) * (bm / 16) + ct) * kFilterParts<DT> + part) * (kFragBytes / 2) + (lk * 16 + row % 16) * 8 + e;
+}
+
+// The sum of channel `row` at output position g, product by product in float32 from global memory:
+// for sums that are not finite.  Where a value is infinite, not a number, or so near the largest
+// float32 that its first part rounds to infinity, the products of parts are not those of the values
+// (infinity less infinity, infinity times a part that is zero), so the value itself decides here.
+template <int BM>
+__device__ __forceinline__ float plain_sum(const GemmArgs &a, int nk, int row, int g)
+{
+    const float *x = static_cast<const float *>(a.x);
+    const unsigned short *wt = static_cast<const unsigned short *>(a.wt);
+    const int st = fast_div(g, a.dNo), q = g - st * a.No;
+    const int qy = fast_div(q, a.dWo), qx = q - qy * a.Wo;
+    const int Cs = a.dVin.d * 4;
+    float s = 0.f;
+    for (int j = 0; j < a.kh; ++j)
+        for (int i = 0; i < a.kw; ++i) {
+            const int iy = qy * a.stride - a.pad + j, ix = qx * a.stride - a.pad + i;
+            if ((unsigned)iy >= (unsigned)a.H || (unsigned)ix >= (unsigned)a.W) continue;
+            const float *px = x + (size_t)((st * a.H + iy) * a.W + ix) * a.pix_words;
+            for (int c = 0; c < a.pix_words; ++c) {
+                const unsigned short *w = wt + filter_fragment<kF32>(BM, nk, row, (j * a.kw + i) * Cs + c);
+                const float wv = bf16_value(w[0]) + (bf16_value(w[kFilterPartStride]) + bf16_value(w[2 * kFilterPartStride]));
+                s = fmaf(px[c], wv, s);
+            }
+        }
+    return s;
+}
+
 // BM x BN workgroup tile; the consumer waves are arranged WM (channels) x WN (pixels).
 //
-// LDS holds a ring of three K slices.  In iteration kc the producers store slice kc+2 and issue
-// the global loads of a slice two or three further on (one per register set), while the consumers
-// multiply slice kc and already read the first fragments of slice kc+1, so the matrix pipeline
-// keeps running across the one barrier per slice.
-template <int DT, int BM, int BN, int WM, int WN, int STAGES, bool DIRECT>
+// LDS holds a ring of STAGES K slices.  In iteration kc the producers issue the loads of slice
+// kc + STAGES - 1, while the consumers multiply slice kc and already read the first fragments of slice
+// kc + 1, so the matrix pipeline keeps running across the one barrier per slice.  Pixel rows lie in LDS as
+// they do in the map, their units permuted against bank conflicts; filter fragments lie as a wave
+// reads them, 16 bytes per lane one lane behind the other, and arrive so from memory.
+//
+// Sub-tiles of the float32 shapes: a wave splits every pixel value it multiplies, so waves that share
+// pixels repeat each other's work; all channels of a 64-channel tile in one wave (1 x 8) took 136 us on
+// 16->64 7x7 at 640x360 against 230 in a 2 x 4 arrangement.  128 channels by one wave would read the
+// filter fragments eight times per slice, more than LDS delivers.
+template <int DT, int BM, int BN, int WM, int WN, int STAGES>
 __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n, float *smem, const Selection sel)
 {
     static_assert(WM * WN == kConsWaves, "one sub-tile per consumer wave");
-    static_assert(DIRECT ? STAGES >= 3 : STAGES == kStagedRing, "ring depth");
+    static_assert(STAGES >= 3, "ring depth");
     constexpr int TP = BN / WN / 16; // 16-pixel MFMA tiles per consumer wave
     constexpr int TC = BM / WM / 16; // 16-channel MFMA tiles per consumer wave
     constexpr int PA = BN / kRP;     // image-matrix rows staged per producer thread and slice
-    constexpr int PB = (BM + kRP - 1) / kRP;
-    constexpr int NS = PA + PB <= kThreeSetsUnits ? 3 : 2; // (register staging) sets of loads in flight per producer thread
+    constexpr int FP = kFilterParts<DT>;
     static_assert(BN % kRP == 0, "whole passes over the pixel rows");
-    constexpr int ASZ = BN * LDK, BSZ = BM * LDK;
+    constexpr int ASZ = BN * LDK, BSZ = BM / 16 * FP * kFragBytes / 4;
     constexpr int SLAB = BM * BN; // floats of one partial-accumulator slab
     static_assert(TP >= 1 && TC >= 1, "tile too small");
     static_assert(BK == 32, "two 16-wide fragment groups per slice");
     static_assert(TC * TP * 4 * NCONS == SLAB, "a slab holds every consumer lane's accumulators");
 
     float *As = smem;                                     // [STAGES][BN][LDK]  gathered image-matrix slices
-    float *Bs = smem + STAGES * ASZ;                      // [STAGES][BM][LDK]  filter-matrix slices
+    float *Bs = smem + STAGES * ASZ;                      // [STAGES][BM/16][FP] filter fragments
     int *sU = reinterpret_cast<int *>(Bs + STAGES * BSZ); // [BN] listed pixels of this tile (-1: none)
     int *sFlag = sU + BN;                                  // ticket of the tile just finished
 
@@ -596,8 +658,7 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
     const bool producer = wave >= kConsWaves;
 
     const int mtiles = a.Mpad / BM;
-    const int krow = a.Kpad / Unit<DT>::N; // units per filter-matrix row
-    const int nk = krow / KU;
+    const int nk = a.Kpad / (Unit<DT>::N * KU); // K slices
     const int W = gridDim.x;
     const Schedule sch = make_schedule(n, BN, mtiles, nk, a.dGrid);
     if (sch.tiles == 0) return;
@@ -637,21 +698,9 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
         const int mt = tile - pt * mtiles;
         const bool partial = (kc1 - kc0) != nk;
 
-        // Producers: the tap descriptors of the first slices do not depend on the tile's pixel list,
-        // so their loads are in flight while the list is made.
         const int ptid = producer ? tid - NCONS : 0;
         const int v = ptid & 7;   // 16-byte unit column inside the K slice
         const int r0 = ptid >> 3; // first row this thread stages
-        const floatx4 *wrow = static_cast<const floatx4 *>(a.wt) + (size_t)(mt * BM + r0) * krow + v;
-        const int2 *taps = a.taps + v;
-        auto tap = [&](int kc) { return taps[(kc < kc1 ? kc : kc0) * KU]; };
-        int2 tp0, tp1, tp[NS];
-        if (producer && !DIRECT) {
-            tp0 = tap(kc0);
-            tp1 = tap(kc0 + 1);
-#pragma unroll
-            for (int u = 0; u < NS; ++u) tp[u] = tap(kc0 + 2 + u);
-        }
         __syncthreads(); // the previous segment's LDS reads are done
         if (sel.words) {
             select_tile<BN>(sel, n, pt * BN, sU, sFlag + 1);
@@ -675,9 +724,8 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
 
         // Both roles execute the same number of barriers: one after the prologue, one per slice.
         if (producer) {
-            // staging through registers: this thread loads unit column v and stores it to slot vs;
-            // direct to LDS: the hardware puts lane l's 16 bytes into slot l & 7 of row l >> 3 of the
-            // eight rows an instruction covers, so the thread fetches the unit that belongs there
+            // the hardware puts lane l's 16 bytes into slot l & 7 of row l >> 3 of the eight rows an
+            // instruction covers, so the thread fetches the unit that belongs there
             const int vs = v ^ lds_swizzle(r0);
             int iy0[PA], ix0[PA], base[PA];
 #pragma unroll
@@ -695,61 +743,16 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                     base[ps] = 0;
                 }
             }
-            if constexpr (DIRECT) {
-                if ((a.dVin.d & (KU - 1)) == 0) {
-                    // a slice lies inside one filter tap: the lane's unit goes into its pixel offsets once
+            if ((a.dVin.d & (KU - 1)) == 0) {
+                // a slice lies inside one filter tap: the lane's unit goes into its pixel offsets once
 #pragma unroll
-                    for (int ps = 0; ps < PA; ++ps) base[ps] += vs * 4;
-                    direct_producer<DT, BM, BN, STAGES, PA, true>(a, As, Bs, kc0, kc1, mt, krow, wave - kConsWaves, r0, vs, iy0,
-                                                                  ix0, base);
-                } else {
-                    direct_producer<DT, BM, BN, STAGES, PA, false>(a, As, Bs, kc0, kc1, mt, krow, wave - kConsWaves, r0, vs,
-                                                                   iy0, ix0, base);
-                }
+                for (int ps = 0; ps < PA; ++ps) base[ps] += vs * 4;
+                direct_producer<DT, BM, BN, STAGES, PA, true>(a, As, Bs, kc0, kc1, mt, nk, wave - kConsWaves, vs, iy0, ix0,
+                                                              base);
             } else {
-            // NS register sets: in iteration kc the slice kc+2, loaded NS iterations ago, is stored to
-            // the LDS ring and the loads of slice kc+2+NS are issued into the same registers.  The
-            // loop runs at the pace of these loads when NS slices of MFMA work are shorter than a
-            // global-memory round trip, so the small tiles get a third set.  The tap descriptor of
-            // a slice is loaded a round before the operand loads that need it.
-            floatx4 ra[NS][PA], rb[NS][PB];
-            // prologue: slices kc0 and kc0+1 into ring slots 0 and 1, slices kc0+2 .. kc0+1+NS in flight
-            gather_rows<PA>(a, tp0, iy0, ix0, base, ra[0]);
-            load_filter_rows<BM, PB>(wrow, krow, kc0, r0, rb[0]);
-            if (kc0 + 1 < kc1) {
-                gather_rows<PA>(a, tp1, iy0, ix0, base, ra[1]);
-                load_filter_rows<BM, PB>(wrow, krow, kc0 + 1, r0, rb[1]);
+                direct_producer<DT, BM, BN, STAGES, PA, false>(a, As, Bs, kc0, kc1, mt, nk, wave - kConsWaves, vs, iy0, ix0,
+                                                               base);
             }
-            stage_rows<BM, PA, PB>(As, Bs, r0, vs, ra[0], rb[0]);
-            if (kc0 + 1 < kc1) stage_rows<BM, PA, PB>(As + ASZ, Bs + BSZ, r0, vs, ra[1], rb[1]);
-#pragma unroll
-            for (int u = 0; u < NS; ++u) {
-                if (kc0 + 2 + u < kc1) {
-                    gather_rows<PA>(a, tp[u], iy0, ix0, base, ra[u]);
-                    load_filter_rows<BM, PB>(wrow, krow, kc0 + 2 + u, r0, rb[u]);
-                }
-                tp[u] = tap(kc0 + 2 + NS + u);
-            }
-            __syncthreads();
-            int slot = 2; // ring slot of slice kc+2
-            for (int kc = kc0; kc < kc1; kc += NS) {
-#pragma unroll
-                for (int u = 0; u < NS; ++u) {
-                    if (kc + u < kc1) {
-                        if (kc + u + 2 < kc1) {
-                            stage_rows<BM, PA, PB>(As + slot * ASZ, Bs + slot * BSZ, r0, vs, ra[u], rb[u]);
-                            if (kc + u + 2 + NS < kc1) {
-                                gather_rows<PA>(a, tp[u], iy0, ix0, base, ra[u]);
-                                load_filter_rows<BM, PB>(wrow, krow, kc + u + 2 + NS, r0, rb[u]);
-                                tp[u] = tap(kc + u + 2 + 2 * NS);
-                            }
-                        }
-                        slot = slot == kStagedRing - 1 ? 0 : slot + 1;
-                        __syncthreads();
-                    }
-                }
-            }
-            } // register staging
 #pragma unroll
             for (int j = 0; j < TC; ++j)
 #pragma unroll
@@ -759,67 +762,131 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
             for (int j = 0; j < TC; ++j)
 #pragma unroll
                 for (int i = 0; i < TP; ++i) acc[j][i] = (floatx4){0.f, 0.f, 0.f, 0.f};
-            // fragment group kk of this lane's row: unit 4*kk + lk, stored in slot (4*kk + lk) ^ swizzle
+            // unit 4*kk + lk of this lane's pixel row, stored in slot (4*kk + lk) ^ swizzle
             const int u0 = (lk ^ lds_swizzle(lrow)) * 4;
             const float *A0 = As + (wpx0 + lrow) * LDK;
-            const float *B0 = Bs + (wch0 + lrow) * LDK;
-            // Each lane reads four consecutive k of its row; MFMA step s then contracts
-            // k = 16*group + 4*slot + s for slot = 0..3 -- both operands use the same permutation.
-            // D = (filter rows) x (pixel columns): D[4*slot + r][lane%16] lands in this lane,
-            // i.e. four consecutive channels of one pixel per accumulator.
-            floatx4 af[2][TP], bf[2][TC];
-            auto read_frags = [&](int set, int slot, int kk) {
-                const float *A = A0 + slot * ASZ + (u0 ^ (kk * 16));
-                const float *B = B0 + slot * BSZ + (u0 ^ (kk * 16));
-#pragma unroll
-                for (int i = 0; i < TP; ++i) af[set][i] = *reinterpret_cast<const floatx4 *>(A + i * 16 * LDK);
-#pragma unroll
-                for (int j = 0; j < TC; ++j) bf[set][j] = *reinterpret_cast<const floatx4 *>(B + j * 16 * LDK);
+            const char *B0 = reinterpret_cast<const char *>(Bs) + wch0 / 16 * FP * kFragBytes + lane * 16;
+            // Both operands of an MFMA hold eight k per lane, in the same order: D = (filter rows) x
+            // (pixel columns), D[4*slot + r][lane%16] lands in this lane, i.e. four consecutive
+            // channels of one pixel per accumulator.
+            auto read_pixels = [&](int slot, int kk, int i) {
+                return *reinterpret_cast<const floatx4 *>(A0 + slot * ASZ + (u0 ^ (kk * 16)) + i * 16 * LDK);
             };
-            auto multiply = [&](int set) {
-                if constexpr (DT == kBF16) {
-                    // one 16-byte fragment = 8 consecutive k: v_mfma_f32_16x16x32_bf16 takes it whole
-#pragma unroll
-                    for (int j = 0; j < TC; ++j)
-#pragma unroll
-                        for (int i = 0; i < TP; ++i)
-                            acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                __builtin_bit_cast(bf16x8, bf[set][j]), __builtin_bit_cast(bf16x8, af[set][i]),
-                                acc[j][i], 0, 0, 0);
-                } else {
-#pragma unroll
-                    for (int s = 0; s < 4; ++s)
-#pragma unroll
-                        for (int j = 0; j < TC; ++j)
-#pragma unroll
-                            for (int i = 0; i < TP; ++i)
-                                acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(bf[set][j][s], af[set][i][s],
-                                                                                 acc[j][i], 0, 0, 0);
-                }
+            auto read_filter = [&](int slot, int j, int part) {
+                return *reinterpret_cast<const uintx4 *>(B0 + slot * (BSZ * 4) + (j * FP + part) * kFragBytes);
+            };
+            auto mfma = [](const uintx4 w, const uintx4 x, const floatx4 c) {
+                return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), c,
+                                                               0, 0, 0);
             };
             __syncthreads();
             // the wave feeding the matrix pipeline wins instruction-issue arbitration on its SIMD
             __builtin_amdgcn_s_setprio(3);
-            read_frags(0, 0, 0);
             int slot = 0; // ring slot of slice kc
-            for (int kc = kc0; kc < kc1; ++kc) {
-                const int nslot = slot == STAGES - 1 ? 0 : slot + 1;
-                // The scheduling barriers pin the order "issue the LDS reads of the next fragment
-                // group, then the MFMAs of the current one", so that LDS latency and bandwidth
-                // are spent while the matrix pipeline is busy.
-                read_frags(1, slot, 1);
-                __builtin_amdgcn_sched_barrier(0);
-                multiply(0);
-                __builtin_amdgcn_sched_barrier(0);
-                // Also in the last iteration, where the slot holds nothing of use: under a condition
-                // the compiler, which counts outstanding LDS reads per path, would make the MFMAs
-                // below wait for these reads too.
-                read_frags(0, nslot, 0);
-                __builtin_amdgcn_sched_barrier(0);
-                multiply(1);
-                __builtin_amdgcn_sched_barrier(0);
-                slot = nslot;
-                __syncthreads();
+            if constexpr (DT == kBF16) {
+                uintx4 af[2][TP], bf[2][TC];
+                auto read_frags = [&](int set, int sl, int kk) {
+#pragma unroll
+                    for (int i = 0; i < TP; ++i) af[set][i] = __builtin_bit_cast(uintx4, read_pixels(sl, kk, i));
+#pragma unroll
+                    for (int j = 0; j < TC; ++j) bf[set][j] = read_filter(sl, j, kk);
+                };
+                auto multiply = [&](int set) {
+#pragma unroll
+                    for (int j = 0; j < TC; ++j)
+#pragma unroll
+                        for (int i = 0; i < TP; ++i) acc[j][i] = mfma(bf[set][j], af[set][i], acc[j][i]);
+                };
+                read_frags(0, 0, 0);
+                for (int kc = kc0; kc < kc1; ++kc) {
+                    const int nslot = slot == STAGES - 1 ? 0 : slot + 1;
+                    // The scheduling barriers pin the order "issue the LDS reads of the next fragment
+                    // group, then the MFMAs of the current one", so that LDS latency and bandwidth
+                    // are spent while the matrix pipeline is busy.
+                    read_frags(1, slot, 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    multiply(0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    // Also in the last iteration, where the slot holds nothing of use: under a condition
+                    // the compiler, which counts outstanding LDS reads per path, would make the MFMAs
+                    // below wait for these reads too.
+                    read_frags(0, nslot, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    multiply(1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    slot = nslot;
+                    __syncthreads();
+                }
+            } else {
+                // float32: six of the nine products of parts, everything down to 2^-24 of the leading one.
+                // Leading products and corrections have accumulators of their own: the corrections are
+                // then summed at their own magnitude and do not round the leading sum again.
+                floatx4 cor[TC][TP];
+#pragma unroll
+                for (int j = 0; j < TC; ++j)
+#pragma unroll
+                    for (int i = 0; i < TP; ++i) cor[j][i] = (floatx4){0.f, 0.f, 0.f, 0.f};
+                Parts x0[TP], x1[TP]; // pixel fragments of two slices in turn
+                uintx4 w[2][3];
+#pragma unroll
+                for (int p = 0; p < 3; ++p) w[0][p] = read_filter(0, 0, p);
+#pragma unroll
+                for (int i = 0; i < TP; ++i) x0[i] = split_fragment(read_pixels(0, 0, i), read_pixels(0, 1, i));
+                // One slice: while channel tile j is multiplied, the filter fragments of the next tile are
+                // on their way from LDS and the next slice's pixels are read and split.
+                auto step = [&](Parts(&x)[TP], Parts(&nx)[TP]) {
+                    const int nslot = slot == STAGES - 1 ? 0 : slot + 1;
+                    floatx4 raw[TP][2];
+#pragma unroll
+                    for (int j = 0; j < TC; ++j) {
+#pragma unroll
+                        for (int p = 0; p < 3; ++p)
+                            w[(j + 1) & 1][p] = j + 1 < TC ? read_filter(slot, j + 1, p) : read_filter(nslot, 0, p);
+                        // pixel fragment i of the next slice is read a channel tile before it is split
+#pragma unroll
+                        for (int i = 0; i < TP; ++i) {
+                            if (j == (i < TC - 1 ? i : (TC > 1 ? TC - 2 : 0))) {
+                                raw[i][0] = read_pixels(nslot, 0, i);
+                                raw[i][1] = read_pixels(nslot, 1, i);
+                            }
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                        const uintx4 *wj = w[j & 1];
+#pragma unroll
+                        for (int i = 0; i < TP; ++i) acc[j][i] = mfma(wj[0], x[i].hi, acc[j][i]);
+#pragma unroll
+                        for (int i = 0; i < TP; ++i) cor[j][i] = mfma(wj[2], x[i].hi, cor[j][i]);
+#pragma unroll
+                        for (int i = 0; i < TP; ++i) cor[j][i] = mfma(wj[1], x[i].mid, cor[j][i]);
+#pragma unroll
+                        for (int i = 0; i < TP; ++i) cor[j][i] = mfma(wj[0], x[i].lo, cor[j][i]);
+#pragma unroll
+                        for (int i = 0; i < TP; ++i) cor[j][i] = mfma(wj[1], x[i].hi, cor[j][i]);
+#pragma unroll
+                        for (int i = 0; i < TP; ++i) cor[j][i] = mfma(wj[0], x[i].mid, cor[j][i]);
+                        // ... in the shadow of that tile's MFMAs
+#pragma unroll
+                        for (int i = 0; i < TP; ++i)
+                            if (j == (i + 1 < TC ? i + 1 : TC - 1)) nx[i] = split_fragment(raw[i][0], raw[i][1]);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if constexpr (TC & 1) {
+#pragma unroll
+                        for (int p = 0; p < 3; ++p) w[0][p] = w[1][p];
+                    }
+                    slot = nslot;
+                    __syncthreads();
+                };
+                int kc = kc0;
+                for (; kc + 1 < kc1; kc += 2) {
+                    step(x0, x1);
+                    step(x1, x0);
+                }
+                if (kc < kc1) step(x0, x1);
+#pragma unroll
+                for (int j = 0; j < TC; ++j)
+#pragma unroll
+                    for (int i = 0; i < TP; ++i) acc[j][i] += cor[j][i];
             }
             __builtin_amdgcn_s_setprio(0);
         }
@@ -879,6 +946,38 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
 #pragma unroll
                             for (int i = 0; i < TP; ++i) acc[j][i] += part[j][i];
                     }
+                }
+            }
+        }
+
+        if constexpr (DT == kF32) {
+            // Sums that are not finite are formed again from the values themselves.  (x * 0 is zero for
+            // every finite x.)  The accumulators pass through this wave's share of the ring, which holds
+            // nothing any more, so that the loop over them is a loop.
+            if (finish && !producer) {
+                float z = 0.f;
+#pragma unroll
+                for (int j = 0; j < TC; ++j)
+#pragma unroll
+                    for (int i = 0; i < TP; ++i) z += acc[j][i][0] * 0.f + acc[j][i][1] * 0.f + acc[j][i][2] * 0.f + acc[j][i][3] * 0.f;
+                if (__builtin_expect(__any(z != 0.f), 0)) { // NaN compares unequal
+                    static_assert(STAGES * (ASZ + BSZ) >= SLAB, "the ring holds the tile's accumulators");
+                    float *mine = smem + wave * (TC * TP * 256);
+#pragma unroll
+                    for (int j = 0; j < TC; ++j)
+#pragma unroll
+                        for (int i = 0; i < TP; ++i) *reinterpret_cast<floatx4 *>(mine + (j * TP + i) * 256 + lane * 4) = acc[j][i];
+#pragma unroll 1
+                    for (int e = 0; e < TC * TP * 4; ++e) {
+                        float *v = mine + (e >> 2) * 256 + lane * 4 + (e & 3);
+                        const int g = sU[wpx0 + (e >> 2) % TP * 16 + lrow];
+                        const int row = mt * BM + wch0 + (e >> 2) / TP * 16 + lk * 4 + (e & 3);
+                        if (!(fabsf(*v) < __builtin_inff()) && g >= 0 && row < a.M) *v = plain_sum<BM>(a, nk, row, g);
+                    }
+#pragma unroll
+                    for (int j = 0; j < TC; ++j)
+#pragma unroll
+                        for (int i = 0; i < TP; ++i) acc[j][i] = *reinterpret_cast<const floatx4 *>(mine + (j * TP + i) * 256 + lane * 4);
                 }
             }
         }
@@ -987,14 +1086,14 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
 // the tile shape that suits it -- BNB listed pixels per tile normally, BNS when even the deepest K
 // split of the big tiles would leave compute units idle (short lists): small tiles then need no
 // or fewer shared tiles, whose partial sums and reduction are pure overhead.
-template <int DT, int BM, int BNB, int WMB, int WNB, int SB, bool DB, int BNS, int WMS, int WNS, int SS, bool DS>
+template <int DT, int BM, int BNB, int WMB, int WNB, int SB, int BNS, int WMS, int WNS, int SS>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((NT + 255) / 256, (NT + 255) / 256))) void gemm_gather_kernel(GemmArgs a)
 {
     extern __shared__ __align__(16) float smem[];
     Selection sel = {nullptr, nullptr, 0};
     int n;
     if (a.sel_words > 0) {
-        char *base = reinterpret_cast<char *>(smem) + KernelSmem<BM, BNB, SB, BNS, SS>::sel_offset;
+        char *base = reinterpret_cast<char *>(smem) + KernelSmem<DT, BM, BNB, SB, BNS, SS>::sel_offset;
         uint64_t *sW = reinterpret_cast<uint64_t *>(base);
         int *sRank = reinterpret_cast<int *>(base + kSelSlots * 8);
         n = rank_selection(a, sW, sRank, sRank + kSelSlots, reinterpret_cast<uint64_t *>(smem));
@@ -1005,10 +1104,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((NT + 255) /
         n = *a.count;
     }
     const long long big_tiles = (long long)((n + BNB - 1) / BNB) * (a.Mpad / BM);
-    if (big_tiles * kSmallTileFactor >= (long long)gridDim.x)
-        gemm_gather_body<DT, BM, BNB, WMB, WNB, SB, DB>(a, n, smem, sel);
+    if (big_tiles * kSmallTileFactor<DT, BM> >= (long long)gridDim.x)
+        gemm_gather_body<DT, BM, BNB, WMB, WNB, SB>(a, n, smem, sel);
     else
-        gemm_gather_body<DT, BM, BNS, WMS, WNS, SS, DS>(a, n, smem, sel);
+        gemm_gather_body<DT, BM, BNS, WMS, WNS, SS>(a, n, smem, sel);
 }
 
 // ---- layers whose whole reduction fits a wave's registers ----------------------------------
@@ -1258,10 +1357,25 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((NT + 255) /
 // positions: the lone waves win as long as (groups of four units) x (channel tiles) stays at or
 // below 32 -- beyond that a wave's chain of MFMAs per tile gets long and the big tiles' reuse of
 // filter fragments pays.
-static bool gemm_is_thin(const GemmArgs &a)
+static bool is_thin(int dtype, int Mpad, int Kpad)
 {
-    const int nu = a.Kpad / elems_per_unit(a.dtype);
-    return nu <= kThinGroups * 4 && (a.Mpad == 16 || a.Mpad == 32 || a.Mpad == 64) && (nu / 4) * (a.Mpad / 16) <= kThinMaxWork;
+    const int nu = Kpad / elems_per_unit(dtype);
+    return nu <= kThinGroups * 4 && (Mpad == 16 || Mpad == 32 || Mpad == 64) && (nu / 4) * (Mpad / 16) <= kThinMaxWork;
+}
+static bool gemm_is_thin(const GemmArgs &a) { return is_thin(a.dtype, a.Mpad, a.Kpad); }
+
+bool gemm_filter_in_fragments(int dtype, int Mpad, int Kpad) { return !is_thin(dtype, Mpad, Kpad); }
+
+size_t gemm_filter_bytes(int dtype, int Mpad, int Kpad)
+{
+    return (size_t)Mpad * Kpad * (gemm_filter_in_fragments(dtype, Mpad, Kpad) && dtype == kF32 ? 6 : elem_bytes(dtype));
+}
+
+size_t gemm_filter_fragment(int dtype, int Mpad, int Kpad, int row, int k)
+{
+    const int ks = gemm_k_multiple(dtype);
+    return dtype == kF32 ? filter_fragment<kF32>(gemm_channel_tile(Mpad), Kpad / ks, row, k)
+                         : filter_fragment<kBF16>(gemm_channel_tile(Mpad), Kpad / ks, row, k);
 }
 
 // ---- host side --------------------------------------------------------------------------
@@ -1328,32 +1442,34 @@ int gemm_grid(const GemmArgs &a, int compute_units)
     const int parts = nk / kMinIters > 1 ? nk / kMinIters : 1;
     // with few pixels the small tile (64 pixels) is used: count those
     const long long big = (long long)((a.max_pixels + bn - 1) / bn) * (a.Mpad / bm);
-    const long long tiles = big * kSmallTileFactor >= W ? big : (long long)((a.max_pixels + 63) / 64) * (a.Mpad / bm);
+    const int factor = a.dtype == kF32 && bm == 128 ? kSmallTileFactor<kF32, 128> : kSmallTileFactor<kF32, 64>;
+    const long long tiles = big * factor >= W ? big : (long long)((a.max_pixels + 63) / 64) * (a.Mpad / bm);
     long long need = tiles >= W ? W : (tiles * parts + 7) / 8 * 8;
     if (need < 8) need = 8;
     return (int)(need < W ? need : W);
 }
 
-// BM; big tile (BN, WM, WN, ring slices, direct-to-LDS producers); small tile (the same)
-#define CBK_VARIANTS(X)                                         \
-    X(16, 256, 1, 8, 3, false, 128, 1, 8, 3, false)             \
-    X(32, 256, 1, 8, 3, false, 64, 2, 4, 3, false)              \
-    X(64, 256, 2, 4, 3, false, 64, 2, 4, 3, false)              \
-    X(64, 128, 2, 4, 3, false, 64, 2, 4, 3, false)              \
-    X(128, 128, 2, 4, 4, true, 64, 4, 2, 5, true)
+// storage type; BM; big tile (BN, WM, WN, ring slices); small tile (the same)
+#define CBK_VARIANTS(X)                                  \
+    X(kF32, 16, 256, 1, 8, 3, 128, 1, 8, 4)              \
+    X(kF32, 32, 256, 1, 8, 3, 64, 2, 4, 4)               \
+    X(kF32, 64, 256, 1, 8, 3, 64, 2, 4, 5)               \
+    X(kF32, 64, 128, 1, 8, 4, 64, 2, 4, 5)               \
+    X(kF32, 128, 128, 2, 4, 3, 64, 4, 2, 4)              \
+    X(kBF16, 16, 256, 1, 8, 3, 128, 1, 8, 4)             \
+    X(kBF16, 32, 256, 1, 8, 3, 64, 2, 4, 4)              \
+    X(kBF16, 64, 256, 2, 4, 3, 64, 2, 4, 5)              \
+    X(kBF16, 64, 128, 2, 4, 4, 64, 2, 4, 5)              \
+    X(kBF16, 128, 128, 2, 4, 4, 64, 4, 2, 5)
 
 hipError_t gemm_prepare(void)
 {
     hipError_t e = hipSuccess;
-#define X(BM_, BNB_, WMB_, WNB_, SB_, DB_, BNS_, WMS_, WNS_, SS_, DS_)                                                        \
-    if (e == hipSuccess)                                                                                                      \
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(                                                               \
-                                    &gemm_gather_kernel<kF32, BM_, BNB_, WMB_, WNB_, SB_, DB_, BNS_, WMS_, WNS_, SS_, DS_>),   \
-                                hipFuncAttributeMaxDynamicSharedMemorySize, KernelSmem<BM_, BNB_, SB_, BNS_, SS_>::bytes);    \
-    if (e == hipSuccess)                                                                                                      \
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(                                                               \
-                                    &gemm_gather_kernel<kBF16, BM_, BNB_, WMB_, WNB_, SB_, DB_, BNS_, WMS_, WNS_, SS_, DS_>),  \
-                                hipFuncAttributeMaxDynamicSharedMemorySize, KernelSmem<BM_, BNB_, SB_, BNS_, SS_>::bytes);
+#define X(DT_, BM_, BNB_, WMB_, WNB_, SB_, BNS_, WMS_, WNS_, SS_)                                                         \
+    if (e == hipSuccess)                                                                                                  \
+        e = hipFuncSetAttribute(                                                                                          \
+            reinterpret_cast<const void *>(&gemm_gather_kernel<DT_, BM_, BNB_, WMB_, WNB_, SB_, BNS_, WMS_, WNS_, SS_>),  \
+            hipFuncAttributeMaxDynamicSharedMemorySize, KernelSmem<DT_, BM_, BNB_, SB_, BNS_, SS_>::bytes);
     CBK_VARIANTS(X)
 #undef X
 #define T(DT_, MT_)                                                                                                \
@@ -1365,19 +1481,6 @@ hipError_t gemm_prepare(void)
     return e;
 }
 
-template <int BM, int BNB, int WMB, int WNB, int SB, bool DB, int BNS, int WMS, int WNS, int SS, bool DS>
-static hipError_t launch(hipStream_t st, const GemmArgs &a, const Timing &tm)
-{
-    constexpr int smem_bytes = KernelSmem<BM, BNB, SB, BNS, SS>::bytes;
-    if (a.dtype == kBF16)
-        launch_kernel(tm, gemm_gather_kernel<kBF16, BM, BNB, WMB, WNB, SB, DB, BNS, WMS, WNS, SS, DS>, dim3(a.grid),
-                      dim3(NT), smem_bytes, st, a);
-    else
-        launch_kernel(tm, gemm_gather_kernel<kF32, BM, BNB, WMB, WNB, SB, DB, BNS, WMS, WNS, SS, DS>, dim3(a.grid),
-                      dim3(NT), smem_bytes, st, a);
-    return hipGetLastError();
-}
-
 hipError_t gemm_gather(hipStream_t st, const GemmArgs &a, const Timing &tm)
 {
     const int bm = gemm_channel_tile(a.M), bn = pixel_tile(bm, a.max_pixels);
@@ -1385,8 +1488,6 @@ hipError_t gemm_gather(hipStream_t st, const GemmArgs &a, const Timing &tm)
     if (a.Mpad % bm != 0 || a.Kpad % gemm_k_multiple(a.dtype) != 0 || a.Ms % eu != 0 || a.pix_words < 1 || !a.partial ||
         !a.tickets || a.grid < 8 || (a.grid & 7) || a.grid > kMaxGrid)
         return hipErrorInvalidValue;
-    // the direct-to-LDS producers address a channel tile's filter rows with 32-bit byte offsets
-    if ((long long)bm * a.Kpad * 4 >= (1ll << 32)) return hipErrorInvalidValue;
     // the divisors must belong to these arguments, and the schedule's 32-bit arithmetic must hold
     if (a.kh < 1 || a.kw < 1 || a.dKw.d != a.kw || a.dVin.d != (a.pix_words + 3) / 4) return hipErrorInvalidValue;
     if (a.dNo.d != a.No || a.dWo.d != a.Wo || a.dHo.d * a.Wo != a.No || a.dGrid.d != a.grid ||
@@ -1409,8 +1510,12 @@ hipError_t gemm_gather(hipStream_t st, const GemmArgs &a, const Timing &tm)
         T(kF32, 1) T(kF32, 2) T(kF32, 4) T(kBF16, 1) T(kBF16, 2) T(kBF16, 4)
 #undef T
     }
-#define X(BM_, BNB_, WMB_, WNB_, SB_, DB_, BNS_, WMS_, WNS_, SS_, DS_) \
-    if (bm == BM_ && bn == BNB_) return launch<BM_, BNB_, WMB_, WNB_, SB_, DB_, BNS_, WMS_, WNS_, SS_, DS_>(st, a, tm);
+#define X(DT_, BM_, BNB_, WMB_, WNB_, SB_, BNS_, WMS_, WNS_, SS_)                                                        \
+    if (a.dtype == DT_ && bm == BM_ && bn == BNB_) {                                                                     \
+        launch_kernel(tm, gemm_gather_kernel<DT_, BM_, BNB_, WMB_, WNB_, SB_, BNS_, WMS_, WNS_, SS_>, dim3(a.grid),      \
+                      dim3(NT), (KernelSmem<DT_, BM_, BNB_, SB_, BNS_, SS_>::bytes), st, a);                             \
+        return hipGetLastError();                                                                                        \
+    }
     CBK_VARIANTS(X)
 #undef X
     return hipErrorInvalidValue;

@@ -1,0 +1,67 @@
+"""float32 layers multiplied as sums of bfloat16 parts (every layer but those of short filter rows): the
+rounding error against 64 bits over the tile shapes, and sums that are not finite."""
+import numpy as np
+import pytest
+
+import paper_1704_04313_amd as cb
+from workloads.networks import conv, make_weights
+
+from gpu_util import to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _reference(L, w, b, x):
+    import torch
+    y = torch.nn.functional.conv2d(torch.from_numpy(x.astype(np.float64))[None], torch.from_numpy(w.astype(np.float64)),
+                                   torch.from_numpy(b.astype(np.float64)), stride=L.stride, padding=L.pad)[0].numpy()
+    return np.maximum(y, 0) if L.relu else y
+
+
+def _dense(L, params, x):
+    net = cb.CBInfer([L], params, x.shape, 0.02)
+    try:
+        net.set_mode(True)
+        return net.process_frame(to_dev(x)).cpu().numpy()[0].astype(np.float64)
+    finally:
+        net.destroy()
+
+
+# channels around the 16 / 32 / 64 / 128 channel tiles, positions around the 64 / 128 / 256 pixel tiles, rows of
+# one slice to 98, taps that straddle slices (cin not a multiple of 32), several rounds of whole tiles
+@pytest.mark.parametrize("cin,cout,k,h,w", [
+    (64, 16, 3, 9, 7), (96, 16, 5, 33, 31), (64, 20, 5, 16, 16), (48, 32, 3, 65, 64), (16, 64, 7, 8, 8),
+    (16, 64, 7, 129, 131), (256, 64, 1, 17, 15), (40, 33, 3, 41, 25), (64, 65, 3, 13, 10), (64, 256, 7, 12, 11),
+    (24, 100, 3, 127, 129), (512, 128, 3, 5, 3), (128, 320, 1, 23, 29), (256, 130, 3, 61, 83)])
+def test_error_against_64_bits(cin, cout, k, h, w):
+    L = conv(cin, cout, k, relu=False)
+    (wt, b), = make_weights([L], 7 * cin + cout)
+    x = np.maximum(np.random.default_rng(cin + h).standard_normal((cin, h, w)), 0).astype(np.float32)
+    got, want = _dense(L, [(wt, b)], x), _reference(L, wt, b, x)
+    slices = (cin * k * k + 31) // 32
+    # each slice's 32 products are added to the leading sum with one rounding (half a unit of 2^-23 of it at most,
+    # doubled for what the matrix unit rounds inside), the corrections and the dropped products add 2^-22 once
+    size = _reference(conv(cin, cout, k, relu=False), np.abs(wt), np.abs(b), np.abs(x))
+    assert np.all(np.abs(got - want) <= (slices + 8) * 2.0 ** -23 * size)
+    # roundings of either sign: they add up like their square root
+    assert np.linalg.norm(got - want) <= np.sqrt(slices + 8) * 2.0 ** -24 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("cin,cout,k,h,w", [(64, 256, 7, 17, 19), (16, 64, 7, 40, 40), (64, 20, 5, 16, 16)])
+@pytest.mark.parametrize("special", [np.inf, -np.inf, np.nan, 3.4028e38, -3.4e38])
+def test_values_that_are_not_finite(cin, cout, k, h, w, special):
+    L = conv(cin, cout, k, relu=False)
+    (wt, b), = make_weights([L], cin)
+    wt[::3] = np.round(wt[::3] * 64) / 64  # weights of one part, zeros among them
+    wt[1::3, :, 0, 0] = 0.0
+    x = np.random.default_rng(3).random((cin, h, w), dtype=np.float32)
+    for n in range(3):
+        x[(7 * n) % cin, (k * n + 1) % h, (k * n + 2) % w] = special
+    with np.errstate(all="ignore"):
+        want = _reference(L, wt, b, x).astype(np.float32).astype(np.float64)
+    got = _dense(L, [(wt, b)], x)
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(want))
+    np.testing.assert_array_equal(np.isinf(got) * np.sign(got), np.isinf(want) * np.sign(want))
+    fine = np.isfinite(want)
+    size = _reference(L, np.abs(wt), np.abs(b), np.where(np.isfinite(x), np.abs(x), 0))
+    assert np.all(np.abs(got - want)[fine] <= ((cin * k * k + 40) * 2.0 ** -23 * size)[fine])
