@@ -62,14 +62,13 @@ struct Plan {
     int S = 1, in_c = 0, in_h = 0, in_w = 0;
     bool hold = false;
     int dtype = cbk::kF32; // storage of maps and filter matrices
-    size_t o_iota = 0, o_const = 0, o_partial = 0, o_tickets = 0;
+    size_t o_partial = 0, o_tickets = 0;
     bool pipeline = false;     // two sets of per-frame scratch, so that consecutive frames may overlap
     size_t o_set0 = 0;         // first byte of the per-frame scratch (everything a frame writes except the stored maps)
     size_t set_bytes = 0;      // its size; with `pipeline` a second set follows directly behind it
     size_t o_flags = 0;        // the byte change maps of all layers behind the first, contiguous
     long long flag_words = 0;  // their total size in 64-bit words
     int compute_units = 256; // sizes the GEMM grids; the device's count replaces it in cbinfer_create if that is smaller
-    int iota_len = 0;
     size_t bytes = 0;
 };
 
@@ -128,7 +127,6 @@ int make_plan(const cbinfer_network *net, float threshold, bool need_threshold, 
     P.ops.clear();
     int c = net->in_c, h = net->in_h, w = net->in_w;
     const long long lim = (1ll << 31) - 1;
-    long long max_px = 0;
     for (int l = 0; l < net->n_layers; ++l) {
         const cbinfer_layer &L = net->layers[l];
         Op op;
@@ -194,7 +192,6 @@ int make_plan(const cbinfer_network *net, float threshold, bool need_threshold, 
         const long long out_elems = (long long)P.S * op.Ho * op.Wo * (L.kind == CBINFER_OP_CONV ? op.Ms : op.Ms);
         if (in_elems > lim || out_elems > lim || (long long)op.Mpad * op.Kpad > lim)
             return fail(CBINFER_EUNSUPPORTED, "layer %d: a map or the filter matrix exceeds 2^31-1 elements", l);
-        max_px = std::max(max_px, std::max((long long)P.S * op.H * op.W, (long long)P.S * op.Ho * op.Wo));
         P.ops.push_back(op);
     }
     // workspace layout: what persists from frame to frame first ...
@@ -214,9 +211,6 @@ int make_plan(const cbinfer_network *net, float threshold, bool need_threshold, 
             op.o_taps = cv.take((size_t)op.Kpad / eu * sizeof(int2));
         }
     }
-    P.iota_len = (int)max_px;
-    P.o_iota = cv.take((size_t)P.iota_len * 4);
-    P.o_const = cv.take(P.ops.size() * 2 * 4);
     // ... then everything a frame writes besides the stored maps: change maps, index lists, counters,
     // the multiplication kernel's partial sums and tickets.  Two such sets when consecutive frames
     // may overlap; state->at() picks the set of the frame in hand.
@@ -591,8 +585,6 @@ int enqueue_frame(cbinfer_state *s, const float *frame, float *out)
     const bool first = !s->initialised;
     s->lists_stale = false;
     const int S = P.S;
-    int *iota = s->at<int>(P.o_iota);
-    int *consts = s->at<int>(P.o_const);
     const int nops = (int)P.ops.size();
 
     for (int l = 0; l < nops; ++l) {
@@ -628,8 +620,7 @@ int enqueue_frame(cbinfer_state *s, const float *frame, float *out)
                 }
             }
             if (l > 0) HIP_TRY(after_previous(l));
-            const int *ulist = iota;
-            const int *ucount = consts + 2 * l;
+            const int *ulist = nullptr, *ucount = nullptr; // every position, unless there is change detection
             const uint64_t *sel_map = nullptr;
             int sel_bytes = 0, sel_dilate = 0;
             if (!s->force_dense) {
@@ -643,8 +634,6 @@ int enqueue_frame(cbinfer_state *s, const float *frame, float *out)
                     sel_map = m.in_gemm ? m.chg : m.upd;
                     sel_bytes = m.in_gemm ? m.chg_bytes : m.upd_bytes;
                     sel_dilate = m.in_gemm ? 1 : 0;
-                    ulist = nullptr;
-                    ucount = nullptr;
                     s->lists_stale = true;
                 } else {
                     StepTimer t(s, l, CBINFER_STEP_COMPACT);
@@ -694,8 +683,8 @@ int enqueue_frame(cbinfer_state *s, const float *frame, float *out)
             HIP_TRY(after_previous(l));
             const Op &cv = P.ops[op.conv_before];
             const int Np = op.Ho * op.Wo;
-            const int *plist = s->force_dense ? iota : s->at<int>(op.o_ulist);
-            const int *pcount = s->force_dense ? consts + 2 * l : s->at<int>(op.o_counts) + 1;
+            const int *plist = s->force_dense ? nullptr : s->at<int>(op.o_ulist);
+            const int *pcount = s->force_dense ? nullptr : s->at<int>(op.o_counts) + 1;
             unsigned char *next_flags = nullptr;
             float next_tau = 0.f;
             if (l + 1 < nops && P.ops[l + 1].kind == CBINFER_OP_CONV && fuses_detection(P, l + 1, s->force_dense)) {
@@ -810,10 +799,8 @@ static cbinfer_state *create_state(const cbinfer_network *net, const Plan &P, ch
         std::vector<unsigned char> wt;
         std::vector<float> bias;
         std::vector<int2> taps;
-        std::vector<int> consts(P.ops.size() * 2, 0);
         for (size_t l = 0; l < P.ops.size(); ++l) {
             const Op &op = P.ops[l];
-            consts[2 * l] = P.S * op.Ho * op.Wo;
             if (op.kind != CBINFER_OP_CONV) continue;
             const cbinfer_layer &L = net->layers[l];
             build_filter_matrix(op, P.dtype, static_cast<const float *>(L.weight), wt);
@@ -827,8 +814,6 @@ static cbinfer_state *create_state(const cbinfer_network *net, const Plan &P, ch
             HIP_TRY(hipMemcpyAsync(s->at<int2>(op.o_taps), taps.data(), taps.size() * sizeof(int2), hipMemcpyHostToDevice, s->stream));
             HIP_TRY(hipStreamSynchronize(s->stream));
         }
-        HIP_TRY(hipMemcpyAsync(s->at<int>(P.o_const), consts.data(), consts.size() * 4, hipMemcpyHostToDevice, s->stream));
-        HIP_TRY(cbk::fill_iota(s->stream, s->at<int>(P.o_iota), P.iota_len));
         HIP_TRY(hipStreamSynchronize(s->stream));
         return CBINFER_OK;
     };
@@ -1088,9 +1073,8 @@ int cbinfer_read_list(cbinfer_state *s, int layer, int which, int32_t *host, int
     HIP_TRY(hipStreamSynchronize(s->work));
     int count = 0;
     const int *src = nullptr;
-    if (s->force_dense) {
+    if (s->force_dense) { // every position
         count = which == CBINFER_LIST_CHANGED ? s->plan.S * op.H * op.W : s->plan.S * op.Ho * op.Wo;
-        src = s->at<int>(s->plan.o_iota);
     } else {
         HIP_TRY(hipMemcpy(&count, s->at<int>(op.o_counts) + (which == CBINFER_LIST_CHANGED ? 0 : 1), 4,
                           hipMemcpyDeviceToHost));
@@ -1098,7 +1082,9 @@ int cbinfer_read_list(cbinfer_state *s, int layer, int which, int32_t *host, int
     }
     if (n) *n = count;
     const int64_t m = count < cap ? count : cap;
-    if (m > 0) HIP_TRY(hipMemcpy(host, src, (size_t)m * 4, hipMemcpyDeviceToHost));
+    if (m > 0 && src) HIP_TRY(hipMemcpy(host, src, (size_t)m * 4, hipMemcpyDeviceToHost));
+    if (!src)
+        for (int64_t i = 0; i < m; ++i) host[i] = (int32_t)i;
     return CBINFER_OK;
 }
 

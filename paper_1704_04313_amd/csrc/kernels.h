@@ -189,7 +189,7 @@ struct GemmArgs {
                         //   .x = offset of that unit, in 4-byte words, from the window origin in the input map,
                         //   .y = j | i << 8 | valid << 16
     const int *list;    // output pixels to recompute
-    const int *count;   // their number (device)
+    const int *count;   // their number (device); both null: all max_pixels of them, in order
     // Alternative to list/count for maps of at most gemm_select_max_words() words: the map of
     // outputs to recompute itself (bit g of word g/64, or one byte per pixel when sel_bytes != 0,
     // padded to whole words).  Every workgroup then ranks the set positions itself and picks those
@@ -255,6 +255,7 @@ hipError_t gemm_gather(hipStream_t st, const GemmArgs &a, const Timing &tm = Tim
 // this very map; compare each recomputed value with the one it replaces against next_tau and set
 // the position's byte in that layer's change map (one byte per pixel, zeroed at the start of the frame).
 // next_force != 0: flag every recomputed position (first frame).
+// list and count null: all max_count positions.
 hipError_t pool_sparse(hipStream_t st, const int *list, const int *count, int max_count, const void *in,
                        void *pooled, int V, int k, int Wo, int No, int Wp, int Np, unsigned char *next_flags,
                        float next_tau, int next_force, int dtype, const Timing &tm = Timing());
@@ -268,8 +269,5 @@ hipError_t pool_masked(hipStream_t st, const uint64_t *bits, int from_outputs, i
 // ---- stored map -> caller's planar output --------------------------------------------------
 hipError_t map_to_planar(hipStream_t st, const void *map, float *planar, int M, int V, int No, int S, int dtype,
                          const Timing &tm = Timing());
-
-// helpers
-hipError_t fill_iota(hipStream_t st, int *list, int n);
 
 } // namespace cbk

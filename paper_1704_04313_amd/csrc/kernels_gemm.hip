@@ -8,7 +8,8 @@
 // the channel-contiguous input map, multiplies on the matrix cores and scatters bias + ReLU
 // results straight into the stored map.  The reduced X never exists in HBM.
 //
-// Which positions: from an index list, or -- for maps small enough to be held in LDS -- from the
+// Which positions: all of them in order (dense evaluation: nothing to wait for; reading an identity list
+// cost every tile two dependent round trips to memory), from an index list, or -- for maps small enough to be held in LDS -- from the
 // map itself.  Every workgroup then loads the map of positions to recompute (or the layer's
 // change map, which it first dilates by the filter support), ranks it with popcounts and a scan,
 // and picks the positions whose rank falls into its tile: the index extraction and the dilation
@@ -707,7 +708,7 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
         } else {
             for (int i = tid; i < BN; i += NT) {
                 const int u = pt * BN + i;
-                sU[i] = (u < n) ? a.list[u] : -1;
+                sU[i] = u < n ? (a.list ? a.list[u] : u) : -1;
             }
         }
         __syncthreads();
@@ -1101,7 +1102,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((NT + 255) /
         sel.rank = sRank;
         sel.nwords = a.sel_words;
     } else {
-        n = *a.count;
+        n = a.count ? *a.count : a.max_pixels;
     }
     const long long big_tiles = (long long)((n + BNB - 1) / BNB) * (a.Mpad / BM);
     if (big_tiles * kSmallTileFactor<DT, BM> >= (long long)gridDim.x)
@@ -1183,7 +1184,7 @@ __device__ __forceinline__ void thin_tiles(const GemmArgs &a, const int n, const
     auto locate = [&](int t) {
         const int r = (t >> cshift) * 16 + lrow;
         Where p = {-1, -(1 << 28), -(1 << 28), 0};
-        if (r < n) p.g = sel.words ? select_rank(sel, r) : a.list[r];
+        if (r < n) p.g = sel.words ? select_rank(sel, r) : (a.list ? a.list[r] : r);
         if (p.g >= 0) {
             const int st = fast_div(p.g, a.dNo), q = p.g - st * a.No;
             const int qy = fast_div(q, a.dWo), qx = q - qy * a.Wo;
@@ -1341,7 +1342,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((NT + 255) /
         sel.rank = sRank;
         sel.nwords = a.sel_words;
     } else {
-        n = *a.count;
+        n = a.count ? *a.count : a.max_pixels;
     }
     __syncthreads();
     if constexpr (MT > 1) {
@@ -1499,7 +1500,7 @@ hipError_t gemm_gather(hipStream_t st, const GemmArgs &a, const Timing &tm)
          (long long)a.sel_in_words * 64 < (long long)a.S * a.N || a.No % a.Wo != 0))
         return hipErrorInvalidValue;
     if (a.sel_words < 0 || a.sel_words > kSelMaxWords || (a.sel_words > 0 && !a.sel_map) ||
-        (a.sel_words == 0 && (!a.list || !a.count)) || (long long)a.sel_words * 64 < a.max_pixels * (a.sel_words > 0))
+        (a.sel_words == 0 && !a.list != !a.count) || (long long)a.sel_words * 64 < a.max_pixels * (a.sel_words > 0))
         return hipErrorInvalidValue;
     if (gemm_is_thin(a)) {
 #define T(DT_, MT_)                                                                                      \

@@ -1127,13 +1127,13 @@ __device__ __forceinline__ void pool_batch_2x2(const bool (&active)[kPoolBatch],
 
 template <int DT>
 __global__ __launch_bounds__(kBlock) void pool_sparse_kernel(const int *__restrict__ list,
-                                                             const int *__restrict__ count,
+                                                             const int *__restrict__ count, int max_count,
                                                              const uint4 *__restrict__ in,
                                                              uint4 *__restrict__ pooled, PoolGeom pg,
                                                              unsigned char *__restrict__ next_flags,
                                                              float next_tau, int next_force)
 {
-    const int total = *count * pg.V; // units: below 2^30 (checked by the host)
+    const int total = (count ? *count : max_count) * pg.V; // units: below 2^30 (checked by the host)
     const int step = (int)gridDim.x * kBlock;
     // whole waves iterate together (the last round with some lanes inactive)
     if (pg.k == 2) {
@@ -1146,7 +1146,7 @@ __global__ __launch_bounds__(kBlock) void pool_sparse_kernel(const int *__restri
                 active[k] = idx < total;
                 const int u = active[k] ? fast_div((int)idx, pg.dV) : 0;
                 v[k] = active[k] ? (int)idx - u * pg.V : 0;
-                g[k] = active[k] ? list[u] : 0;
+                g[k] = active[k] ? (list ? list[u] : u) : 0;
             }
             pool_batch_2x2<DT>(active, g, v, in, pooled, pg, next_flags, next_tau, next_force);
         }
@@ -1156,7 +1156,7 @@ __global__ __launch_bounds__(kBlock) void pool_sparse_kernel(const int *__restri
         const int idx = i0 + (int)threadIdx.x;
         const bool active = idx < total;
         const int u = active ? fast_div(idx, pg.dV) : 0, v = active ? idx - u * pg.V : 0;
-        const int g = active ? list[u] : 0;
+        const int g = active ? (list ? list[u] : u) : 0;
         pool_unit<DT>(active, g, v, in, pooled, pg, next_flags, next_tau, next_force);
     }
 }
@@ -1216,7 +1216,7 @@ hipError_t pool_sparse(hipStream_t st, const int *list, const int *count, int ma
                        float next_tau, int next_force, int dtype, const Timing &tm)
 {
     long long work = (long long)max_count * V;
-    if (work >= (1ll << 30) || V < 1 || Np < 1 || Wp < 1) return hipErrorInvalidValue; // 32-bit indices, with room for the grid stride
+    if (work >= (1ll << 30) || V < 1 || Np < 1 || Wp < 1 || !list != !count) return hipErrorInvalidValue; // 32-bit indices, with room for the grid stride
     const PoolGeom pg = pool_geom(V, k, Wo, No, Wp, Np);
     const int per_thread = k == 2 ? kPoolBatch : 1;
     long long grid = (work + (long long)kBlock * per_thread - 1) / ((long long)kBlock * per_thread);
@@ -1225,10 +1225,10 @@ hipError_t pool_sparse(hipStream_t st, const int *list, const int *count, int ma
     const uint4 *i4 = static_cast<const uint4 *>(in);
     uint4 *p4 = static_cast<uint4 *>(pooled);
     if (dtype == kBF16)
-        launch_kernel(tm, pool_sparse_kernel<kBF16>, dim3((int)grid), dim3(kBlock), 0, st, list, count, i4, p4, pg,
+        launch_kernel(tm, pool_sparse_kernel<kBF16>, dim3((int)grid), dim3(kBlock), 0, st, list, count, max_count, i4, p4, pg,
                       next_flags, next_tau, next_force);
     else
-        launch_kernel(tm, pool_sparse_kernel<kF32>, dim3((int)grid), dim3(kBlock), 0, st, list, count, i4, p4, pg,
+        launch_kernel(tm, pool_sparse_kernel<kF32>, dim3((int)grid), dim3(kBlock), 0, st, list, count, max_count, i4, p4, pg,
                       next_flags, next_tau, next_force);
     return hipGetLastError();
 }
@@ -1339,20 +1339,6 @@ hipError_t map_to_planar(hipStream_t st, const void *map, float *planar, int M, 
     else
         launch_kernel(tm, map_to_planar_kernel<kF32>, dim3((int)grid), dim3(kBlock), 0, st, m4, planar, M, V, No,
                       (int)total, dNo, dV);
-    return hipGetLastError();
-}
-
-__global__ void iota_kernel(int *list, int n)
-{
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) list[i] = i;
-}
-
-hipError_t fill_iota(hipStream_t st, int *list, int n)
-{
-    int grid = (n + 255) / 256;
-    if (grid > 1024) grid = 1024;
-    if (grid < 1) grid = 1;
-    launch_kernel(Timing(), iota_kernel, dim3(grid), dim3(256), 0, st, list, n);
     return hipGetLastError();
 }
 
