@@ -40,8 +40,8 @@
 // Work distribution: one workgroup per compute unit.  Output tiles are dealt out whole as long
 // as every workgroup gets one; the (tiles mod workgroups) left over are cut along K into
 // equal iteration ranges, one per workgroup, so that all compute units finish together whatever
-// the number of positions is.  A workgroup that computed only part of a tile's K range stores its
-// partial accumulators; the last workgroup to finish a tile (an atomic ticket, nobody waits)
+// the number of positions is.  A wave that computed only part of a sub-tile's K range stores its
+// partial accumulators; the last wave to finish a sub-tile (an atomic ticket, nobody waits)
 // adds all parts in ascending K order, which keeps results deterministic, and performs the
 // output update.
 //
@@ -104,13 +104,16 @@ template <int DT>
 static constexpr int kFilterParts = DT == kBF16 ? 2 : 3;
 static constexpr int kFragBytes = 1024; // one fragment: 64 lanes x 16 bytes
 
-// LDS of one tile shape: a ring of STAGES K slices of both operands, then the tile's pixel list,
-// the ticket and two ints for the tile selection.
+// LDS of one tile shape: a ring of STAGES K slices of both operands, then pixel lists.
 template <int DT, int BM, int BN, int STAGES>
 struct TileSmem {
     static constexpr int a_floats = BN * LDK;
     static constexpr int b_floats = BM / 16 * kFilterParts<DT> * kFragBytes / 4;
-    static constexpr int tile_bytes = STAGES * (a_floats + b_floats) * 4 + BN * 4 + 16;
+    // Pixel lists: of the segment the consumers finish and of those that the slices after it belong to.
+    // A segment has a slice at least; of the 64-channel tiles in float32 (rows of five slices or more, the
+    // shorter ones are the thin kernel's) at most two can be that short in a row, and LDS has no room for more.
+    static constexpr int lists = DT == kF32 && BM == 64 && BN == 256 ? 3 : STAGES + 1;
+    static constexpr int tile_bytes = STAGES * (a_floats + b_floats) * 4 + lists * BN * 4;
 };
 // LDS of a kernel instantiation (a big and a small tile shape share it): behind the larger of the
 // two tiles the selection map's words, their exclusive ranks, and the wave totals of the scan.
@@ -347,34 +350,26 @@ __device__ __forceinline__ int rank_selection(const GemmArgs &a, uint64_t *sW, i
     return total;
 }
 
-// The selected pixels of rank r0 .. r0 + BN - 1 into sU (-1 where the selection ends before).
-// sRange: two ints of LDS.  All NT threads take part.
-template <int BN>
-__device__ __forceinline__ void select_tile(const Selection &sel, int n, int r0, int *sU, int *sRange)
+// The position of rank r (0 <= r < number of selected positions) in a ranked selection map.
+__device__ __forceinline__ int select_rank(const Selection &sel, int r)
 {
-    const int tid = threadIdx.x;
-    const int r1 = (r0 + BN < n ? r0 + BN : n) - 1; // last rank wanted (r0 <= r1: the tile is not empty)
-    for (int i = tid; i < BN; i += NT) sU[i] = -1;
-    // the words holding rank r0 and rank r1: each is found by the one thread that ranks it
+    // the last word whose exclusive rank is <= r holds it: later words start at a higher rank,
+    // and of the words sharing its rank it is the last (the others are empty)
+    int w = 0;
 #pragma unroll
-    for (int j = 0; j < kSelWordsPerThread; ++j) {
-        const int i = kSelWordsPerThread * tid + j;
-        if (i >= kSelSlots) break;
-        const int e = sel.rank[i], c = __popcll(sel.words[i]);
-        if (e <= r0 && r0 < e + c) sRange[0] = i;
-        if (e <= r1 && r1 < e + c) sRange[1] = i;
-    }
-    __syncthreads();
-    const int wlo = sRange[0], whi = sRange[1];
-    // one lane per pixel of those words
-    for (int idx = tid; idx < (whi - wlo + 1) * 64; idx += NT) {
-        const int i = wlo + (idx >> 6), b = idx & 63;
-        const uint64_t bits = sel.words[i];
-        if ((bits >> b) & 1ull) {
-            const int r = sel.rank[i] + __popcll(bits & ((1ull << b) - 1ull)) - r0;
-            if ((unsigned)r < (unsigned)BN) sU[r] = i * 64 + b;
+    for (int step = kSelMaxWords; step; step >>= 1)
+        if (w + step < sel.nwords && sel.rank[w + step] <= r) w += step;
+    const uint64_t bits = sel.words[w];
+    int k = r - sel.rank[w], pos = 0; // the k-th set bit of the word, counted from 0
+#pragma unroll
+    for (int sh = 32; sh; sh >>= 1) {
+        const int c = __popcll((bits >> pos) & ((1ull << sh) - 1ull));
+        if (k >= c) {
+            k -= c;
+            pos += sh;
         }
     }
+    return w * 64 + pos;
 }
 
 // The split of one launch's work over W workgroups; a pure function of its arguments.  32-bit
@@ -388,6 +383,17 @@ struct Schedule {
     int iters; // rem * nk: K-slice iterations of the left-over tiles
     int q, r;  // iters = q * wr + r
 };
+
+// a / b for 0 <= a < 2^30, b >= 1 and quotients below 2^20: the estimate in float is off by one at most
+// (the division that the compiler makes of an integer one takes about four times as long).
+__device__ __forceinline__ int small_div(int a, int b)
+{
+    int q = (int)((float)a * __builtin_amdgcn_rcpf((float)b));
+    const int r = a - q * b;
+    if (r < 0) --q;
+    if (r >= b) ++q;
+    return __builtin_amdgcn_readfirstlane(q); // its arguments are the same for the whole workgroup
+}
 
 __device__ __forceinline__ Schedule make_schedule(int n, int bn, int mtiles, int nk, const FastDiv &dW)
 {
@@ -404,7 +410,7 @@ __device__ __forceinline__ Schedule make_schedule(int n, int bn, int mtiles, int
     const int max_parts = nk / kMinIters > 1 ? nk / kMinIters : 1;
     int wr = 1;
     if (s.rem > 0) {
-        int p = W / s.rem;
+        int p = small_div(W, s.rem);
         if (p > max_parts) p = max_parts;
         if (p < 1) p = 1;
         wr = s.rem * p;
@@ -412,13 +418,13 @@ __device__ __forceinline__ Schedule make_schedule(int n, int bn, int mtiles, int
         if (wr > W) wr = W;
     }
     s.wr = wr;
-    s.q = s.iters / wr;
+    s.q = small_div(s.iters, wr);
     s.r = s.iters - s.q * wr;
     return s;
 }
 
 // First iteration of workgroup w's share: floor(iters * w / wr), and the workgroup owning an iteration.
-__device__ __forceinline__ int share_begin(const Schedule &s, int w) { return s.q * w + s.r * w / s.wr; }
+__device__ __forceinline__ int share_begin(const Schedule &s, int w) { return s.q * w + small_div(s.r * w, s.wr); }
 
 __device__ __forceinline__ int share_owner(const Schedule &s, int it)
 {
@@ -456,43 +462,130 @@ __device__ __forceinline__ void producer_barrier()
 typedef __attribute__((address_space(1))) const void *GlobalPtr;
 typedef __attribute__((address_space(3))) void *LdsPtr;
 
-// Producer waves, direct-to-LDS variant: global_load_lds_dwordx4 moves 16 bytes per lane from
-// global memory into LDS without passing through registers -- lane l of an instruction lands at
-// the wave-uniform LDS base + 16 l, i.e. in slot l & 7 of row l >> 3 of eight consecutive rows --
-// so the producers only compute addresses.  Wave pw covers rows 8 pw .. 8 pw + 7 of every pass of
-// kRP rows; vf is the unit column this lane fetches (its slot with the row permutation undone).
-// The ring holds STAGES slices: slice kc + STAGES - 1 is issued in iteration kc into the slot
-// that slice kc - 1 occupied, and has to have landed by the barrier that ends iteration
-// kc + STAGES - 3 (the consumers read the first fragments of a slice one iteration early).  The
-// loads of a wave complete in order, so "at most (STAGES - 3) slices' worth of instructions
-// outstanding" means slice kc + 2 is in LDS.  No LDS reads and no other vector memory
-// instructions occur in this loop, which keeps the instruction count per slice exact.
+// s_waitcnt lgkmcnt(0), everything else unconstrained.
+__device__ __forceinline__ void wait_lgkmcnt0() { __builtin_amdgcn_s_waitcnt(0xC07F); }
+
+// The workgroup barrier as the consumers execute it: their LDS reads are complete (the slice they read
+// may be overwritten), stores to global memory need not be.
+__device__ __forceinline__ void consumer_barrier()
+{
+    asm volatile("" ::: "memory");
+    wait_lgkmcnt0();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// The work of one workgroup: first whole tiles, then its share of the K ranges of the left-over ones.  A
+// segment is a tile with the range of K slices to multiply.  Producers and consumers each walk it.
+struct Segment {
+    int tile, kc0, kc1, shared_j; // shared_j: index among the left-over tiles, or -1
+};
+struct Walk {
+    Schedule sch;
+    int W, nk, w;         // workgroups; slices per tile; this workgroup's number in the whole rounds
+    int wsh;              // ... and among those that share the left-over tiles
+    int it_begin, it_end; // its iterations of those
+    int slices;           // K slices of all its segments
+    int round, it;        // the cursor
+
+    __device__ __forceinline__ bool next(const GemmArgs &a, Segment &s)
+    {
+        if (round < sch.whole) {
+            s.tile = round * W + w;
+            s.kc0 = 0;
+            s.kc1 = nk;
+            s.shared_j = -1;
+            ++round;
+            return true;
+        }
+        if (it >= it_end) return false;
+        s.shared_j = fast_div(it, a.dNk);
+        s.kc0 = it - s.shared_j * nk;
+        const int left = it_end - it;
+        s.kc1 = left < nk - s.kc0 ? s.kc0 + left : nk;
+        s.tile = sch.whole * W + s.shared_j;
+        it += s.kc1 - s.kc0;
+        return true;
+    }
+};
+
+// Producer waves: global_load_lds_dwordx4 moves 16 bytes per lane from global memory into LDS without
+// passing through registers -- lane l of an instruction lands at the wave-uniform LDS base + 16 l, i.e.
+// in slot l & 7 of row l >> 3 of eight consecutive rows -- so the producers only compute addresses.
+// Wave pw covers rows 8 pw .. 8 pw + 7 of every pass of kRP rows; vf is the unit column this lane
+// fetches (its slot with the row permutation undone).  The ring holds STAGES slices of all the
+// workgroup's segments, one behind the other: slice t + STAGES - 1 is issued in iteration t into the
+// slot that slice t - 1 occupied, and has to have landed by the barrier that ends iteration
+// t + STAGES - 3 (the consumers read the first fragments of a slice one iteration early).  The loads of
+// a wave complete in order, so "at most (STAGES - 3) slices' worth of instructions outstanding" means
+// slice t + 2 is in LDS (the loads of a list entry or two in between make it wait for more, never for
+// less).  The ring does not stop at a tile's end: while the consumers update the outputs of one tile or
+// hand over its partial sums, the first slices of the next are on their way, found by the producers
+// alone.  (With a prologue per tile, 2 us of list, addresses and a memory round trip in which
+// nothing multiplies: bfloat16 64->128 3x3 at 320x240 31 us instead of 26, 128->128 44 instead of 39; float32
+// 64->256 7x7 at 80x60 58 instead of 52, 128->128 3x3 at 320x240 143 instead of 128.)
 // While two consumer waves keep the matrix pipeline of a SIMD busy, a vector-ALU instruction of the
-// producer wave on that SIMD gets issued about once per MFMA (measured: 40 cycles per instruction),
-// so the producers' instruction count per slice, not the memory system, is what can hold up the loop.
-// Hence: everything wave-uniform is computed on the scalar unit (the ring slot and the LDS
-// destinations; with UT also the filter tap of the slice), filter fragments are addressed as a uniform
-// base plus 16 bytes per lane, and what is left per image-matrix row is the bounds test of its tap and
-// the choice between the pixel's address and the zero unit.
+// producer wave on that SIMD gets issued about once per MFMA, so the producers' instruction count per
+// slice, not the memory system, is what can hold up the loop.  Hence: everything wave-uniform is
+// computed on the scalar unit (the ring slot and the LDS destinations; with UT also the filter tap of the
+// slice), filter fragments are addressed as a uniform base plus 16 bytes per lane, and what is left per
+// image-matrix row is the bounds test of its tap and the choice between the pixel's address and the zero
+// unit.
 // UT ("uniform tap"): the units per pixel are a multiple of the eight units of a slice, so a slice
 // lies inside one filter tap and the tap is the same for all lanes; base[] then already contains
 // the lane's own unit offset.
-template <int DT, int BM, int BN, int STAGES, int PA, bool UT>
-__device__ __forceinline__ void direct_producer(const GemmArgs &a, float *As, float *Bs, int kc0, int kc1, int mt,
-                                                int nk, int pw_, int vf, const int (&iy0)[PA],
-                                                const int (&ix0)[PA], const int (&base)[PA])
+template <int DT, int BM, int BN, int STAGES, bool UT>
+__device__ __forceinline__ void direct_producer(const GemmArgs &a, const int n, float *As, float *Bs, int *sU, const Selection &sel,
+                                                Walk walk, int mtiles, int pw_)
 {
+    constexpr int PA = BN / kRP;                        // image-matrix rows per producer thread and slice
     constexpr int FB = BM / 16 * kFilterParts<DT>;      // filter fragments per slice
     constexpr int PB = (FB + kProdWaves - 1) / kProdWaves; // ... per wave (the last ones repeat others' when FB does not divide)
     constexpr int PS = PA + PB;                         // instructions per slice and wave
     constexpr int ASZ = BN * LDK, BSZ = FB * kFragBytes / 4;
+    constexpr int NL = TileSmem<DT, BM, BN, STAGES>::lists;
     static_assert((STAGES - 3) * PS < 64, "outstanding loads must fit the counter");
     const int pw = __builtin_amdgcn_readfirstlane(pw_); // the wave's number among the producers, as a scalar
+    const int lane = threadIdx.x & 63;
+    const int r0 = pw * 8 + (lane >> 3);                // first row this lane stages
+    // the hardware puts lane l's 16 bytes into slot l & 7 of row l >> 3 of the eight rows an
+    // instruction covers, so the lane fetches the unit that belongs there
+    const int vf = (lane & 7) ^ lds_swizzle(r0);
     const float *x = static_cast<const float *>(a.x);
-    // this channel tile's slices of the filter matrix, one behind the other as they lie in LDS
-    const char *wtile = static_cast<const char *>(a.wt) + (size_t)mt * nk * (FB * kFragBytes);
-    const unsigned lofs = (threadIdx.x & 63) * 16u;
-    auto issue = [&](int kc, int slot) {
+    const unsigned lofs = lane * 16u;
+    int iy0[PA], ix0[PA], base[PA];
+    const char *wtile = nullptr; // the channel tile's slices of the filter matrix, one behind the other as they lie in LDS
+    Segment seg = {0, 0, 0, -1};
+    int kc = 0, list = 0;
+    // the next segment's positions: where this lane's rows start in the map, and the list for the consumers
+    auto enter = [&]() {
+        walk.next(a, seg);
+        kc = seg.kc0;
+        const int pt = small_div(seg.tile, mtiles), mt = seg.tile - pt * mtiles;
+        wtile = static_cast<const char *>(a.wt) + (size_t)mt * walk.nk * (FB * kFragBytes);
+#pragma unroll
+        for (int ps = 0; ps < PA; ++ps) {
+            const int u = pt * BN + r0 + kRP * ps;
+            int g = -1;
+            if (u < n) g = sel.words ? select_rank(sel, u) : (a.list ? a.list[u] : u);
+            if ((lane & 7) == 0) sU[list * BN + r0 + kRP * ps] = g;
+            if (g >= 0) {
+                const int st = fast_div(g, a.dNo), q = g - st * a.No;
+                const int qy = fast_div(q, a.dWo), qx = q - qy * a.Wo;
+                iy0[ps] = qy * a.stride - a.pad;
+                ix0[ps] = qx * a.stride - a.pad;
+                base[ps] = ((st * a.H + iy0[ps]) * a.W + ix0[ps]) * a.pix_words + (UT ? vf * 4 : 0);
+            } else {
+                iy0[ps] = -(1 << 28);
+                ix0[ps] = -(1 << 28);
+                base[ps] = 0;
+            }
+        }
+        list = list == NL - 1 ? 0 : list + 1;
+        wait_lgkmcnt0(); // the list is in LDS before this wave's next barrier
+    };
+    auto issue = [&](int slot) {
+        if (kc == seg.kc1) enter();
         // tap of this lane's unit in slice kc: unit index -> (filter tap, channel unit) -> (j, i)
         const int q = kc * KU + (UT ? 0 : vf);
         const int tap = fast_div(q, a.dVin), cu = q - tap * a.dVin.d;
@@ -515,23 +608,23 @@ __device__ __forceinline__ void direct_producer(const GemmArgs &a, float *As, fl
             __builtin_amdgcn_global_load_lds((GlobalPtr)(wslice + f * kFragBytes + lofs), (LdsPtr)(B + f * (kFragBytes / 4)), 16,
                                              0, 0);
         }
+        ++kc;
     };
-    // Nothing of this wave is in flight here; saying so keeps the compiler, which tracks loads into
-    // registers along every path through the kernel, from waiting for imagined ones inside the loop.
-    wait_vmcnt<0>();
     // prologue: STAGES - 1 slices in flight, the first two landed
-#pragma unroll
+    const int slices = walk.slices;
+#pragma unroll 1
     for (int d = 0; d < STAGES - 1; ++d)
-        if (kc0 + d < kc1) issue(kc0 + d, d);
-    if (kc0 + STAGES - 2 < kc1)
+        if (d < slices) issue(d);
+    if (STAGES - 2 < slices)
         wait_vmcnt<(STAGES - 3) * PS>();
     else
         wait_vmcnt<0>();
     producer_barrier();
-    int slot = STAGES - 1; // ring slot of slice kc + STAGES - 1
-    for (int kc = kc0; kc < kc1; ++kc) {
-        if (kc + STAGES - 1 < kc1) {
-            issue(kc + STAGES - 1, slot);
+    int slot = STAGES - 1; // ring slot of slice t + STAGES - 1
+#pragma unroll 1
+    for (int t = 0; t < slices; ++t) {
+        if (t + STAGES - 1 < slices) {
+            issue(slot);
             wait_vmcnt<(STAGES - 3) * PS>();
         } else {
             wait_vmcnt<0>();
@@ -639,7 +732,6 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
     static_assert(STAGES >= 3, "ring depth");
     constexpr int TP = BN / WN / 16; // 16-pixel MFMA tiles per consumer wave
     constexpr int TC = BM / WM / 16; // 16-channel MFMA tiles per consumer wave
-    constexpr int PA = BN / kRP;     // image-matrix rows staged per producer thread and slice
     constexpr int FP = kFilterParts<DT>;
     static_assert(BN % kRP == 0, "whole passes over the pixel rows");
     constexpr int ASZ = BN * LDK, BSZ = BM / 16 * FP * kFragBytes / 4;
@@ -650,115 +742,58 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
 
     float *As = smem;                                     // [STAGES][BN][LDK]  gathered image-matrix slices
     float *Bs = smem + STAGES * ASZ;                      // [STAGES][BM/16][FP] filter fragments
-    int *sU = reinterpret_cast<int *>(Bs + STAGES * BSZ); // [BN] listed pixels of this tile (-1: none)
-    int *sFlag = sU + BN;                                  // ticket of the tile just finished
+    int *sU = reinterpret_cast<int *>(Bs + STAGES * BSZ); // [lists][BN] pixels of a tile (-1: none)
 
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const bool producer = wave >= kConsWaves;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
     const int mtiles = a.Mpad / BM;
-    const int nk = a.Kpad / (Unit<DT>::N * KU); // K slices
-    const int W = gridDim.x;
-    const Schedule sch = make_schedule(n, BN, mtiles, nk, a.dGrid);
+    Walk walk;
+    walk.nk = a.Kpad / (Unit<DT>::N * KU); // K slices
+    walk.W = gridDim.x;
+    walk.sch = make_schedule(n, BN, mtiles, walk.nk, a.dGrid);
+    const Schedule &sch = walk.sch;
     if (sch.tiles == 0) return;
     // Workgroups are dealt round-robin over the 8 XCDs.  Number them so that each XCD works on a
     // contiguous range of tiles / iterations: neighbours share gathered pixels (channel tiles of
     // one pixel tile) or filter slices, and that sharing then happens inside one L2.
-    const int w = (int)(blockIdx.x & 7) * (W >> 3) + (int)(blockIdx.x >> 3);
+    walk.w = (int)(blockIdx.x & 7) * (walk.W >> 3) + (int)(blockIdx.x >> 3);
     const bool xcd_ranges = (sch.wr & 7) == 0;
-    const int wsh = xcd_ranges ? (int)(blockIdx.x & 7) * (sch.wr >> 3) + (int)(blockIdx.x >> 3)
-                               : (int)blockIdx.x; // number inside the K-sharing group
+    walk.wsh = xcd_ranges ? (int)(blockIdx.x & 7) * (sch.wr >> 3) + (int)(blockIdx.x >> 3)
+                          : (int)blockIdx.x; // number inside the K-sharing group
     const bool sharing =
         sch.rem > 0 && (xcd_ranges ? (int)(blockIdx.x >> 3) < (sch.wr >> 3) : (int)blockIdx.x < sch.wr);
-    const int it_begin = sharing ? share_begin(sch, wsh) : 0;
-    const int it_end = sharing ? share_begin(sch, wsh + 1) : 0;
+    walk.it_begin = sharing ? share_begin(sch, walk.wsh) : 0;
+    walk.it_end = sharing ? share_begin(sch, walk.wsh + 1) : 0;
+    walk.slices = sch.whole * walk.nk + walk.it_end - walk.it_begin;
+    walk.round = 0;
+    walk.it = walk.it_begin;
+    if (walk.slices == 0) return;
 
-    int round = 0;
-    int it = it_begin;
-    while (true) {
-        // ---- next segment of this workgroup: a whole tile, or part of a shared tile's K range
-        int tile, kc0, kc1, shared_j = -1;
-        if (round < sch.whole) {
-            tile = round * W + w;
-            kc0 = 0;
-            kc1 = nk;
-            ++round;
-        } else if (it < it_end) {
-            shared_j = fast_div(it, a.dNk);
-            kc0 = it - shared_j * nk;
-            const int left = it_end - it;
-            kc1 = (left < nk - kc0) ? kc0 + left : nk;
-            tile = sch.whole * W + shared_j;
-            it += kc1 - kc0;
-        } else {
-            break;
-        }
-        const int pt = tile / mtiles;
-        const int mt = tile - pt * mtiles;
+    // Both roles execute the same number of barriers: one after the prologue, one per slice.
+    if (wave >= kConsWaves) {
+        if ((a.dVin.d & (KU - 1)) == 0)
+            direct_producer<DT, BM, BN, STAGES, true>(a, n, As, Bs, sU, sel, walk, mtiles, wave - kConsWaves);
+        else
+            direct_producer<DT, BM, BN, STAGES, false>(a, n, As, Bs, sU, sel, walk, mtiles, wave - kConsWaves);
+        return;
+    }
+
+    const int wpx0 = (wave % WN) * (BN / WN);
+    const int wch0 = (wave / WN) * (BM / WM);
+    const int lrow = lane & 15; // row of the 16-row operand tiles this lane feeds
+    const int lk = lane >> 4;   // k slot this lane feeds
+    const int nk = walk.nk;
+    int slot = 0; // ring slot of the slice in hand
+    const int *list = sU;
+    consumer_barrier();
+    Segment seg;
+    while (walk.next(a, seg)) {
+        const int kc0 = seg.kc0, kc1 = seg.kc1, shared_j = seg.shared_j;
+        const int pt = small_div(seg.tile, mtiles), mt = seg.tile - pt * mtiles;
         const bool partial = (kc1 - kc0) != nk;
-
-        const int ptid = producer ? tid - NCONS : 0;
-        const int v = ptid & 7;   // 16-byte unit column inside the K slice
-        const int r0 = ptid >> 3; // first row this thread stages
-        __syncthreads(); // the previous segment's LDS reads are done
-        if (sel.words) {
-            select_tile<BN>(sel, n, pt * BN, sU, sFlag + 1);
-        } else {
-            for (int i = tid; i < BN; i += NT) {
-                const int u = pt * BN + i;
-                sU[i] = u < n ? (a.list ? a.list[u] : u) : -1;
-            }
-        }
-        __syncthreads();
-
-        // consumer coordinates (used again after the role-specific loops)
-        const int cw = producer ? 0 : wave;
-        const int wpx0 = (cw % WN) * (BN / WN);
-        const int wch0 = (cw / WN) * (BM / WM);
-        const int lrow = lane & 15; // row of the 16-row operand tiles this lane feeds
-        const int lk = lane >> 4;   // k slot this lane feeds
-        // cleared inside the role branches, for the producers after their loop: registers that
-        // hold nothing while they stage slices
         floatx4 acc[TC][TP];
-
-        // Both roles execute the same number of barriers: one after the prologue, one per slice.
-        if (producer) {
-            // the hardware puts lane l's 16 bytes into slot l & 7 of row l >> 3 of the eight rows an
-            // instruction covers, so the thread fetches the unit that belongs there
-            const int vs = v ^ lds_swizzle(r0);
-            int iy0[PA], ix0[PA], base[PA];
-#pragma unroll
-            for (int ps = 0; ps < PA; ++ps) {
-                const int g = sU[r0 + kRP * ps];
-                if (g >= 0) {
-                    const int st = fast_div(g, a.dNo), q = g - st * a.No;
-                    const int qy = fast_div(q, a.dWo), qx = q - qy * a.Wo;
-                    iy0[ps] = qy * a.stride - a.pad;
-                    ix0[ps] = qx * a.stride - a.pad;
-                    base[ps] = ((st * a.H + iy0[ps]) * a.W + ix0[ps]) * a.pix_words;
-                } else {
-                    iy0[ps] = -(1 << 28);
-                    ix0[ps] = -(1 << 28);
-                    base[ps] = 0;
-                }
-            }
-            if ((a.dVin.d & (KU - 1)) == 0) {
-                // a slice lies inside one filter tap: the lane's unit goes into its pixel offsets once
-#pragma unroll
-                for (int ps = 0; ps < PA; ++ps) base[ps] += vs * 4;
-                direct_producer<DT, BM, BN, STAGES, PA, true>(a, As, Bs, kc0, kc1, mt, nk, wave - kConsWaves, vs, iy0, ix0,
-                                                              base);
-            } else {
-                direct_producer<DT, BM, BN, STAGES, PA, false>(a, As, Bs, kc0, kc1, mt, nk, wave - kConsWaves, vs, iy0, ix0,
-                                                               base);
-            }
-#pragma unroll
-            for (int j = 0; j < TC; ++j)
-#pragma unroll
-                for (int i = 0; i < TP; ++i) acc[j][i] = (floatx4){0.f, 0.f, 0.f, 0.f};
-        } else {
+        {
 #pragma unroll
             for (int j = 0; j < TC; ++j)
 #pragma unroll
@@ -780,10 +815,8 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                 return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), c,
                                                                0, 0, 0);
             };
-            __syncthreads();
             // the wave feeding the matrix pipeline wins instruction-issue arbitration on its SIMD
             __builtin_amdgcn_s_setprio(3);
-            int slot = 0; // ring slot of slice kc
             if constexpr (DT == kBF16) {
                 uintx4 af[2][TP], bf[2][TC];
                 auto read_frags = [&](int set, int sl, int kk) {
@@ -798,7 +831,7 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
 #pragma unroll
                         for (int i = 0; i < TP; ++i) acc[j][i] = mfma(bf[set][j], af[set][i], acc[j][i]);
                 };
-                read_frags(0, 0, 0);
+                read_frags(0, slot, 0);
                 for (int kc = kc0; kc < kc1; ++kc) {
                     const int nslot = slot == STAGES - 1 ? 0 : slot + 1;
                     // The scheduling barriers pin the order "issue the LDS reads of the next fragment
@@ -816,7 +849,7 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                     multiply(1);
                     __builtin_amdgcn_sched_barrier(0);
                     slot = nslot;
-                    __syncthreads();
+                    consumer_barrier();
                 }
             } else {
                 // float32: six of the nine products of parts, everything down to 2^-24 of the leading one.
@@ -830,9 +863,9 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                 Parts x0[TP], x1[TP]; // pixel fragments of two slices in turn
                 uintx4 w[2][3];
 #pragma unroll
-                for (int p = 0; p < 3; ++p) w[0][p] = read_filter(0, 0, p);
+                for (int p = 0; p < 3; ++p) w[0][p] = read_filter(slot, 0, p);
 #pragma unroll
-                for (int i = 0; i < TP; ++i) x0[i] = split_fragment(read_pixels(0, 0, i), read_pixels(0, 1, i));
+                for (int i = 0; i < TP; ++i) x0[i] = split_fragment(read_pixels(slot, 0, i), read_pixels(slot, 1, i));
                 // One slice: while channel tile j is multiplied, the filter fragments of the next tile are
                 // on their way from LDS and the next slice's pixels are read and split.
                 auto step = [&](Parts(&x)[TP], Parts(&nx)[TP]) {
@@ -876,7 +909,7 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                         for (int p = 0; p < 3; ++p) w[0][p] = w[1][p];
                     }
                     slot = nslot;
-                    __syncthreads();
+                    consumer_barrier();
                 };
                 int kc = kc0;
                 for (; kc + 1 < kc1; kc += 2) {
@@ -892,100 +925,91 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
             __builtin_amdgcn_s_setprio(0);
         }
 
-        // ---- a shared tile: store this K range's accumulators, take a ticket; the workgroup
-        //      holding the last ticket adds up all ranges (ascending K) and does the output update.
-        //      Slab stores are complete (vmcnt(0)) before the ticket is taken.
+        // ---- a shared tile: store this K range's accumulators, take a ticket; the wave holding the last
+        //      ticket of its sub-tile adds up all ranges (ascending K) and does the output update.  A
+        //      sub-tile belongs to the same wave of every workgroup, so waves need no barrier for this:
+        //      a wave's slab stores are complete (vmcnt(0)) before it takes its ticket.
         bool finish = true;
         if (partial) {
             const int t0 = shared_j * nk;
             const int w_first = share_owner(sch, t0);
             const int w_last = share_owner(sch, t0 + nk - 1);
-            const int ctid = producer ? 0 : tid;
-            if (!producer) {
-                // slab 2*wsh + (0: first tile this workgroup touches, 1: a later one), register layout:
-                // one float4 per lane and accumulator, consecutive lanes consecutive addresses
-                const int first_j = fast_div(it_begin, a.dNk);
-                const __amdgpu_buffer_rsrc_t slab = slab_resource(
-                    a.partial + (size_t)(2 * wsh + (shared_j == first_j ? 0 : 1)) * SLAB, SLAB * 4);
+            // slab 2*wsh + (0: first tile this workgroup touches, 1: a later one), register layout:
+            // one float4 per lane and accumulator, consecutive lanes consecutive addresses
+            const int first_j = fast_div(walk.it_begin, a.dNk);
+            const __amdgpu_buffer_rsrc_t slab = slab_resource(
+                a.partial + (size_t)(2 * walk.wsh + (shared_j == first_j ? 0 : 1)) * SLAB, SLAB * 4);
+            const int ofs = wave * (TC * TP * kFragBytes) + lane * 16;
+#pragma unroll
+            for (int j = 0; j < TC; ++j)
+#pragma unroll
+                for (int i = 0; i < TP; ++i)
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uintx4, acc[j][i]), slab,
+                                                           ofs + (j * TP + i) * kFragBytes, 0, kDeviceCoherent);
+            // all of this wave's slab stores have reached the device-coherent level
+            wait_vmcnt<0>();
+            int *ticket = a.tickets + shared_j * kConsWaves + wave;
+            int drawn = 0;
+            if (lane == 0) drawn = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            drawn = __builtin_amdgcn_readfirstlane(drawn);
+            finish = drawn == w_last - w_first;
+            if (finish) {
+                if (lane == 0) *ticket = 0; // ready for the next launch
+                // Sum the parts in ascending K order, whichever wave finishes (its own part is read
+                // back like the others, which keeps the accumulators in one register set).
 #pragma unroll
                 for (int j = 0; j < TC; ++j)
 #pragma unroll
-                    for (int i = 0; i < TP; ++i)
-                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uintx4, acc[j][i]), slab,
-                                                               ((j * TP + i) * NCONS + ctid) * 16, 0, kDeviceCoherent);
-                // all of this lane's slab stores have reached the device-coherent level
-                __builtin_amdgcn_s_waitcnt(0x0F70); // vmcnt(0)
-            }
-            __syncthreads();
-            if (tid == 0)
-                *sFlag = __hip_atomic_fetch_add(a.tickets + shared_j, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __syncthreads();
-            finish = (*sFlag == w_last - w_first);
-            if (finish) {
-                if (tid == 0) a.tickets[shared_j] = 0; // ready for the next launch
-                if (!producer) {
-                    // Sum the parts in ascending K order, whichever workgroup finishes (its own part
-                    // is read back like the others, which keeps the accumulators in one register set).
+                    for (int i = 0; i < TP; ++i) acc[j][i] = (floatx4){0.f, 0.f, 0.f, 0.f};
+                for (int ww = w_first; ww <= w_last; ++ww) {
+                    const int fj = fast_div(share_begin(sch, ww), a.dNk);
+                    const __amdgpu_buffer_rsrc_t part_slab = slab_resource(
+                        a.partial + (size_t)(2 * ww + (shared_j == fj ? 0 : 1)) * SLAB, SLAB * 4);
+                    floatx4 part[TC][TP];
 #pragma unroll
                     for (int j = 0; j < TC; ++j)
 #pragma unroll
-                        for (int i = 0; i < TP; ++i) acc[j][i] = (floatx4){0.f, 0.f, 0.f, 0.f};
-                    for (int ww = w_first; ww <= w_last; ++ww) {
-                        const int fj = fast_div(share_begin(sch, ww), a.dNk);
-                        const __amdgpu_buffer_rsrc_t slab = slab_resource(
-                            a.partial + (size_t)(2 * ww + (shared_j == fj ? 0 : 1)) * SLAB, SLAB * 4);
-                        floatx4 part[TC][TP];
+                        for (int i = 0; i < TP; ++i)
+                            part[j][i] = __builtin_bit_cast(
+                                floatx4, __builtin_amdgcn_raw_buffer_load_b128(part_slab, ofs + (j * TP + i) * kFragBytes, 0,
+                                                                               kDeviceCoherent));
 #pragma unroll
-                        for (int j = 0; j < TC; ++j)
+                    for (int j = 0; j < TC; ++j)
 #pragma unroll
-                            for (int i = 0; i < TP; ++i)
-                                part[j][i] = __builtin_bit_cast(
-                                    floatx4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                 slab, ((j * TP + i) * NCONS + ctid) * 16, 0, kDeviceCoherent));
-#pragma unroll
-                        for (int j = 0; j < TC; ++j)
-#pragma unroll
-                            for (int i = 0; i < TP; ++i) acc[j][i] += part[j][i];
-                    }
+                        for (int i = 0; i < TP; ++i) acc[j][i] += part[j][i];
                 }
             }
         }
 
         if constexpr (DT == kF32) {
             // Sums that are not finite are formed again from the values themselves.  (x * 0 is zero for
-            // every finite x.)  The accumulators pass through this wave's share of the ring, which holds
-            // nothing any more, so that the loop over them is a loop.
-            if (finish && !producer) {
+            // every finite x.)
+            if (finish) {
                 float z = 0.f;
 #pragma unroll
                 for (int j = 0; j < TC; ++j)
 #pragma unroll
                     for (int i = 0; i < TP; ++i) z += acc[j][i][0] * 0.f + acc[j][i][1] * 0.f + acc[j][i][2] * 0.f + acc[j][i][3] * 0.f;
                 if (__builtin_expect(__any(z != 0.f), 0)) { // NaN compares unequal
-                    static_assert(STAGES * (ASZ + BSZ) >= SLAB, "the ring holds the tile's accumulators");
-                    float *mine = smem + wave * (TC * TP * 256);
-#pragma unroll
-                    for (int j = 0; j < TC; ++j)
-#pragma unroll
-                        for (int i = 0; i < TP; ++i) *reinterpret_cast<floatx4 *>(mine + (j * TP + i) * 256 + lane * 4) = acc[j][i];
+                    // one value at a time, picked from the registers by comparison: the loop stays a loop
 #pragma unroll 1
                     for (int e = 0; e < TC * TP * 4; ++e) {
-                        float *v = mine + (e >> 2) * 256 + lane * 4 + (e & 3);
-                        const int g = sU[wpx0 + (e >> 2) % TP * 16 + lrow];
+                        float v = 0.f;
+#pragma unroll
+                        for (int f = 0; f < TC * TP * 4; ++f) v = f == e ? acc[f / (TP * 4)][f / 4 % TP][f % 4] : v;
+                        const int g = list[wpx0 + (e >> 2) % TP * 16 + lrow];
                         const int row = mt * BM + wch0 + (e >> 2) / TP * 16 + lk * 4 + (e & 3);
-                        if (!(fabsf(*v) < __builtin_inff()) && g >= 0 && row < a.M) *v = plain_sum<BM>(a, nk, row, g);
+                        if (!(fabsf(v) < __builtin_inff()) && g >= 0 && row < a.M) v = plain_sum<BM>(a, nk, row, g);
+#pragma unroll
+                        for (int f = 0; f < TC * TP * 4; ++f) acc[f / (TP * 4)][f / 4 % TP][f % 4] = f == e ? v : acc[f / (TP * 4)][f / 4 % TP][f % 4];
                     }
-#pragma unroll
-                    for (int j = 0; j < TC; ++j)
-#pragma unroll
-                        for (int i = 0; i < TP; ++i) acc[j][i] = *reinterpret_cast<const floatx4 *>(mine + (j * TP + i) * 256 + lane * 4);
                 }
             }
         }
 
         // ---- output update: bias, activation, scatter to the stored map; optionally the change
         //      detection of the layer this map feeds (new value against the one it replaces)
-        if (finish && !producer) {
+        if (finish) {
             const bool detect = a.next_flags != nullptr && !a.next_force;
             bool changed[TP];
 #pragma unroll
@@ -1007,7 +1031,7 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                     for (int qq = 0; qq < CH; ++qq) {
                         const int j = (q0 + qq) / TP, i = (q0 + qq) % TP;
                         const int ch = mt * BM + wch0 + j * 16 + lk * 4;
-                        const int g = sU[wpx0 + i * 16 + lrow];
+                        const int g = list[wpx0 + i * 16 + lrow];
                         replaced[qq] = (uintx4){0u, 0u, 0u, 0u};
                         if (g >= 0 && ch < a.Ms) {
                             if constexpr (DT == kBF16) {
@@ -1027,7 +1051,7 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                     const int j = (q0 + qq) / TP, i = (q0 + qq) % TP;
                     const int ch = mt * BM + wch0 + j * 16 + lk * 4;
                     const float4 bv = bias[j];
-                    const int g = sU[wpx0 + i * 16 + lrow];
+                    const int g = list[wpx0 + i * 16 + lrow];
                     if (g >= 0 && ch < a.Ms) {
                         float4 o;
                         o.x = acc[j][i][0] + bv.x;
@@ -1071,7 +1095,7 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
             if (a.next_flags) {
 #pragma unroll
                 for (int i = 0; i < TP; ++i) {
-                    const int g = sU[wpx0 + i * 16 + lrow];
+                    const int g = list[wpx0 + i * 16 + lrow];
                     int f = a.next_force ? 1 : (int)changed[i];
                     // the other channels of this pixel sit in the lanes 16, 32 and 48 further on
                     f |= __shfl_xor(f, 16);
@@ -1080,6 +1104,7 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                 }
             }
         }
+        list = list == sU + (TileSmem<DT, BM, BN, STAGES>::lists - 1) * BN ? sU : list + BN;
     }
 }
 
@@ -1134,28 +1159,6 @@ static constexpr int kThinTapBytes = kThinGroups * 4 * (int)sizeof(int2);
 static constexpr int kThinSelOffset = kThinScratchBytes + kThinFilterBytes + kThinTapBytes;
 static constexpr int kThinSmemBytes = kThinSelOffset + kSelSlots * 12 + 64;
 static_assert(kThinSmemBytes <= 160 * 1024, "a workgroup has 160 KiB of LDS");
-
-// The position of rank r (0 <= r < number of selected positions) in a ranked selection map.
-__device__ __forceinline__ int select_rank(const Selection &sel, int r)
-{
-    // the last word whose exclusive rank is <= r holds it: later words start at a higher rank,
-    // and of the words sharing its rank it is the last (the others are empty)
-    int w = 0;
-#pragma unroll
-    for (int step = kSelMaxWords; step; step >>= 1)
-        if (w + step < sel.nwords && sel.rank[w + step] <= r) w += step;
-    const uint64_t bits = sel.words[w];
-    int k = r - sel.rank[w], pos = 0; // the k-th set bit of the word, counted from 0
-#pragma unroll
-    for (int sh = 32; sh; sh >>= 1) {
-        const int c = __popcll((bits >> pos) & ((1ull << sh) - 1ull));
-        if (k >= c) {
-            k -= c;
-            pos += sh;
-        }
-    }
-    return w * 64 + pos;
-}
 
 // One wave's share of the tiles: 16 positions x TC channel tiles of 16.  In program order per tile:
 // find the next tile's positions, multiply the current tile (its gathers were issued a tile ago),
@@ -1421,8 +1424,8 @@ size_t gemm_partial_bytes(int M, int grid)
     return (size_t)2 * grid * bm * pixel_tile(bm, 0x7fffffff) * sizeof(float); // the widest tile of that channel tile
 }
 
-// One ticket counter per shared tile (fewer than the workgroup count); zero between launches.
-size_t gemm_ticket_bytes(int grid) { return (size_t)grid * sizeof(int); }
+// One ticket counter per shared tile (fewer than the workgroup count) and wave; zero between launches.
+size_t gemm_ticket_bytes(int grid) { return (size_t)grid * kConsWaves * sizeof(int); }
 
 // Workgroups to launch: one per compute unit, fewer if even the longest list gives less work.
 int gemm_grid(const GemmArgs &a, int compute_units)
@@ -1489,6 +1492,8 @@ hipError_t gemm_gather(hipStream_t st, const GemmArgs &a, const Timing &tm)
     if (a.Mpad % bm != 0 || a.Kpad % gemm_k_multiple(a.dtype) != 0 || a.Ms % eu != 0 || a.pix_words < 1 || !a.partial ||
         !a.tickets || a.grid < 8 || (a.grid & 7) || a.grid > kMaxGrid)
         return hipErrorInvalidValue;
+    // the 64-channel tiles in float32 count on rows of four slices or more (TileSmem::lists)
+    if (a.dtype == kF32 && bm == 64 && bn == 256 && !gemm_is_thin(a) && a.Kpad < 4 * gemm_k_multiple(kF32)) return hipErrorInvalidValue;
     // the divisors must belong to these arguments, and the schedule's 32-bit arithmetic must hold
     if (a.kh < 1 || a.kw < 1 || a.dKw.d != a.kw || a.dVin.d != (a.pix_words + 3) / 4) return hipErrorInvalidValue;
     if (a.dNo.d != a.No || a.dWo.d != a.Wo || a.dHo.d * a.Wo != a.No || a.dGrid.d != a.grid ||
