@@ -52,6 +52,15 @@ __host__ __device__ inline float bf16_value(unsigned short b)
     return c.f;
 }
 
+// The same on the device, two at a time: the conversion instruction rounds as bf16_bits does (compared
+// on all 2^32 bit patterns, NaN included) in one instruction instead of eight per value.
+__device__ __forceinline__ unsigned bf16_pair(float a, float b)
+{
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const bf16x2 v = {(__bf16)a, (__bf16)b};
+    return __builtin_bit_cast(unsigned, v);
+}
+
 // One 16-byte unit of a map: 4 floats or 8 bfloat16.
 template <int DT>
 struct Unit;
@@ -71,7 +80,7 @@ struct Unit<kBF16> {
     }
     static __device__ __forceinline__ void set(uint4 &u, int i, float f) // rounds to bfloat16
     {
-        const unsigned int b = bf16_bits(f);
+        const unsigned int b = __builtin_bit_cast(unsigned short, (__bf16)f);
         unsigned int &w = (&u.x)[i >> 1];
         w = (i & 1) ? ((w & 0x0000ffffu) | (b << 16)) : ((w & 0xffff0000u) | b);
     }

@@ -563,12 +563,19 @@ __device__ __forceinline__ void direct_producer(const GemmArgs &a, const int n, 
         kc = seg.kc0;
         const int pt = small_div(seg.tile, mtiles), mt = seg.tile - pt * mtiles;
         wtile = static_cast<const char *>(a.wt) + (size_t)mt * walk.nk * (FB * kFragBytes);
-#pragma unroll
-        for (int ps = 0; ps < PA; ++ps) {
-            const int u = pt * BN + r0 + kRP * ps;
+        // a lane per row of this wave: eight in each pass (one search of the ranks instead of one per pass)
+        static_assert(PA <= 8, "the wave's rows fit its lanes");
+        int *rows = sU + list * BN + pw * 8;
+        if (lane < 8 * PA) {
+            const int row = (lane & 7) + kRP * (lane >> 3), u = pt * BN + pw * 8 + row;
             int g = -1;
             if (u < n) g = sel.words ? select_rank(sel, u) : (a.list ? a.list[u] : u);
-            if ((lane & 7) == 0) sU[list * BN + r0 + kRP * ps] = g;
+            rows[row] = g;
+        }
+        __builtin_amdgcn_wave_barrier(); // written and read by this wave, in order
+#pragma unroll
+        for (int ps = 0; ps < PA; ++ps) {
+            const int g = rows[(lane >> 3) + kRP * ps];
             if (g >= 0) {
                 const int st = fast_div(g, a.dNo), q = g - st * a.No;
                 const int qy = fast_div(q, a.dWo), qx = q - qy * a.Wo;
@@ -642,11 +649,6 @@ struct Parts {
     uintx4 hi, mid, lo;
 };
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ unsigned bf16_pair(float a, float b)
-{
-    const bf16x2 v = {(__bf16)a, (__bf16)b};
-    return __builtin_bit_cast(unsigned, v);
-}
 __device__ __forceinline__ float minus_part(float x, unsigned pair, unsigned which)
 {
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, which), __builtin_bit_cast(bf16x2, pair), x, false);
@@ -815,6 +817,12 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                 return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), c,
                                                                0, 0, 0);
             };
+            // Operands stay alive to the end of a group of MFMAs.  Otherwise the register allocator puts the
+            // result of an operand's last MFMA over that operand instead of over its own accumulator, and
+            // the next MFMA of that accumulator has to wait for the result to be written: with two of sixteen
+            // MFMAs like that 256->256 3x3 in bfloat16 took 42 us instead of 36, with a third of them float32
+            // 256->256 3x3 131 instead of 122 and 16->64 7x7 at 640x360 133 instead of 127.
+            auto keep = [](const uintx4 &v) { asm volatile("" ::"v"(v)); };
             // the wave feeding the matrix pipeline wins instruction-issue arbitration on its SIMD
             __builtin_amdgcn_s_setprio(3);
             if constexpr (DT == kBF16) {
@@ -830,6 +838,10 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                     for (int j = 0; j < TC; ++j)
 #pragma unroll
                         for (int i = 0; i < TP; ++i) acc[j][i] = mfma(bf[set][j], af[set][i], acc[j][i]);
+#pragma unroll
+                    for (int j = 0; j < TC; ++j) keep(bf[set][j]);
+#pragma unroll
+                    for (int i = 0; i < TP; ++i) keep(af[set][i]);
                 };
                 read_frags(0, slot, 0);
                 for (int kc = kc0; kc < kc1; ++kc) {
@@ -898,6 +910,16 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                         for (int i = 0; i < TP; ++i) cor[j][i] = mfma(wj[1], x[i].hi, cor[j][i]);
 #pragma unroll
                         for (int i = 0; i < TP; ++i) cor[j][i] = mfma(wj[0], x[i].mid, cor[j][i]);
+                        keep(wj[0]);
+                        keep(wj[1]);
+                        keep(wj[2]);
+#pragma unroll
+                        for (int i = 0; i < TP; ++i) {
+                            if (j < TC - 1) continue;
+                            keep(x[i].hi);
+                            keep(x[i].mid);
+                            keep(x[i].lo);
+                        }
                         // ... in the shadow of that tile's MFMAs
 #pragma unroll
                         for (int i = 0; i < TP; ++i)
@@ -956,7 +978,8 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
             if (finish) {
                 if (lane == 0) *ticket = 0; // ready for the next launch
                 // Sum the parts in ascending K order, whichever wave finishes (its own part is read
-                // back like the others, which keeps the accumulators in one register set).
+                // back like the others, which keeps the accumulators in one register set).  A part is a
+                // round trip to the level that all XCDs share, almost 1 us: three are on their way at a time.
 #pragma unroll
                 for (int j = 0; j < TC; ++j)
 #pragma unroll
@@ -1069,8 +1092,8 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                             uint2 *dst = reinterpret_cast<uint2 *>(static_cast<unsigned short *>(a.out) +
                                                                    (size_t)g * a.Ms + ch);
                             uint2 nv;
-                            nv.x = (unsigned)bf16_bits(o.x) | ((unsigned)bf16_bits(o.y) << 16);
-                            nv.y = (unsigned)bf16_bits(o.z) | ((unsigned)bf16_bits(o.w) << 16);
+                            nv.x = bf16_pair(o.x, o.y);
+                            nv.y = bf16_pair(o.z, o.w);
                             if (detect) {
                                 const uint2 ov = make_uint2(replaced[qq][0], replaced[qq][1]);
                                 changed[i] |= fabsf(bf16_value(nv.x & 0xffff) - bf16_value(ov.x & 0xffff)) > a.next_tau ||
@@ -1285,8 +1308,8 @@ __device__ __forceinline__ void thin_tiles(const GemmArgs &a, const int n, const
                 }
                 if constexpr (DT == kBF16) {
                     uint2 nv;
-                    nv.x = (unsigned)bf16_bits(o.x) | ((unsigned)bf16_bits(o.y) << 16);
-                    nv.y = (unsigned)bf16_bits(o.z) | ((unsigned)bf16_bits(o.w) << 16);
+                    nv.x = bf16_pair(o.x, o.y);
+                    nv.y = bf16_pair(o.z, o.w);
                     if (detect)
                         changed |= fabsf(bf16_value(nv.x & 0xffff) - bf16_value(old[j][0] & 0xffff)) > a.next_tau ||
                                    fabsf(bf16_value(nv.x >> 16) - bf16_value(old[j][0] >> 16)) > a.next_tau ||
