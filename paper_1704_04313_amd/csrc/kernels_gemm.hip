@@ -1380,6 +1380,91 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((NT + 255) /
     thin_tiles<DT, 1>(a, n, sel, sB, sTap, G, pitch);
 }
 
+// ---- 1x1 layers on pixels of one or two units ------------------------------------------------
+//
+// A handful of products per output: nothing for the matrix cores, whose operands would be padding for
+// the most part (3->8: 3 of 32 k, 8 of 16 channels), and a chain of search, gather, MFMA and store per
+// sixteen positions.  Here a thread owns one 16-byte unit of output channels, keeps its weights in
+// registers and takes positions, kPointBatch at a time so that as many pixels are on their way at once;
+// the threads of a position sit next to each other, so that a wave stores one contiguous run.
+// Bound by HBM: 3->8 on 2048 x 2048, every position, 133 -> 34 us from a list (24 + 16 + 64 + 128 MB of
+// list, frame values and outputs: 6 TB/s), 111 -> 31 in order; 3->64 on 1024 x 1024 102 -> 54, 8->64 there
+// 108 -> 78, bfloat16 3->8 34 -> 12.
+static constexpr int kPointBatch = 4;
+
+template <int DT, int VIN>
+__global__ __launch_bounds__(256) void gemm_point_kernel(GemmArgs a, int mshift)
+{
+    constexpr int E = Unit<DT>::N, B = kPointBatch;
+    const int n = a.count ? *a.count : a.max_pixels;
+    // a map without padding has the next pixel's values behind its channels
+    const int C = DT == kBF16 ? VIN * E : (a.pix_words < VIN * E ? a.pix_words : VIN * E);
+    const int m = (int)threadIdx.x & ((1 << mshift) - 1);
+    const bool detect = a.next_flags != nullptr && !a.next_force;
+    const float *x = static_cast<const float *>(a.x);
+    uint4 *out = static_cast<uint4 *>(a.out);
+    float w[E][VIN * E], bias[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const size_t row = (size_t)(m * E + e) * a.Kpad; // rows up to Mpad exist, zero beyond M
+        bias[e] = a.bias[m * E + e];
+#pragma unroll
+        for (int c = 0; c < VIN * E; ++c)
+            w[e][c] = DT == kBF16 ? bf16_value(static_cast<const unsigned short *>(a.wt)[row + c]) : static_cast<const float *>(a.wt)[row + c];
+    }
+    const int per = 256 >> mshift, step = (int)gridDim.x * per; // positions per workgroup and pass
+    for (long long r0 = (long long)blockIdx.x * per + ((int)threadIdx.x >> mshift); r0 < n; r0 += (long long)B * step) {
+        int g[B];
+        uint4 v[B][VIN], old[B];
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            const long long r = r0 + (long long)b * step;
+            g[b] = r < n ? (a.list ? a.list[r] : (int)r) : -1;
+        }
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            old[b] = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+            for (int u = 0; u < VIN; ++u) v[b][u] = old[b];
+            if (g[b] < 0) continue;
+#pragma unroll
+            for (int u = 0; u < VIN; ++u)
+                v[b][u] = __builtin_bit_cast(uint4, *reinterpret_cast<const floatx4_a4 *>(x + (size_t)g[b] * a.pix_words + u * 4));
+            if (detect) old[b] = out[((size_t)g[b] << mshift) + m];
+        }
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            if (g[b] < 0) continue;
+            uint4 nv = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                float s = 0.f;
+#pragma unroll
+                for (int c = 0; c < VIN * E; ++c)
+                    if (c < C) s = fmaf(Unit<DT>::get(v[b][c / E], c % E), w[e][c], s);
+                s += bias[e];
+                if (a.relu) s = fmaxf(s, 0.f);
+                Unit<DT>::set(nv, e, s);
+            }
+            out[((size_t)g[b] << mshift) + m] = nv;
+            // several threads of a position may store the same 1
+            if (a.next_flags && (a.next_force || unit_exceeds<DT>(nv, old[b], a.next_tau))) a.next_flags[g[b]] = 1;
+        }
+    }
+}
+
+// Whether a launch goes to gemm_point_kernel: a 1x1 layer of few enough weights per output unit for
+// registers (8 float32 or 8 bfloat16 values per pixel), units of output that divide a wave, positions from a
+// list or all of them.  Positions that the launch has to rank itself stay with the thin kernel: they are
+// few, and the ranking needs its LDS and threads.  On 400 x 400 positions it takes 6.6 us for 3->8 (thin: 9.7),
+// 16 for 3->64 (22) and 22 for 8->64 (21).
+static bool gemm_is_point(const GemmArgs &a)
+{
+    const int units = a.Ms / elems_per_unit(a.dtype);
+    return a.kh == 1 && a.kw == 1 && a.stride == 1 && a.pad == 0 && a.sel_words == 0 &&
+           a.dVin.d <= (a.dtype == kBF16 ? 1 : 2) && (units & (units - 1)) == 0 && a.Ms <= a.Mpad;
+}
+
 // Measured against the tile pipeline on 3..256 input and 8..64 output channels, 4 800 to 4 million
 // positions: the lone waves win as long as (groups of four units) x (channel tiles) stays at or
 // below 32 -- beyond that a wave's chain of MFMAs per tile gets long and the big tiles' reuse of
@@ -1530,6 +1615,20 @@ hipError_t gemm_gather(hipStream_t st, const GemmArgs &a, const Timing &tm)
     if (a.sel_words < 0 || a.sel_words > kSelMaxWords || (a.sel_words > 0 && !a.sel_map) ||
         (a.sel_words == 0 && !a.list != !a.count) || (long long)a.sel_words * 64 < a.max_pixels * (a.sel_words > 0))
         return hipErrorInvalidValue;
+    if (gemm_is_thin(a) && gemm_is_point(a)) {
+        int mshift = 0;
+        while ((1 << mshift) < a.Ms / eu) ++mshift;
+        long long grid = (((long long)a.max_pixels << mshift) + 256 * kPointBatch - 1) / (256 * kPointBatch);
+        if (grid > 4096) grid = 4096;
+        if (grid < 1) grid = 1;
+#define P(DT_, V_)                                                                                           \
+    if (a.dtype == DT_ && a.dVin.d == V_) {                                                                   \
+        launch_kernel(tm, gemm_point_kernel<DT_, V_>, dim3((int)grid), dim3(256), 0, st, a, mshift);          \
+        return hipGetLastError();                                                                            \
+    }
+        P(kF32, 1) P(kF32, 2) P(kBF16, 1)
+#undef P
+    }
     if (gemm_is_thin(a)) {
 #define T(DT_, MT_)                                                                                      \
     if (a.dtype == DT_ && a.Mpad == 16 * MT_) {                                                           \

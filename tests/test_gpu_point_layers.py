@@ -1,0 +1,57 @@
+"""1x1 layers on pixels of one or two 16-byte units, positions from a list or all of them (the kernel in
+which a thread owns one unit of output channels), against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1704_04313_amd as cb
+from workloads.networks import conv, make_weights, pool
+
+from gpu_util import compare_sequence, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _frames(C, H, W, n, seed):
+    """Small integers with a moving block, so that sums are exact and all lists can be compared."""
+    r = np.random.default_rng(seed)
+    bg = r.integers(0, 4, (C, H, W)).astype(np.float32)
+    out = []
+    for t in range(n):
+        f = bg.copy()
+        f[:, t:t + 5, 2 * t:2 * t + 7] = r.integers(0, 4, (C, 1, 1))
+        out.append(f)
+    return out
+
+
+# channels of one and two units with and without padding, one to sixteen units of output, ragged positions
+@pytest.mark.parametrize("cin,cout,h,w,bf16", [
+    (1, 3, 9, 11, False), (3, 8, 37, 41, False), (4, 16, 64, 65, False), (5, 32, 33, 29, False), (8, 64, 31, 50, False),
+    (3, 8, 37, 41, True), (8, 64, 40, 33, True), (3, 20, 19, 23, False)])
+def test_listed_positions(cin, cout, h, w, bf16):
+    L = conv(cin, cout, 1)
+    frames = [np.random.default_rng(5).random((cin, h, w), dtype=np.float32)]
+    for t in range(2):
+        f = frames[-1].copy()
+        f[:, 2:2 + h // 3, 3:3 + w // 2] += np.float32(0.25 * (t + 1))
+        frames.append(f)
+    compare_sequence([L], make_weights([L], cin), frames, 0.02, bf16=bf16, lists_every_frame=True)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("dense", [False, True])
+def test_detection_of_the_layer_behind_bit_exact(bf16, dense):
+    layers = [conv(3, 8, 1), conv(8, 16, 1), pool(), conv(16, 4, 3, relu=False)]
+    r = np.random.default_rng(9)
+    params = [None if L.kind != "conv" else (r.integers(-1, 2, (L.cout, L.cin, L.kh, L.kw)).astype(np.float32),
+                                             r.integers(-2, 3, L.cout).astype(np.float32)) for L in layers]
+    net = cb.CBInfer(layers, params, (3, 26, 38), 0.5, lists_every_frame=True, dtype=cb.BF16 if bf16 else cb.F32)
+    orc = oracle.OracleCBNet(layers, params, 0.5, bf16=bf16)
+    net.set_mode(dense)
+    for t, f in enumerate(_frames(3, 26, 38, 4, 3)):
+        want = orc.process_frame(f) if not dense else oracle.dense_forward(layers, params, f, bf16=bf16)[-1]
+        np.testing.assert_array_equal(net.process_frame(to_dev(f)).cpu().numpy()[0], want, err_msg="frame %d" % t)
+        for l in (0, 1, 3) if not dense else ():
+            np.testing.assert_array_equal(net.read_list(l, cb.LIST_CHANGED), orc.trace[l]["C"], err_msg="layer %d frame %d" % (l, t))
+            np.testing.assert_array_equal(net.read_list(l, cb.LIST_UPDATE), orc.trace[l]["U"], err_msg="layer %d frame %d" % (l, t))
+    net.destroy()
