@@ -1515,21 +1515,22 @@ int gemm_channel_tile(int M)
     return 128;
 }
 
-// Pixels per big tile.  The 64-channel kernel takes 128 instead of 256 on maps of at most
-// kNarrowTilePixels positions, where a 256-pixel tile would leave most workgroups a third of a tile's K
-// range (16->64 7x7: 35.5 -> 33.6 us at 160x120, but 230 -> 248 us at 640x360).
-static constexpr int kNarrowTilePixels = 65536;
-static int pixel_tile(int bm, int max_pixels)
+// Pixels per big tile.  The 64-channel kernel takes 128 instead of 256 on maps of few positions, where
+// 256-pixel tiles leave workgroups idle in the last round or most of them a third of a tile's K range.  The line
+// lies higher for float32, whose slices carry six products per value and hide their loads at either
+// width: 32->64 3x3 at 320x240 33.7 -> 28.1 us, 16->64 7x7 at 640x360 131.4 -> 131.0, and 6.90 -> 7.05 ms for
+// two frames of 64 streams (1.2 million positions).  bfloat16, 16->64 7x7 at 640x360: 55.1 -> 57.7 us.
+static int pixel_tile(int bm, int max_pixels, int dtype)
 {
     if (bm == 128) return 128;
-    return bm == 64 && max_pixels <= kNarrowTilePixels ? 128 : 256;
+    return bm == 64 && max_pixels <= (dtype == kF32 ? 1 << 19 : 1 << 16) ? 128 : 256;
 }
 
 // Two partial-accumulator slabs per workgroup.
 size_t gemm_partial_bytes(int M, int grid)
 {
     const int bm = gemm_channel_tile(M);
-    return (size_t)2 * grid * bm * pixel_tile(bm, 0x7fffffff) * sizeof(float); // the widest tile of that channel tile
+    return (size_t)2 * grid * bm * pixel_tile(bm, 0x7fffffff, kF32) * sizeof(float); // the widest tile of that channel tile
 }
 
 // One ticket counter per shared tile (fewer than the workgroup count) and wave; zero between launches.
@@ -1538,7 +1539,7 @@ size_t gemm_ticket_bytes(int grid) { return (size_t)grid * kConsWaves * sizeof(i
 // Workgroups to launch: one per compute unit, fewer if even the longest list gives less work.
 int gemm_grid(const GemmArgs &a, int compute_units)
 {
-    const int bm = gemm_channel_tile(a.M), bn = pixel_tile(bm, a.max_pixels);
+    const int bm = gemm_channel_tile(a.M), bn = pixel_tile(bm, a.max_pixels, a.dtype);
     int W = compute_units & ~7;
     if (W < 8) W = 8;
     if (W > kMaxGrid) W = kMaxGrid;
@@ -1595,7 +1596,7 @@ hipError_t gemm_prepare(void)
 
 hipError_t gemm_gather(hipStream_t st, const GemmArgs &a, const Timing &tm)
 {
-    const int bm = gemm_channel_tile(a.M), bn = pixel_tile(bm, a.max_pixels);
+    const int bm = gemm_channel_tile(a.M), bn = pixel_tile(bm, a.max_pixels, a.dtype);
     const int eu = elems_per_unit(a.dtype);
     if (a.Mpad % bm != 0 || a.Kpad % gemm_k_multiple(a.dtype) != 0 || a.Ms % eu != 0 || a.pix_words < 1 || !a.partial ||
         !a.tickets || a.grid < 8 || (a.grid & 7) || a.grid > kMaxGrid)
