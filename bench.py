@@ -32,8 +32,8 @@ import numpy as np
 
 ROOT = os.path.dirname(os.path.abspath(__file__))
 MI355X_HBM_GBS = 8000.0
-MI355X_FP32_MFMA_TFLOPS = 157.3
 MI355X_BF16_MFMA_TFLOPS = 2500.0
+MI355X_FP32_MFMA_TFLOPS = MI355X_BF16_MFMA_TFLOPS / 6  # float32 layers: six bfloat16 products of parts per product
 # Counter-measured HBM bytes per launch of the dominant kernel: written next to
 # profiles/cfg2_hbm_traffic.md from the same two rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE,
 # scaled by a plain copy of known size).  Missing or for another kernel: traffic is null.

@@ -65,3 +65,18 @@ def test_values_that_are_not_finite(cin, cout, k, h, w, special):
     fine = np.isfinite(want)
     size = _reference(L, np.abs(wt), np.abs(b), np.where(np.isfinite(x), np.abs(x), 0))
     assert np.all(np.abs(got - want)[fine] <= ((cin * k * k + 40) * 2.0 ** -23 * size)[fine])
+
+
+def test_static_workspace_with_fewer_workgroups():
+    """A network a little too large for the static workspace at full width runs there with half the workgroups
+    per launch; sums are cut along K in other places then, so results agree within rounding."""
+    L = conv(512, 1536, 3, relu=False)
+    params = make_weights([L], 5)
+    assert cb.cbinfer_workspace_bytes([L], params, (512, 10, 10)) > 64 << 20
+    x = np.random.default_rng(1).random((512, 10, 10), dtype=np.float32)
+    got = []
+    for static in (True, False):
+        net = cb.CBInfer([L], params, (512, 10, 10), 0.02, static_workspace=static)
+        got.append(net.process_frame(to_dev(x)).cpu().numpy().astype(np.float64))
+        net.destroy()
+    assert np.linalg.norm(got[0] - got[1]) <= 2 * np.sqrt(144 + 8) * 2.0 ** -24 * np.linalg.norm(got[1])
