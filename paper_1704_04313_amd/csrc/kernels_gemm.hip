@@ -1454,14 +1454,16 @@ __global__ __launch_bounds__(256) void gemm_point_kernel(GemmArgs a, int mshift)
 }
 
 // Whether a launch goes to gemm_point_kernel: a 1x1 layer of few enough weights per output unit for
-// registers (8 float32 or 8 bfloat16 values per pixel), units of output that divide a wave, positions from a
-// list or all of them.  Positions that the launch has to rank itself stay with the thin kernel: they are
-// few, and the ranking needs its LDS and threads.  On 400 x 400 positions it takes 6.6 us for 3->8 (thin: 9.7),
-// 16 for 3->64 (22) and 22 for 8->64 (21).
+// registers (8 float32 or 8 bfloat16 values per pixel) and units of output that divide a wave, on a map too
+// large to be ranked in the kernel.  That is a property of the layer alone, and has to be: the two kernels add
+// a position's products in different orders, and the same layer must give the same bits whether its positions
+// come from the map, from a list or are all of them.  (Maps that can be ranked are in the thin kernel's hands
+// whichever way their positions come: in order, 3->8 on 320 x 240 takes 7.7 us there and 4.5 here.)  On
+// 400 x 400 positions it takes 6.6 us for 3->8 (thin: 9.7), 16 for 3->64 (22) and 22 for 8->64 (21).
 static bool gemm_is_point(const GemmArgs &a)
 {
     const int units = a.Ms / elems_per_unit(a.dtype);
-    return a.kh == 1 && a.kw == 1 && a.stride == 1 && a.pad == 0 && a.sel_words == 0 &&
+    return a.kh == 1 && a.kw == 1 && a.stride == 1 && a.pad == 0 && a.sel_words == 0 && a.max_pixels > kSelMaxWords * 64 &&
            a.dVin.d <= (a.dtype == kBF16 ? 1 : 2) && (units & (units - 1)) == 0 && a.Ms <= a.Mpad;
 }
 

@@ -55,3 +55,26 @@ def test_detection_of_the_layer_behind_bit_exact(bf16, dense):
             np.testing.assert_array_equal(net.read_list(l, cb.LIST_CHANGED), orc.trace[l]["C"], err_msg="layer %d frame %d" % (l, t))
             np.testing.assert_array_equal(net.read_list(l, cb.LIST_UPDATE), orc.trace[l]["U"], err_msg="layer %d frame %d" % (l, t))
     net.destroy()
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("cin,cout,h,w", [(3, 8, 61, 83), (8, 16, 61, 83), (8, 64, 40, 52), (6, 32, 128, 1024)])
+def test_same_bits_however_positions_arrive(cin, cout, h, w, bf16):
+    """Real-valued data: positions ranked in the kernel, from the list of every frame, and all of them in
+    order must give the same sums bit for bit (and with them the same flags for the layer behind)."""
+    layers = [conv(cin, cout, 1), conv(cout, 8, 3, relu=False)]
+    params = make_weights(layers, cin + cout)
+    r = np.random.default_rng(h)
+    frames = [r.standard_normal((cin, h, w), dtype=np.float32) for _ in range(3)]  # every position changes
+    out = {}
+    for name, kw in (("ranked", {}), ("listed", {"lists_every_frame": True}), ("dense", {})):
+        net = cb.CBInfer(layers, params, (cin, h, w), 0.0, dtype=cb.BF16 if bf16 else cb.F32, **kw)
+        net.set_mode(name == "dense")
+        out[name] = []
+        for f in frames:
+            y = net.process_frame(to_dev(f)).cpu().numpy()
+            out[name] += [net.read_map(0, cb.MAP_OUTPUT), y]
+        net.destroy()
+    for a, b, c in zip(out["ranked"], out["listed"], out["dense"]):
+        np.testing.assert_array_equal(a, b)
+        np.testing.assert_array_equal(a, c)
