@@ -1022,7 +1022,8 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                         for (int f = 0; f < TC * TP * 4; ++f) v = f == e ? acc[f / (TP * 4)][f / 4 % TP][f % 4] : v;
                         const int g = list[wpx0 + (e >> 2) % TP * 16 + lrow];
                         const int row = mt * BM + wch0 + (e >> 2) / TP * 16 + lk * 4 + (e & 3);
-                        if (!(fabsf(v) < __builtin_inff()) && g >= 0 && row < a.M) v = plain_sum<BM>(a, nk, row, g);
+                        // rows behind the last channel are padding channels of the stored map: zeros, which the next layer multiplies with
+                        if (!(fabsf(v) < __builtin_inff()) && g >= 0) v = plain_sum<BM>(a, nk, row, g);
 #pragma unroll
                         for (int f = 0; f < TC * TP * 4; ++f) acc[f / (TP * 4)][f / 4 % TP][f % 4] = f == e ? v : acc[f / (TP * 4)][f / 4 % TP][f % 4];
                     }

@@ -67,6 +67,25 @@ def test_values_that_are_not_finite(cin, cout, k, h, w, special):
     assert np.all(np.abs(got - want)[fine] <= ((cin * k * k + 40) * 2.0 ** -23 * size)[fine])
 
 
+def test_padding_channels_stay_zero_beside_the_largest_values():
+    """A finite pixel whose first part rounds to infinity, in front of six channels stored as eight: the two
+    padding channels must stay zero, or the layer behind multiplies its zero weights with NaN."""
+    layers = [conv(64, 6, 5, relu=False), conv(6, 8, 3, relu=False)]
+    (w0, b0), (w1, b1) = make_weights(layers, 11)
+    w0 = w0 * np.float32(2.0 ** -100)
+    b0 = b0 * 0
+    x = np.random.default_rng(2).random((64, 14, 15), dtype=np.float32)
+    x[7, 4, 5] = 3.4028e38
+    x[50, 13, 14] = -3.4028e38
+    net = cb.CBInfer(layers, [(w0, b0), (w1, b1)], x.shape, 0.02)
+    got = net.process_frame(to_dev(x)).cpu().numpy()[0].astype(np.float64)
+    net.destroy()
+    mid = _reference(layers[0], w0, b0, x)
+    want = _reference(layers[1], w1, b1, mid.astype(np.float32))
+    size = _reference(layers[1], np.abs(w1), np.abs(b1), _reference(layers[0], np.abs(w0), b0, np.abs(x)).astype(np.float32))
+    assert np.all(np.abs(got - want) <= (64 * 25 + 6 * 9 + 8) * 2.0 ** -23 * size)
+
+
 def test_static_workspace_with_fewer_workgroups():
     """A network a little too large for the static workspace at full width runs there with half the workgroups
     per launch; sums are cut along K in other places then, so results agree within rounding."""
