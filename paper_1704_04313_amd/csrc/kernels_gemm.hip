@@ -704,12 +704,13 @@ __device__ __forceinline__ float plain_sum(const GemmArgs &a, int nk, int row, i
     for (int j = 0; j < a.kh; ++j)
         for (int i = 0; i < a.kw; ++i) {
             const int iy = qy * a.stride - a.pad + j, ix = qx * a.stride - a.pad + i;
-            if ((unsigned)iy >= (unsigned)a.H || (unsigned)ix >= (unsigned)a.W) continue;
-            const float *px = x + (size_t)((st * a.H + iy) * a.W + ix) * a.pix_words;
+            // outside the image is zero, and zero times a weight that is not finite is not a number
+            const bool in = (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W;
+            const float *px = x + (in ? (size_t)((st * a.H + iy) * a.W + ix) * a.pix_words : 0);
             for (int c = 0; c < a.pix_words; ++c) {
                 const unsigned short *w = wt + filter_fragment<kF32>(BM, nk, row, (j * a.kw + i) * Cs + c);
                 const float wv = bf16_value(w[0]) + (bf16_value(w[kFilterPartStride]) + bf16_value(w[2 * kFilterPartStride]));
-                s = fmaf(px[c], wv, s);
+                s = fmaf(in ? px[c] : 0.f, wv, s);
             }
         }
     return s;

@@ -86,6 +86,28 @@ def test_padding_channels_stay_zero_beside_the_largest_values():
     assert np.all(np.abs(got - want) <= (64 * 25 + 6 * 9 + 8) * 2.0 ** -23 * size)
 
 
+@pytest.mark.parametrize("special", [np.inf, -np.inf, np.nan])
+def test_weights_that_are_not_finite(special):
+    """An infinite weight on a tap that lies in the zero padding of some outputs: zero times infinity is not a
+    number there, infinity elsewhere."""
+    L = conv(64, 20, 5, relu=False)
+    (wt, b), = make_weights([L], 3)
+    wt[3, 5, 0, 0] = special
+    wt[17, 60, 4, 2] = special
+    x = np.random.default_rng(4).random((64, 17, 16), dtype=np.float32) + np.float32(0.5)
+    padded = np.pad(x, ((0, 0), (2, 2), (2, 2)))
+    with np.errstate(all="ignore"):
+        win = np.lib.stride_tricks.sliding_window_view(padded.astype(np.float64), (5, 5), axis=(1, 2))
+        want = np.stack([(win * wt[o].astype(np.float64)[:, None, None]).sum(axis=(0, 3, 4)) + b[o] for o in range(20)])
+    got = _dense(L, [(wt, b)], x)
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(want))
+    np.testing.assert_array_equal(np.isposinf(got), np.isposinf(want))
+    np.testing.assert_array_equal(np.isneginf(got), np.isneginf(want))
+    fine = np.isfinite(want)
+    size = _reference(L, np.where(np.isfinite(wt), np.abs(wt), 0), np.abs(b), x)
+    assert fine[4].all() and np.all((np.abs(got - want) <= (64 * 25 + 8) * 2.0 ** -23 * size)[fine])
+
+
 def test_static_workspace_with_fewer_workgroups():
     """A network a little too large for the static workspace at full width runs there with half the workgroups
     per launch; sums are cut along K in other places then, so results agree within rounding."""
