@@ -439,12 +439,16 @@ __device__ __forceinline__ int share_owner(const Schedule &s, int it)
 
 __device__ __forceinline__ int lds_swizzle(int row) { return (row >> 1) & 7; }
 
-// s_waitcnt vmcnt(N), everything else unconstrained (gfx9 encoding: vmcnt in bits 3:0 and 15:14).
+// s_waitcnt vmcnt(N), everything else unconstrained (gfx9 encoding: vmcnt in bits 3:0 and 15:14).  What is
+// waited for are loads and stores issued before it, on behalf of what comes behind it: the compiler must
+// not move memory operations across in either direction, and the builtin alone does not say so.
 template <int N>
 __device__ __forceinline__ void wait_vmcnt()
 {
     static_assert(N >= 0 && N < 64, "vmcnt is a six-bit counter");
+    asm volatile("" ::: "memory");
     __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);
+    asm volatile("" ::: "memory");
 }
 
 // The workgroup barrier as the direct-to-LDS producers execute it: the bare instruction.  The
@@ -462,14 +466,18 @@ __device__ __forceinline__ void producer_barrier()
 typedef __attribute__((address_space(1))) const void *GlobalPtr;
 typedef __attribute__((address_space(3))) void *LdsPtr;
 
-// s_waitcnt lgkmcnt(0), everything else unconstrained.
-__device__ __forceinline__ void wait_lgkmcnt0() { __builtin_amdgcn_s_waitcnt(0xC07F); }
+// s_waitcnt lgkmcnt(0), everything else unconstrained; ordered like wait_vmcnt.
+__device__ __forceinline__ void wait_lgkmcnt0()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    asm volatile("" ::: "memory");
+}
 
 // The workgroup barrier as the consumers execute it: their LDS reads are complete (the slice they read
 // may be overwritten), stores to global memory need not be.
 __device__ __forceinline__ void consumer_barrier()
 {
-    asm volatile("" ::: "memory");
     wait_lgkmcnt0();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
@@ -622,7 +630,7 @@ __device__ __forceinline__ void direct_producer(const GemmArgs &a, const int n, 
 #pragma unroll 1
     for (int d = 0; d < STAGES - 1; ++d)
         if (d < slices) issue(d);
-    if (STAGES - 2 < slices)
+    if (STAGES > 3 && STAGES - 2 < slices)
         wait_vmcnt<(STAGES - 3) * PS>();
     else
         wait_vmcnt<0>();
@@ -630,12 +638,12 @@ __device__ __forceinline__ void direct_producer(const GemmArgs &a, const int n, 
     int slot = STAGES - 1; // ring slot of slice t + STAGES - 1
 #pragma unroll 1
     for (int t = 0; t < slices; ++t) {
-        if (t + STAGES - 1 < slices) {
-            issue(slot);
+        const bool more = t + STAGES - 1 < slices;
+        if (more) issue(slot);
+        if (STAGES > 3 && more) // (three slices: nothing may stay in flight either way)
             wait_vmcnt<(STAGES - 3) * PS>();
-        } else {
+        else
             wait_vmcnt<0>();
-        }
         slot = slot == STAGES - 1 ? 0 : slot + 1;
         producer_barrier();
     }
@@ -975,6 +983,7 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
             int drawn = 0;
             if (lane == 0) drawn = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             drawn = __builtin_amdgcn_readfirstlane(drawn);
+            asm volatile("" ::: "memory"); // the other waves' parts are read behind the ticket, not before it
             finish = drawn == w_last - w_first;
             if (finish) {
                 if (lane == 0) *ticket = 0; // ready for the next launch
