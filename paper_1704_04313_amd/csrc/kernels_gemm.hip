@@ -696,32 +696,75 @@ __host__ __device__ inline size_t filter_fragment(int bm, int nk, int row, int k
     return ((((size_t)mt * nk + kc) * (bm / 16) + ct) * kFilterParts<DT> + part) * (kFragBytes / 2) + (lk * 16 + row % 16) * 8 + e;
 }
 
-// The sum of channel `row` at output position g, product by product in float32 from global memory:
-// for sums that are not finite.  Where a value is infinite, not a number, or so near the largest
-// float32 that its first part rounds to infinity, the products of parts are not those of the values
-// (infinity less infinity, infinity times a part that is zero), so the value itself decides here.
-template <int BM>
-__device__ __forceinline__ float plain_sum(const GemmArgs &a, int nk, int row, int g)
+// Slices kc0 .. kc1 - 1 of a wave's sub-tile once more, multiplied by the float32 instruction straight from
+// global memory (wt: its filter fragments of the first slice): for sums that the parts do not give.  Where a value is infinite, not a number, or so near the largest float32 that its
+// first part rounds to infinity, the products of parts are not those of the values (infinity less infinity,
+// infinity times a part that is zero), so the values themselves decide.  Filter values are put together from
+// their parts; channels behind the last one of a packed pixel count as zero.  Bound by the loads, which are
+// issued one group of four units ahead; see the figures where it is called.
+template <int BM, int TP, int TC>
+__device__ __forceinline__ void plain_sums(const GemmArgs &a, int kc0, int kc1, const char *wt, const int *list, floatx4 (&sum)[TC][TP])
 {
+    const int lane = threadIdx.x & 63, lrow = lane & 15, lk = lane >> 4;
     const float *x = static_cast<const float *>(a.x);
-    const unsigned short *wt = static_cast<const unsigned short *>(a.wt);
-    const int st = fast_div(g, a.dNo), q = g - st * a.No;
-    const int qy = fast_div(q, a.dWo), qx = q - qy * a.Wo;
-    const int Cs = a.dVin.d * 4;
-    float s = 0.f;
-    for (int j = 0; j < a.kh; ++j)
-        for (int i = 0; i < a.kw; ++i) {
-            const int iy = qy * a.stride - a.pad + j, ix = qx * a.stride - a.pad + i;
-            // outside the image is zero, and zero times a weight that is not finite is not a number
-            const bool in = (unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W;
-            const float *px = x + (in ? (size_t)((st * a.H + iy) * a.W + ix) * a.pix_words : 0);
-            for (int c = 0; c < a.pix_words; ++c) {
-                const unsigned short *w = wt + filter_fragment<kF32>(BM, nk, row, (j * a.kw + i) * Cs + c);
-                const float wv = bf16_value(w[0]) + (bf16_value(w[kFilterPartStride]) + bf16_value(w[2 * kFilterPartStride]));
-                s = fmaf(in ? px[c] : 0.f, wv, s);
-            }
+    int iy0[TP], ix0[TP], base[TP];
+#pragma unroll
+    for (int i = 0; i < TP; ++i) {
+        const int g = list[i * 16 + lrow];
+        const int st = fast_div(g < 0 ? 0 : g, a.dNo), q = g - st * a.No;
+        const int qy = fast_div(g < 0 ? 0 : q, a.dWo), qx = q - qy * a.Wo;
+        iy0[i] = g < 0 ? -(1 << 28) : qy * a.stride - a.pad;
+        ix0[i] = g < 0 ? -(1 << 28) : qx * a.stride - a.pad;
+        base[i] = g < 0 ? 0 : ((st * a.H + iy0[i]) * a.W + ix0[i]) * a.pix_words;
+    }
+#pragma unroll
+    for (int j = 0; j < TC; ++j)
+#pragma unroll
+        for (int i = 0; i < TP; ++i) sum[j][i] = (floatx4){0.f, 0.f, 0.f, 0.f};
+    struct Group {
+        floatx4 px[TP];
+        uint2 w[TC][3];
+        int c; // channel of the unit's first value
+    };
+    // units 4 u .. 4 u + 3 of the filter rows, the one of number 4 u + lk in this lane; h = u & 1
+    auto load = [&](Group &v, int u, int h) {
+        const int unit = 4 * u + lk, tap = fast_div(unit, a.dVin), cu = unit - tap * a.dVin.d;
+        const int tj = fast_div(tap, a.dKw), ti = tap - tj * a.kw;
+        const int off = (tj * a.W + ti) * a.pix_words + cu * 4;
+        v.c = cu * 4;
+#pragma unroll
+        for (int i = 0; i < TP; ++i) {
+            const bool ok = tj < a.kh && (unsigned)(iy0[i] + tj) < (unsigned)a.H && (unsigned)(ix0[i] + ti) < (unsigned)a.W;
+            v.px[i] = *reinterpret_cast<const floatx4_a4 *>(x + (ok ? (unsigned)(base[i] + off) : (unsigned)a.zero_word));
         }
-    return s;
+        const char *slice = wt + (size_t)((u >> 1) - kc0) * (BM / 16 * 3 * kFragBytes) + lane * 16 + h * 8;
+#pragma unroll
+        for (int j = 0; j < TC; ++j)
+#pragma unroll
+            for (int p = 0; p < 3; ++p) v.w[j][p] = *reinterpret_cast<const uint2 *>(slice + (j * 3 + p) * kFragBytes);
+    };
+    // k = 16 u + 4 lk + e in step e
+    auto multiply = [&](const Group &v) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            auto part = [&](int j, int p) { return bf16_value((unsigned short)((e < 2 ? v.w[j][p].x : v.w[j][p].y) >> (e & 1 ? 16 : 0))); };
+#pragma unroll
+            for (int j = 0; j < TC; ++j)
+#pragma unroll
+                for (int i = 0; i < TP; ++i)
+                    sum[j][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(part(j, 0) + (part(j, 1) + part(j, 2)),
+                                                                     v.c + e < a.pix_words ? v.px[i][e] : 0.f, sum[j][i], 0, 0, 0);
+        }
+    };
+    Group v0, v1;
+    load(v0, 2 * kc0, 0);
+#pragma unroll 1
+    for (int u = 2 * kc0; u < 2 * kc1; u += 2) {
+        load(v1, u + 1, 1);
+        multiply(v0);
+        load(v0, u + 2 < 2 * kc1 ? u + 2 : u, 0);
+        multiply(v1);
+    }
 }
 
 // BM x BN workgroup tile; the consumer waves are arranged WM (channels) x WN (pixels).
@@ -956,6 +999,32 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
             __builtin_amdgcn_s_setprio(0);
         }
 
+        if constexpr (DT == kF32) {
+            // Sums that are not finite are formed again from the values themselves, by each wave for its own K
+            // range.  (x * 0 is zero for every finite x.)  A tile with such a sum takes two to four times as long:
+            // 64->256 7x7 on 160 x 90 positions 130 us, with one NaN in the map 440, with nothing else in it 470; on
+            // 20 x 20 23, 37 and 38; 16->64 7x7 on 640 x 900 345, 357 and 986 (one lane per sum, product by product:
+            // 11 150 us for that one NaN, 25 700 for the full map).
+            float z = 0.f;
+#pragma unroll
+            for (int j = 0; j < TC; ++j)
+#pragma unroll
+                for (int i = 0; i < TP; ++i) z += acc[j][i][0] * 0.f + acc[j][i][1] * 0.f + acc[j][i][2] * 0.f + acc[j][i][3] * 0.f;
+            if (__builtin_expect(__any(z != 0.f), 0)) { // NaN compares unequal
+                floatx4 sum[TC][TP];
+                const char *wt = static_cast<const char *>(a.wt) +
+                                 (((size_t)mt * nk + kc0) * (BM / 16) + wch0 / 16) * (3 * kFragBytes);
+                plain_sums<BM, TP, TC>(a, kc0, kc1, wt, list + wpx0, sum);
+#pragma unroll
+                for (int j = 0; j < TC; ++j)
+#pragma unroll
+                    for (int i = 0; i < TP; ++i)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (!(fabsf(acc[j][i][e]) < __builtin_inff())) acc[j][i][e] = sum[j][i][e];
+            }
+        }
+
         // ---- a shared tile: store this K range's accumulators, take a ticket; the wave holding the last
         //      ticket of its sub-tile adds up all ranges (ascending K) and does the output update.  A
         //      sub-tile belongs to the same wave of every workgroup, so waves need no barrier for this:
@@ -1010,33 +1079,6 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                     for (int j = 0; j < TC; ++j)
 #pragma unroll
                         for (int i = 0; i < TP; ++i) acc[j][i] += part[j][i];
-                }
-            }
-        }
-
-        if constexpr (DT == kF32) {
-            // Sums that are not finite are formed again from the values themselves.  (x * 0 is zero for
-            // every finite x.)
-            if (finish) {
-                float z = 0.f;
-#pragma unroll
-                for (int j = 0; j < TC; ++j)
-#pragma unroll
-                    for (int i = 0; i < TP; ++i) z += acc[j][i][0] * 0.f + acc[j][i][1] * 0.f + acc[j][i][2] * 0.f + acc[j][i][3] * 0.f;
-                if (__builtin_expect(__any(z != 0.f), 0)) { // NaN compares unequal
-                    // one value at a time, picked from the registers by comparison: the loop stays a loop
-#pragma unroll 1
-                    for (int e = 0; e < TC * TP * 4; ++e) {
-                        float v = 0.f;
-#pragma unroll
-                        for (int f = 0; f < TC * TP * 4; ++f) v = f == e ? acc[f / (TP * 4)][f / 4 % TP][f % 4] : v;
-                        const int g = list[wpx0 + (e >> 2) % TP * 16 + lrow];
-                        const int row = mt * BM + wch0 + (e >> 2) / TP * 16 + lk * 4 + (e & 3);
-                        // rows behind the last channel are padding channels of the stored map: zeros, which the next layer multiplies with
-                        if (!(fabsf(v) < __builtin_inff()) && g >= 0) v = plain_sum<BM>(a, nk, row, g);
-#pragma unroll
-                        for (int f = 0; f < TC * TP * 4; ++f) acc[f / (TP * 4)][f / 4 % TP][f % 4] = f == e ? v : acc[f / (TP * 4)][f / 4 % TP][f % 4];
-                    }
                 }
             }
         }

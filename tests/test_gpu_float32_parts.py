@@ -108,6 +108,31 @@ def test_weights_that_are_not_finite(special):
     assert fine[4].all() and np.all((np.abs(got - want) <= (64 * 25 + 8) * 2.0 ** -23 * size)[fine])
 
 
+@pytest.mark.parametrize("h,w", [(20, 20), (90, 160)])
+def test_cost_of_a_value_that_is_not_finite(h, w):
+    """One NaN pixel, and a map of nothing else, in a wide layer: the sums formed again take two to four times
+    as long (measured), not a hundred times; the bound leaves room for a loaded machine."""
+    import torch
+    L = conv(64, 256, 7, relu=False)
+    net = cb.CBInfer([L], make_weights([L], 3), (64, h, w), 0.02)
+    net.set_mode(True)
+    us = []
+    for fill in (0, 1, 2):
+        x = torch.rand((1, 64, h, w), device="cuda")
+        if fill:
+            x.view(-1)[slice(h * w // 2, h * w // 2 + 1) if fill == 1 else slice(None)] = float("nan")
+        for _ in range(3):
+            net.process_frame(x)
+        net.set_profiling(True)
+        for _ in range(5):
+            net.process_frame(x)
+        ms, n = net.read_profile(0, cb.STEP_NAMES.index("gemm"))
+        net.set_profiling(False)
+        us.append(1e3 * ms / n)
+    net.destroy()
+    assert max(us[1:]) <= 12 * us[0], us
+
+
 def test_static_workspace_with_fewer_workgroups():
     """A network a little too large for the static workspace at full width runs there with half the workgroups
     per launch; sums are cut along K in other places then, so results agree within rounding."""
