@@ -46,6 +46,7 @@ struct Op {
     float tau = 0.f;
     int K = 0, Kpad = 0, Mpad = 0;
     int gemm_grid = 0;
+    unsigned tiny_sum = 0; // CONV: GemmArgs::tiny_sum
     bool select = false; // CONV: maps small enough for the GEMM (and the pooling after it) to pick their
                          // positions from the update maps themselves; index lists are then only
                          // extracted when the caller asks for them
@@ -383,6 +384,21 @@ void bf16_parts(const float *x, int n, int parts, unsigned short *p0, unsigned s
     }
 }
 
+// The magnitude of the largest finite of n weights.  (Bits of magnitudes compare like integers.)
+float largest_weight(const float *w, size_t n)
+{
+    int m = 0;
+    for (size_t i = 0; i < n; ++i) {
+        int u;
+        memcpy(&u, w + i, 4);
+        u &= 0x7fffffff;
+        if (u > m && u < 0x7f800000) m = u;
+    }
+    float f;
+    memcpy(&f, &m, 4);
+    return f;
+}
+
 // Filter matrix K (Section 3) re-laid-out for the gather: row o, column k = (j*kw + i)*Cs + c, as
 // float32 or bfloat16 (round to nearest even), row by row or in fragments.
 void build_filter_matrix(const Op &op, int dtype, const float *w, std::vector<unsigned char> &bytes)
@@ -664,6 +680,7 @@ int enqueue_frame(cbinfer_state *s, const float *frame, float *out)
             a.zero_word = S * N * op.pix_words;
             a.M = op.M; a.Mpad = op.Mpad; a.Ms = op.Ms; a.relu = op.relu;
             a.max_pixels = S * No;
+            a.tiny_sum = op.tiny_sum;
             a.partial = s->at<float>(P.o_partial);
             a.tickets = s->at<int>(P.o_tickets);
             a.grid = op.gemm_grid;
@@ -800,9 +817,12 @@ static cbinfer_state *create_state(const cbinfer_network *net, const Plan &P, ch
         std::vector<float> bias;
         std::vector<int2> taps;
         for (size_t l = 0; l < P.ops.size(); ++l) {
-            const Op &op = P.ops[l];
+            Op &op = s->plan.ops[l];
             if (op.kind != CBINFER_OP_CONV) continue;
             const cbinfer_layer &L = net->layers[l];
+            if (P.dtype == cbk::kF32 && cbk::gemm_filter_in_fragments(P.dtype, op.Mpad, op.Kpad))
+                op.tiny_sum = cbk::gemm_tiny_sum(
+                    op.K, largest_weight(static_cast<const float *>(L.weight), (size_t)op.M * op.C * op.kh * op.kw));
             build_filter_matrix(op, P.dtype, static_cast<const float *>(L.weight), wt);
             bias.assign(op.Mpad, 0.0f);
             if (L.bias)

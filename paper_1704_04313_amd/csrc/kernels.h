@@ -226,6 +226,9 @@ struct GemmArgs {
     int Kpad;           // filter-matrix row length in elements, a multiple of gemm_k_multiple(dtype)
     int M, Mpad, Ms, relu;
     int max_pixels;     // upper bound of *count
+    // float32 in parts: sums v != 0 with (bits of v << 1) - 1 < tiny_sum are formed again from the values
+    // themselves (gemm_tiny_sum).  0: none.
+    unsigned tiny_sum;
     float *partial;     // scratch for partial accumulators, gemm_partial_bytes(M, grid) bytes
     int *tickets;       // gemm_ticket_bytes(grid) bytes, zero before the first launch (each launch
                         // leaves them zero again)
@@ -252,6 +255,12 @@ bool gemm_filter_in_fragments(int dtype, int Mpad, int Kpad);
 size_t gemm_filter_bytes(int dtype, int Mpad, int Kpad);
 size_t gemm_filter_fragment(int dtype, int Mpad, int Kpad, int row, int k);
 constexpr int kFilterPartStride = 512;
+// GemmArgs::tiny_sum for rows of K weights of at most that magnitude.  The parts of a pixel value are off by half the
+// smallest bfloat16 at most, 2^-134, and a sum by 2^-134 K times the largest weight: below 2^24 times that
+// it is less exact than float32, so it is formed again.  (A sum that is exactly zero is taken as it is:
+// blank parts of a map are full of them.  If all its pixels are below 2^-134 it should be below
+// 2^-134 K times the largest weight.)
+unsigned gemm_tiny_sum(int K, float largest_weight);
 size_t gemm_partial_bytes(int M, int grid);
 size_t gemm_ticket_bytes(int grid);
 hipError_t gemm_prepare(void);  // one-time function attributes (dynamic LDS size)

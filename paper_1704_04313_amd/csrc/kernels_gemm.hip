@@ -50,8 +50,11 @@
 // which every wave multiplies 16 positions by the whole reduction out of its own registers.
 #include "kernels.h"
 
+#include <cfloat>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 
 namespace cbk {
 
@@ -652,7 +655,10 @@ __device__ __forceinline__ void direct_producer(const GemmArgs &a, const int n, 
 // A float32 as the sum of three bfloat16: hi = x rounded to 8 significant bits, mid = the rest rounded
 // likewise, lo = what is left; 24 bits need no fourth.  Both differences are exact (the rest of a
 // rounding to nearest has at most 16 significant bits, the next one at most 8), so hi + mid + lo is x
-// itself.  Eight consecutive values of a lane become one 16-byte fragment of each part.
+// itself from 2^-110 on.  Below, lo ends at the smallest bfloat16, 2^-133, and hi + mid + lo is x to half of
+// that; sums in which this counts are formed again (GemmArgs::tiny_sum).  (Neither the dot product nor the
+// matrix instruction flushes subnormal operands: measured.)
+// Eight consecutive values of a lane become one 16-byte fragment of each part.
 struct Parts {
     uintx4 hi, mid, lo;
 };
@@ -699,13 +705,16 @@ __host__ __device__ inline size_t filter_fragment(int bm, int nk, int row, int k
 // Slices kc0 .. kc1 - 1 of a wave's sub-tile once more, multiplied by the float32 instruction straight from
 // global memory (wt: its filter fragments of the first slice): for sums that the parts do not give.  Where a value is infinite, not a number, or so near the largest float32 that its
 // first part rounds to infinity, the products of parts are not those of the values (infinity less infinity,
-// infinity times a part that is zero), so the values themselves decide.  Filter values are put together from
+// infinity times a part that is zero), and values below 2^-110 are not the sum of theirs, so the values
+// themselves decide.  Filter values are put together from
 // their parts; channels behind the last one of a packed pixel count as zero.  Bound by the loads, which are
 // issued one group of four units ahead; see the figures where it is called.
 template <int BM, int TP, int TC>
 __device__ __forceinline__ void plain_sums(const GemmArgs &a, int kc0, int kc1, const char *wt, const int *list, floatx4 (&sum)[TC][TP])
 {
-    const int lane = threadIdx.x & 63, lrow = lane & 15, lk = lane >> 4;
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane)); // nothing of this is computed ahead of the K loop and kept across it
+    const int lrow = lane & 15, lk = lane >> 4;
     const float *x = static_cast<const float *>(a.x);
     int iy0[TP], ix0[TP], base[TP];
 #pragma unroll
@@ -1000,17 +1009,25 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
         }
 
         if constexpr (DT == kF32) {
-            // Sums that are not finite are formed again from the values themselves, by each wave for its own K
+            // Sums that are not finite, and such small ones that parts below the smallest bfloat16 count
+            // (GemmArgs::tiny_sum), are formed again from the values themselves, by each wave for its own K
             // range.  (x * 0 is zero for every finite x.)  A tile with such a sum takes two to four times as long:
             // 64->256 7x7 on 160 x 90 positions 130 us, with one NaN in the map 440, with nothing else in it 470; on
             // 20 x 20 23, 37 and 38; 16->64 7x7 on 640 x 900 345, 357 and 986 (one lane per sum, product by product:
             // 11 150 us for that one NaN, 25 700 for the full map).
             float z = 0.f;
+            unsigned least = ~0u;
+            auto size = [](float v) { return (__float_as_uint(v) << 1) - 1u; }; // grows with |v|; largest for zero
 #pragma unroll
             for (int j = 0; j < TC; ++j)
 #pragma unroll
-                for (int i = 0; i < TP; ++i) z += acc[j][i][0] * 0.f + acc[j][i][1] * 0.f + acc[j][i][2] * 0.f + acc[j][i][3] * 0.f;
-            if (__builtin_expect(__any(z != 0.f), 0)) { // NaN compares unequal
+                for (int i = 0; i < TP; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        z = fmaf(acc[j][i][e], 0.f, z);
+                        least = min(least, size(acc[j][i][e]));
+                    }
+            if (__builtin_expect(__any(z != 0.f || least < a.tiny_sum), 0)) { // NaN compares unequal
                 floatx4 sum[TC][TP];
                 const char *wt = static_cast<const char *>(a.wt) +
                                  (((size_t)mt * nk + kc0) * (BM / 16) + wch0 / 16) * (3 * kFragBytes);
@@ -1020,8 +1037,11 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
 #pragma unroll
                     for (int i = 0; i < TP; ++i)
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (!(fabsf(acc[j][i][e]) < __builtin_inff())) acc[j][i][e] = sum[j][i][e];
+                        for (int e = 0; e < 4; ++e) {
+                            float v = acc[j][i][e];
+                            asm("" : "+v"(v)); // compared anew: the results from above would all be kept in registers
+                            if (!(fabsf(v) < __builtin_inff()) || size(v) < a.tiny_sum) acc[j][i][e] = sum[j][i][e];
+                        }
             }
         }
 
@@ -1546,6 +1566,15 @@ size_t gemm_filter_fragment(int dtype, int Mpad, int Kpad, int row, int k)
 }
 
 // ---- host side --------------------------------------------------------------------------
+unsigned gemm_tiny_sum(int K, float largest_weight)
+{
+    const double t = std::ldexp((double)K * largest_weight, -110);
+    const float f = t < FLT_MAX ? (float)t : FLT_MAX;
+    unsigned u;
+    memcpy(&u, &f, 4);
+    return u ? (u << 1) - 1 : 0;
+}
+
 int gemm_k_multiple(int dtype) { return BK * 4 / elem_bytes(dtype); }
 
 void gemm_set_divisors(GemmArgs &a)

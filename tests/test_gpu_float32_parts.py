@@ -108,6 +108,23 @@ def test_weights_that_are_not_finite(special):
     assert fine[4].all() and np.all((np.abs(got - want) <= (64 * 25 + 8) * 2.0 ** -23 * size)[fine])
 
 
+@pytest.mark.parametrize("exponent", [0, -100, -108, -111, -114, -118, -122, -126])
+def test_pixels_near_the_smallest_float32(exponent):
+    """Below 2^-110 a value is not the sum of its bfloat16 parts; sums of such values must be as exact as
+    others all the same.  A third of the map is zero, a third holds ordinary values."""
+    L = conv(64, 64, 3, relu=False)
+    (wt, b), = make_weights([L], 6)
+    x = np.random.default_rng(8).random((64, 20, 33), dtype=np.float32)
+    x[:, :, :22] *= np.float32(2.0 ** exponent)
+    x[:, :, 11:22] = 0
+    got, want = _dense(L, [(wt, b * 0)], x), _reference(L, wt, b * 0, x)
+    # float32 sums of 576 products whose roundings have either sign: a quarter unit each relative to the sum in
+    # the mean; where the sums are subnormal each addition rounds by up to half of 2^-149
+    for cols in (slice(0, 10), slice(12, 21), slice(23, 33)):
+        g, e = got[:, :, cols], want[:, :, cols]
+        assert np.linalg.norm(g - e) <= np.sqrt(576 / 4) * 2.0 ** -24 * np.linalg.norm(e) + np.sqrt(576 * e.size) * 2.0 ** -150
+
+
 @pytest.mark.parametrize("h,w", [(20, 20), (90, 160)])
 def test_cost_of_a_value_that_is_not_finite(h, w):
     """One NaN pixel, and a map of nothing else, in a wide layer: the sums formed again take two to four times
