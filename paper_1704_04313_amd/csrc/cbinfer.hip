@@ -46,7 +46,8 @@ struct Op {
     float tau = 0.f;
     int K = 0, Kpad = 0, Mpad = 0;
     int gemm_grid = 0;
-    unsigned tiny_sum = 0; // CONV: GemmArgs::tiny_sum
+    unsigned tiny_sum = 0;     // CONV: GemmArgs::tiny_sum, ...
+    int filter_exp = 0;        // ... and filter_exp
     bool select = false; // CONV: maps small enough for the GEMM (and the pooling after it) to pick their
                          // positions from the update maps themselves; index lists are then only
                          // extracted when the caller asks for them
@@ -359,7 +360,7 @@ int collect_profile(cbinfer_state *s)
 }
 
 // The bfloat16 parts of n float32 weights, rounded to nearest even: the first alone (bfloat16 storage), or
-// three that add up to the weight exactly.  A finite weight next to the largest float32 must not round to
+// three that add up to the weight exactly (from 2^-110 on).  A finite weight next to the largest float32 must not round to
 // infinity then (its first part is cut off instead); of one that is not finite only the first part
 // is kept.  Without branches, for the sake of the compiler's vectors: a network has millions of weights.
 void bf16_parts(const float *x, int n, int parts, unsigned short *p0, unsigned short *p1, unsigned short *p2)
@@ -384,19 +385,32 @@ void bf16_parts(const float *x, int n, int parts, unsigned short *p0, unsigned s
     }
 }
 
-// The magnitude of the largest finite of n weights.  (Bits of magnitudes compare like integers.)
-float largest_weight(const float *w, size_t n)
+// The magnitude of the largest finite of n weights, and whether any but zero is below 2^-110.  (Bits of
+// magnitudes compare like integers.)
+float largest_weight(const float *w, size_t n, bool &tiny)
 {
-    int m = 0;
+    int m = 0, t = 0;
     for (size_t i = 0; i < n; ++i) {
         int u;
         memcpy(&u, w + i, 4);
         u &= 0x7fffffff;
         if (u > m && u < 0x7f800000) m = u;
+        t |= u && u < (127 - 110) << 23;
     }
     float f;
     memcpy(&f, &m, 4);
+    tiny = t != 0;
     return f;
+}
+
+// The power of two that float32 weights are multiplied with before they are split into parts: 0, or what brings
+// the smallest float32 to 2^-110, from where on a value is the sum of its parts, as long as the largest weight
+// stays below 2^88.  (Sums grow alike; those that overflow are formed again from the values.)
+int filter_exponent(float largest, bool tiny)
+{
+    int e = tiny ? 39 : 0;
+    while (e > 0 && std::ldexp((double)largest, e) >= std::ldexp(1.0, 88)) --e;
+    return e;
 }
 
 // Filter matrix K (Section 3) re-laid-out for the gather: row o, column k = (j*kw + i)*Cs + c, as
@@ -411,11 +425,12 @@ void build_filter_matrix(const Op &op, int dtype, const float *w, std::vector<un
     std::vector<float> row(op.Kpad, 0.0f);
     std::vector<unsigned short> part((size_t)op.Kpad * 3, 0);
     std::vector<size_t> place(fragments ? op.Kpad / eu : 0); // of a row's units, from where the row begins
+    const float scale = std::ldexp(1.0f, op.filter_exp);
     for (size_t v = 0; v < place.size(); ++v)
         place[v] = cbk::gemm_filter_fragment(dtype, op.Mpad, op.Kpad, 0, (int)v * eu);
     for (int o = 0; o < op.M; ++o) {
         for (int c = 0; c < op.C; ++c)
-            for (int t = 0; t < area; ++t) row[(size_t)t * op.Cs + c] = w[((size_t)o * op.C + c) * area + t];
+            for (int t = 0; t < area; ++t) row[(size_t)t * op.Cs + c] = w[((size_t)o * op.C + c) * area + t] * scale;
         if (!fragments && dtype == cbk::kF32) {
             memcpy(f + (size_t)o * op.Kpad, row.data(), (size_t)op.Kpad * 4);
             continue;
@@ -681,6 +696,7 @@ int enqueue_frame(cbinfer_state *s, const float *frame, float *out)
             a.M = op.M; a.Mpad = op.Mpad; a.Ms = op.Ms; a.relu = op.relu;
             a.max_pixels = S * No;
             a.tiny_sum = op.tiny_sum;
+            a.filter_exp = op.filter_exp;
             a.partial = s->at<float>(P.o_partial);
             a.tickets = s->at<int>(P.o_tickets);
             a.grid = op.gemm_grid;
@@ -820,9 +836,12 @@ static cbinfer_state *create_state(const cbinfer_network *net, const Plan &P, ch
             Op &op = s->plan.ops[l];
             if (op.kind != CBINFER_OP_CONV) continue;
             const cbinfer_layer &L = net->layers[l];
-            if (P.dtype == cbk::kF32 && cbk::gemm_filter_in_fragments(P.dtype, op.Mpad, op.Kpad))
-                op.tiny_sum = cbk::gemm_tiny_sum(
-                    op.K, largest_weight(static_cast<const float *>(L.weight), (size_t)op.M * op.C * op.kh * op.kw));
+            if (P.dtype == cbk::kF32 && cbk::gemm_filter_in_fragments(P.dtype, op.Mpad, op.Kpad)) {
+                bool tiny = false;
+                const float m = largest_weight(static_cast<const float *>(L.weight), (size_t)op.M * op.C * op.kh * op.kw, tiny);
+                op.tiny_sum = cbk::gemm_tiny_sum(op.K, m);
+                op.filter_exp = filter_exponent(m, tiny);
+            }
             build_filter_matrix(op, P.dtype, static_cast<const float *>(L.weight), wt);
             bias.assign(op.Mpad, 0.0f);
             if (L.bias)

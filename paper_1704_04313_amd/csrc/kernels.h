@@ -229,6 +229,7 @@ struct GemmArgs {
     // float32 in parts: sums v != 0 with (bits of v << 1) - 1 < tiny_sum are formed again from the values
     // themselves (gemm_tiny_sum).  0: none.
     unsigned tiny_sum;
+    int filter_exp;     // float32 in parts: the filter matrix holds the weights times 2^filter_exp
     float *partial;     // scratch for partial accumulators, gemm_partial_bytes(M, grid) bytes
     int *tickets;       // gemm_ticket_bytes(grid) bytes, zero before the first launch (each launch
                         // leaves them zero again)

@@ -761,7 +761,7 @@ __device__ __forceinline__ void plain_sums(const GemmArgs &a, int kc0, int kc1, 
             for (int j = 0; j < TC; ++j)
 #pragma unroll
                 for (int i = 0; i < TP; ++i)
-                    sum[j][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(part(j, 0) + (part(j, 1) + part(j, 2)),
+                    sum[j][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_ldexpf(part(j, 0) + (part(j, 1) + part(j, 2)), -a.filter_exp),
                                                                      v.c + e < a.pix_words ? v.px[i][e] : 0.f, sum[j][i], 0, 0, 0);
         }
     };
@@ -1003,7 +1003,9 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
 #pragma unroll
                 for (int j = 0; j < TC; ++j)
 #pragma unroll
-                    for (int i = 0; i < TP; ++i) acc[j][i] += cor[j][i];
+                    for (int i = 0; i < TP; ++i)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[j][i][e] = __builtin_ldexpf(acc[j][i][e] + cor[j][i][e], -a.filter_exp);
             }
             __builtin_amdgcn_s_setprio(0);
         }

@@ -125,6 +125,25 @@ def test_pixels_near_the_smallest_float32(exponent):
         assert np.linalg.norm(g - e) <= np.sqrt(576 / 4) * 2.0 ** -24 * np.linalg.norm(e) + np.sqrt(576 * e.size) * 2.0 ** -150
 
 
+@pytest.mark.parametrize("exponent,pixels", [(0, 0), (-100, 0), (-108, 0), (-112, 0), (-116, 0), (-120, 0), (-125, 0),
+                                              (-112, 30), (-120, 60), (-125, 80), (-136, 100), (-126, 126)])
+def test_weights_near_the_smallest_float32(exponent, pixels):
+    """The same for weights: rows of nothing but such weights, and of some among ordinary ones that meet only
+    zeros.  With large pixels the sums of the scaled weights overflow."""
+    L = conv(64, 64, 3, relu=False)
+    (wt, b), = make_weights([L], 7)
+    r = np.random.default_rng(12)
+    wt[:32] *= np.float32(2.0 ** exponent)
+    wt[32:, :32] *= np.float32(2.0 ** exponent)
+    x = r.random((64, 20, 33), dtype=np.float32) * np.float32(2.0 ** pixels)
+    x[32:, :, 11:] = 0
+    got, want = _dense(L, [(wt, b * 0)], x), _reference(L, wt, b * 0, x)
+    for rows, cols in ((slice(0, 32), slice(None)), (slice(32, 64), slice(0, 10)), (slice(32, 64), slice(12, 33))):
+        g, e = got[rows, :, cols], want[rows, :, cols]
+        # as above
+        assert np.linalg.norm(g - e) <= np.sqrt(576 / 4) * 2.0 ** -24 * np.linalg.norm(e) + np.sqrt(576 * e.size) * 2.0 ** -150
+
+
 @pytest.mark.parametrize("h,w", [(20, 20), (90, 160)])
 def test_cost_of_a_value_that_is_not_finite(h, w):
     """One NaN pixel, and a map of nothing else, in a wide layer: the sums formed again take two to four times
