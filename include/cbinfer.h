@@ -123,10 +123,12 @@ cbinfer_state *cbinfer_create(const cbinfer_network *net, float threshold);
  * Errors (NULL returned, message in cbinfer_last_error): everything cbinfer_create rejects;
  * CBINFER_ENOMEM if the network needs more than CBINFER_STATIC_WORKSPACE_BYTES
  * (cbinfer_workspace_bytes tells how much it needs; the 320x240 scene-labeling network fits, the
- * 1280x720 and 64-stream workloads do not; a network a little too large runs with half or a quarter
- * of the workgroups per launch, whose partial sums then take that much less); CBINFER_ESTATE while another state created by this
- * call is still alive on the same device: there is one array per device, so at most one such
- * state per device may exist at a time, and two processes' worth of frames must not be
+ * 1280x720 and 64-stream workloads do not).  A network for which cbinfer_workspace_bytes says a little
+ * more than fits runs with half or a quarter of the workgroups per launch, whose partial sums then take that
+ * much less: results agree with those of a full-size workspace within rounding, and a layer that would fill
+ * the device takes longer (512->2048 3x3 on 10x10 positions 35 us instead of 29).  CBINFER_ESTATE while
+ * another state created by this call is still alive on the same device: there is one array per device, so at
+ * most one such state per device may exist at a time, and two processes' worth of frames must not be
  * interleaved through it.  The array keeps the previous state's contents; this call clears the
  * part it uses.  cbinfer_destroy releases the array for the next state (and frees nothing).
  * Everything else (cbinfer_process_frame, reset, introspection) works as for any other state. */

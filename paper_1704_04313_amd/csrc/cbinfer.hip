@@ -84,14 +84,14 @@ struct Carver {
     }
 };
 
-// Workgroups of op's multiplication on a device of that many compute units.
-int gemm_grid_of(const Op &op, int streams, int dtype, int compute_units)
+// What the shape of op's multiplication depends on.
+cbk::GemmArgs gemm_shape(const Op &op, int streams, int dtype)
 {
     cbk::GemmArgs a{};
     a.dtype = dtype;
     a.M = op.M; a.Mpad = op.Mpad; a.Kpad = op.Kpad;
     a.max_pixels = streams * op.Ho * op.Wo;
-    return cbk::gemm_grid(a, compute_units);
+    return a;
 }
 
 // Validates the description and lays out the workspace for launches of at most max_grid workgroups.
@@ -254,7 +254,7 @@ int make_plan(const cbinfer_network *net, float threshold, bool need_threshold, 
         size_t pb = 0;
         for (const Op &op : P.ops)
             if (op.kind == CBINFER_OP_CONV)
-                pb = std::max(pb, cbk::gemm_partial_bytes(op.M, gemm_grid_of(op, P.S, P.dtype, max_grid)));
+                pb = std::max(pb, cbk::gemm_partial_bytes(gemm_shape(op, P.S, P.dtype), max_grid));
         P.o_partial = cv.take(pb);
         P.o_tickets = cv.take(cbk::gemm_ticket_bytes(kMaxGemmGrid));
     }
@@ -810,7 +810,7 @@ static cbinfer_state *create_state(const cbinfer_network *net, const Plan &P, ch
             s->plan.compute_units = cus < P.compute_units ? cus : P.compute_units;
     }
     for (Op &op : s->plan.ops)
-        if (op.kind == CBINFER_OP_CONV) op.gemm_grid = gemm_grid_of(op, P.S, P.dtype, s->plan.compute_units);
+        if (op.kind == CBINFER_OP_CONV) op.gemm_grid = cbk::gemm_grid(gemm_shape(op, P.S, P.dtype), s->plan.compute_units);
     s->prof_ms.assign(P.ops.size() * CBINFER_STEP_COUNT, 0.0);
     s->prof_n.assign(P.ops.size() * CBINFER_STEP_COUNT, 0);
 
@@ -905,8 +905,8 @@ cbinfer_state *cbinfer_create_static(const cbinfer_network *net, float threshold
 {
     Plan P;
     if (make_plan(net, threshold, true, P) != CBINFER_OK) return nullptr;
-    // Partial sums take 64 KiB to 128 KiB per workgroup, a third to a half of what fits: a network of large filter
-    // matrices runs with fewer workgroups rather than not at all.
+    // Partial sums take up to 128 KiB per workgroup, half of what fits: a network of large filter matrices runs
+    // with fewer workgroups rather than not at all.
     for (int grid = kMaxGemmGrid / 2; P.bytes > (size_t)CBINFER_STATIC_WORKSPACE_BYTES && grid >= kMaxGemmGrid / 4; grid /= 2) {
         Plan Q;
         if (make_plan(net, threshold, true, Q, grid) == CBINFER_OK && Q.bytes <= (size_t)CBINFER_STATIC_WORKSPACE_BYTES) P = Q;

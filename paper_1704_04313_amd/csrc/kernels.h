@@ -230,7 +230,7 @@ struct GemmArgs {
     // themselves (gemm_tiny_sum).  0: none.
     unsigned tiny_sum;
     int filter_exp;     // float32 in parts: the filter matrix holds the weights times 2^filter_exp
-    float *partial;     // scratch for partial accumulators, gemm_partial_bytes(M, grid) bytes
+    float *partial;     // scratch for partial accumulators, gemm_partial_bytes() bytes
     int *tickets;       // gemm_ticket_bytes(grid) bytes, zero before the first launch (each launch
                         // leaves them zero again)
     int grid;           // workgroups to launch, from gemm_grid()
@@ -245,7 +245,7 @@ struct GemmArgs {
 };
 int gemm_channel_tile(int M);   // channel tile BM used for M output channels (Mpad = M rounded up to it)
 int gemm_k_multiple(int dtype); // Kpad must be a multiple of this many elements (128 bytes)
-int gemm_grid(const GemmArgs &a, int compute_units); // needs M, Mpad, Kpad, max_pixels
+int gemm_grid(const GemmArgs &a, int compute_units); // needs dtype, M, Mpad, Kpad, max_pixels
 int gemm_select_max_words(void);
 // How the filter matrix lies in memory.  Layers of the kernel for short filter rows: [Mpad][Kpad] in the
 // storage type.  All others: in the order in which the multiplication reads it, as bfloat16 fragments of
@@ -262,7 +262,7 @@ constexpr int kFilterPartStride = 512;
 // blank parts of a map are full of them.  If all its pixels are below 2^-134 it should be below
 // 2^-134 K times the largest weight.)
 unsigned gemm_tiny_sum(int K, float largest_weight);
-size_t gemm_partial_bytes(int M, int grid);
+size_t gemm_partial_bytes(const GemmArgs &a, int compute_units); // for gemm_grid(a, that many or fewer)
 size_t gemm_ticket_bytes(int grid);
 hipError_t gemm_prepare(void);  // one-time function attributes (dynamic LDS size)
 void gemm_set_divisors(GemmArgs &a); // fills dNo ... dGrid from No, Wo, Kpad, dtype and grid

@@ -1612,15 +1612,10 @@ static int pixel_tile(int bm, int max_pixels, int dtype)
     return bm == 64 && max_pixels <= (dtype == kF32 ? 1 << 19 : 1 << 16) ? 128 : 256;
 }
 
-// Two partial-accumulator slabs per workgroup.
-size_t gemm_partial_bytes(int M, int grid)
-{
-    const int bm = gemm_channel_tile(M);
-    return (size_t)2 * grid * bm * pixel_tile(bm, 0x7fffffff, kF32) * sizeof(float); // the widest tile of that channel tile
-}
-
 // One ticket counter per shared tile (fewer than the workgroup count) and wave; zero between launches.
 size_t gemm_ticket_bytes(int grid) { return (size_t)grid * kConsWaves * sizeof(int); }
+
+static int small_tile_factor(int dtype, int bm) { return dtype == kF32 && bm == 128 ? kSmallTileFactor<kF32, 128> : kSmallTileFactor<kF32, 64>; }
 
 // Workgroups to launch: one per compute unit, fewer if even the longest list gives less work.
 int gemm_grid(const GemmArgs &a, int compute_units)
@@ -1641,11 +1636,23 @@ int gemm_grid(const GemmArgs &a, int compute_units)
     const int parts = nk / kMinIters > 1 ? nk / kMinIters : 1;
     // with few pixels the small tile (64 pixels) is used: count those
     const long long big = (long long)((a.max_pixels + bn - 1) / bn) * (a.Mpad / bm);
-    const int factor = a.dtype == kF32 && bm == 128 ? kSmallTileFactor<kF32, 128> : kSmallTileFactor<kF32, 64>;
-    const long long tiles = big * factor >= W ? big : (long long)((a.max_pixels + 63) / 64) * (a.Mpad / bm);
+    const long long tiles = big * small_tile_factor(a.dtype, bm) >= W ? big : (long long)((a.max_pixels + 63) / 64) * (a.Mpad / bm);
     long long need = tiles >= W ? W : (tiles * parts + 7) / 8 * 8;
     if (need < 8) need = 8;
     return (int)(need < W ? need : W);
+}
+
+// Two slabs of partial sums per workgroup, of the tile shape that the launch uses.  That is the big one only if
+// its tiles of the longest list come to the launch's workgroups / small_tile_factor, which on a map of few
+// positions they do in launches of few workgroups alone.  (Fewer compute units never make for more workgroups.)
+size_t gemm_partial_bytes(const GemmArgs &a, int compute_units)
+{
+    if (gemm_is_thin(a)) return 0;
+    const int bm = gemm_channel_tile(a.M), bn = pixel_tile(bm, a.max_pixels, a.dtype), bns = bm == 16 ? 128 : 64;
+    const long long grid = gemm_grid(a, compute_units);
+    const long long big = (long long)((a.max_pixels + bn - 1) / bn) * (a.Mpad / bm) * small_tile_factor(a.dtype, bm);
+    const long long wide = (big < grid ? big : grid) * bn, narrow = grid * bns;
+    return 2 * sizeof(float) * bm * (size_t)(wide > narrow ? wide : narrow);
 }
 
 // storage type; BM; big tile (BN, WM, WN, ring slices); small tile (the same)
@@ -1660,6 +1667,11 @@ int gemm_grid(const GemmArgs &a, int compute_units)
     X(kBF16, 64, 256, 2, 4, 3, 64, 2, 4, 5)              \
     X(kBF16, 64, 128, 2, 4, 4, 64, 2, 4, 5)              \
     X(kBF16, 128, 128, 2, 4, 4, 64, 4, 2, 5)
+
+#define X(DT_, BM_, BNB_, WMB_, WNB_, SB_, BNS_, WMS_, WNS_, SS_) \
+    static_assert(BNS_ == (BM_ == 16 ? 128 : 64) && BNB_ >= BNS_, "gemm_partial_bytes counts on these tiles");
+CBK_VARIANTS(X)
+#undef X
 
 hipError_t gemm_prepare(void)
 {

@@ -178,3 +178,14 @@ def test_static_workspace_size_limit_is_checked_before_any_device_call():
     net, keep = _net_for([conv(3, 4, 3), conv(5, 2, 1)], make_weights([conv(3, 4, 3), conv(5, 2, 1)], 0), (3, 8, 8))
     assert not lib.cbinfer_create_static(C.byref(net), C.c_float(0.02))
     assert "does not match" in lib.cbinfer_last_error().decode()
+
+
+@pytest.mark.parametrize("layers,shape", [([conv(512, 1536, 3)], (512, 10, 10)), ([conv(256, 850, 6, pad=0)], (256, 12, 12)),
+                                          ([conv(1024, 64, 11)], (1024, 12, 12))])
+def test_networks_of_seven_million_filter_values_fit_the_static_workspace(layers, shape):
+    """float32 filters lie in memory with six bytes per value.  On small maps, whose launches use the small tile,
+    the partial sums of 256 workgroups leave them the room that four bytes per value would need beside the big one."""
+    lib = cb.load_library()
+    n = cb.cbinfer_workspace_bytes(layers, make_weights(layers, 0), shape)
+    values = sum(L.cin * L.cout * L.kh * L.kw for L in layers)
+    assert values > 7.0e6 and n <= lib.cbinfer_static_workspace_bytes()
