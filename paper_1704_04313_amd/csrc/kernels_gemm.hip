@@ -1466,12 +1466,21 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((NT + 255) /
 // list, frame values and outputs: 6 TB/s), 111 -> 31 in order; 3->64 on 1024 x 1024 102 -> 54, 8->64 there
 // 108 -> 78, bfloat16 3->8 34 -> 12.
 static constexpr int kPointBatch = 4;
+static constexpr int kPointGroups = 512; // workgroups up to which a short list is spread out: one position per thread
 
 template <int DT, int VIN>
 __global__ __launch_bounds__(256) void gemm_point_kernel(GemmArgs a, int mshift)
 {
     constexpr int E = Unit<DT>::N, B = kPointBatch;
     const int n = a.count ? *a.count : a.max_pixels;
+    // A list shorter than the map leaves workgroups idle rather than threads with fewer positions than their weights
+    // are worth loading for: 8->64 on a tenth of 1024 x 1024 positions 15 us, with all workgroups 21.9 (thin kernel
+    // 15), 3->8 on 2048 x 2048 6.9 and 8.5 (17).  Up to kPointGroups it spreads out: with fewer positions than
+    // that the compute units, not the weights, are what is short (8->64 on a hundredth 6.4 us otherwise, now 4.7).
+    const long long one = (((long long)n << mshift) + 255) / 256; // workgroups for a position per thread
+    const long long want = one <= kPointGroups ? one : (one <= (long long)kPointGroups * B ? kPointGroups : (one + B - 1) / B);
+    const int groups = want < (long long)gridDim.x ? (int)want : (int)gridDim.x;
+    if ((int)blockIdx.x >= groups) return;
     // a map without padding has the next pixel's values behind its channels
     const int C = DT == kBF16 ? VIN * E : (a.pix_words < VIN * E ? a.pix_words : VIN * E);
     const int m = (int)threadIdx.x & ((1 << mshift) - 1);
@@ -1487,7 +1496,7 @@ __global__ __launch_bounds__(256) void gemm_point_kernel(GemmArgs a, int mshift)
         for (int c = 0; c < VIN * E; ++c)
             w[e][c] = DT == kBF16 ? bf16_value(static_cast<const unsigned short *>(a.wt)[row + c]) : static_cast<const float *>(a.wt)[row + c];
     }
-    const int per = 256 >> mshift, step = (int)gridDim.x * per; // positions per workgroup and pass
+    const int per = 256 >> mshift, step = groups * per; // positions per workgroup and pass
     for (long long r0 = (long long)blockIdx.x * per + ((int)threadIdx.x >> mshift); r0 < n; r0 += (long long)B * step) {
         int g[B];
         uint4 v[B][VIN], old[B];
@@ -1534,12 +1543,15 @@ __global__ __launch_bounds__(256) void gemm_point_kernel(GemmArgs a, int mshift)
 // a position's products in different orders, and the same layer must give the same bits whether its positions
 // come from the map, from a list or are all of them.  (Maps that can be ranked are in the thin kernel's hands
 // whichever way their positions come: in order, 3->8 on 320 x 240 takes 7.7 us there and 4.5 here.)  On
-// 400 x 400 positions it takes 6.6 us for 3->8 (thin: 9.7), 16 for 3->64 (22) and 22 for 8->64 (21).
+// 400 x 400 positions it takes 6 us for 3->8 (thin: 9.5) and 15 for 3->64 (21).  Two units of pixel into sixteen
+// of output are 64 weights a thread, and pay from 2^19 positions on: 8->64 on 400 x 400 20.9 (20.3), 512 x 512
+// 30 (27.7), 1024 x 1024 78 (112).
 static bool gemm_is_point(const GemmArgs &a)
 {
     const int units = a.Ms / elems_per_unit(a.dtype);
     return a.kh == 1 && a.kw == 1 && a.stride == 1 && a.pad == 0 && a.sel_words == 0 && a.max_pixels > kSelMaxWords * 64 &&
-           a.dVin.d <= (a.dtype == kBF16 ? 1 : 2) && (units & (units - 1)) == 0 && a.Ms <= a.Mpad;
+           a.dVin.d <= (a.dtype == kBF16 ? 1 : 2) && (units & (units - 1)) == 0 && a.Ms <= a.Mpad &&
+           (a.dVin.d * units < 32 || a.max_pixels >= 1 << 19);
 }
 
 // Measured against the tile pipeline on 3..256 input and 8..64 output channels, 4 800 to 4 million
