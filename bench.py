@@ -33,7 +33,8 @@ import numpy as np
 ROOT = os.path.dirname(os.path.abspath(__file__))
 MI355X_HBM_GBS = 8000.0
 MI355X_BF16_MFMA_TFLOPS = 2500.0
-MI355X_FP32_MFMA_TFLOPS = MI355X_BF16_MFMA_TFLOPS / 6  # float32 layers: six bfloat16 products of parts per product
+MI355X_FP32_TFLOPS = 157.3  # float32 instruction, matrix and vector unit alike
+MI355X_FP32_PARTS_TFLOPS = MI355X_BF16_MFMA_TFLOPS / 6  # float32 in bfloat16 parts: six products per product
 # Counter-measured HBM bytes per launch of the dominant kernel: written next to
 # profiles/cfg2_hbm_traffic.md from the same two rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE,
 # scaled by a plain copy of known size).  Missing or for another kernel: traffic is null.
@@ -139,13 +140,24 @@ def timed_blocks(net, frames_dev, out, n_frames, warmup, steps, blocks):
             for b in range(blocks)]
 
 
+def matrix_peak(L, bf16):
+    """Rate in TFLOP/s that bounds a convolution layer's multiplication by the instruction it uses.  float32
+    layers of short filter rows (at most 64 units of four channels, 64 outputs, and 32 groups of four units times
+    tiles of 16 outputs) run on the float32 instruction, all others on bfloat16 parts."""
+    if bf16:
+        return MI355X_BF16_MFMA_TFLOPS
+    units = (L.kh * L.kw * ((L.cin + 3) // 4) + 7) // 8 * 8
+    tiles = 1 if L.cout <= 16 else 2 if L.cout <= 32 else 4
+    short = L.cout <= 64 and units <= 64 and units // 4 * tiles <= 32
+    return MI355X_FP32_TFLOPS if short else MI355X_FP32_PARTS_TFLOPS
+
+
 def kernel_entries(cfg, net, prof, sums, P, in_shape, propagate=False):
     """Per-kernel records (mean microseconds, algorithmic bytes or flops per launch, rates) and
     the measured change rates per layer."""
     import paper_1704_04313_amd as cb
     bf16 = cfg.dtype == "bf16"
     esz = 2.0 if bf16 else 4.0         # bytes per stored map element
-    mfma_peak = MI355X_BF16_MFMA_TFLOPS if bf16 else MI355X_FP32_MFMA_TFLOPS
     n_ops = len(cfg.layers)
     S = cfg.n_streams
     shapes = [in_shape] + [net.layer_shape(l) for l in range(n_ops)]
@@ -173,7 +185,8 @@ def kernel_entries(cfg, net, prof, sums, P, in_shape, propagate=False):
                 by = S * ((4.0 + 2.0 * esz) * c_in * h_in * w_in + h_in * w_in / 8.0)
             elif name == "gemm":
                 fl = 2.0 * L.cout * L.cin * L.kh * L.kw * n_u
-                e.update(flops=fl, TFLOPs=fl / (ms * 1e-3) / 1e12, frac_mfma=fl / (ms * 1e-3) / 1e12 / mfma_peak)
+                peak = matrix_peak(L, bf16)
+                e.update(flops=fl, TFLOPs=fl / (ms * 1e-3) / 1e12, peak_TFLOPs=peak, frac_mfma=fl / (ms * 1e-3) / 1e12 / peak)
                 # the least it has to move: the filters, the input values under the updated outputs'
                 # receptive fields (each once, never more than the whole map), a list entry and the
                 # output values per updated position; what counts for layers of few channels
@@ -282,12 +295,10 @@ def measure(cfg, args, *, steps, warmup, blocks, profile=True, one_at_a_time=Fal
 
 def roofline_of(cfg, kernels):
     """The dominant kernel (largest mean time per launch) against the peak that bounds it."""
-    bf16 = cfg.dtype == "bf16"
     dom = max(kernels, key=lambda k: kernels[k]["us"])
     d = kernels[dom]
     if "TFLOPs" in d and d["frac_mfma"] >= d.get("frac_hbm", 0.0):
-        roof = {"bound": "mfma", "achieved": d["TFLOPs"],
-                "peak": MI355X_BF16_MFMA_TFLOPS if bf16 else MI355X_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",
+        roof = {"bound": "mfma", "achieved": d["TFLOPs"], "peak": d["peak_TFLOPs"], "unit": "TFLOP/s",
                 "frac": d["frac_mfma"], "traffic": None}
     else:
         roof = {"bound": "hbm", "achieved": d.get("GBps"), "peak": MI355X_HBM_GBS, "unit": "GB/s",
