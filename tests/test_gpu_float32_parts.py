@@ -27,8 +27,9 @@ def _dense(L, params, x):
         net.destroy()
 
 
-# channels around the 16 / 32 / 64 / 128 channel tiles, positions around the 64 / 128 / 256 pixel tiles, rows of
-# one slice to 98, taps that straddle slices (cin not a multiple of 32), several rounds of whole tiles
+# channels around the 16 / 32 / 64 / 128 channel tiles, positions around the 64 and 128 pixel tiles, rows of
+# one slice to 98, taps that straddle slices (cin not a multiple of 32); the last but three has a round of whole
+# tiles, larger maps are in test_gpu_tile_shapes.py
 @pytest.mark.parametrize("cin,cout,k,h,w", [
     (64, 16, 3, 9, 7), (96, 16, 5, 33, 31), (64, 20, 5, 16, 16), (48, 32, 3, 65, 64), (16, 64, 7, 8, 8),
     (16, 64, 7, 129, 131), (256, 64, 1, 17, 15), (40, 33, 3, 41, 25), (64, 65, 3, 13, 10), (64, 256, 7, 12, 11),
