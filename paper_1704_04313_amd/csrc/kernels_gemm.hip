@@ -28,14 +28,16 @@
 // leading one and the corrections in accumulators of their own.  The matrix unit takes 16 cycles for 32 k
 // of a 16 x 16 tile in bfloat16 and 256 in float32, so six products cost 96: the float32 instruction bounded
 // these layers at 151 TFLOP/s (measured for a plain product), 64->256 7x7 on 320x180 ran at 126 and
-// runs at 209 TFLOP/s (736 -> 443 us), 16->64 7x7 on 640x360 at 105 and 163 (220 -> 142 us).  What bounds
-// them now is the bfloat16 matrix rate that the card sustains on such data: 209 x 6 = 1 254 TFLOP/s, the
-// plain library product of 8192 and 16384 rows reaches 1 120 to 1 340.  The sums are
+// runs at 218 TFLOP/s (736 -> 425 us), 16->64 7x7 on 640x360 at 105 and 178 (220 -> 130 us).  What bounds
+// them now is the bfloat16 matrix rate that the card sustains on such data: 218 x 6 = 1 308 TFLOP/s, the
+// plain library product of 8192 and 16384 rows reaches 1 120 to 1 340.  (Figures of single steps further down were
+// taken when the step was made and say what it gave.)  The sums are
 // more exact than before: 2.8e-7 against 7.1e-7 (2-norm, K = 3 136, against 64 bits), because 32 products
 // enter the leading accumulator with one rounding instead of eight; with one accumulator for all
-// six the error would be 8.1e-7.  The filter matrix is split once, when the state is created, and lies
-// in memory in the order in which it is read; pixels are split in registers (3.5 instructions per
-// value) in the shadow of the MFMAs.
+// six the error would be 8.1e-7.  Only a sum of a single nonzero product loses by the three products left
+// out: up to 0.7 units of 2^-23 instead of half of one, 2 % more in the 2-norm.  The filter matrix is split
+// once, when the state is created, and lies in memory in the order in which it is read; pixels are split in
+// registers (3.5 instructions per value) in the shadow of the MFMAs.
 //
 // Work distribution: one workgroup per compute unit.  Output tiles are dealt out whole as long
 // as every workgroup gets one; the (tiles mod workgroups) left over are cut along K into
@@ -703,12 +705,12 @@ __host__ __device__ inline size_t filter_fragment(int bm, int nk, int row, int k
 }
 
 // Slices kc0 .. kc1 - 1 of a wave's sub-tile once more, multiplied by the float32 instruction straight from
-// global memory (wt: its filter fragments of the first slice): for sums that the parts do not give.  Where a value is infinite, not a number, or so near the largest float32 that its
-// first part rounds to infinity, the products of parts are not those of the values (infinity less infinity,
-// infinity times a part that is zero), and values below 2^-110 are not the sum of theirs, so the values
-// themselves decide.  Filter values are put together from
-// their parts; channels behind the last one of a packed pixel count as zero.  Bound by the loads, which are
-// issued one group of four units ahead; see the figures where it is called.
+// global memory (wt: its filter fragments of the first slice): for sums that the parts do not give.  Where a
+// value is infinite, not a number, or so near the largest float32 that its first part rounds to infinity, the
+// products of parts are not those of the values (infinity less infinity, infinity times a part that is zero),
+// and values below 2^-110 are not the sum of theirs, so the values themselves decide.  Filter values are put
+// together from their parts; channels behind the last one of a packed pixel count as zero.  Bound by the loads,
+// which are issued one group of four units ahead; see the figures where it is called.
 template <int BM, int TP, int TC>
 __device__ __forceinline__ void plain_sums(const GemmArgs &a, int kc0, int kc1, const char *wt, const int *list, floatx4 (&sum)[TC][TP])
 {
@@ -761,8 +763,9 @@ __device__ __forceinline__ void plain_sums(const GemmArgs &a, int kc0, int kc1, 
             for (int j = 0; j < TC; ++j)
 #pragma unroll
                 for (int i = 0; i < TP; ++i)
-                    sum[j][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_ldexpf(part(j, 0) + (part(j, 1) + part(j, 2)), -a.filter_exp),
-                                                                     v.c + e < a.pix_words ? v.px[i][e] : 0.f, sum[j][i], 0, 0, 0);
+                    sum[j][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                        __builtin_ldexpf(part(j, 0) + (part(j, 1) + part(j, 2)), -a.filter_exp),
+                        v.c + e < a.pix_words ? v.px[i][e] : 0.f, sum[j][i], 0, 0, 0);
         }
     };
     Group v0, v1;
@@ -1080,7 +1083,8 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                 if (lane == 0) *ticket = 0; // ready for the next launch
                 // Sum the parts in ascending K order, whichever wave finishes (its own part is read
                 // back like the others, which keeps the accumulators in one register set).  A part is a
-                // round trip to the level that all XCDs share, almost 1 us: three are on their way at a time.
+                // round trip to the level that all XCDs share, almost 1 us, one behind the other: three parts
+                // in flight need registers that the K loop then spills, and were not faster.
 #pragma unroll
                 for (int j = 0; j < TC; ++j)
 #pragma unroll
@@ -1554,10 +1558,14 @@ static bool gemm_is_point(const GemmArgs &a)
            (a.dVin.d * units < 32 || a.max_pixels >= 1 << 19);
 }
 
-// Measured against the tile pipeline on 3..256 input and 8..64 output channels, 4 800 to 4 million
-// positions: the lone waves win as long as (groups of four units) x (channel tiles) stays at or
-// below 32 -- beyond that a wave's chain of MFMAs per tile gets long and the big tiles' reuse of
-// filter fragments pays.
+// The lone waves win as long as (groups of four units) x (channel tiles) stays at or below 32 -- beyond that
+// a wave's chain of MFMAs per tile gets long and the big tiles' reuse of filter fragments pays.  Against the tile
+// pipeline, float32, dense and with a tenth of the input changed, in us (thin / tiles): 3->16 7x7 on 320 x 240
+// 13.1 / 20.4 and 11.9 / 13.5, on 1280 x 720 98.7 / 119 and 13.5 / 20.2, on 3840 x 2160 788 / 982 and 86 / 103;
+// 5x5/2 3->32 on 640 x 480 23.0 / 24.8 and 5.8 / 7.4; 3x3 3->64 there 39.0 / 40.9 and 10.8 / 9.2; 3x3 16->32 on
+// 320 x 240 25.8 / 26.3 and 11.2 / 11.7 (with three quarters changed 26.1 / 21.2, the largest loss found); 256->16
+// 1x1 on 160 x 120 8.2 / 8.1 and 7.8 / 9.5, on 320 x 240 16.4 / 25.0 and 7.8 / 9.6.  bfloat16 3->16 7x7 on
+// 1280 x 720 56 / 88 and 9.7 / 16.7.
 static bool is_thin(int dtype, int Mpad, int Kpad)
 {
     const int nu = Kpad / elems_per_unit(dtype);
@@ -1627,7 +1635,10 @@ static int pixel_tile(int bm, int max_pixels, int dtype)
 // One ticket counter per shared tile (fewer than the workgroup count) and wave; zero between launches.
 size_t gemm_ticket_bytes(int grid) { return (size_t)grid * kConsWaves * sizeof(int); }
 
-static int small_tile_factor(int dtype, int bm) { return dtype == kF32 && bm == 128 ? kSmallTileFactor<kF32, 128> : kSmallTileFactor<kF32, 64>; }
+static int small_tile_factor(int dtype, int bm)
+{
+    return dtype == kF32 && bm == 128 ? kSmallTileFactor<kF32, 128> : kSmallTileFactor<kF32, 64>;
+}
 
 // Workgroups to launch: one per compute unit, fewer if even the longest list gives less work.
 int gemm_grid(const GemmArgs &a, int compute_units)
@@ -1711,7 +1722,7 @@ hipError_t gemm_gather(hipStream_t st, const GemmArgs &a, const Timing &tm)
     if (a.Mpad % bm != 0 || a.Kpad % gemm_k_multiple(a.dtype) != 0 || a.Ms % eu != 0 || a.pix_words < 1 || !a.partial ||
         !a.tickets || a.grid < 8 || (a.grid & 7) || a.grid > kMaxGrid)
         return hipErrorInvalidValue;
-    // the 64-channel tiles in float32 count on rows of four slices or more (TileSmem::lists)
+    // the wide 64-channel tile in float32 counts on rows of four slices or more (TileSmem::lists); those it gets have five
     if (a.dtype == kF32 && bm == 64 && bn == 256 && !gemm_is_thin(a) && a.Kpad < 4 * gemm_k_multiple(kF32)) return hipErrorInvalidValue;
     // the divisors must belong to these arguments, and the schedule's 32-bit arithmetic must hold
     if (a.kh < 1 || a.kw < 1 || a.dKw.d != a.kw || a.dVin.d != (a.pix_words + 3) / 4) return hipErrorInvalidValue;
