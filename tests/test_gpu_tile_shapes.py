@@ -43,6 +43,9 @@ def _frames(C, H, W, seed):
     (16, 64, 7, 725, 727, False), (24, 100, 3, 257, 259, False), (64, 256, 7, 83, 101, False),
     (64, 16, 3, 363, 365, True), (96, 32, 3, 363, 365, True), (16, 64, 7, 363, 365, True), (32, 64, 5, 161, 163, True),
     (24, 100, 7, 257, 259, True),
+    # few positions: every tile cut along K, into 24, 85 and (unevenly, across tiles) six or seven parts
+    (128, 32, 7, 19, 32, False), (512, 16, 7, 20, 17, False), (96, 32, 5, 67, 41, False), (128, 32, 7, 19, 32, True),
+    (512, 16, 7, 20, 17, True), (192, 32, 5, 67, 41, True),
     # frames of 2^18 positions and more in float32 are stored without padding channels: units at any word
     (3, 64, 7, 515, 513, False), (3, 64, 7, 725, 727, False), (1, 20, 9, 513, 515, False), (2, 128, 5, 515, 517, False),
     (3, 16, 11, 515, 513, False), (5, 64, 5, 513, 515, False), (7, 32, 7, 515, 513, False)])
