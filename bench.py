@@ -240,7 +240,7 @@ def measure(cfg, args, *, steps, warmup, blocks, profile=True, one_at_a_time=Fal
 
     def both_modes(net):
         sec_cb = timed_blocks(net, frames_dev, out, cfg.n_frames, warmup, steps, blocks)
-        # dense HIP baseline: same kernels, identity lists, no change detection
+        # dense HIP baseline: same kernels, every position in order, no change detection
         net.set_mode(True)
         sec_dense = timed_blocks(net, frames_dev, out, cfg.n_frames, warmup, steps, blocks)
         net.set_mode(False)

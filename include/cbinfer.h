@@ -165,9 +165,10 @@ void cbinfer_destroy(cbinfer_state *s);
 
 const char *cbinfer_last_error(void); /* never NULL */
 
-/* 1: per-frame dense evaluation of every layer through the same kernels with the identity
- * index list and no change detection (the dense baseline the speed-up is measured against;
- * Section 3.1: the reduced multiplication is at worst the full-frame convolution).
+/* 1: per-frame dense evaluation of every layer through the same kernels, every position in order
+ * and no change detection; cbinfer_read_list answers with all positions.  (The dense baseline the
+ * speed-up is measured against; Section 3.1: the reduced multiplication is at worst the full-frame
+ * convolution.)
  * 0: change-based evaluation.  Switching also resets the history. */
 int cbinfer_set_mode(cbinfer_state *s, int force_dense);
 
