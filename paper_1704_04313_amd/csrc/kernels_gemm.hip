@@ -92,12 +92,16 @@ static constexpr int NT = NCONS + NPROD;          // threads per workgroup
 static constexpr int kEpiChunk = 4;       // accumulators whose replaced values are loaded together in the output update
 static constexpr int kMinIters = 8;       // shortest K range worth giving to a workgroup
 static constexpr int kMaxGrid = 1024;
-// Big tiles are used from (workgroups / this) of them on.  Their K range is cut for the others then, so
-// 128 channels of float32 split further: the small tile reads LDS for longer than it multiplies
-// (64->256 7x7, 4 800 positions: 60 us with 64-pixel tiles, 56 us with 128; the 256->64 1x1, eight slices
-// long, 9.1 with the small ones and 11.5 with the big).
-template <int DT, int BM>
-static constexpr int kSmallTileFactor = DT == kF32 && BM == 128 ? 4 : 2;
+// Big tiles are used from (workgroups / this) of them on.  128 channels of float32 split further where their K
+// range is long enough to be cut for the other workgroups: the small tile reads LDS for longer than it
+// multiplies (64->256 7x7, 98 slices, 4 800 positions: 60 us with 64-pixel tiles, 56 with 128; 64->128 5x5, 50
+// slices, 99 tiles of 128 pixels 43.9 and 42.5).  Shorter ranges are better off in small tiles from half the
+// workgroups down (64->128 3x3, 18 slices, 20 and 99 tiles: 14.7 and 24.9 us, in big ones 20.6 and 26.6; 128->128
+// 1x1, 4 slices, 99 tiles 12.2 and 15.7; 128->128 3x3, 36 slices, 66 tiles 29.0 and 33.8).
+__host__ __device__ inline int small_tile_factor(int dtype, int bm, int nk)
+{
+    return dtype == kF32 && bm == 128 && nk >= 48 ? 4 : 2;
+}
 
 static constexpr int kSelMaxWords = 2048; // largest selection map ranked in-kernel (131072 pixels)
 static constexpr int kSelWordsPerThread = (kSelMaxWords + NT - 1) / NT;
@@ -1251,7 +1255,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((NT + 255) /
         n = a.count ? *a.count : a.max_pixels;
     }
     const long long big_tiles = (long long)((n + BNB - 1) / BNB) * (a.Mpad / BM);
-    if (big_tiles * kSmallTileFactor<DT, BM> >= (long long)gridDim.x)
+    if (big_tiles * small_tile_factor(DT, BM, a.dNk.d) >= (long long)gridDim.x)
         gemm_gather_body<DT, BM, BNB, WMB, WNB, SB>(a, n, smem, sel);
     else
         gemm_gather_body<DT, BM, BNS, WMS, WNS, SS>(a, n, smem, sel);
@@ -1654,11 +1658,6 @@ static int pixel_tile(int bm, int max_pixels, int dtype)
 // One ticket counter per shared tile (fewer than the workgroup count) and wave; zero between launches.
 size_t gemm_ticket_bytes(int grid) { return (size_t)grid * kConsWaves * sizeof(int); }
 
-static int small_tile_factor(int dtype, int bm)
-{
-    return dtype == kF32 && bm == 128 ? kSmallTileFactor<kF32, 128> : kSmallTileFactor<kF32, 64>;
-}
-
 // Workgroups to launch: one per compute unit, fewer if even the longest list gives less work.
 int gemm_grid(const GemmArgs &a, int compute_units)
 {
@@ -1678,7 +1677,7 @@ int gemm_grid(const GemmArgs &a, int compute_units)
     const int parts = nk / kMinIters > 1 ? nk / kMinIters : 1;
     // with few pixels the small tile (64 pixels) is used: count those
     const long long big = (long long)((a.max_pixels + bn - 1) / bn) * (a.Mpad / bm);
-    const long long tiles = big * small_tile_factor(a.dtype, bm) >= W ? big : (long long)((a.max_pixels + 63) / 64) * (a.Mpad / bm);
+    const long long tiles = big * small_tile_factor(a.dtype, bm, nk) >= W ? big : (long long)((a.max_pixels + 63) / 64) * (a.Mpad / bm);
     long long need = tiles >= W ? W : (tiles * parts + 7) / 8 * 8;
     if (need < 8) need = 8;
     return (int)(need < W ? need : W);
@@ -1692,7 +1691,8 @@ size_t gemm_partial_bytes(const GemmArgs &a, int compute_units)
     if (gemm_is_thin(a)) return 0;
     const int bm = gemm_channel_tile(a.M), bn = pixel_tile(bm, a.max_pixels, a.dtype), bns = bm == 16 ? 128 : 64;
     const long long grid = gemm_grid(a, compute_units);
-    const long long big = (long long)((a.max_pixels + bn - 1) / bn) * (a.Mpad / bm) * small_tile_factor(a.dtype, bm);
+    const long long big = (long long)((a.max_pixels + bn - 1) / bn) * (a.Mpad / bm) *
+                          small_tile_factor(a.dtype, bm, a.Kpad / gemm_k_multiple(a.dtype));
     const long long wide = (big < grid ? big : grid) * bn, narrow = grid * bns;
     return 2 * sizeof(float) * bm * (size_t)(wide > narrow ? wide : narrow);
 }
