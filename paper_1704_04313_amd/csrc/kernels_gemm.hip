@@ -1087,29 +1087,39 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                 if (lane == 0) *ticket = 0; // ready for the next launch
                 // Sum the parts in ascending K order, whichever wave finishes (its own part is read
                 // back like the others, which keeps the accumulators in one register set).  A part is a
-                // round trip to the level that all XCDs share, half a microsecond, one behind the other: two to
-                // four parts in flight were no faster for the 64- and 128-channel tiles (and spill in the big ones).
-                // Waves of a single accumulator have two under way: 128->32 7x7 on 32 x 19 positions, 24 parts,
-                // 24 -> 21 us (bfloat16 14.4 -> 12.8), 512->16 7x7 on a hundredth of 224 x 115, 85 parts, 58 -> 48.
+                // round trip to the level that all XCDs share, half a microsecond.  Waves of one or two accumulators
+                // (the small tiles up to 64 channels) have two under way: 128->32 7x7 on 32 x 19 positions, 24 parts,
+                // 24.5 -> 20.4 us (bfloat16 14.7 -> 12.7), 512->16 7x7 on a hundredth of 224 x 115, 85 parts, 59 -> 45,
+                // 64->64 7x7 on 40 x 30 19.3 -> 17.0.  Three or four gained nothing, and waves of four accumulators
+                // (128 channels) nothing from two: 64->256 7x7 on 361 positions 23.4 -> 25; big tiles spill.
 #pragma unroll
                 for (int j = 0; j < TC; ++j)
 #pragma unroll
                     for (int i = 0; i < TP; ++i) acc[j][i] = (floatx4){0.f, 0.f, 0.f, 0.f};
                 int ww = w_first;
-                if constexpr (TC * TP == 1) {
+                if constexpr (TC * TP <= 2) {
                     // the tile is the first one of every workgroup that shares it but the one that began before it
                     const int first_slab = 2 * w_first + (share_begin(sch, w_first) < t0 ? 1 : 0);
                     for (; ww < w_last; ww += 2) {
-                        floatx4 part[2];
+                        floatx4 part[2][TC][TP];
 #pragma unroll
                         for (int d = 0; d < 2; ++d) {
                             const int slab_index = ww + d == w_first ? first_slab : 2 * (ww + d);
-                            part[d] = __builtin_bit_cast(
-                                floatx4, __builtin_amdgcn_raw_buffer_load_b128(
-                                             slab_resource(a.partial + (size_t)slab_index * SLAB, SLAB * 4), ofs, 0, kDeviceCoherent));
+                            const __amdgpu_buffer_rsrc_t part_slab = slab_resource(a.partial + (size_t)slab_index * SLAB, SLAB * 4);
+#pragma unroll
+                            for (int j = 0; j < TC; ++j)
+#pragma unroll
+                                for (int i = 0; i < TP; ++i)
+                                    part[d][j][i] = __builtin_bit_cast(
+                                        floatx4, __builtin_amdgcn_raw_buffer_load_b128(part_slab, ofs + (j * TP + i) * kFragBytes,
+                                                                                       0, kDeviceCoherent));
                         }
-                        acc[0][0] += part[0];
-                        acc[0][0] += part[1];
+#pragma unroll
+                        for (int d = 0; d < 2; ++d)
+#pragma unroll
+                            for (int j = 0; j < TC; ++j)
+#pragma unroll
+                                for (int i = 0; i < TP; ++i) acc[j][i] += part[d][j][i];
                     }
                 }
                 for (; ww <= w_last; ++ww) {
