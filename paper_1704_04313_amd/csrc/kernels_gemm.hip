@@ -708,13 +708,13 @@ __host__ __device__ inline size_t filter_fragment(int bm, int nk, int row, int k
     return ((((size_t)mt * nk + kc) * (bm / 16) + ct) * kFilterParts<DT> + part) * (kFragBytes / 2) + (lk * 16 + row % 16) * 8 + e;
 }
 
-// Slices kc0 .. kc1 - 1 of a wave's sub-tile once more, multiplied by the float32 instruction straight from
-// global memory (wt: its filter fragments of the first slice): for sums that the parts do not give.  Where a
-// value is infinite, not a number, or so near the largest float32 that its first part rounds to infinity, the
+// Slices kc0 .. kc1 - 1 of TC channel tiles of a wave's sub-tile once more, multiplied by the float32 instruction
+// straight from global memory (wt: their filter fragments of the first slice): for sums that the parts do not give.
+// Where a value is infinite, not a number, or so near the largest float32 that its first part rounds to infinity, the
 // products of parts are not those of the values (infinity less infinity, infinity times a part that is zero),
 // and values below 2^-110 are not the sum of theirs, so the values themselves decide.  Filter values are put
 // together from their parts; channels behind the last one of a packed pixel count as zero.  Bound by the loads,
-// which are issued one group of four units ahead; see the figures where it is called.
+// which are issued one slice ahead, as wide as they come; see the figures where it is called.
 template <int BM, int TP, int TC>
 __device__ __forceinline__ void plain_sums(const GemmArgs &a, int kc0, int kc1, const char *wt, const int *list, floatx4 (&sum)[TC][TP])
 {
@@ -736,51 +736,56 @@ __device__ __forceinline__ void plain_sums(const GemmArgs &a, int kc0, int kc1, 
     for (int j = 0; j < TC; ++j)
 #pragma unroll
         for (int i = 0; i < TP; ++i) sum[j][i] = (floatx4){0.f, 0.f, 0.f, 0.f};
-    struct Group {
-        floatx4 px[TP];
-        uint2 w[TC][3];
-        int c; // channel of the unit's first value
+    struct Slice {
+        floatx4 px[2][TP];
+        uint4 w[TC][3];
+        int c[2]; // channel of the units' first values
     };
-    // units 4 u .. 4 u + 3 of the filter rows, the one of number 4 u + lk in this lane; h = u & 1
-    auto load = [&](Group &v, int u, int h) {
-        const int unit = 4 * u + lk, tap = fast_div(unit, a.dVin), cu = unit - tap * a.dVin.d;
-        const int tj = fast_div(tap, a.dKw), ti = tap - tj * a.kw;
-        const int off = (tj * a.W + ti) * a.pix_words + cu * 4;
-        v.c = cu * 4;
+    // units 8 kc + lk and 8 kc + 4 + lk of the filter rows
+    auto load = [&](Slice &v, int kc) {
 #pragma unroll
-        for (int i = 0; i < TP; ++i) {
-            const bool ok = tj < a.kh && (unsigned)(iy0[i] + tj) < (unsigned)a.H && (unsigned)(ix0[i] + ti) < (unsigned)a.W;
-            v.px[i] = *reinterpret_cast<const floatx4_a4 *>(x + (ok ? (unsigned)(base[i] + off) : (unsigned)a.zero_word));
+        for (int h = 0; h < 2; ++h) {
+            const int unit = 8 * kc + 4 * h + lk, tap = fast_div(unit, a.dVin), cu = unit - tap * a.dVin.d;
+            const int tj = fast_div(tap, a.dKw), ti = tap - tj * a.kw;
+            const int off = (tj * a.W + ti) * a.pix_words + cu * 4;
+            v.c[h] = cu * 4;
+#pragma unroll
+            for (int i = 0; i < TP; ++i) {
+                const bool ok = tj < a.kh && (unsigned)(iy0[i] + tj) < (unsigned)a.H && (unsigned)(ix0[i] + ti) < (unsigned)a.W;
+                v.px[h][i] = *reinterpret_cast<const floatx4_a4 *>(x + (ok ? (unsigned)(base[i] + off) : (unsigned)a.zero_word));
+            }
         }
-        const char *slice = wt + (size_t)((u >> 1) - kc0) * (BM / 16 * 3 * kFragBytes) + lane * 16 + h * 8;
+        const char *slice = wt + (size_t)(kc - kc0) * (BM / 16 * 3 * kFragBytes) + lane * 16;
 #pragma unroll
         for (int j = 0; j < TC; ++j)
 #pragma unroll
-            for (int p = 0; p < 3; ++p) v.w[j][p] = *reinterpret_cast<const uint2 *>(slice + (j * 3 + p) * kFragBytes);
+            for (int p = 0; p < 3; ++p) v.w[j][p] = *reinterpret_cast<const uint4 *>(slice + (j * 3 + p) * kFragBytes);
     };
-    // k = 16 u + 4 lk + e in step e
-    auto multiply = [&](const Group &v) {
+    // k = 32 kc + 16 h + 4 lk + e in step (h, e)
+    auto multiply = [&](const Slice &v) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            auto part = [&](int j, int p) { return bf16_value((unsigned short)((e < 2 ? v.w[j][p].x : v.w[j][p].y) >> (e & 1 ? 16 : 0))); };
+        for (int e = 0; e < 8; ++e) {
+            auto part = [&](int j, int p) { return bf16_value((unsigned short)((&v.w[j][p].x)[e >> 1] >> (e & 1 ? 16 : 0))); };
 #pragma unroll
             for (int j = 0; j < TC; ++j)
 #pragma unroll
                 for (int i = 0; i < TP; ++i)
                     sum[j][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(
                         __builtin_ldexpf(part(j, 0) + (part(j, 1) + part(j, 2)), -a.filter_exp),
-                        v.c + e < a.pix_words ? v.px[i][e] : 0.f, sum[j][i], 0, 0, 0);
+                        v.c[e >> 2] + (e & 3) < a.pix_words ? v.px[e >> 2][i][e & 3] : 0.f, sum[j][i], 0, 0, 0);
         }
     };
-    Group v0, v1;
-    load(v0, 2 * kc0, 0);
+    Slice v0, v1;
+    load(v0, kc0);
+    int kc = kc0;
 #pragma unroll 1
-    for (int u = 2 * kc0; u < 2 * kc1; u += 2) {
-        load(v1, u + 1, 1);
+    for (; kc + 1 < kc1; kc += 2) {
+        load(v1, kc + 1);
         multiply(v0);
-        load(v0, u + 2 < 2 * kc1 ? u + 2 : u, 0);
+        load(v0, kc + 2 < kc1 ? kc + 2 : kc);
         multiply(v1);
     }
+    if (kc < kc1) multiply(v0);
 }
 
 // BM x BN workgroup tile; the consumer waves are arranged WM (channels) x WN (pixels).
@@ -792,9 +797,12 @@ __device__ __forceinline__ void plain_sums(const GemmArgs &a, int kc0, int kc1, 
 // reads them, 16 bytes per lane one lane behind the other, and arrive so from memory.
 //
 // Sub-tiles of the float32 shapes: a wave splits every pixel value it multiplies, so waves that share
-// pixels repeat each other's work; all channels of a 64-channel tile in one wave (1 x 8) took 136 us on
-// 16->64 7x7 at 640x360 against 230 in a 2 x 4 arrangement.  128 channels by one wave would read the
-// filter fragments eight times per slice, more than LDS delivers.
+// pixels repeat each other's work, and vector instructions are not hidden behind the MFMAs of either wave of
+// a SIMD but add to them (a loop of this tile's 48 MFMAs per wave and slice takes 713 ns, with the fragment reads
+// 806, with the splits of a 2 x 4 arrangement 994).  All channels of a 64-channel tile in one wave (1 x 8) took 136 us on
+// 16->64 7x7 at 640x360 against 230 in a 2 x 4 arrangement; of a 128-channel tile, 64->256 7x7 at 320x180 418 us
+// against 440, 256->256 3x3 at 160x120 127 against 131, although every wave then reads all filter fragments: LDS
+// delivers 430 bytes per ns and compute unit, twice what that takes.
 template <int DT, int BM, int BN, int WM, int WN, int STAGES>
 __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n, float *smem, const Selection sel)
 {
@@ -1020,9 +1028,9 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
         if constexpr (DT == kF32) {
             // Sums that are not finite, and such small ones that parts below the smallest bfloat16 count
             // (GemmArgs::tiny_sum), are formed again from the values themselves, by each wave for its own K
-            // range.  (x * 0 is zero for every finite x.)  A tile with such a sum takes two to four times as long:
-            // 64->256 7x7 on 160 x 90 positions 130 us, with one NaN in the map 440, with nothing else in it 470; on
-            // 20 x 20 23, 37 and 38; 16->64 7x7 on 640 x 900 345, 357 and 986 (one lane per sum, product by product:
+            // range.  (x * 0 is zero for every finite x.)  A tile with such a sum takes two to five times as long:
+            // 64->256 7x7 on 160 x 90 positions 118 us, with one NaN in the map 380, with nothing else in it 545; on
+            // 20 x 20 20, 36 and 38; 16->64 7x7 on 640 x 900 325, 370 and 1200 (one lane per sum, product by product:
             // 11 150 us for that one NaN, 25 700 for the full map).
             float z = 0.f;
             unsigned least = ~0u;
@@ -1037,20 +1045,28 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                         least = min(least, size(acc[j][i][e]));
                     }
             if (__builtin_expect(__any(z != 0.f || least < a.tiny_sum), 0)) { // NaN compares unequal
-                floatx4 sum[TC][TP];
                 const char *wt = static_cast<const char *>(a.wt) +
                                  (((size_t)mt * nk + kc0) * (BM / 16) + wch0 / 16) * (3 * kFragBytes);
-                plain_sums<BM, TP, TC>(a, kc0, kc1, wt, list + wpx0, sum);
+                // few channel tiles at a time: more would not leave their operands registers
+                constexpr int CJ = TC * TP % 2 == 0 && TP == 1 ? 2 : 1;
+                static_assert(TC % CJ == 0, "whole steps");
+#pragma unroll 1
+                for (int j0 = 0; j0 < TC; j0 += CJ) {
+                    floatx4 sum[CJ][TP];
+                    plain_sums<BM, TP, CJ>(a, kc0, kc1, wt + j0 * (3 * kFragBytes), list + wpx0, sum);
 #pragma unroll
-                for (int j = 0; j < TC; ++j)
+                    for (int j = 0; j < TC; ++j) {
+                        if (j / CJ != j0 / CJ) continue;
 #pragma unroll
-                    for (int i = 0; i < TP; ++i)
+                        for (int i = 0; i < TP; ++i)
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            float v = acc[j][i][e];
-                            asm("" : "+v"(v)); // compared anew: the results from above would all be kept in registers
-                            if (!(fabsf(v) < __builtin_inff()) || size(v) < a.tiny_sum) acc[j][i][e] = sum[j][i][e];
-                        }
+                            for (int e = 0; e < 4; ++e) {
+                                float v = acc[j][i][e];
+                                asm("" : "+v"(v)); // compared anew: the results from above would all be kept in registers
+                                if (!(fabsf(v) < __builtin_inff()) || size(v) < a.tiny_sum) acc[j][i][e] = sum[j % CJ][i][e];
+                            }
+                    }
+                }
             }
         }
 
@@ -1713,7 +1729,7 @@ size_t gemm_partial_bytes(const GemmArgs &a, int compute_units)
     X(kF32, 32, 256, 1, 8, 3, 64, 2, 4, 4)               \
     X(kF32, 64, 256, 1, 8, 3, 64, 2, 4, 5)               \
     X(kF32, 64, 128, 1, 8, 4, 64, 2, 4, 5)               \
-    X(kF32, 128, 128, 2, 4, 3, 64, 4, 2, 4)              \
+    X(kF32, 128, 128, 1, 8, 3, 64, 2, 4, 4)              \
     X(kBF16, 16, 256, 1, 8, 3, 128, 1, 8, 4)             \
     X(kBF16, 32, 256, 1, 8, 3, 64, 2, 4, 4)              \
     X(kBF16, 64, 256, 2, 4, 3, 64, 2, 4, 5)              \
