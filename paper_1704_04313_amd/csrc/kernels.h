@@ -188,6 +188,7 @@ hipError_t compact(hipStream_t st, const CompactJob *jobs, int njobs, bool group
 
 
 // ---- gathered matrix generation + multiplication + output update (Section 3.1) -------------
+enum { kTapGeneral = 0, kTapUniform = 1, kTapPerLane = 2 }; // GemmArgs::taps_mode
 struct GemmArgs {
     int dtype;          // kF32 or kBF16: storage of x, wt and out
     const void *x;      // input map, pix_words 4-byte words per pixel, followed by at least 16 bytes of zeros
@@ -219,6 +220,7 @@ struct GemmArgs {
     int N, H, W, No, Wo, stride, pad;
     FastDiv dNo, dWo, dHo, dNk, dGrid; // by No, Wo, No / Wo, Kpad / gemm_k_multiple(dtype) and grid (gemm_set_divisors)
     FastDiv dVin, dKw;  // by the 16-byte units per filter tap, (pix_words + 3) / 4, and by kw
+    int taps_mode;      // kTapGeneral, kTapUniform or kTapPerLane (gemm_set_divisors)
     int pix_words;      // 4-byte words per input pixel: a multiple of four (whole 16-byte units), or the channel
                         // count of a float32 map stored without padding (units then start at any word and
                         // run into the next pixel's channels, which meet zero filter weights)
@@ -265,7 +267,7 @@ unsigned gemm_tiny_sum(int K, float largest_weight);
 size_t gemm_partial_bytes(const GemmArgs &a, int compute_units); // for gemm_grid(a, that many or fewer)
 size_t gemm_ticket_bytes(int grid);
 hipError_t gemm_prepare(void);  // one-time function attributes (dynamic LDS size)
-void gemm_set_divisors(GemmArgs &a); // fills dNo ... dGrid from No, Wo, Kpad, dtype and grid
+void gemm_set_divisors(GemmArgs &a); // fills dNo ... taps_mode from the fields above and grid
 // Matrix generation, multiplication and output update (bias, activation, scatter) in one launch.
 hipError_t gemm_gather(hipStream_t st, const GemmArgs &a, const Timing &tm = Timing());
 

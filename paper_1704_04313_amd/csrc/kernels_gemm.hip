@@ -64,6 +64,7 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef floatx4 floatx4_a4 __attribute__((aligned(4))); // a 16-byte unit that starts at any 4-byte word
 typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned short ushortx2 __attribute__((ext_vector_type(2)));
 
 // Partial accumulators cross between workgroups that may sit on different XCDs (separate L2s).
 // They are written and read with buffer instructions carrying the sc1 bit: write-through to, and
@@ -541,17 +542,21 @@ struct Walk {
 // alone.  (With a prologue per tile, 2 us of list, addresses and a memory round trip in which
 // nothing multiplies: bfloat16 64->128 3x3 at 320x240 31 us instead of 26, 128->128 44 instead of 39; float32
 // 64->256 7x7 at 80x60 58 instead of 52, 128->128 3x3 at 320x240 143 instead of 128.)
-// While two consumer waves keep the matrix pipeline of a SIMD busy, a vector-ALU instruction of the
-// producer wave on that SIMD gets issued about once per MFMA, so the producers' instruction count per
-// slice, not the memory system, is what can hold up the loop.  Hence: everything wave-uniform is
-// computed on the scalar unit (the ring slot and the LDS destinations; with UT also the filter tap of the
-// slice), filter fragments are addressed as a uniform base plus 16 bytes per lane, and what is left per
-// image-matrix row is the bounds test of its tap and the choice between the pixel's address and the zero
-// unit.
-// UT ("uniform tap"): the units per pixel are a multiple of the eight units of a slice, so a slice
-// lies inside one filter tap and the tap is the same for all lanes; base[] then already contains
-// the lane's own unit offset.
-template <int DT, int BM, int BN, int STAGES, bool UT>
+// A producer's vector instructions are not hidden behind the MFMAs of the consumer waves on its SIMD, they
+// add to them, so they are what is saved here.  Everything wave-uniform is computed on the scalar unit (the ring
+// slot and the LDS destinations), loads take a 32-bit byte offset per lane from a scalar base, and per
+// image-matrix row there remain, by what the layer allows (TAPS):
+//   kTapUniform   The units per pixel are a multiple of the eight units of a slice, so a slice lies inside one filter
+//                 tap and the tap is the same for all lanes (filters up to 32 wide, no higher than the map).  The base moves with the tap, a row keeps its lane's
+//                 offset and one bit per tap column; a bit extraction makes the mask that selects between it and
+//                 the zero unit: 14 vector instructions per slice of the 128-pixel tile instead of 50.
+//   kTapPerLane   Any other, with maps up to 16000 x 16000: a lane per unit finds tap and offset of eight slices at
+//                 once, to be fetched by a lane exchange; a row's test of both coordinates is one addition and one
+//                 saturating subtraction of 16-bit pairs: 28 instead of 75, integer multiplications among them.
+//   kTapGeneral   Maps of 4 GiB or longer sides: 64-bit addresses, tap and tests anew for every slice.
+// bfloat16 64->64 3x3 at 640x480 53.5 -> 51.6 us, 512->512 3x3 at 80x60 38.9 -> 37.3, 16->64 7x7 at 640x360 55.1 -> 52.0;
+// float32 64->256 7x7 at 320x180 420 -> 416, 96->100 5x5 at 101x37 27.0 -> 24.0.
+template <int DT, int BM, int BN, int STAGES, int TAPS>
 __device__ __forceinline__ void direct_producer(const GemmArgs &a, const int n, float *As, float *Bs, int *sU, const Selection &sel,
                                                 Walk walk, int mtiles, int pw_)
 {
@@ -570,7 +575,15 @@ __device__ __forceinline__ void direct_producer(const GemmArgs &a, const int n, 
     const int vf = (lane & 7) ^ lds_swizzle(r0);
     const float *x = static_cast<const float *>(a.x);
     const unsigned lofs = lane * 16u;
+    // General: a row's window origin, and its offset in words.  Otherwise: its offset in bytes, from bias words
+    // before the map on (a uniform tap) or from the map's start, and the taps inside the image: the origin's row
+    // and the columns' bits (uniform), or the origin's coordinates modulo 2^16.
     int iy0[PA], ix0[PA], base[PA];
+    unsigned columns[PA], inside[PA]; // a uniform tap: bit i for column i, of the tap row in hand and in general
+    int row_in_hand = -1;
+    const int bias = a.pad * (a.W + 1) * a.pix_words;
+    unsigned unit_tap = 0, unit_ofs = 0; // taps per lane: lane l's unit, of 64 units in eight slices
+    int unit_slice = 0;
     const char *wtile = nullptr; // the channel tile's slices of the filter matrix, one behind the other as they lie in LDS
     Segment seg = {0, 0, 0, -1};
     int kc = 0, list = 0;
@@ -598,39 +611,97 @@ __device__ __forceinline__ void direct_producer(const GemmArgs &a, const int n, 
                 const int qy = fast_div(q, a.dWo), qx = q - qy * a.Wo;
                 iy0[ps] = qy * a.stride - a.pad;
                 ix0[ps] = qx * a.stride - a.pad;
-                base[ps] = ((st * a.H + iy0[ps]) * a.W + ix0[ps]) * a.pix_words + (UT ? vf * 4 : 0);
+                base[ps] = ((st * a.H + iy0[ps]) * a.W + ix0[ps]) * a.pix_words;
             } else {
                 iy0[ps] = -(1 << 28);
                 ix0[ps] = -(1 << 28);
                 base[ps] = 0;
             }
+            if (TAPS == kTapUniform) {
+                // columns lo .. hi - 1 of the window lie in the image, 0 <= lo < hi <= 32
+                const int lo = ix0[ps] < 0 ? -ix0[ps] : 0, hi = a.W - ix0[ps] < a.kw ? a.W - ix0[ps] : a.kw;
+                columns[ps] = g >= 0 ? (~0u >> ((32 - hi) & 31)) & (~0u << (lo & 31)) : 0u;
+                base[ps] = g >= 0 ? (int)((unsigned)(base[ps] + bias + vf * 4) * 4u) : 0;
+                row_in_hand = -1;
+            }
+            if (TAPS == kTapPerLane) {
+                inside[ps] = g >= 0 ? (unsigned)iy0[ps] << 16 | ((unsigned)ix0[ps] & 0xffffu) : 0x80008000u;
+                base[ps] = (int)((unsigned)base[ps] * 4u);
+            }
         }
         list = list == NL - 1 ? 0 : list + 1;
         wait_lgkmcnt0(); // the list is in LDS before this wave's next barrier
     };
-    auto issue = [&](int slot) {
-        if (kc == seg.kc1) enter();
-        // tap of this lane's unit in slice kc: unit index -> (filter tap, channel unit) -> (j, i)
-        const int q = kc * KU + (UT ? 0 : vf);
-        const int tap = fast_div(q, a.dVin), cu = q - tap * a.dVin.d;
+    // taps per lane: the units of slices kc .. kc + 7, one per lane
+    auto unit_taps = [&]() {
+        const int q = kc * KU + lane, tap = fast_div(q, a.dVin), cu = q - tap * a.dVin.d;
         const int tj = fast_div(tap, a.dKw), ti = tap - tj * a.kw;
-        const bool tv = tj < a.kh;
-        const int off = (tj * a.W + ti) * a.pix_words + cu * 4;
+        unit_tap = tj < a.kh ? (unsigned)tj << 16 | (unsigned)ti : 0x40004000u;
+        unit_ofs = (unsigned)((tj * a.W + ti) * a.pix_words + cu * 4) * 4u;
+        unit_slice = kc;
+    };
+    auto issue = [&](int slot) {
+        if (kc == seg.kc1) {
+            enter();
+            if (TAPS == kTapPerLane) unit_taps();
+        }
         float *A = As + slot * ASZ + pw * 8 * LDK, *B = Bs + slot * BSZ;
+        if constexpr (TAPS == kTapUniform) {
+            const int q = kc * KU, tap = fast_div(q, a.dVin), cu = q - tap * a.dVin.d;
+            const int tj = fast_div(tap, a.dKw), ti = tap - tj * a.kw;
+            const int off = (tj * a.W + ti) * a.pix_words + cu * 4 - bias;
+            if (tj != row_in_hand) {
+                row_in_hand = tj;
 #pragma unroll
-        for (int ps = 0; ps < PA; ++ps) {
-            const bool ok = tv && (unsigned)(iy0[ps] + tj) < (unsigned)a.H && (unsigned)(ix0[ps] + ti) < (unsigned)a.W;
-            // outside the image (or no pixel in this row): the zero unit kept behind the map, so that the
-            // load needs no predication
-            const unsigned idx = ok ? (unsigned)(base[ps] + off) : (unsigned)a.zero_word;
-            __builtin_amdgcn_global_load_lds((GlobalPtr)(x + idx), (LdsPtr)(A + kRP * ps * LDK), 16, 0, 0);
+                for (int ps = 0; ps < PA; ++ps)
+                    inside[ps] = tj < a.kh && (unsigned)(iy0[ps] + tj) < (unsigned)a.H ? columns[ps] : 0u;
+            }
+            const char *xt = reinterpret_cast<const char *>(x + off);
+            const unsigned zero = (unsigned)(a.zero_word - off) * 4u;
+#pragma unroll
+            for (int ps = 0; ps < PA; ++ps) {
+                const unsigned m = (unsigned)__builtin_amdgcn_sbfe((int)inside[ps], ti, 1);
+                const unsigned ofs = ((unsigned)base[ps] & m) | (zero & ~m);
+                __builtin_amdgcn_global_load_lds((GlobalPtr)(xt + ofs), (LdsPtr)(A + kRP * ps * LDK), 16, 0, 0);
+            }
+        } else if constexpr (TAPS == kTapPerLane) {
+            if (kc - unit_slice >= 8 || kc < unit_slice) unit_taps();
+            const int from = ((kc - unit_slice) * KU + vf) * 4;
+            const unsigned tap = (unsigned)__builtin_amdgcn_ds_bpermute(from, (int)unit_tap);
+            const unsigned ofs = (unsigned)__builtin_amdgcn_ds_bpermute(from, (int)unit_ofs);
+            const unsigned zero = (unsigned)a.zero_word * 4u;
+            const ushortx2 last = {(unsigned short)(a.W - 1), (unsigned short)(a.H - 1)};
+#pragma unroll
+            for (int ps = 0; ps < PA; ++ps) {
+                const ushortx2 at = __builtin_bit_cast(ushortx2, inside[ps]) + __builtin_bit_cast(ushortx2, tap);
+                const bool ok = __builtin_bit_cast(unsigned, __builtin_elementwise_sub_sat(at, last)) == 0u;
+                const unsigned o = ok ? (unsigned)base[ps] + ofs : zero;
+                __builtin_amdgcn_global_load_lds((GlobalPtr)(reinterpret_cast<const char *>(x) + o), (LdsPtr)(A + kRP * ps * LDK),
+                                                 16, 0, 0);
+            }
+        } else {
+            // tap of this lane's unit in slice kc: unit index -> (filter tap, channel unit) -> (j, i)
+            const int q = kc * KU + vf;
+            const int tap = fast_div(q, a.dVin), cu = q - tap * a.dVin.d;
+            const int tj = fast_div(tap, a.dKw), ti = tap - tj * a.kw;
+            const bool tv = tj < a.kh;
+            const int off = (tj * a.W + ti) * a.pix_words + cu * 4;
+#pragma unroll
+            for (int ps = 0; ps < PA; ++ps) {
+                const bool ok = tv && (unsigned)(iy0[ps] + tj) < (unsigned)a.H && (unsigned)(ix0[ps] + ti) < (unsigned)a.W;
+                // outside the image (or no pixel in this row): the zero unit kept behind the map, so that the
+                // load needs no predication
+                const unsigned idx = ok ? (unsigned)(base[ps] + off) : (unsigned)a.zero_word;
+                __builtin_amdgcn_global_load_lds((GlobalPtr)(x + idx), (LdsPtr)(A + kRP * ps * LDK), 16, 0, 0);
+            }
         }
         const char *wslice = wtile + (size_t)kc * (FB * kFragBytes);
 #pragma unroll
         for (int ps = 0; ps < PB; ++ps) {
             const int f = (pw + kProdWaves * ps) % FB;
-            __builtin_amdgcn_global_load_lds((GlobalPtr)(wslice + f * kFragBytes + lofs), (LdsPtr)(B + f * (kFragBytes / 4)), 16,
-                                             0, 0);
+            unsigned l = lofs;
+            asm volatile("" : "+v"(l)); // its extension to 64 bits stays with the load, which takes a 32-bit lane offset as it is
+            __builtin_amdgcn_global_load_lds((GlobalPtr)(wslice + f * kFragBytes + l), (LdsPtr)(B + f * (kFragBytes / 4)), 16, 0, 0);
         }
         ++kc;
     };
@@ -850,10 +921,12 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
 
     // Both roles execute the same number of barriers: one after the prologue, one per slice.
     if (wave >= kConsWaves) {
-        if ((a.dVin.d & (KU - 1)) == 0)
-            direct_producer<DT, BM, BN, STAGES, true>(a, n, As, Bs, sU, sel, walk, mtiles, wave - kConsWaves);
+        if (a.taps_mode == kTapUniform)
+            direct_producer<DT, BM, BN, STAGES, kTapUniform>(a, n, As, Bs, sU, sel, walk, mtiles, wave - kConsWaves);
+        else if (a.taps_mode == kTapPerLane)
+            direct_producer<DT, BM, BN, STAGES, kTapPerLane>(a, n, As, Bs, sU, sel, walk, mtiles, wave - kConsWaves);
         else
-            direct_producer<DT, BM, BN, STAGES, false>(a, n, As, Bs, sU, sel, walk, mtiles, wave - kConsWaves);
+            direct_producer<DT, BM, BN, STAGES, kTapGeneral>(a, n, As, Bs, sU, sel, walk, mtiles, wave - kConsWaves);
         return;
     }
 
@@ -1648,6 +1721,17 @@ unsigned gemm_tiny_sum(int K, float largest_weight)
 
 int gemm_k_multiple(int dtype) { return BK * 4 / elem_bytes(dtype); }
 
+// How the producers of the tile kernel address image-matrix rows (direct_producer): with 32-bit byte offsets, and
+// tests of tap rows and columns in 16 bits or as bits of a word, wherever the map allows it.
+static int taps_mode(const GemmArgs &a)
+{
+    const long long pixels = (long long)a.S * a.N, above = (long long)a.pad * (a.W + 1);
+    if ((pixels + above) * a.pix_words * 4 + 16 >= 1ll << 32) return kTapGeneral;
+    // the zero unit must not lie before the window of the last tap, from which its offset is counted
+    if (a.dVin.d % KU == 0 && a.kw <= 32 && pixels + above >= (long long)a.kh * a.W + a.kw) return kTapUniform;
+    return a.H <= 16000 && a.W <= 16000 ? kTapPerLane : kTapGeneral;
+}
+
 void gemm_set_divisors(GemmArgs &a)
 {
     a.dNo = make_fastdiv(a.No > 0 ? a.No : 1);
@@ -1658,6 +1742,7 @@ void gemm_set_divisors(GemmArgs &a)
     a.dGrid = make_fastdiv(a.grid > 0 ? a.grid : 1);
     a.dVin = make_fastdiv(a.pix_words > 0 ? (a.pix_words + 3) / 4 : 1);
     a.dKw = make_fastdiv(a.kw > 0 ? a.kw : 1);
+    a.taps_mode = taps_mode(a);
 }
 
 int gemm_select_max_words(void) { return kSelMaxWords; }
