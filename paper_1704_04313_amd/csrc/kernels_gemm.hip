@@ -123,7 +123,9 @@ struct TileSmem {
     // A segment has a slice at least; of the 64-channel tiles in float32 (rows of five slices or more, the
     // shorter ones are the thin kernel's) at most two can be that short in a row, and LDS has no room for more.
     static constexpr int lists = DT == kF32 && BM == 64 && BN == 256 ? 3 : STAGES + 1;
-    static constexpr int tile_bytes = STAGES * (a_floats + b_floats) * 4 + lists * BN * 4;
+    // with a list go the biases of its tile's channels
+    static constexpr int list_words = BN + BM;
+    static constexpr int tile_bytes = STAGES * (a_floats + b_floats) * 4 + lists * list_words * 4;
 };
 // LDS of a kernel instantiation (a big and a small tile shape share it): behind the larger of the
 // two tiles the selection map's words, their exclusive ranks, and the wave totals of the scan.
@@ -595,7 +597,12 @@ __device__ __forceinline__ void direct_producer(const GemmArgs &a, const int n, 
         wtile = static_cast<const char *>(a.wt) + (size_t)mt * walk.nk * (FB * kFragBytes);
         // a lane per row of this wave: eight in each pass (one search of the ranks instead of one per pass)
         static_assert(PA <= 8, "the wave's rows fit its lanes");
-        int *rows = sU + list * BN + pw * 8;
+        int *rows = sU + list * TileSmem<DT, BM, BN, STAGES>::list_words + pw * 8;
+        // The biases travel like the slices that follow them (loads complete in order): loaded by the consumers, at
+        // the end of a tile, they cost it a trip to memory of 0.3 to 0.8 us (bfloat16 128->128 3x3 at 320x240 37.5 ->
+        // 36.4 us, 128->256 at 160x120, everything changed, 30.5 -> 29.3).
+        if (pw * 64 < BM && lane < BM - pw * 64)
+            __builtin_amdgcn_global_load_lds((GlobalPtr)(a.bias + mt * BM + pw * 64 + lane), (LdsPtr)(rows - pw * 8 + BN + pw * 64), 4, 0, 0);
         if (lane < 8 * PA) {
             const int row = (lane & 7) + kRP * (lane >> 3), u = pt * BN + pw * 8 + row;
             int g = -1;
@@ -779,6 +786,10 @@ __host__ __device__ inline size_t filter_fragment(int bm, int nk, int row, int k
     return ((((size_t)mt * nk + kc) * (bm / 16) + ct) * kFilterParts<DT> + part) * (kFragBytes / 2) + (lk * 16 + row % 16) * 8 + e;
 }
 
+// Parts of a shared tile's sum that the finishing wave has under way, by its accumulators.
+template <int ACC>
+static constexpr int kPartsUnderWay = ACC <= 4 ? 4 : 2;
+
 // Slices kc0 .. kc1 - 1 of TC channel tiles of a wave's sub-tile once more, multiplied by the float32 instruction
 // straight from global memory (wt: their filter fragments of the first slice): for sums that the parts do not give.
 // Where a value is infinite, not a number, or so near the largest float32 that its first part rounds to infinity, the
@@ -891,7 +902,7 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
 
     float *As = smem;                                     // [STAGES][BN][LDK]  gathered image-matrix slices
     float *Bs = smem + STAGES * ASZ;                      // [STAGES][BM/16][FP] filter fragments
-    int *sU = reinterpret_cast<int *>(Bs + STAGES * BSZ); // [lists][BN] pixels of a tile (-1: none)
+    int *sU = reinterpret_cast<int *>(Bs + STAGES * BSZ); // [lists][BN + BM] pixels of a tile (-1: none), biases
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1174,59 +1185,43 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
             finish = drawn == w_last - w_first;
             if (finish) {
                 if (lane == 0) *ticket = 0; // ready for the next launch
-                // Sum the parts in ascending K order, whichever wave finishes (its own part is read
-                // back like the others, which keeps the accumulators in one register set).  A part is a
-                // round trip to the level that all XCDs share, half a microsecond.  Waves of one or two accumulators
-                // (the small tiles up to 64 channels) have two under way: 128->32 7x7 on 32 x 19 positions, 24 parts,
-                // 24.5 -> 20.4 us (bfloat16 14.7 -> 12.7), 512->16 7x7 on a hundredth of 224 x 115, 85 parts, 59 -> 45,
-                // 64->64 7x7 on 40 x 30 19.3 -> 17.0.  Three or four gained nothing, and waves of four accumulators
-                // (128 channels) nothing from two: 64->256 7x7 on 361 positions 23.4 -> 25; big tiles spill.
+                // Sum the parts in ascending K order, whichever wave finishes (its own part is read back like the
+                // others, which keeps the accumulators in one register set).  A part is a round trip to the level
+                // that all XCDs share, half a microsecond, so several are under way: four for waves of up to four
+                // accumulators (64->256 7x7 on 169 of 83 x 61 positions, 12 parts, 25.1 us with one, now 22.2; 64->256 on
+                // 144 of 80 x 60 24.2 -> 21.8; bfloat16 512->512 3x3 on 64 17.8 -> 16.8), two for the big tiles (three:
+                // 64->256 7x7 on 4 800 positions 64 -> 66 us).
 #pragma unroll
                 for (int j = 0; j < TC; ++j)
 #pragma unroll
                     for (int i = 0; i < TP; ++i) acc[j][i] = (floatx4){0.f, 0.f, 0.f, 0.f};
-                int ww = w_first;
-                if constexpr (TC * TP <= 2) {
-                    // the tile is the first one of every workgroup that shares it but the one that began before it
-                    const int first_slab = 2 * w_first + (share_begin(sch, w_first) < t0 ? 1 : 0);
-                    for (; ww < w_last; ww += 2) {
-                        floatx4 part[2][TC][TP];
+                constexpr int D = kPartsUnderWay<TC * TP>;
+                // the tile is the first one of every workgroup that shares it but the one that began before it
+                const int first_slab = 2 * w_first + (share_begin(sch, w_first) < t0 ? 1 : 0);
+#pragma unroll 1
+                for (int ww = w_first; ww <= w_last; ww += D) {
+                    floatx4 part[D][TC][TP];
 #pragma unroll
-                        for (int d = 0; d < 2; ++d) {
-                            const int slab_index = ww + d == w_first ? first_slab : 2 * (ww + d);
-                            const __amdgpu_buffer_rsrc_t part_slab = slab_resource(a.partial + (size_t)slab_index * SLAB, SLAB * 4);
+                    for (int d = 0; d < D; ++d) {
+                        // behind the last part: a buffer of no bytes, which reads as zeros
+                        const int slab_index = ww + d == w_first ? first_slab : (ww + d > w_last ? 0 : 2 * (ww + d));
+                        const __amdgpu_buffer_rsrc_t part_slab =
+                            slab_resource(a.partial + (size_t)slab_index * SLAB, ww + d > w_last ? 0 : SLAB * 4);
 #pragma unroll
-                            for (int j = 0; j < TC; ++j)
+                        for (int j = 0; j < TC; ++j)
 #pragma unroll
-                                for (int i = 0; i < TP; ++i)
-                                    part[d][j][i] = __builtin_bit_cast(
-                                        floatx4, __builtin_amdgcn_raw_buffer_load_b128(part_slab, ofs + (j * TP + i) * kFragBytes,
-                                                                                       0, kDeviceCoherent));
-                        }
-#pragma unroll
-                        for (int d = 0; d < 2; ++d)
-#pragma unroll
-                            for (int j = 0; j < TC; ++j)
-#pragma unroll
-                                for (int i = 0; i < TP; ++i) acc[j][i] += part[d][j][i];
+                            for (int i = 0; i < TP; ++i)
+                                part[d][j][i] = __builtin_bit_cast(
+                                    floatx4, __builtin_amdgcn_raw_buffer_load_b128(part_slab, ofs + (j * TP + i) * kFragBytes, 0,
+                                                                                   kDeviceCoherent));
                     }
-                }
-                for (; ww <= w_last; ++ww) {
-                    const int fj = fast_div(share_begin(sch, ww), a.dNk);
-                    const __amdgpu_buffer_rsrc_t part_slab = slab_resource(
-                        a.partial + (size_t)(2 * ww + (shared_j == fj ? 0 : 1)) * SLAB, SLAB * 4);
-                    floatx4 part[TC][TP];
 #pragma unroll
-                    for (int j = 0; j < TC; ++j)
+                    for (int d = 0; d < D; ++d) {
 #pragma unroll
-                        for (int i = 0; i < TP; ++i)
-                            part[j][i] = __builtin_bit_cast(
-                                floatx4, __builtin_amdgcn_raw_buffer_load_b128(part_slab, ofs + (j * TP + i) * kFragBytes, 0,
-                                                                               kDeviceCoherent));
+                        for (int j = 0; j < TC; ++j)
 #pragma unroll
-                    for (int j = 0; j < TC; ++j)
-#pragma unroll
-                        for (int i = 0; i < TP; ++i) acc[j][i] += part[j][i];
+                            for (int i = 0; i < TP; ++i) acc[j][i] += part[d][j][i];
+                    }
                 }
             }
         }
@@ -1240,7 +1235,7 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
             for (int i = 0; i < TP; ++i) changed[i] = false;
             float4 bias[TC];
 #pragma unroll
-            for (int j = 0; j < TC; ++j) bias[j] = *reinterpret_cast<const float4 *>(a.bias + mt * BM + wch0 + j * 16 + lk * 4);
+            for (int j = 0; j < TC; ++j) bias[j] = *reinterpret_cast<const float4 *>(list + BN + wch0 + j * 16 + lk * 4);
             // The values about to be replaced are loaded kEpiChunk accumulators at a time before the
             // stores of those accumulators (the compiler cannot move a load across a store to the
             // same map, and one round trip to memory per accumulator would line up at the very end
@@ -1328,7 +1323,8 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                 }
             }
         }
-        list = list == sU + (TileSmem<DT, BM, BN, STAGES>::lists - 1) * BN ? sU : list + BN;
+        constexpr int LW = TileSmem<DT, BM, BN, STAGES>::list_words;
+        list = list == sU + (TileSmem<DT, BM, BN, STAGES>::lists - 1) * LW ? sU : list + LW;
     }
 }
 
