@@ -129,9 +129,10 @@ hipError_t detect_map(hipStream_t st, const void *x, void *ref, uint64_t *bits, 
 // multiplication (integer division is emulated with dozens of instructions on this hardware).
 // Exact for 0 <= n < 2^31 and 1 <= d < 2^31: with l = ceil(log2 d) and m = floor(2^(31+l) / d) + 1,
 // m*d - 2^(31+l) lies in (0, d], which keeps floor(n*m / 2^(31+l)) equal to floor(n / d).
+// On the device that is one high product and two shifts: 2 n m / 2^32 / 2^l.
 struct FastDiv {
     unsigned m;
-    int shift;
+    int shift; // l
     int d;
 };
 inline FastDiv make_fastdiv(int d)
@@ -140,13 +141,13 @@ inline FastDiv make_fastdiv(int d)
     while ((1ll << l) < d) ++l;
     FastDiv f;
     f.d = d;
-    f.shift = 31 + l;
+    f.shift = l;
     f.m = (unsigned)(((1ull << (31 + l)) / (unsigned long long)d) + 1ull);
     return f;
 }
 __host__ __device__ inline int fast_div(int n, const FastDiv &f)
 {
-    return (int)(((unsigned long long)(unsigned)n * f.m) >> f.shift);
+    return (int)((unsigned)(((unsigned long long)((unsigned)n << 1) * f.m) >> 32) >> f.shift);
 }
 
 // ---- dilation by the filter support (Section 3.1, second formula) -------------------------
@@ -210,11 +211,15 @@ struct GemmArgs {
     // sel_dilate != 0 (stride 1, kw <= 16, change map and the S*H*Wo intermediate map of at most
     // gemm_select_max_words() words each): sel_map is the layer's *change* map over its
     // sel_in_words * 64 input positions, and the kernel derives the outputs to recompute itself
-    // by dilating it with the kh x kw filter support (Section 3.1, second formula); workgroup 0
-    // writes the resulting bitmap (sel_words words) to upd_out.
+    // by dilating it with the kh x kw filter support (Section 3.1, second formula); the workgroups
+    // write the resulting bitmap (sel_words words) to upd_out.
     int sel_dilate;
     int sel_in_words;
     uint64_t *upd_out;
+    // Words that the ranking holds: sel_words or, of a map derived here, the words of its rows if each begins
+    // with a word of its own and all of them fit; dSelRow: by the words of a row then, else d == 0 (gemm_set_divisors).
+    int sel_ranked;
+    FastDiv dSelRow;
     int kh, kw, S;      // filter size; number of streams (used by sel_dilate only)
     void *out;          // stored output map [S*No][Ms]
     int N, H, W, No, Wo, stride, pad;

@@ -57,6 +57,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <type_traits>
 
 namespace cbk {
 
@@ -140,136 +141,12 @@ struct KernelSmem {
 // Selection-map mode: the words of the map and the rank of each word's first set bit, in LDS.
 struct Selection {
     const uint64_t *words; // nullptr: list mode
-    const int *rank;
-    int nwords;
+    const int *rank; // of words behind the last: larger than any
+    int top;         // the power of two below the number of words that steps of the search begin with, 0 for one word
 };
-
-// A map of nw words (64 positions each) from global memory into LDS as a bitmap.  bytes != 0: the
-// map has one byte per position and is packed on the way -- for eight of them in a 64-bit value x
-// the high bits of (x | (x & 0x7f..7f) + 0x7f..7f) mark the nonzero bytes and the multiplication
-// gathers the eight marks into one byte, which is byte i of the bitmap.  The caller synchronises.
-__device__ __forceinline__ void load_bitmap(const uint64_t *__restrict__ map, int bytes, int nw, uint64_t *sM)
+__device__ __forceinline__ Selection make_selection(const GemmArgs &a, const uint64_t *words, const int *rank)
 {
-    const int tid = threadIdx.x;
-    if (bytes) {
-        unsigned char *sB = reinterpret_cast<unsigned char *>(sM);
-        const int n8 = nw * 8;
-        for (int i0 = 0; i0 < n8; i0 += 4 * NT) {
-            uint64_t x[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int i = i0 + j * NT + tid;
-                x[j] = i < n8 ? map[i] : 0ull;
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int i = i0 + j * NT + tid;
-                const uint64_t nz =
-                    ((x[j] | ((x[j] & 0x7f7f7f7f7f7f7f7full) + 0x7f7f7f7f7f7f7f7full)) & 0x8080808080808080ull) >> 7;
-                if (i < n8) sB[i] = (unsigned char)((nz * 0x0102040810204080ull) >> 56);
-            }
-        }
-    } else {
-        for (int i0 = 0; i0 < nw; i0 += 4 * NT) {
-            uint64_t x[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int i = i0 + j * NT + tid;
-                x[j] = i < nw ? map[i] : 0ull;
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int i = i0 + j * NT + tid;
-                if (i < nw) sM[i] = x[j];
-            }
-        }
-    }
-}
-
-// Bits [a, a + len) of an LDS bitmap as the low bits of the result; 1 <= len <= 64, a >= 0.  Reads
-// the word holding bit a and the one behind it, so a zero word must follow the map; no branches.
-__device__ __forceinline__ uint64_t lds_bit_run(const uint64_t *m, int a, int len)
-{
-    const int w = a >> 6, o = a & 63;
-    const uint64_t lo = m[w], hi = m[w + 1];
-    const uint64_t v = (lo >> o) | ((hi << 1) << (63 - o));
-    return v & (~0ull >> (64 - len));
-}
-
-// Dilation by the filter support for a stride-1 layer (Section 3.1, second formula), in two
-// separable steps on bitmaps in LDS.  sC: change bitmap over the input positions
-// [(st*H + iy)*W + ix].  Step 1 writes sH over [(st*H + iy)*Wo + qx]: is any changed pixel in row
-// iy under the kw taps of output column qx.  Step 2 (dilated_word_rows) ORs the kh rows of sH that an
-// output row reads.  All bitmaps are followed by a zero word.
-__device__ __forceinline__ uint64_t row_dilated_word(const GemmArgs &a, const uint64_t *sC, int v, int total)
-{
-    const int p0 = v * 64, p1 = p0 + 64 < total ? p0 + 64 : total;
-    uint64_t res = 0;
-    int pos = p0;
-    int row = fast_div(pos, a.dWo), x = pos - row * a.Wo; // row = st*H + iy
-    while (pos < p1) {
-        const int len = a.Wo - x < p1 - pos ? a.Wo - x : p1 - pos;
-        // window of input columns xs .. xs + L - 1 of that row; output column x + t reads t .. t + kw - 1
-        const int xs = x - a.pad, L = len + a.kw - 1;
-        const int k0 = xs < 0 ? -xs : 0, k1 = L < a.W - xs ? L : a.W - xs;
-        uint64_t lo = 0, hi = 0;
-        if (k1 > k0) {
-            const int base = row * a.W + xs;
-            if (k0 < 64) lo = lds_bit_run(sC, base + k0, (k1 < 64 ? k1 : 64) - k0) << k0;
-            if (k1 > 64) {
-                const int s0 = k0 > 64 ? k0 : 64;
-                hi = lds_bit_run(sC, base + s0, k1 - s0) << (s0 - 64);
-            }
-        }
-        // OR of the kw shifted copies of the (up to 79-bit) window, by doubling
-        int cover = 1;
-        while (cover * 2 <= a.kw) {
-            lo |= (lo >> cover) | (hi << (64 - cover));
-            hi |= hi >> cover;
-            cover *= 2;
-        }
-        if (cover < a.kw) {
-            const int sft = a.kw - cover;
-            lo |= (lo >> sft) | (hi << (64 - sft));
-        }
-        if (len < 64) lo &= (1ull << len) - 1ull;
-        res |= lo << (pos - p0);
-        pos += len;
-        x = 0; // a segment ends at the end of its row or of the word
-        ++row;
-    }
-    return res;
-}
-
-// The share of tap rows j0, j0 + dj, j0 + 2 dj, ... in word w of the update map: for each output row
-// the word touches, the bits of the sH rows qy - pad + j (nothing for rows outside the image).
-__device__ __forceinline__ uint64_t dilated_word_rows(const GemmArgs &a, const uint64_t *sH, int w, int j0, int dj,
-                                                      int total)
-{
-    const int p0 = w * 64, p1 = p0 + 64 < total ? p0 + 64 : total;
-    const int Ho = a.dHo.d;
-    uint64_t res = 0;
-    int pos = p0;
-    const int orow = fast_div(pos, a.dWo);
-    int x = pos - orow * a.Wo, st = fast_div(orow, a.dHo), qy = orow - st * Ho;
-    while (pos < p1) {
-        const int len = a.Wo - x < p1 - pos ? a.Wo - x : p1 - pos;
-        uint64_t r = 0;
-        for (int j = j0; j < a.kh; j += dj) {
-            const int iy = qy - a.pad + j;
-            const bool in = (unsigned)iy < (unsigned)a.H;
-            const uint64_t b = lds_bit_run(sH, in ? (st * a.H + iy) * a.Wo + x : 0, len);
-            r |= in ? b : 0ull;
-        }
-        res |= r << (pos - p0);
-        pos += len;
-        x = 0;
-        if (++qy == Ho) {
-            qy = 0;
-            ++st;
-        }
-    }
-    return res;
+    return {words, rank, a.sel_ranked > 1 ? 1 << (31 - __builtin_clz(a.sel_ranked - 1)) : 0};
 }
 
 // Inclusive prefix sum over the 64 lanes of a wave with data-parallel-primitive moves: shifts by
@@ -286,60 +163,210 @@ __device__ __forceinline__ int wave_inclusive_sum(int x)
     return x;
 }
 
+// Change maps with a byte per position hold 0 or 1 in each; two dot products gather eight of them into a byte.
+__device__ __forceinline__ unsigned byte_flags(unsigned lo, unsigned hi)
+{
+    return __builtin_amdgcn_udot4(hi, 0x80402010u, __builtin_amdgcn_udot4(lo, 0x08040201u, 0u, false), false);
+}
+__device__ __forceinline__ unsigned byte_flags(const uint4 &v) { return byte_flags(v.x, v.y) | byte_flags(v.z, v.w) << 8; }
+
+// A map of nw words (64 positions each; bytes: a byte per position) from global memory into LDS as a bitmap, kSelGuard
+// zero words before and behind it.  All loads of a thread are under way together.  The caller synchronises.
+static constexpr int kSelGuard = 2;
+__device__ __forceinline__ void load_bitmap(const uint64_t *__restrict__ map, int bytes, int nw, uint64_t *sM)
+{
+    const int tid = threadIdx.x;
+    if (tid < 2 * kSelGuard) sM[tid < kSelGuard ? tid : nw + tid] = 0ull;
+    sM += kSelGuard;
+    if (bytes) {
+        constexpr int B = 5; // 61 440 positions in a round
+        const uint4 *m16 = reinterpret_cast<const uint4 *>(map);
+        unsigned short *s16 = reinterpret_cast<unsigned short *>(sM);
+        const int n16 = nw * 4;
+        for (int i0 = tid; i0 < n16; i0 += B * NT) {
+            uint4 v[B];
+#pragma unroll
+            for (int j = 0; j < B; ++j)
+                if (i0 + j * NT < n16) v[j] = m16[i0 + j * NT];
+#pragma unroll
+            for (int j = 0; j < B; ++j)
+                if (i0 + j * NT < n16) s16[i0 + j * NT] = (unsigned short)byte_flags(v[j]);
+        }
+    } else {
+        uint64_t v[kSelWordsPerThread];
+#pragma unroll
+        for (int j = 0; j < kSelWordsPerThread; ++j)
+            if (tid + j * NT < nw) v[j] = map[tid + j * NT];
+#pragma unroll
+        for (int j = 0; j < kSelWordsPerThread; ++j)
+            if (tid + j * NT < nw) sM[tid + j * NT] = v[j];
+    }
+}
+
+// Dilation by the filter support (Section 3.1, second formula) for a stride-1 layer, from its change map (sC: bits
+// in LDS behind the guard): the outputs x .. x + len - 1, at most 64, of output row qy of stream st.  The rows of the
+// change map under them are OR-ed as windows of 96 bits, then the kw shifted copies of the window by
+// doubling.  `lanes` lanes take a tap row each, in turn, from the one of number `first` on.
+__device__ __forceinline__ uint64_t dilated_piece(const GemmArgs &a, const unsigned *sC, int st, int qy, int x, int len, int first,
+                                                  int lanes)
+{
+    constexpr int R = 4; // rows read together
+    const int xs = x - a.pad; // the window's first column
+    const int bit = ((st * a.H + qy - a.pad) * a.W + xs) + kSelGuard * 64;
+    unsigned w0 = 0, w1 = 0, w2 = 0;
+    const int j0 = a.pad - qy > 0 ? a.pad - qy : 0; // tap rows j0 .. j0 + jn - 1 lie in the image
+    const int j1 = a.H + a.pad - qy, jn = (j1 < a.kh ? j1 : a.kh) - j0;
+#pragma unroll 1
+    for (int jb = 0; jb < a.kh; jb += R * lanes) {
+        unsigned m[R][4], sh[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int j = jb + first + r * lanes;
+            // outside the image or behind the filter: the guard's zeros
+            const int b = (unsigned)(j - j0) < (unsigned)jn ? bit + j * a.W : 0;
+            sh[r] = b & 31;
+#pragma unroll
+            for (int d = 0; d < 4; ++d) m[r][d] = sC[(b >> 5) + d];
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            w0 |= __builtin_amdgcn_alignbit(m[r][1], m[r][0], sh[r]);
+            w1 |= __builtin_amdgcn_alignbit(m[r][2], m[r][1], sh[r]);
+            w2 |= __builtin_amdgcn_alignbit(m[r][3], m[r][2], sh[r]);
+        }
+    }
+    // columns outside the image belong to other rows (pad < kw <= 16)
+    auto first_bits = [](int n) { // the lowest n bits; all for n >= 32, none for n <= 0
+        const int c = n < 0 ? 0 : (n > 32 ? 32 : n);
+        return (unsigned)((1ull << c) - 1ull);
+    };
+    const int in = a.W - xs, before = xs < 0 ? -xs : 0;
+    w0 = (w0 & first_bits(in)) >> before << before;
+    w1 &= first_bits(in - 32);
+    w2 &= first_bits(in - 64);
+    int cover = 1; // the window's bits t .. t + cover - 1 are in bit t
+#pragma unroll
+    for (int q = 0; q < 4; ++q) { // kw <= 16
+        const int sft = cover < a.kw - cover ? cover : a.kw - cover;
+        w0 |= __builtin_amdgcn_alignbit(w1, w0, sft);
+        w1 |= __builtin_amdgcn_alignbit(w2, w1, sft);
+        w2 |= w2 >> sft;
+        cover += sft;
+    }
+    return (uint64_t)(w1 & first_bits(len - 32)) << 32 | (w0 & first_bits(len));
+}
+
+// Word i of the map of outputs to recompute: inside one output row when rows begin on words (GemmArgs::dSelRow),
+// else put together from pieces of rows.
+__device__ __forceinline__ uint64_t dilated_word(const GemmArgs &a, const unsigned *sC, int i, int first, int lanes)
+{
+    const int Ho = a.dHo.d;
+    if (a.dSelRow.d) {
+        const int row = fast_div(i, a.dSelRow), x = (i - row * a.dSelRow.d) * 64;
+        const int st = a.S > 1 ? fast_div(row, a.dHo) : 0;
+        return dilated_piece(a, sC, st, row - st * Ho, x, a.Wo - x < 64 ? a.Wo - x : 64, first, lanes);
+    }
+    const int pos = i * 64, total = a.S * a.No;
+    const int row = fast_div(pos, a.dWo);
+    int x = pos - row * a.Wo, left = total - pos < 64 ? total - pos : 64, at = 0;
+    int st = fast_div(row, a.dHo), qy = row - st * Ho;
+    uint64_t word = 0;
+#pragma unroll 1
+    while (left > 0) {
+        const int len = a.Wo - x < left ? a.Wo - x : left;
+        word |= dilated_piece(a, sC, st, qy, x, len, first, lanes) << at;
+        at += len;
+        left -= len;
+        x = 0;
+        if (++qy == Ho) {
+            qy = 0;
+            ++st;
+        }
+    }
+    return word;
+}
+
+// Word i of a map of a.sel_words words over all outputs, from words of which rows begin on words.
+__device__ __forceinline__ uint64_t packed_word(const GemmArgs &a, const uint64_t *sW, int i)
+{
+    const int total = a.S * a.No, P = a.dSelRow.d;
+    int pos = i * 64, at = 0, left = total - pos < 64 ? total - pos : 64;
+    int row = fast_div(pos, a.dWo), x = pos - row * a.Wo;
+    uint64_t word = 0;
+    while (left > 0) {
+        const int len = a.Wo - x < left ? a.Wo - x : left, q = x >> 6, sh = x & 63;
+        uint64_t v = sW[row * P + q] >> sh;
+        if (sh && q + 1 < P) v |= sW[row * P + q + 1] << (64 - sh);
+        if (len < 64) v &= (1ull << len) - 1ull;
+        word |= v << at;
+        at += len;
+        left -= len;
+        x = 0;
+        ++row;
+    }
+    return word;
+}
+
 // Brings the map of positions to recompute into LDS (sW) and ranks it: sRank[i] = number of
 // selected positions in the words before word i.  Returns the number of selected positions.
-// The map is either given (bits or bytes) or, sel_dilate != 0, derived here from the layer's
-// change map by dilation (scratch: LDS that the tile ring will use later); workgroup 0 then also
-// writes it to a.upd_out for the kernels that follow.  All NT threads take part; thread t ranks
-// the kSelWordsPerThread consecutive words starting at kSelWordsPerThread * t.
+// The map is either given (bits or bytes) or, sel_dilate != 0, derived here from the layer's change map (scratch:
+// LDS that the tile ring will use later); the workgroups then share in writing it to a.upd_out for the kernels that
+// follow.  All NT threads take part; thread t ranks `per` consecutive words, or 2^sh threads a word between them.
+// Three barriers and one pass from the change map to the words: with a pass over rows, one over columns and
+// words re-read for the ranking (seven barriers), 4 800 positions under a 7x7 filter took 4.1 us from the
+// kernel's start to their number, 57 600 6.5 and 76 800 from bits 5.6; now 2.7, 4.7 and 4.5 (64->256 7x7 on 169 of
+// 83 x 61 positions 22.2 -> 20.6 us, bfloat16 256->256 3x3 on a hundredth of 160 x 120 14.8 -> 13.5).
 __device__ __forceinline__ int rank_selection(const GemmArgs &a, uint64_t *sW, int *sRank, int *sTot,
                                               uint64_t *scratch)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int nw = a.sel_words;
+    const int nw = a.sel_ranked, per = nw <= NT ? 1 : (nw <= 2 * NT ? 2 : 3);
     uint64_t w[kSelWordsPerThread];
+    int sh = 0, i0 = per * tid;
+    bool holds = true; // of the threads of a word, one holds it
     if (a.sel_dilate) {
-        const int in_words = a.sel_in_words;
-        const int hd_total = a.S * a.H * a.Wo, hd_words = (hd_total + 63) >> 6;
-        uint64_t *sC = scratch, *sH = scratch + in_words + 2;
-        load_bitmap(a.sel_map, a.sel_bytes, in_words, sC);
-        if (tid < 2) sC[in_words + tid] = 0ull;
+        load_bitmap(a.sel_map, a.sel_bytes, a.sel_in_words, scratch);
+        while (sh < 3 && (nw << (sh + 1)) <= NT && (1 << sh) < a.kh) ++sh;
+        if (sh) i0 = tid >> sh;
+        const int first = tid & ((1 << sh) - 1);
+        holds = first == 0;
         __syncthreads();
-        for (int v = tid; v < hd_words; v += NT) sH[v] = row_dilated_word(a, sC, v, hd_total);
-        if (tid < 2) sH[hd_words + tid] = 0ull;
-        for (int i = tid; i < nw; i += NT) sW[i] = 0ull;
+#pragma unroll
+        for (int j = 0; j < kSelWordsPerThread; ++j) w[j] = 0;
+#pragma unroll 1
+        for (int j = 0; j < per; ++j) { // one copy of the code
+            const uint64_t d = i0 + j < nw ? dilated_word(a, reinterpret_cast<const unsigned *>(scratch), i0 + j, first, 1 << sh) : 0ull;
+#pragma unroll
+            for (int q = 0; q < kSelWordsPerThread; ++q) w[q] = q == j ? d : w[q];
+        }
+        if (sh) { // per == 1
+            unsigned lo = (unsigned)w[0], hi = (unsigned)(w[0] >> 32);
+            auto merge = [&](unsigned v, auto ctrl) { return v | (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, 0xf, 0xf, false); };
+            lo = merge(lo, std::integral_constant<int, 0xB1>()); // lanes 1, 0, 3, 2 of each four
+            hi = merge(hi, std::integral_constant<int, 0xB1>());
+            if (sh > 1) {
+                lo = merge(lo, std::integral_constant<int, 0x4E>()); // lanes 2, 3, 0, 1
+                hi = merge(hi, std::integral_constant<int, 0x4E>());
+            }
+            if (sh > 2) {
+                lo = merge(lo, std::integral_constant<int, 0x141>()); // of each eight in reverse
+                hi = merge(hi, std::integral_constant<int, 0x141>());
+            }
+            w[0] = (uint64_t)hi << 32 | lo;
+        }
+    } else if (a.sel_bytes) { // through LDS: a thread's words of bytes lie far apart for loads
+        load_bitmap(a.sel_map, 1, nw, scratch);
         __syncthreads();
-        // 2^sh threads per word share its kh tap rows (as many as keeps all words in one round, at
-        // most one thread per row); their parts are OR-ed together in LDS
-        const int out_total = a.S * a.No;
-        int sh = 0;
-        while ((1 << sh) < a.kh && (nw << (sh + 1)) <= NT) ++sh;
-        for (int t = tid; t < (nw << sh); t += NT) {
-            const int i = t >> sh, j0 = t & ((1 << sh) - 1);
-            const uint64_t d = dilated_word_rows(a, sH, i, j0, 1 << sh, out_total);
-            if (d) atomicOr(reinterpret_cast<unsigned long long *>(sW + i), (unsigned long long)d);
-        }
-        if (blockIdx.x == 0) {
-            __syncthreads();
-            for (int i = tid; i < nw; i += NT) a.upd_out[i] = sW[i];
-        }
+#pragma unroll
+        for (int j = 0; j < kSelWordsPerThread; ++j) w[j] = j < per && i0 + j < nw ? scratch[kSelGuard + i0 + j] : 0ull;
     } else {
-        load_bitmap(a.sel_map, a.sel_bytes, nw, sW);
-    }
-    __syncthreads();
 #pragma unroll
-    for (int j = 0; j < kSelWordsPerThread; ++j) {
-        const int i = kSelWordsPerThread * tid + j;
-        w[j] = i < nw ? sW[i] : 0ull;
+        for (int j = 0; j < kSelWordsPerThread; ++j) w[j] = j < per && i0 + j < nw ? a.sel_map[i0 + j] : 0ull;
     }
-    __syncthreads(); // every thread has read its words before they are rewritten below
-#pragma unroll
-    for (int j = 0; j < kSelWordsPerThread; ++j)
-        if (kSelWordsPerThread * tid + j < kSelSlots) sW[kSelWordsPerThread * tid + j] = w[j]; // zero beyond the map
     int c[kSelWordsPerThread], sum = 0;
 #pragma unroll
     for (int j = 0; j < kSelWordsPerThread; ++j) {
-        c[j] = __popcll(w[j]);
+        c[j] = holds ? __popcll(w[j]) : 0;
         sum += c[j];
     }
     const int incl = wave_inclusive_sum(sum);
@@ -355,33 +382,54 @@ __device__ __forceinline__ int rank_selection(const GemmArgs &a, uint64_t *sW, i
     int e = before + incl - sum;
 #pragma unroll
     for (int j = 0; j < kSelWordsPerThread; ++j) {
-        if (kSelWordsPerThread * tid + j < kSelSlots) sRank[kSelWordsPerThread * tid + j] = e;
+        if (holds && j < per && i0 + j < nw) {
+            sW[i0 + j] = w[j];
+            sRank[i0 + j] = e;
+        }
         e += c[j];
     }
+    // the search reads ranks up to the next power of two
+    for (int i = nw + tid; i < 2 * make_selection(a, sW, sRank).top; i += NT) sRank[i] = 0x7fffffff;
     __syncthreads();
     return total;
 }
 
+// This workgroup's share of a map derived by rank_selection, to a.upd_out for the kernels that follow; by the 64 lanes of a
+// wave that the others do not wait for.
+__device__ __forceinline__ void write_update_map(const GemmArgs &a, const uint64_t *sW)
+{
+    for (int i = (int)blockIdx.x + (int)gridDim.x * (int)(threadIdx.x & 63); i < a.sel_words; i += (int)gridDim.x * 64)
+        a.upd_out[i] = a.Wo & 63 && a.dSelRow.d ? packed_word(a, sW, i) : sW[i];
+}
+
 // The position of rank r (0 <= r < number of selected positions) in a ranked selection map.
-__device__ __forceinline__ int select_rank(const Selection &sel, int r)
+__device__ __forceinline__ int select_rank(const GemmArgs &a, const Selection &sel, int r)
 {
     // the last word whose exclusive rank is <= r holds it: later words start at a higher rank,
     // and of the words sharing its rank it is the last (the others are empty)
     int w = 0;
-#pragma unroll
-    for (int step = kSelMaxWords; step; step >>= 1)
-        if (w + step < sel.nwords && sel.rank[w + step] <= r) w += step;
-    const uint64_t bits = sel.words[w];
+    for (int step = sel.top; step; step >>= 1)
+        if (sel.rank[w + step] <= r) w += step;
+    const uint64_t word = sel.words[w];
     int k = r - sel.rank[w], pos = 0; // the k-th set bit of the word, counted from 0
-#pragma unroll
-    for (int sh = 32; sh; sh >>= 1) {
-        const int c = __popcll((bits >> pos) & ((1ull << sh) - 1ull));
-        if (k >= c) {
-            k -= c;
-            pos += sh;
-        }
+    unsigned bits = (unsigned)word;
+    const int low = __popc(bits);
+    if (k >= low) {
+        k -= low;
+        bits = (unsigned)(word >> 32);
+        pos = 32;
     }
-    return w * 64 + pos;
+#pragma unroll
+    for (int sh = 16; sh; sh >>= 1) {
+        const int c = __popc(bits & ((1u << sh) - 1u));
+        const bool up = k >= c;
+        k -= up ? c : 0;
+        pos += up ? sh : 0;
+        bits = up ? bits >> sh : bits;
+    }
+    if (!(a.Wo & 63 && a.dSelRow.d)) return w * 64 + pos;
+    const int row = fast_div(w, a.dSelRow);
+    return row * a.Wo + (w - row * a.dSelRow.d) * 64 + pos;
 }
 
 // The split of one launch's work over W workgroups; a pure function of its arguments.  32-bit
@@ -606,7 +654,7 @@ __device__ __forceinline__ void direct_producer(const GemmArgs &a, const int n, 
         if (lane < 8 * PA) {
             const int row = (lane & 7) + kRP * (lane >> 3), u = pt * BN + pw * 8 + row;
             int g = -1;
-            if (u < n) g = sel.words ? select_rank(sel, u) : (a.list ? a.list[u] : u);
+            if (u < n) g = sel.words ? select_rank(a, sel, u) : (a.list ? a.list[u] : u);
             rows[row] = g;
         }
         __builtin_amdgcn_wave_barrier(); // written and read by this wave, in order
@@ -1343,9 +1391,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((NT + 255) /
         uint64_t *sW = reinterpret_cast<uint64_t *>(base);
         int *sRank = reinterpret_cast<int *>(base + kSelSlots * 8);
         n = rank_selection(a, sW, sRank, sRank + kSelSlots, reinterpret_cast<uint64_t *>(smem));
-        sel.words = sW;
-        sel.rank = sRank;
-        sel.nwords = a.sel_words;
+        sel = make_selection(a, sW, sRank);
+        if (a.sel_dilate && threadIdx.x < 64) write_update_map(a, sW); // a consumer wave: the first slices are awaited
     } else {
         n = a.count ? *a.count : a.max_pixels;
     }
@@ -1373,7 +1420,7 @@ static constexpr int kThinGroups = 16;
 static constexpr int kThinChannels = 64;
 static constexpr int kThinMaxWork = 32;     // groups x channel tiles up to which this kernel is used
 static constexpr int kThinWholeFactor = 2; // tiles of 16 positions per wave from which a wave takes all channel tiles
-static constexpr int kThinScratchBytes = (2 * kSelMaxWords + 4) * 8;                           // front-end scratch
+static constexpr int kThinScratchBytes = (kSelMaxWords + 2 * kSelGuard) * 8;                   // front-end scratch
 static constexpr int kThinFilterBytes = kThinChannels * (kThinGroups * 4 + 1) * 16;              // [Mpad][units + 1]
 static constexpr int kThinTapBytes = kThinGroups * 4 * (int)sizeof(int2);
 static constexpr int kThinSelOffset = kThinScratchBytes + kThinFilterBytes + kThinTapBytes;
@@ -1407,7 +1454,7 @@ __device__ __forceinline__ void thin_tiles(const GemmArgs &a, const int n, const
     auto locate = [&](int t) {
         const int r = (t >> cshift) * 16 + lrow;
         Where p = {-1, -(1 << 28), -(1 << 28), 0};
-        if (r < n) p.g = sel.words ? select_rank(sel, r) : (a.list ? a.list[r] : r);
+        if (r < n) p.g = sel.words ? select_rank(a, sel, r) : (a.list ? a.list[r] : r);
         if (p.g >= 0) {
             const int st = fast_div(p.g, a.dNo), q = p.g - st * a.No;
             const int qy = fast_div(q, a.dWo), qx = q - qy * a.Wo;
@@ -1561,9 +1608,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((NT + 255) /
         uint64_t *sW = reinterpret_cast<uint64_t *>(lds + kThinSelOffset);
         int *sRank = reinterpret_cast<int *>(lds + kThinSelOffset + kSelSlots * 8);
         n = rank_selection(a, sW, sRank, sRank + kSelSlots, reinterpret_cast<uint64_t *>(lds));
-        sel.words = sW;
-        sel.rank = sRank;
-        sel.nwords = a.sel_words;
+        sel = make_selection(a, sW, sRank);
+        if (a.sel_dilate && threadIdx.x >= NT - 64) write_update_map(a, sW); // the wave with the fewest tiles
     } else {
         n = a.count ? *a.count : a.max_pixels;
     }
@@ -1739,6 +1785,15 @@ void gemm_set_divisors(GemmArgs &a)
     a.dVin = make_fastdiv(a.pix_words > 0 ? (a.pix_words + 3) / 4 : 1);
     a.dKw = make_fastdiv(a.kw > 0 ? a.kw : 1);
     a.taps_mode = taps_mode(a);
+    a.sel_ranked = a.sel_words;
+    a.dSelRow = FastDiv{0, 0, 0};
+    if (a.sel_words > 0 && a.sel_dilate) {
+        const long long per_row = (a.Wo + 63) / 64, words = per_row * (a.max_pixels / a.Wo);
+        if (words <= kSelMaxWords) {
+            a.sel_ranked = (int)words;
+            a.dSelRow = make_fastdiv((int)per_row);
+        }
+    }
 }
 
 int gemm_select_max_words(void) { return kSelMaxWords; }
