@@ -30,6 +30,12 @@ int fail(int code, const char *fmt, ...)
 }
 
 constexpr size_t kAlign = 256;
+// Outputs up to here have no copy launch of their own (enqueue_frame): of frames that recompute everything, and of
+// others, for which the detection launch copies what stays.  Everything recomputed, 32 channels on 320 x 240 28 -> 15 us
+// a frame, 256 on 320 x 180 104 -> 106 with the copy kernel for wide maps.  Some: 16 channels on 64 x 64 14.7 -> 11.5 us,
+// 64 on 128 x 128 (4 MB) 13.9 -> 11.8, 256 on 64 x 64 22.8 -> 22.6; 128 on 100 x 100 (5 MB) 24.0 -> 26.5, 256 on
+// 83 x 61 30.6 -> 33.3.
+constexpr size_t kDirectOutputAll = 1u << 30, kDirectOutputSome = 4 << 20;
 constexpr int kMaxGemmGrid = 256; // workgroups of one GEMM launch (one per compute unit of an MI355X)
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 inline int round_up(int v, int m) { return (v + m - 1) / m * m; }
@@ -617,6 +623,16 @@ int enqueue_frame(cbinfer_state *s, const float *frame, float *out)
     s->lists_stale = false;
     const int S = P.S;
     const int nops = (int)P.ops.size();
+    // A small output is not copied by a launch of its own: the detection launch copies the stored map as it is before
+    // the frame, where anything may stay as it is, and the last layer writes what it recomputes to both.
+    const Op &last = P.ops.back();
+    const size_t out_bytes = (size_t)S * last.M * last.Ho * last.Wo * 4, in_bytes = (size_t)S * P.in_c * P.in_h * P.in_w * 4;
+    const char *fb = reinterpret_cast<const char *>(frame), *ob = reinterpret_cast<const char *>(out);
+    const bool direct_out = !pipe && last.kind == CBINFER_OP_CONV && out_bytes <= (first || s->force_dense ? kDirectOutputAll : kDirectOutputSome) &&
+                            words_for((long long)S * last.Ho * last.Wo) <= cbk::gemm_select_max_words() &&
+                            (ob >= fb + in_bytes || fb >= ob + out_bytes); // the frame is still read when the copy begins
+    const cbk::PlanarCopy old_output = cbk::planar_copy(s->at<void>(last.o_out), out, last.M, last.Ms / cbk::elems_per_unit(P.dtype),
+                                                        last.Ho * last.Wo, S);
 
     for (int l = 0; l < nops; ++l) {
         const Op &op = P.ops[l];
@@ -640,7 +656,8 @@ int enqueue_frame(cbinfer_state *s, const float *frame, float *out)
                 uint64_t *flags = s->force_dense ? nullptr : s->at<uint64_t>(P.o_flags);
                 HIP_TRY(cbk::detect_frame(st, frame, ref, s->at<void>(op.o_cur), s->at<uint64_t>(op.o_chg), op.C,
                                           op.Cs / eu, N, S, op.tau, hold, all ? 1 : 0, P.dtype,
-                                          op.pix_words == op.C && op.C % 4 != 0, flags, P.flag_words, t.timing()));
+                                          op.pix_words == op.C && op.C % 4 != 0, flags, P.flag_words,
+                                          direct_out && !first && !s->force_dense ? &old_output : nullptr, t.timing()));
                 x = hold ? s->at<void>(op.o_cur) : ref;
             } else {
                 x = s->at<void>(P.ops[l - 1].o_out);
@@ -700,6 +717,7 @@ int enqueue_frame(cbinfer_state *s, const float *frame, float *out)
             a.partial = s->at<float>(P.o_partial);
             a.tickets = s->at<int>(P.o_tickets);
             a.grid = op.gemm_grid;
+            a.planar = direct_out && l + 1 == nops ? out : nullptr;
             a.next_flags = nullptr;
             a.next_tau = 0.f;
             a.next_force = first ? 1 : 0;
@@ -740,8 +758,7 @@ int enqueue_frame(cbinfer_state *s, const float *frame, float *out)
                                          next_flags, next_tau, first ? 1 : 0, P.dtype, completion(l, t.timing())));
         }
     }
-    const Op &last = P.ops.back();
-    {
+    if (!direct_out) {
         StepTimer t(s, nops - 1, CBINFER_STEP_OUTPUT);
         HIP_TRY(cbk::map_to_planar(st, s->at<void>(last.o_out), out, last.M, last.Ms / cbk::elems_per_unit(P.dtype),
                                    last.Ho * last.Wo, S, P.dtype, completion(nops, t.timing())));

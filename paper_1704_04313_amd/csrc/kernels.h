@@ -106,25 +106,6 @@ __device__ __forceinline__ uint4 unit_max(const uint4 &a, const uint4 &b)
     return m;
 }
 
-// ---- change detection (Section 3.1, first formula) ---------------------------------------
-// Planar float32 frame [S][C][N] against the stored previous input kept as a map of V units per
-// pixel (bfloat16 storage: the frame is rounded to bfloat16 first and compared as such).
-// Writes the change bitmap; refreshes the stored input (hold == 0: everywhere;
-// hold == 1: `cur` receives the frame as a map and `ref` is refreshed only where flagged).
-// force != 0: every pixel is flagged and ref is not read (first frame / dense mode).
-// clear_words 64-bit words starting at clear are zeroed by the same launch (the byte change maps
-// that later kernels of the frame fill in); they must not overlap bits.
-// packed != 0 (only where detect_frame_packs(dtype, C, S * N)): the stored map holds C float32 values
-// per pixel and no padding channels.
-bool detect_frame_packs(int dtype, int C, long long pixels);
-hipError_t detect_frame(hipStream_t st, const float *frame, void *ref, void *cur, uint64_t *bits, int C, int V,
-                        int N, int S, float tau, int hold, int force, int dtype, int packed, uint64_t *clear,
-                        long long clear_words, const Timing &tm = Timing());
-
-// Map against map (layers fed by a stored output map).  x and ref are [S*N][V units].
-hipError_t detect_map(hipStream_t st, const void *x, void *ref, uint64_t *bits, int V, int total, float tau,
-                      int hold, int force, int dtype, const Timing &tm = Timing());
-
 // Division of a non-negative 32-bit number by an invariant divisor through one 64-bit
 // multiplication (integer division is emulated with dozens of instructions on this hardware).
 // Exact for 0 <= n < 2^31 and 1 <= d < 2^31: with l = ceil(log2 d) and m = floor(2^(31+l) / d) + 1,
@@ -149,6 +130,44 @@ __host__ __device__ inline int fast_div(int n, const FastDiv &f)
 {
     return (int)((unsigned)(((unsigned long long)((unsigned)n << 1) * f.m) >> 32) >> f.shift);
 }
+
+// A stored map of V units per pixel and its M channels as planar float32 [S][M][No]; S * V * No < 2^30.
+struct PlanarCopy {
+    const uint4 *map = nullptr;
+    float *planar = nullptr;
+    int M = 0, V = 0, No = 0, total = 0; // units of the map
+    FastDiv dNo, dV;
+};
+inline PlanarCopy planar_copy(const void *map, float *planar, int M, int V, int No, int S)
+{
+    PlanarCopy c;
+    c.map = static_cast<const uint4 *>(map);
+    c.planar = planar;
+    c.M = M; c.V = V; c.No = No; c.total = S * V * No;
+    c.dNo = make_fastdiv(No);
+    c.dV = make_fastdiv(V);
+    return c;
+}
+
+// ---- change detection (Section 3.1, first formula) ---------------------------------------
+// Planar float32 frame [S][C][N] against the stored previous input kept as a map of V units per
+// pixel (bfloat16 storage: the frame is rounded to bfloat16 first and compared as such).
+// Writes the change bitmap; refreshes the stored input (hold == 0: everywhere;
+// hold == 1: `cur` receives the frame as a map and `ref` is refreshed only where flagged).
+// force != 0: every pixel is flagged and ref is not read (first frame / dense mode).
+// clear_words 64-bit words starting at clear are zeroed by the same launch (the byte change maps
+// that later kernels of the frame fill in); they must not overlap bits.
+// old_output: null, or a copy that further workgroups of the launch make; it must not touch what the detection does.
+// packed != 0 (only where detect_frame_packs(dtype, C, S * N)): the stored map holds C float32 values
+// per pixel and no padding channels.
+bool detect_frame_packs(int dtype, int C, long long pixels);
+hipError_t detect_frame(hipStream_t st, const float *frame, void *ref, void *cur, uint64_t *bits, int C, int V,
+                        int N, int S, float tau, int hold, int force, int dtype, int packed, uint64_t *clear,
+                        long long clear_words, const PlanarCopy *old_output = nullptr, const Timing &tm = Timing());
+
+// Map against map (layers fed by a stored output map).  x and ref are [S*N][V units].
+hipError_t detect_map(hipStream_t st, const void *x, void *ref, uint64_t *bits, int V, int total, float tau,
+                      int hold, int force, int dtype, const Timing &tm = Timing());
 
 // ---- dilation by the filter support (Section 3.1, second formula) -------------------------
 // upd bit (stream, qy, qx) = OR of the change bits inside that output's receptive field.
@@ -249,6 +268,8 @@ struct GemmArgs {
     unsigned char *next_flags; // nullptr: off
     float next_tau;
     int next_force;            // flag every recomputed position (first frame)
+    float *planar;             // not null: recomputed values also go to this planar float32 map [S][M][No]; maps
+                               // of at most gemm_select_max_words() words only
 };
 int gemm_channel_tile(int M);   // channel tile BM used for M output channels (Mpad = M rounded up to it)
 int gemm_k_multiple(int dtype); // Kpad must be a multiple of this many elements (128 bytes)

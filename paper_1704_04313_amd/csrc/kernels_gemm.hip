@@ -402,6 +402,21 @@ __device__ __forceinline__ void write_update_map(const GemmArgs &a, const uint64
         a.upd_out[i] = a.Wo & 63 && a.dSelRow.d ? packed_word(a, sW, i) : sW[i];
 }
 
+// Channels ch .. ch + 3 of position g in the planar output.
+__device__ __forceinline__ void store_planar(const GemmArgs &a, int g, int ch, const float4 &v)
+{
+    const int st = a.S > 1 ? fast_div(g, a.dNo) : 0;
+    float *dst = a.planar + ((size_t)st * a.M + ch) * a.No + (g - st * a.No);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (ch + e < a.M) dst[(size_t)e * a.No] = (&v.x)[e];
+}
+__device__ __forceinline__ float4 bf16_values(const uint2 &v)
+{
+    return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16),
+                       __uint_as_float(v.y & 0xffff0000u));
+}
+
 // The position of rank r (0 <= r < number of selected positions) in a ranked selection map.
 __device__ __forceinline__ int select_rank(const GemmArgs &a, const Selection &sel, int r)
 {
@@ -1346,6 +1361,8 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                                               fabsf(bf16_value(nv.y >> 16) - bf16_value(ov.y >> 16)) > a.next_tau;
                             }
                             *dst = nv;
+                            const float4 r = bf16_values(nv);
+                            acc[j][i] = (floatx4){r.x, r.y, r.z, r.w};
                         } else {
                             float4 *dst = reinterpret_cast<float4 *>(static_cast<float *>(a.out) + (size_t)g * a.Ms + ch);
                             if (detect) {
@@ -1355,8 +1372,19 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                                               fabsf(o.z - ov.z) > a.next_tau || fabsf(o.w - ov.w) > a.next_tau;
                             }
                             *dst = o;
+                            acc[j][i] = (floatx4){o.x, o.y, o.z, o.w};
                         }
                     }
+                }
+            }
+            if (a.planar) {
+#pragma unroll
+                for (int i = 0; i < TP; ++i) {
+                    const int g = list[wpx0 + i * 16 + lrow];
+                    if (g < 0) continue;
+#pragma unroll
+                    for (int j = 0; j < TC; ++j)
+                        store_planar(a, g, mt * BM + wch0 + j * 16 + lk * 4, make_float4(acc[j][i][0], acc[j][i][1], acc[j][i][2], acc[j][i][3]));
                 }
             }
             if (a.next_flags) {
@@ -1560,6 +1588,7 @@ __device__ __forceinline__ void thin_tiles(const GemmArgs &a, const int n, const
                                    fabsf(bf16_value(nv.y & 0xffff) - bf16_value(old[j][1] & 0xffff)) > a.next_tau ||
                                    fabsf(bf16_value(nv.y >> 16) - bf16_value(old[j][1] >> 16)) > a.next_tau;
                     *reinterpret_cast<uint2 *>(static_cast<unsigned short *>(a.out) + (size_t)cur.g * a.Ms + ch) = nv;
+                    if (a.planar) store_planar(a, cur.g, ch, bf16_values(nv));
                 } else {
                     if (detect)
                         changed |= fabsf(o.x - __uint_as_float(old[j][0])) > a.next_tau ||
@@ -1567,6 +1596,7 @@ __device__ __forceinline__ void thin_tiles(const GemmArgs &a, const int n, const
                                    fabsf(o.z - __uint_as_float(old[j][2])) > a.next_tau ||
                                    fabsf(o.w - __uint_as_float(old[j][3])) > a.next_tau;
                     *reinterpret_cast<float4 *>(static_cast<float *>(a.out) + (size_t)cur.g * a.Ms + ch) = o;
+                    if (a.planar) store_planar(a, cur.g, ch, o);
                 }
             }
         }
@@ -1919,6 +1949,7 @@ hipError_t gemm_gather(hipStream_t st, const GemmArgs &a, const Timing &tm)
         (a.sel_words == 0 && !a.list != !a.count) || (long long)a.sel_words * 64 < a.max_pixels * (a.sel_words > 0))
         return hipErrorInvalidValue;
     if (gemm_is_thin(a) && gemm_is_point(a)) {
+        if (a.planar) return hipErrorInvalidValue; // maps that may be ranked only
         int mshift = 0;
         while ((1 << mshift) < a.Ms / eu) ++mshift;
         long long grid = (((long long)a.max_pixels << mshift) + 256 * kPointBatch - 1) / (256 * kPointBatch);
