@@ -530,14 +530,14 @@ __global__ __launch_bounds__(kBlock) void dilate_kernel(const uint64_t *__restri
 // Dilation a word at a time, for layers of stride 1 with filters up to 16 wide (and a 2 x 2
 // pooling behind them, if any) and of stride 2 without pooling behind them (Section 3: a strided
 // convolution drops the unused columns of the image matrix; here it keeps every other bit of the
-// dilated row).  A workgroup produces kCountWords words of the update map or of
+// dilated row).  A workgroup produces kBlock / LANES words of the update map or of
 // the pooled map, or counts as many of the change map.  It first brings the input rows its
 // outputs read -- a contiguous piece of the change map -- into LDS as bits (a byte map is packed
-// on the way): one round of coalesced loads, everything after that reads LDS.  Eight lanes then
-// share one 64-position word: lane r takes the input rows r, r + 8, ... of the receptive fields.
+// on the way): one round of coalesced loads, everything after that reads LDS.  LANES lanes then
+// share one 64-position word: lane r takes the input rows r, r + LANES, ... of the receptive fields.
 // Dilation is separable and OR commutes, so each lane ORs the raw change bits of its rows (a
 // window of the outputs' columns plus the filter's reach), then the shifted copies of that
-// window by doubling, and the eight partial words are OR-ed across the lanes.  The fields of the
+// window by doubling, and the partial words are OR-ed across the lanes.  The fields of the
 // 2 x 2 outputs under a pooled position tile one (kh+1) x (kw+1) window, so the pooled map is a
 // dilation with that window at stride 2.  The workgroup also leaves the number of set bits of
 // its words, which is what the index extraction needs to place its output.
@@ -547,9 +547,8 @@ static constexpr int kCompactTwoWordsFrom = 65536; // maps of more words than th
 static constexpr int kCompactStage = 2048; // list entries a workgroup stages in LDS (8 KiB); more go straight to the list
 static constexpr int kCompactDense = 12;   // words with more set bits than this are expanded by a whole wave
 static constexpr int kCountWords = 32;    // words per entry of the group-count arrays
-static constexpr int kWordLanes = 8;
+static constexpr int kWordLanes = 8;      // lanes that share a word of the dilated map, at most
 static constexpr int kRegionWords = 4096; // LDS bitmap of the input piece: 32 KiB
-static_assert(kCountWords * kWordLanes == kBlock, "one word per eight lanes");
 
 // Bits [a, a + len) of the LDS bitmap as the low bits of the result; 1 <= len <= 64; the word
 // behind the one holding bit a is read too (zero words follow the piece).
@@ -615,12 +614,13 @@ __device__ __forceinline__ uint64_t even_bits(uint64_t x)
     return x;
 }
 
-// OR over the kWordLanes lanes that share a word
+// OR over the LANES lanes that share a word
+template <int LANES>
 __device__ __forceinline__ uint64_t word_lanes_or(uint64_t v)
 {
     unsigned lo = (unsigned)v, hi = (unsigned)(v >> 32);
 #pragma unroll
-    for (int d = 1; d < kWordLanes; d <<= 1) {
+    for (int d = 1; d < LANES; d <<= 1) {
         lo |= (unsigned)__shfl_xor((int)lo, d, 64);
         hi |= (unsigned)__shfl_xor((int)hi, d, 64);
     }
@@ -646,20 +646,22 @@ struct DilateWords {
     int region_words;            // capacity of the LDS piece in words
 };
 
-template <bool BYTES>
+template <bool BYTES, int LANES>
 __global__ __launch_bounds__(kBlock) void dilate_words_kernel(DilateWords a)
 {
     extern __shared__ uint64_t sM[]; // region_words + 2 words: the piece of the change map this workgroup reads
+    constexpr int kWords = kBlock / LANES; // per workgroup
+    constexpr int kGroupLanes = kCountWords * LANES < 64 ? kCountWords * LANES : 64; // lanes of a wave that count for one group
     __shared__ int swave[kBlock / 64];
     const DilateGeom &g = a.g;
-    const int tid = threadIdx.x, r = tid & (kWordLanes - 1);
+    const int tid = threadIdx.x, r = tid & (LANES - 1);
     int b = blockIdx.x;
     const int role = b < a.upd_blocks ? 0 : (b < a.upd_blocks + a.pool_blocks ? 1 : 2);
     if (role >= 1) b -= a.upd_blocks;
     if (role == 2) b -= a.pool_blocks;
     const int nwords = role == 0 ? a.upd_words : (role == 1 ? a.pool_words : a.chg_words);
     int *groups = role == 0 ? a.upd_groups : (role == 1 ? a.pool_groups : a.chg_groups);
-    const int i = b * kCountWords + (tid >> 3); // this lane's word (shared with seven neighbours)
+    const int i = b * kWords + tid / LANES; // this lane's word
     uint64_t word = 0;
 
     if (role < 2) {
@@ -667,8 +669,8 @@ __global__ __launch_bounds__(kBlock) void dilate_words_kernel(DilateWords a)
         const int per = role == 0 ? g.Wo : g.Wp, rows = role == 0 ? g.Ho : g.Hp;
         const FastDiv &dper = role == 0 ? a.dWo : a.dWp, &drows = role == 0 ? a.dHo : a.dHp;
         const int total = g.S * rows * per;
-        const int q_lo = b * kCountWords * 64;
-        const int q_hi = (q_lo + kCountWords * 64 < total ? q_lo + kCountWords * 64 : total) - 1;
+        const int q_lo = b * kWords * 64;
+        const int q_hi = (q_lo + kWords * 64 < total ? q_lo + kWords * 64 : total) - 1;
         // first and last row (stream * rows + y) of those positions, then their first and last input row
         const int r_lo = fast_div(q_lo, dper), r_hi = fast_div(q_hi, dper);
         const int st_lo = fast_div(r_lo, drows), st_hi = fast_div(r_hi, drows);
@@ -705,17 +707,17 @@ __global__ __launch_bounds__(kBlock) void dilate_words_kernel(DilateWords a)
                 const int len = per - x < p1 - pos ? per - x : p1 - pos;
                 uint64_t bits;
                 if (role == 0 && g.stride == 1) {
-                    Window wd = rows_or(sM, bit0, g, st, y - g.pad, g.kh, x - g.pad, len + g.kw - 1, r, kWordLanes);
+                    Window wd = rows_or(sM, bit0, g, st, y - g.pad, g.kh, x - g.pad, len + g.kw - 1, r, LANES);
                     spread(wd, g.kw);
                     bits = wd.w[0];
                 } else if (role == 0) { // stride 2: the dilation at every input column, then every other bit
                     Window wd = rows_or(sM, bit0, g, st, 2 * y - g.pad, g.kh, 2 * x - g.pad, 2 * (len - 1) + g.kw, r,
-                                        kWordLanes);
+                                        LANES);
                     spread(wd, g.kw);
                     bits = even_bits(wd.w[0]) | (even_bits(wd.w[1]) << 32);
                 } else {
                     Window wd = rows_or(sM, bit0, g, st, 2 * y - g.pad, g.kh + 1, 2 * x - g.pad, 2 * len + g.kw - 1, r,
-                                        kWordLanes);
+                                        LANES);
                     spread(wd, g.kw + 1);
                     bits = even_bits(wd.w[0]) | (even_bits(wd.w[1]) << 32);
                 }
@@ -730,12 +732,13 @@ __global__ __launch_bounds__(kBlock) void dilate_words_kernel(DilateWords a)
             }
         }
     } else if (i < nwords) {
-        if (BYTES) // lane r packs positions 8r .. 8r+7 (the byte maps are padded to whole words)
-            word = (uint64_t)nonzero_bytes(a.chg[(size_t)i * 8 + r]) << (8 * r);
-        else if (r == 0)
+        if (BYTES) { // lane r packs positions 8r .. 8r+7, 8(r+LANES) ... (the byte maps are padded to whole words)
+#pragma unroll
+            for (int k = 0; k < 8; k += LANES) word |= (uint64_t)nonzero_bytes(a.chg[(size_t)i * 8 + k + r]) << (8 * (k + r));
+        } else if (r == 0)
             word = a.chg[i];
     }
-    word = word_lanes_or(word);
+    word = word_lanes_or<LANES>(word);
     int count = 0;
     if (r == 0 && i < nwords) {
         if (role == 0) a.upd[i] = word;
@@ -744,22 +747,27 @@ __global__ __launch_bounds__(kBlock) void dilate_words_kernel(DilateWords a)
     }
     if (!groups) return;
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) count += __shfl_xor(count, d, 64);
-    if ((tid & 63) == 0) swave[tid >> 6] = count;
-    __syncthreads();
-    if (tid == 0 && b * kCountWords < nwords) {
-        int c = 0;
-        for (int w = 0; w < kBlock / 64; ++w) c += swave[w];
-        groups[b] = c;
+    for (int d = kGroupLanes / 2; d >= 1; d >>= 1) count += __shfl_xor(count, d, 64);
+    if constexpr (kCountWords * LANES <= 64) { // one or more whole groups per wave
+        if ((tid & (kGroupLanes - 1)) == 0 && i < nwords) groups[i / kCountWords] = count;
+    } else {
+        constexpr int kWaves = kCountWords * LANES / 64; // per group
+        if ((tid & 63) == 0) swave[tid >> 6] = count;
+        __syncthreads();
+        if (tid % (64 * kWaves) == 0 && i < nwords) {
+            int c = 0;
+            for (int w = 0; w < kWaves; ++w) c += swave[(tid >> 6) + w];
+            groups[i / kCountWords] = c;
+        }
     }
 }
 
-// Words of the change map that kCountWords output words (pooled: every pooled position stands
+// Words of the change map that `words` output words (pooled: every pooled position stands
 // for two rows and columns of outputs) can need at most.
-static long long dilate_region_words(const DilateGeom &g, bool pooled)
+static long long dilate_region_words(const DilateGeom &g, bool pooled, int words)
 {
     const long long per = pooled ? g.Wp : g.Wo, rows_per_stream = pooled ? g.Hp : g.Ho;
-    const long long out_rows = (long long)kCountWords * 64 / per + 2; // rows touched by that many positions
+    const long long out_rows = (long long)words * 64 / per + 2; // rows touched by that many positions
     const long long streams = out_rows / rows_per_stream + 2;         // streams those rows can span
     // outputs' own rows, the filter's reach at both ends, and per stream boundary crossed the
     // rows by which a stream's input is taller than the output rows that count here; never more
@@ -774,7 +782,22 @@ bool dilate_counts(const DilateGeom &g)
     return (g.stride == 1 || (g.stride == 2 && g.pool_k == 0)) && g.kw >= 1 && g.kw <= 16 && g.kh >= 1 &&
            (g.pool_k == 0 || g.pool_k == 2) &&
            (long long)g.S * g.H * g.W < (1ll << 31) && (long long)g.S * g.Ho * g.Wo < (1ll << 31) &&
-           dilate_region_words(g, false) <= kRegionWords && (g.pool_k == 0 || dilate_region_words(g, true) <= kRegionWords);
+           dilate_region_words(g, false, kBlock / kWordLanes) <= kRegionWords &&
+           (g.pool_k == 0 || dilate_region_words(g, true, kBlock / kWordLanes) <= kRegionWords);
+}
+
+// Lanes per word: two filter rows a lane where that leaves kShareFrom workgroups or more (four per compute unit),
+// otherwise eight.  With eight lanes most of a wave has no row to read when filters are short: 1x1 with pooling on
+// 4096 x 4096 22.2 us and now 6.3, 7x7 on 64 maps of 320 x 240 (four lanes) 10.1 and 8.0.  Launches of fewer workgroups
+// take the 4 to 5 us that a launch costs either way.
+static constexpr int kShareFrom = 1024;
+static int dilate_lanes(const DilateGeom &g, bool pooled, long long words)
+{
+    int lanes = 1;
+    while (lanes < kWordLanes && 2 * lanes < g.kh) lanes *= 2;
+    const bool fits = dilate_region_words(g, false, kBlock / lanes) <= kRegionWords &&
+                      (!pooled || dilate_region_words(g, true, kBlock / lanes) <= kRegionWords);
+    return fits && words * lanes >= (long long)kShareFrom * kBlock ? lanes : kWordLanes;
 }
 
 hipError_t dilate(hipStream_t st, const uint64_t *chg_bits, uint64_t *upd_bits, uint64_t *pool_bits,
@@ -794,19 +817,26 @@ hipError_t dilate(hipStream_t st, const uint64_t *chg_bits, uint64_t *upd_bits, 
         a.upd_words = (int)(((long long)g.S * g.Ho * g.Wo + 63) / 64);
         a.pool_words = pooled ? (int)(((long long)g.S * g.Hp * g.Wp + 63) / 64) : 0;
         a.chg_words = (int)(((long long)g.S * g.H * g.W + 63) / 64);
-        a.upd_blocks = (a.upd_words + kCountWords - 1) / kCountWords;
-        a.pool_blocks = (a.pool_words + kCountWords - 1) / kCountWords;
-        const int grid = a.upd_blocks + a.pool_blocks + (count ? (a.chg_words + kCountWords - 1) / kCountWords : 0);
+        const int lanes = dilate_lanes(g, pooled, (long long)a.upd_words + a.pool_words + (count ? a.chg_words : 0));
+        const int per = kBlock / lanes;
+        a.upd_blocks = (a.upd_words + per - 1) / per;
+        a.pool_blocks = (a.pool_words + per - 1) / per;
+        const int grid = a.upd_blocks + a.pool_blocks + (count ? (a.chg_words + per - 1) / per : 0);
         // LDS for the largest piece any workgroup reads (at most kRegionWords, or dilate_counts() is
         // false): small pieces leave room for more workgroups per compute unit
-        long long rw = dilate_region_words(g, false);
-        if (pooled && dilate_region_words(g, true) > rw) rw = dilate_region_words(g, true);
+        long long rw = dilate_region_words(g, false, per);
+        if (pooled && dilate_region_words(g, true, per) > rw) rw = dilate_region_words(g, true, per);
         a.region_words = (int)rw;
         const unsigned lds = (unsigned)(rw + 2) * 8u;
-        if (g.chg_bytes)
-            launch_kernel(tm, dilate_words_kernel<true>, dim3(grid), dim3(kBlock), lds, st, a);
-        else
-            launch_kernel(tm, dilate_words_kernel<false>, dim3(grid), dim3(kBlock), lds, st, a);
+#define L(LANES_)                                                                                     \
+    if (lanes == LANES_) {                                                                            \
+        if (g.chg_bytes)                                                                              \
+            launch_kernel(tm, dilate_words_kernel<true, LANES_>, dim3(grid), dim3(kBlock), lds, st, a);  \
+        else                                                                                          \
+            launch_kernel(tm, dilate_words_kernel<false, LANES_>, dim3(grid), dim3(kBlock), lds, st, a); \
+    }
+        L(1) L(2) L(4) L(8)
+#undef L
         return hipGetLastError();
     }
     const int ub = (g.S * g.Ho * g.Wo + kBlock - 1) / kBlock;
