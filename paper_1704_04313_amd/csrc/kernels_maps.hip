@@ -51,6 +51,12 @@ __device__ __forceinline__ bool copies_output(const OldOutput &o)
 // ------------------------------------------------------------------------------------------
 static constexpr int kDetectPix = 4;
 
+// Not for values: -0 and 0 differ, a NaN does not from itself.
+__device__ __forceinline__ bool unit_differs(const uint4 &a, const uint4 &b)
+{
+    return ((a.x ^ b.x) | (a.y ^ b.y) | (a.z ^ b.z) | (a.w ^ b.w)) != 0;
+}
+
 template <int DT, int HOLD>
 __global__ __launch_bounds__(kBlock) void detect_frame_kernel(const float *__restrict__ frame,
                                                               uint4 *__restrict__ ref, uint4 *__restrict__ cur,
@@ -90,7 +96,7 @@ __global__ __launch_bounds__(kBlock) void detect_frame_kernel(const float *__res
         if (ok[k]) {
             flag[k] = force || unit_exceeds<DT>(xv[k], rv[k], tau);
             if (HOLD) cur[g] = xv[k];
-            if (!HOLD || flag[k]) ref[g] = xv[k];
+            if (HOLD ? flag[k] : force || __any(unit_differs(xv[k], rv[k]))) ref[g] = xv[k];
         }
         const uint64_t word = __ballot(flag[k]);
         if (lane == 0 && g < total) bits[g >> 6] = word;
@@ -176,11 +182,18 @@ __global__ __launch_bounds__(64 * kUnitWaves) void detect_frame_units_kernel(con
 // bitmap words.  All global accesses stay full-wave coalesced.
 // ------------------------------------------------------------------------------------------
 static constexpr int kPackMaxC = 7;
+// Every channel count has its kernel, with the registers and the LDS that it needs: eight waves per SIMD hide the way
+// through LDS for three channels, where arrays for seven left room for five (detection on 1280 x 720 9.9 us and now 7.4,
+// 64 x 320 x 240 33.3 and 30.0, 5 channels on 1200 x 1000 14.6 and 10.7, one channel 7.7 and 4.2).  What a pass moves
+// beyond the last-level cache arrives faster with five workgroups per compute unit: 104 and 110 us on 4096 x 4096, every
+// value changed 128 and 131, held 131 and 136.  So such launches ask for LDS up to kPackLdsFar, which they do not use.
+static constexpr long long kLastLevelBytes = 256ll << 20;
+static constexpr int kPackLdsFar = 32 << 10;
 
-template <int HOLD>
+template <int HOLD, int C>
 __global__ __launch_bounds__(kBlock) void detect_frame_packed_kernel(const float *__restrict__ frame,
                                                                      float *__restrict__ ref, float *__restrict__ cur,
-                                                                     uint64_t *__restrict__ bits, int C, int N,
+                                                                     uint64_t *__restrict__ bits, int N,
                                                                      int total, float tau, int force,
                                                                      uint64_t *__restrict__ clear, long long clear_words,
                                                                      FastDiv dN, OldOutput old)
@@ -188,7 +201,7 @@ __global__ __launch_bounds__(kBlock) void detect_frame_packed_kernel(const float
     constexpr int P = kDetectPix;       // pixels per lane
     constexpr int WP = 64 * P;          // pixels per wave
     constexpr int WAVES = kBlock / 64;
-    __shared__ __align__(16) float sX[WAVES][WP * kPackMaxC];
+    __shared__ __align__(16) float sX[WAVES][WP * C];
     __shared__ int sF[WAVES][WP];
     const int tid = blockIdx.x * kBlock + threadIdx.x;
     for (long long i = tid; i < clear_words; i += (long long)gridDim.x * kBlock) clear[i] = 0ull;
@@ -199,22 +212,22 @@ __global__ __launch_bounds__(kBlock) void detect_frame_packed_kernel(const float
     int *sf = sF[wave];
     const long long e0 = (long long)p0 * C;          // the wave's first map element (a multiple of 4)
     const long long e_end = (long long)total * C;    // elements of the whole map
-    const int inv = (65536 + C - 1) / C;             // e / C == (e * inv) >> 16 for e < 256 * 7, C <= 7
+    constexpr int inv = (65536 + C - 1) / C;         // e / C == (e * inv) >> 16 for e < 256 * 7, C <= 7
     // all global loads first: the frame's values of this lane's pixels and its float4 of the stored map
-    float fv[P][kPackMaxC];
-    float4 xv[kPackMaxC], rv[kPackMaxC];
+    float fv[P][C];
+    float4 xv[C], rv[C];
 #pragma unroll
     for (int k = 0; k < P; ++k) {
         const int g = p0 + lane + 64 * k;
         const int st = g < total ? fast_div(g, dN) : 0;
         const float *fp = frame + (size_t)st * C * N + (g < total ? g - st * N : 0);
 #pragma unroll
-        for (int c = 0; c < kPackMaxC; ++c) fv[k][c] = (c < C && g < total) ? fp[(size_t)c * N] : 0.f;
+        for (int c = 0; c < C; ++c) fv[k][c] = g < total ? fp[(size_t)c * N] : 0.f;
     }
 #pragma unroll
-    for (int j = 0; j < kPackMaxC; ++j) {
+    for (int j = 0; j < C; ++j) {
         rv[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (j >= C || force) continue;
+        if (force) continue;
         const long long e = e0 + 4ll * (lane + 64 * j);
         if (e + 4 <= e_end) {
             rv[j] = *reinterpret_cast<const float4 *>(ref + e);
@@ -230,17 +243,15 @@ __global__ __launch_bounds__(kBlock) void detect_frame_packed_kernel(const float
         const int pl = lane + 64 * k;
         sf[pl] = (force && p0 + pl < total) ? 1 : 0;
 #pragma unroll
-        for (int c = 0; c < kPackMaxC; ++c)
-            if (c < C) sx[pl * C + c] = fv[k][c];
+        for (int c = 0; c < C; ++c) sx[pl * C + c] = fv[k][c];
     }
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < kPackMaxC; ++j)
-        xv[j] = j < C ? *reinterpret_cast<const float4 *>(sx + 4 * (lane + 64 * j)) : make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int j = 0; j < C; ++j)
+        xv[j] = *reinterpret_cast<const float4 *>(sx + 4 * (lane + 64 * j));
     if (!force) {
 #pragma unroll
-        for (int j = 0; j < kPackMaxC; ++j) {
-            if (j >= C) break;
+        for (int j = 0; j < C; ++j) {
             const int el = 4 * (lane + 64 * j); // element inside the wave's piece
             const long long e = e0 + el;
             if (e + 0 < e_end && fabsf(xv[j].x - rv[j].x) > tau) sf[((el + 0) * inv) >> 16] = 1;
@@ -250,30 +261,40 @@ __global__ __launch_bounds__(kBlock) void detect_frame_packed_kernel(const float
         }
     }
     __syncthreads();
-    // the stored map: everything (hold: the current frame everywhere, the reference where flagged)
+    // The stored map: everything (hold: the current frame everywhere, the reference where flagged), unless the wave's
+    // piece holds those very bits already, as it does wherever a noise-free or decoded video stands still: the launch
+    // is bound by HBM and a third of its bytes are this write.  4096 x 4096, 82 % of the pixels as before: 118 us with
+    // the write and 104, the output copy at the end of that frame 55 and 48; every value changed: 127 and 128.
+    bool differs = force;
 #pragma unroll
-    for (int j = 0; j < kPackMaxC; ++j) {
-        if (j >= C) break;
+    for (int j = 0; j < C; ++j) {
         const int el = 4 * (lane + 64 * j);
         const long long e = e0 + el;
         if (e >= e_end) continue;
         float4 nr = xv[j];
         if (HOLD) {
+            if (e + 4 <= e_end)
+                *reinterpret_cast<float4 *>(cur + e) = xv[j];
+            else
+                for (int i = 0; i < 3; ++i)
+                    if (e + i < e_end) cur[e + i] = (&xv[j].x)[i];
             if (!sf[((el + 0) * inv) >> 16]) nr.x = rv[j].x;
             if (!sf[((el + 1) * inv) >> 16]) nr.y = rv[j].y;
             if (!sf[((el + 2) * inv) >> 16]) nr.z = rv[j].z;
             if (!sf[((el + 3) * inv) >> 16]) nr.w = rv[j].w;
         }
-        if (e + 4 <= e_end) {
-            if (HOLD) *reinterpret_cast<float4 *>(cur + e) = xv[j];
-            *reinterpret_cast<float4 *>(ref + e) = nr;
-        } else { // the map's last elements: nothing may be written behind them
-            const float xs[3] = {xv[j].x, xv[j].y, xv[j].z}, ns[3] = {nr.x, nr.y, nr.z};
-            for (int i = 0; i < 3; ++i)
-                if (e + i < e_end) {
-                    if (HOLD) cur[e + i] = xs[i];
-                    ref[e + i] = ns[i];
-                }
+        xv[j] = nr;
+        differs |= unit_differs(__builtin_bit_cast(uint4, nr), __builtin_bit_cast(uint4, rv[j]));
+    }
+    if (__any(differs)) {
+#pragma unroll
+        for (int j = 0; j < C; ++j) {
+            const long long e = e0 + 4 * (lane + 64 * j);
+            if (e + 4 <= e_end)
+                *reinterpret_cast<float4 *>(ref + e) = xv[j];
+            else // the map's last elements: nothing may be written behind them
+                for (int i = 0; i < 3; ++i)
+                    if (e + i < e_end) ref[e + i] = (&xv[j].x)[i];
         }
     }
 #pragma unroll
@@ -313,12 +334,19 @@ hipError_t detect_frame(hipStream_t st, const float *frame, void *ref, void *cur
     if (packed) {
         if (!detect_frame_packs(dtype, C, total)) return hipErrorInvalidValue;
         float *r = static_cast<float *>(ref), *c = static_cast<float *>(cur);
-        if (hold)
-            launch_kernel(tm, detect_frame_packed_kernel<1>, dim3(grid), dim3(kBlock), 0, st, frame, r, c, bits, C, N, total,
-                          tau, force, clear, clear_words, dN, old);
-        else
-            launch_kernel(tm, detect_frame_packed_kernel<0>, dim3(grid), dim3(kBlock), 0, st, frame, r, c, bits, C, N, total,
-                          tau, force, clear, clear_words, dN, old);
+        const int lds = kBlock / 64 * 64 * kDetectPix * (C + 1) * 4; // static: values and flags
+        const unsigned more = (long long)total * C * (hold ? 16 : 12) > kLastLevelBytes && lds < kPackLdsFar ? kPackLdsFar - lds : 0;
+#define P(C_)                                                                                                              \
+    if (C == C_) {                                                                                                         \
+        if (hold)                                                                                                          \
+            launch_kernel(tm, detect_frame_packed_kernel<1, C_>, dim3(grid), dim3(kBlock), more, st, frame, r, c, bits, N,    \
+                          total, tau, force, clear, clear_words, dN, old);                                                 \
+        else                                                                                                               \
+            launch_kernel(tm, detect_frame_packed_kernel<0, C_>, dim3(grid), dim3(kBlock), more, st, frame, r, c, bits, N,    \
+                          total, tau, force, clear, clear_words, dN, old);                                                 \
+    }
+        P(1) P(2) P(3) P(5) P(6) P(7)
+#undef P
         return hipGetLastError();
     }
     uint4 *r = static_cast<uint4 *>(ref), *c = static_cast<uint4 *>(cur);
