@@ -858,8 +858,9 @@ static constexpr int kPartsUnderWay = ACC <= 4 ? 4 : 2;
 // Where a value is infinite, not a number, or so near the largest float32 that its first part rounds to infinity, the
 // products of parts are not those of the values (infinity less infinity, infinity times a part that is zero),
 // and values below 2^-110 are not the sum of theirs, so the values themselves decide.  Filter values are put
-// together from their parts; channels behind the last one of a packed pixel count as zero.  Bound by the loads,
-// which are issued one slice ahead, as wide as they come; see the figures where it is called.
+// together from their parts; channels behind the last one of a packed pixel count as zero.  Bound by putting the
+// filter values together, vector instructions that add to the MFMAs, so a value serves all pixels of the sub-tile,
+// and by the loads, which are issued one group ahead; see the figures where it is called.
 template <int BM, int TP, int TC>
 __device__ __forceinline__ void plain_sums(const GemmArgs &a, int kc0, int kc1, const char *wt, const int *list, floatx4 (&sum)[TC][TP])
 {
@@ -881,16 +882,22 @@ __device__ __forceinline__ void plain_sums(const GemmArgs &a, int kc0, int kc1, 
     for (int j = 0; j < TC; ++j)
 #pragma unroll
         for (int i = 0; i < TP; ++i) sum[j][i] = (floatx4){0.f, 0.f, 0.f, 0.f};
+    // G groups of four units are loaded together: a slice, as wide as loads come, or half of one where two tiles of
+    // pixels would not leave two of channels their registers (with whole slices and one tile of channels 16->64
+    // 7x7 on 640 x 900 positions that are all NaN 1190 us, now 1024; 64->32 5x5 on 320 x 240 197 and 167, with one NaN
+    // 130 and 115).
+    constexpr int G = TP == 1 ? 2 : 1;
+    typedef typename std::conditional<G == 2, uint4, uint2>::type Part;
     struct Slice {
-        floatx4 px[2][TP];
-        uint4 w[TC][3];
-        int c[2]; // channel of the units' first values
+        floatx4 px[G][TP];
+        Part w[TC][3];
+        int c[G]; // channel of the units' first values
     };
-    // units 8 kc + lk and 8 kc + 4 + lk of the filter rows
+    // units 4 G kc + lk and, of a whole slice, 4 more of the filter rows
     auto load = [&](Slice &v, int kc) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int unit = 8 * kc + 4 * h + lk, tap = fast_div(unit, a.dVin), cu = unit - tap * a.dVin.d;
+        for (int h = 0; h < G; ++h) {
+            const int unit = 4 * G * kc + 4 * h + lk, tap = fast_div(unit, a.dVin), cu = unit - tap * a.dVin.d;
             const int tj = fast_div(tap, a.dKw), ti = tap - tj * a.kw;
             const int off = (tj * a.W + ti) * a.pix_words + cu * 4;
             v.c[h] = cu * 4;
@@ -900,16 +907,16 @@ __device__ __forceinline__ void plain_sums(const GemmArgs &a, int kc0, int kc1, 
                 v.px[h][i] = *reinterpret_cast<const floatx4_a4 *>(x + (ok ? (unsigned)(base[i] + off) : (unsigned)a.zero_word));
             }
         }
-        const char *slice = wt + (size_t)(kc - kc0) * (BM / 16 * 3 * kFragBytes) + lane * 16;
+        const char *slice = wt + (size_t)((G == 2 ? kc : kc >> 1) - kc0) * (BM / 16 * 3 * kFragBytes) + lane * 16 + (G == 2 ? 0 : (kc & 1) * 8);
 #pragma unroll
         for (int j = 0; j < TC; ++j)
 #pragma unroll
-            for (int p = 0; p < 3; ++p) v.w[j][p] = *reinterpret_cast<const uint4 *>(slice + (j * 3 + p) * kFragBytes);
+            for (int p = 0; p < 3; ++p) v.w[j][p] = *reinterpret_cast<const Part *>(slice + (j * 3 + p) * kFragBytes);
     };
-    // k = 32 kc + 16 h + 4 lk + e in step (h, e)
+    // k = 16 G kc + 16 h + 4 lk + e in step (h, e)
     auto multiply = [&](const Slice &v) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
+        for (int e = 0; e < 4 * G; ++e) {
             auto part = [&](int j, int p) { return bf16_value((unsigned short)((&v.w[j][p].x)[e >> 1] >> (e & 1 ? 16 : 0))); };
 #pragma unroll
             for (int j = 0; j < TC; ++j)
@@ -921,16 +928,17 @@ __device__ __forceinline__ void plain_sums(const GemmArgs &a, int kc0, int kc1, 
         }
     };
     Slice v0, v1;
-    load(v0, kc0);
-    int kc = kc0;
+    const int end = 2 / G * kc1;
+    int kc = 2 / G * kc0;
+    load(v0, kc);
 #pragma unroll 1
-    for (; kc + 1 < kc1; kc += 2) {
+    for (; kc + 1 < end; kc += 2) {
         load(v1, kc + 1);
         multiply(v0);
-        load(v0, kc + 2 < kc1 ? kc + 2 : kc);
+        load(v0, kc + 2 < end ? kc + 2 : kc);
         multiply(v1);
     }
-    if (kc < kc1) multiply(v0);
+    if (kc < end) multiply(v0);
 }
 
 // BM x BN workgroup tile; the consumer waves are arranged WM (channels) x WN (pixels).
@@ -1176,9 +1184,11 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
             // Sums that are not finite, and such small ones that parts below the smallest bfloat16 count
             // (GemmArgs::tiny_sum), are formed again from the values themselves, by each wave for its own K
             // range.  (x * 0 is zero for every finite x.)  A tile with such a sum takes two to five times as long:
-            // 64->256 7x7 on 160 x 90 positions 118 us, with one NaN in the map 380, with nothing else in it 545; on
-            // 20 x 20 20, 36 and 38; 16->64 7x7 on 640 x 900 325, 370 and 1200 (one lane per sum, product by product:
-            // 11 150 us for that one NaN, 25 700 for the full map).
+            // 64->256 7x7 on 160 x 90 positions 115 us, with one NaN in the map 374, with nothing else in it 524; on
+            // 20 x 20 21, 37 and 38; 16->64 7x7 on 640 x 900 289, 340 and 1024 (one lane per sum, product by product:
+            // 11 150 us for that one NaN, 25 700 for the full map).  The 128-channel tile in a 2 x 4 arrangement of waves
+            // took 428 us for the map of nothing else, as a filter value put together served two tiles of pixels, and 120
+            // and 425 for the others.
             float z = 0.f;
             unsigned least = ~0u;
             auto size = [](float v) { return (__float_as_uint(v) << 1) - 1u; }; // grows with |v|; largest for zero
@@ -1194,8 +1204,8 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
             if (__builtin_expect(__any(z != 0.f || least < a.tiny_sum), 0)) { // NaN compares unequal
                 const char *wt = static_cast<const char *>(a.wt) +
                                  (((size_t)mt * nk + kc0) * (BM / 16) + wch0 / 16) * (3 * kFragBytes);
-                // few channel tiles at a time: more would not leave their operands registers
-                constexpr int CJ = TC * TP % 2 == 0 && TP == 1 ? 2 : 1;
+                // two channel tiles at a time: more would not leave their operands registers
+                constexpr int CJ = TC % 2 == 0 ? 2 : 1;
                 static_assert(TC % CJ == 0, "whole steps");
 #pragma unroll 1
                 for (int j0 = 0; j0 < TC; j0 += CJ) {

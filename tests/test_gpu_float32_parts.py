@@ -147,7 +147,7 @@ def test_weights_near_the_smallest_float32(exponent, pixels):
 
 @pytest.mark.parametrize("h,w", [(20, 20), (90, 160)])
 def test_cost_of_a_value_that_is_not_finite(h, w):
-    """One NaN pixel, and a map of nothing else, in a wide layer: the sums formed again take two to four times
+    """One NaN pixel, and a map of nothing else, in a wide layer: the sums formed again take two to five times
     as long (measured), not a hundred times; the bound leaves room for a loaded machine."""
     import torch
     L = conv(64, 256, 7, relu=False)
