@@ -1817,6 +1817,14 @@ static int taps_mode(const GemmArgs &a)
     return a.H <= 16000 && a.W <= 16000 ? kTapPerLane : kTapGeneral;
 }
 
+// Words of a row in the ranking where rows begin with words of their own (GemmArgs::sel_ranked, dSelRow), else 0.
+static int sel_row_words(const GemmArgs &a)
+{
+    if (a.sel_words <= 0 || !a.sel_dilate || a.Wo < 1) return 0;
+    const long long per_row = (a.Wo + 63) / 64;
+    return per_row * (a.max_pixels / a.Wo) <= kSelMaxWords ? (int)per_row : 0;
+}
+
 void gemm_set_divisors(GemmArgs &a)
 {
     a.dNo = make_fastdiv(a.No > 0 ? a.No : 1);
@@ -1828,15 +1836,9 @@ void gemm_set_divisors(GemmArgs &a)
     a.dVin = make_fastdiv(a.pix_words > 0 ? (a.pix_words + 3) / 4 : 1);
     a.dKw = make_fastdiv(a.kw > 0 ? a.kw : 1);
     a.taps_mode = taps_mode(a);
-    a.sel_ranked = a.sel_words;
-    a.dSelRow = FastDiv{0, 0, 0};
-    if (a.sel_words > 0 && a.sel_dilate) {
-        const long long per_row = (a.Wo + 63) / 64, words = per_row * (a.max_pixels / a.Wo);
-        if (words <= kSelMaxWords) {
-            a.sel_ranked = (int)words;
-            a.dSelRow = make_fastdiv((int)per_row);
-        }
-    }
+    const int per_row = sel_row_words(a);
+    a.sel_ranked = per_row ? per_row * (a.max_pixels / a.Wo) : a.sel_words;
+    a.dSelRow = per_row ? make_fastdiv(per_row) : FastDiv{0, 0, 0};
 }
 
 int gemm_select_max_words(void) { return kSelMaxWords; }
@@ -1952,6 +1954,10 @@ hipError_t gemm_gather(hipStream_t st, const GemmArgs &a, const Timing &tm)
     if (a.kh < 1 || a.kw < 1 || a.dKw.d != a.kw || a.dVin.d != (a.pix_words + 3) / 4) return hipErrorInvalidValue;
     if (a.dNo.d != a.No || a.dWo.d != a.Wo || a.dHo.d * a.Wo != a.No || a.dGrid.d != a.grid ||
         a.dNk.d != a.Kpad / gemm_k_multiple(a.dtype) || a.dNk.d >= (1 << 20))
+        return hipErrorInvalidValue;
+    // so must what else was derived from them: the ranking's room in LDS, where ranked words lie, the producers' 32-bit offsets
+    const int per_row = sel_row_words(a);
+    if (a.taps_mode != taps_mode(a) || a.dSelRow.d != per_row || a.sel_ranked != (per_row ? per_row * (a.max_pixels / a.Wo) : a.sel_words))
         return hipErrorInvalidValue;
     if (a.sel_words > 0 && a.sel_dilate &&
         (a.stride != 1 || a.kw > 16 || a.kw < 1 || a.kh < 1 || a.kh > 16 || !a.upd_out || a.S < 1 || a.sel_in_words < 1 ||
