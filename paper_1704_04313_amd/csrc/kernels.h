@@ -227,11 +227,10 @@ struct GemmArgs {
     const uint64_t *sel_map;
     int sel_bytes;
     int sel_words;
-    // sel_dilate != 0 (stride 1, kw <= 16, change map and the S*H*Wo intermediate map of at most
-    // gemm_select_max_words() words each): sel_map is the layer's *change* map over its
-    // sel_in_words * 64 input positions, and the kernel derives the outputs to recompute itself
-    // by dilating it with the kh x kw filter support (Section 3.1, second formula); the workgroups
-    // write the resulting bitmap (sel_words words) to upd_out.
+    // sel_dilate != 0 (stride 1, kh and kw <= 16, change map of at most gemm_select_max_words() words):
+    // sel_map is the layer's *change* map over its sel_in_words * 64 input positions, and the kernel
+    // derives the outputs to recompute itself by dilating it with the kh x kw filter support
+    // (Section 3.1, second formula); the workgroups write the resulting bitmap (sel_words words) to upd_out.
     int sel_dilate;
     int sel_in_words;
     uint64_t *upd_out;

@@ -1961,8 +1961,7 @@ hipError_t gemm_gather(hipStream_t st, const GemmArgs &a, const Timing &tm)
         return hipErrorInvalidValue;
     if (a.sel_words > 0 && a.sel_dilate &&
         (a.stride != 1 || a.kw > 16 || a.kw < 1 || a.kh < 1 || a.kh > 16 || !a.upd_out || a.S < 1 || a.sel_in_words < 1 ||
-         a.sel_in_words > kSelMaxWords || ((long long)a.S * a.H * a.Wo + 63) / 64 > kSelMaxWords ||
-         (long long)a.sel_in_words * 64 < (long long)a.S * a.N || a.No % a.Wo != 0))
+         a.sel_in_words > kSelMaxWords || (long long)a.sel_in_words * 64 < (long long)a.S * a.N || a.No % a.Wo != 0))
         return hipErrorInvalidValue;
     if (a.sel_words < 0 || a.sel_words > kSelMaxWords || (a.sel_words > 0 && !a.sel_map) ||
         (a.sel_words == 0 && !a.list != !a.count) || (long long)a.sel_words * 64 < a.max_pixels * (a.sel_words > 0))
