@@ -30,12 +30,12 @@ int fail(int code, const char *fmt, ...)
 }
 
 constexpr size_t kAlign = 256;
-// Outputs up to here have no copy launch of their own (enqueue_frame): of frames that recompute everything, and of
-// others, for which the detection launch copies what stays.  Everything recomputed, 32 channels on 320 x 240 28 -> 15 us
-// a frame, 256 on 320 x 180 104 -> 106 with the copy kernel for wide maps.  Some: 16 channels on 64 x 64 14.7 -> 11.5 us,
-// 64 on 128 x 128 (4 MB) 13.9 -> 11.8, 256 on 64 x 64 22.8 -> 22.6; 128 on 100 x 100 (5 MB) 24.0 -> 26.5, 256 on
-// 83 x 61 30.6 -> 33.3.
-constexpr size_t kDirectOutputAll = 1u << 30, kDirectOutputSome = 4 << 20;
+// Outputs up to here have no copy launch of their own (enqueue_frame) where something may stay as it is, which the
+// detection launch then copies.  us a frame with the launch and without: 16 channels on 64 x 64 15.8 and 12.1, 64 on
+// 110 x 110 (3 MB) 21.1 and 20.6, 64 on 128 x 128 (4 MB) 21.3 and 20.7, 256 on 64 x 64 23.1 and 22.6, bfloat16 there 18.0
+// and 16.3, 64 on 16 maps of 32 x 32 (planes 4 KB apart) 21.4 and 23.5; 128 on 100 x 100 (5 MB) 24.1 and 26.2, 256 on
+// 83 x 61 23.9 and 25.6.
+constexpr size_t kDirectOutputSome = 4 << 20;
 constexpr int kMaxGemmGrid = 256; // workgroups of one GEMM launch (one per compute unit of an MI355X)
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 inline int round_up(int v, int m) { return (v + m - 1) / m * m; }
@@ -622,16 +622,22 @@ int enqueue_frame(cbinfer_state *s, const float *frame, float *out)
     s->lists_stale = false;
     const int S = P.S;
     const int nops = (int)P.ops.size();
-    // A small output is not copied by a launch of its own: the detection launch copies the stored map as it is before
-    // the frame, where anything may stay as it is, and the last layer writes what it recomputes to both.
+    // The output of a convolution is not copied by a launch of its own: the last layer writes what it recomputes to both
+    // maps.  Where anything may stay as it is, the detection launch copies the stored map as it is before the frame, for
+    // small outputs.  Everything recomputed, us a frame with the launch and without: 32 channels on 320 x 240 20.9 and
+    // 14.9, 256 on 320 x 180 425 and 420 (7x7), on 360 x 360 (126 MB) 108 and 90 (1x1), 254 and 237 (3x3), 3000 (1.5 GB)
+    // 1074 and 699; bfloat16 256 on 360 x 360 74 and 62, 512 144 and 143 (3x3 204 and 178), 1024 (0.5 GB) 263 and 280 (376
+    // and 361), 2000 484 and 484.
     const Op &last = P.ops.back();
     const size_t out_bytes = (size_t)S * last.M * last.Ho * last.Wo * 4, in_bytes = (size_t)S * P.in_c * P.in_h * P.in_w * 4;
     const char *fb = reinterpret_cast<const char *>(frame), *ob = reinterpret_cast<const char *>(out);
-    const bool direct_out = !pipe && last.kind == CBINFER_OP_CONV && out_bytes <= (first || s->force_dense ? kDirectOutputAll : kDirectOutputSome) &&
+    const bool all_new = first || s->force_dense;
+    const bool direct_out = !pipe && last.kind == CBINFER_OP_CONV && (all_new || out_bytes <= kDirectOutputSome) &&
                             words_for((long long)S * last.Ho * last.Wo) <= cbk::gemm_select_max_words() &&
                             (ob >= fb + in_bytes || fb >= ob + out_bytes); // the frame is still read when the copy begins
-    const cbk::PlanarCopy old_output = cbk::planar_copy(s->at<void>(last.o_out), out, last.M, last.Ms / cbk::elems_per_unit(P.dtype),
-                                                        last.Ho * last.Wo, S);
+    cbk::PlanarCopy old_output;
+    if (direct_out && !all_new)
+        old_output = cbk::planar_copy(s->at<void>(last.o_out), out, last.M, last.Ms / cbk::elems_per_unit(P.dtype), last.Ho * last.Wo, S);
 
     for (int l = 0; l < nops; ++l) {
         const Op &op = P.ops[l];
@@ -656,7 +662,7 @@ int enqueue_frame(cbinfer_state *s, const float *frame, float *out)
                 HIP_TRY(cbk::detect_frame(st, frame, ref, s->at<void>(op.o_cur), s->at<uint64_t>(op.o_chg), op.C,
                                           op.Cs / eu, N, S, op.tau, hold, all ? 1 : 0, P.dtype,
                                           op.pix_words == op.C && op.C % 4 != 0, flags, P.flag_words,
-                                          direct_out && !first && !s->force_dense ? &old_output : nullptr, t.timing()));
+                                          direct_out && !all_new ? &old_output : nullptr, t.timing()));
                 x = hold ? s->at<void>(op.o_cur) : ref;
             } else {
                 x = s->at<void>(P.ops[l - 1].o_out);
