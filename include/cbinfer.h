@@ -201,12 +201,17 @@ int cbinfer_read_map(cbinfer_state *s, int layer, int which, float *host, size_t
 /* ---- per-step timing -------------------------------------------------------------------- */
 
 enum {
-    CBINFER_STEP_DETECT = 0,  /* change detection + update of the stored previous input */
+    CBINFER_STEP_DETECT = 0,  /* change detection + update of the stored previous input (layer 0: and, where
+                                 OUTPUT has no launch, the copy of what stays as it is) */
     CBINFER_STEP_DILATE = 1,  /* change map -> map of outputs to update (and of pooled outputs) */
     CBINFER_STEP_COMPACT = 2, /* maps -> ascending index lists and counts */
-    CBINFER_STEP_GEMM = 3,    /* gathered matrix generation + multiplication + output update */
+    CBINFER_STEP_GEMM = 3,    /* gathered matrix generation + multiplication + output update (layer = last:
+                                 and, where OUTPUT has no launch, of the caller's buffer) */
     CBINFER_STEP_POOL = 4,    /* max-pooling at the listed pooled positions */
-    CBINFER_STEP_OUTPUT = 5,  /* copy of the last stored map to the caller's buffer (layer = last) */
+    CBINFER_STEP_OUTPUT = 5,  /* copy of the last stored map to the caller's buffer (layer = last).  No launch, and
+                                 its time in the two steps named above: outputs of a convolution on at most 131072
+                                 positions of all streams, in frames that recompute everything or of up to 4 MiB, one
+                                 frame at a time, unless frame and output overlap */
     CBINFER_STEP_COUNT = 6
 };
 

@@ -1817,7 +1817,11 @@ static int taps_mode(const GemmArgs &a)
     return a.H <= 16000 && a.W <= 16000 ? kTapPerLane : kTapGeneral;
 }
 
-// Words of a row in the ranking where rows begin with words of their own (GemmArgs::sel_ranked, dSelRow), else 0.
+// Words of a row in the ranking where rows begin with words of their own (GemmArgs::sel_ranked, dSelRow), else 0.  Words
+// that run across rows are put together from a piece per row, one after the other, which takes longer than the more words
+// of short rows do, as long as LDS holds them: 64->64 3x3 on 64 maps of 10 x 10 (100 words or 640) 17.8 and 14.5 us, 7x7
+// 23.9 and 21.0, 3->16 3x3 on 400 of 5 x 5 (157 or 2000) 15.9 and 9.6, 64->64 7x7 on 600 of 3 x 3 37.6 and 26.5, on 2000 x 5
+// 23.9 and 17.4, on 1000 x 65 16.9 and 16.4, on 83 x 61 15.8 and 14.6.
 static int sel_row_words(const GemmArgs &a)
 {
     if (a.sel_words <= 0 || !a.sel_dilate || a.Wo < 1) return 0;
