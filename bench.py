@@ -152,9 +152,26 @@ def matrix_peak(L, bf16):
     return MI355X_FP32_TFLOPS if short else MI355X_FP32_PARTS_TFLOPS
 
 
-def kernel_entries(cfg, net, prof, sums, P, in_shape, propagate=False):
+def write_share(prev, cur, bf16):
+    """Share of the stored frame that the detection pass on frame `cur` behind `prev` ([S][C][H][W]) writes: a piece of
+    256 consecutive pixels is left as it is if it holds the same bits already.  Frames whose pixels are several 16-byte
+    units of the stored map are written whole."""
+    import torch
+    S, C, H, W = cur.shape
+    if C > (8 if bf16 else 4) and (bf16 or C > 7 or S * H * W < 1 << 18):
+        return 1.0
+    bits = (lambda f: f.to(torch.bfloat16).view(torch.int16)) if bf16 else (lambda f: f.view(torch.int32))
+    differs = (bits(prev.contiguous()) != bits(cur.contiguous())).any(1).reshape(-1)
+    pieces = torch.nn.functional.pad(differs, (0, -differs.numel() % 256)).view(-1, 256).any(1)
+    sizes = torch.full(pieces.shape, 256, device=cur.device)
+    sizes[-1] = differs.numel() - 256 * (pieces.numel() - 1)
+    return float((pieces * sizes).sum()) / differs.numel()
+
+
+def kernel_entries(cfg, net, prof, sums, P, in_shape, propagate=False, detect_write=1.0):
     """Per-kernel records (mean microseconds, algorithmic bytes or flops per launch, rates) and
-    the measured change rates per layer."""
+    the measured change rates per layer.  detect_write: share of the stored frame that the first layer's detection
+    writes."""
     import paper_1704_04313_amd as cb
     bf16 = cfg.dtype == "bf16"
     esz = 2.0 if bf16 else 4.0         # bytes per stored map element
@@ -162,6 +179,8 @@ def kernel_entries(cfg, net, prof, sums, P, in_shape, propagate=False):
     S = cfg.n_streams
     shapes = [in_shape] + [net.layer_shape(l) for l in range(n_ops)]
     rates, kernels = {}, {}
+    # without a launch of its own the output's copy is made by the detection launch and the last layer
+    no_copy = (n_ops - 1, "output") not in prof
     for l in range(n_ops):
         L = cfg.layers[l]
         c_in, h_in, w_in = shapes[l]
@@ -181,8 +200,14 @@ def kernel_entries(cfg, net, prof, sums, P, in_shape, propagate=False):
             e = {"us": 1e3 * ms}
             by = None
             if name == "detect":
-                # frame read (float32) + stored previous input read and written + change bitmap
-                by = S * ((4.0 + 2.0 * esz) * c_in * h_in * w_in + h_in * w_in / 8.0)
+                # frame read (float32) + stored previous input read, and written as far as it is + change bitmap
+                share = detect_write if l == 0 else 1.0
+                by = S * ((4.0 + (1.0 + share) * esz) * c_in * h_in * w_in + h_in * w_in / 8.0)
+                if l == 0:
+                    e["write_share"] = share
+                    if no_copy:  # the last map as it was before the frame, to the caller's buffer
+                        c_last, h_last, w_last = shapes[-1]
+                        by += S * (esz + 4.0) * c_last * h_last * w_last
             elif name == "gemm":
                 fl = 2.0 * L.cout * L.cin * L.kh * L.kw * n_u
                 peak = matrix_peak(L, bf16)
@@ -193,6 +218,8 @@ def kernel_entries(cfg, net, prof, sums, P, in_shape, propagate=False):
                 by = esz * L.cout * L.cin * L.kh * L.kw + \
                     esz * c_in * min(n_u * L.kh * L.kw, float(S * h_in * w_in)) + \
                     (4.0 + (2.0 if compares else 1.0) * esz * c_out) * n_u
+                if no_copy and l == n_ops - 1:
+                    by += 4.0 * c_out * n_u
             elif name == "dilate":
                 # change map read (one bit per pixel; one byte behind the first layer), update and pooled bitmaps written
                 chg = S * h_in * w_in * (1.0 if l > 0 else 0.125)
@@ -279,6 +306,16 @@ def measure(cfg, args, *, steps, warmup, blocks, profile=True, one_at_a_time=Fal
             net.process_frame(frames_dev[t], out)
             for l in range(n_ops):
                 sums[l] += np.maximum(np.array(net.layer_counts(l), dtype=np.float64), 0)
+        # what the detection passes of these frames write; with held references the present frame, which they keep
+        # beside them, whole (and the references, where flagged, which is not counted)
+        order = list(frame_order(cfg.n_frames, P + 1, max(warmup - 1, 0)))
+        as_streams = lambda t: frames_dev[t].view((cfg.n_streams,) + in_shape)
+        known = {}
+        for p, t in zip(order, order[1:]):
+            key = (min(p, t), max(p, t))
+            if not args.hold and key not in known:
+                known[key] = write_share(as_streams(p), as_streams(t), bf16)
+        detect_write = 1.0 if args.hold else float(np.mean([known[min(p, t), max(p, t)] for p, t in zip(order, order[1:])]))
         prof = {}
         for l in range(n_ops):
             for s, name in enumerate(cb.STEP_NAMES):
@@ -286,7 +323,8 @@ def measure(cfg, args, *, steps, warmup, blocks, profile=True, one_at_a_time=Fal
                 if n:
                     prof[(l, name)] = (ms / n, n)
         net.set_profiling(False)
-        res["kernels"], res["change_rates"] = kernel_entries(cfg, net, prof, sums, P, in_shape, propagate=args.propagate)
+        res["kernels"], res["change_rates"] = kernel_entries(cfg, net, prof, sums, P, in_shape, propagate=args.propagate,
+                                                             detect_write=detect_write)
     net.destroy()
     del frames_dev, out
     torch.cuda.empty_cache()
@@ -475,11 +513,14 @@ def run(args) -> dict:
         pick = {k: v for k, v in h["kernels"].items() if "frac_hbm" in v}
         result["hbm"] = {"workload": hcfg.name, "sigma": hcfg.sigma, "tau": hcfg.tau,
                          "peak_GBps": MI355X_HBM_GBS, "change_rates": h["change_rates"],
-                         "kernels": {k: {"us": v["us"], "bytes": v["bytes"], "GBps": v["GBps"], "frac_hbm": v["frac_hbm"]}
+                         "kernels": {k: {"us": v["us"], "bytes": v["bytes"], "GBps": v["GBps"], "frac_hbm": v["frac_hbm"],
+                                         **({"write_share": v["write_share"]} if "write_share" in v else {})}
                                      for k, v in pick.items()},
                          "plain_torch_kernels": plain_memory_rates(),
                          "note": "algorithmic bytes per launch / mean kernel time (events attached to the launch); "
                                  "there is no stand-alone scatter kernel: the output update is the GEMM's epilogue; "
+                                 "write_share: part of the stored frame that detection writes, as it leaves 256 pixels alone "
+                                 "that hold the same bits already; only that part is counted; "
                                  "plain_torch_kernels: a 1 GiB device copy (read + written) and fill (written) of "
                                  "torch on the same box, for scale"}
         print("hbm leg done", file=sys.stderr, flush=True)
