@@ -16,9 +16,19 @@ pytestmark = pytest.mark.gpu
     (6, 513, 517, True), (7, 611, 513, False),  # whole bytes per pixel, through LDS
     (3, 61, 83, False), (4, 600, 511, False), (4, 61, 83, True)])  # 16-byte units
 def test_lists_over_small_steps(c, h, w, hold):
+    _compare(c, h, w, hold, cb.F32)
+
+
+# pieces of 256 pixels in bfloat16: a few and many, the last one short; the steps are exact in bfloat16
+@pytest.mark.parametrize("c,h,w,hold", [(1, 17, 15, False), (3, 61, 83, True), (3, 515, 513, False), (8, 300, 257, False), (8, 61, 83, True)])
+def test_lists_over_small_steps_bfloat16(c, h, w, hold):
+    _compare(c, h, w, hold, cb.BF16)
+
+
+def _compare(c, h, w, hold, dtype):
     tau = 0.5
     net = cb.CBInfer([conv(c, 1, 1, relu=False)], [(np.ones((1, c, 1, 1), np.float32), np.zeros(1, np.float32))], (c, h, w), tau,
-                     hold_reference=hold)
+                     hold_reference=hold, dtype=dtype)
     r = np.random.default_rng(c + h)
     f = np.zeros((c, h * w), np.float32)
     ref = f.copy()
