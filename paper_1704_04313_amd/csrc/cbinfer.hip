@@ -53,7 +53,9 @@ struct Op {
     int K = 0, Kpad = 0, Mpad = 0;
     int gemm_grid = 0;
     unsigned tiny_sum = 0;     // CONV: GemmArgs::tiny_sum, ...
-    int filter_exp = 0;        // ... and filter_exp
+    int filter_exp = 0;        // ... filter_exp
+    int halves_exp = 0;        // ... and halves_exp
+    bool halves = false;       // CONV: the weights are multiplied in halves where sums are long (o_halves exists)
     bool select = false; // CONV: maps small enough for the GEMM (and the pooling after it) to pick their
                          // positions from the update maps themselves; index lists are then only
                          // extracted when the caller asks for them
@@ -62,7 +64,7 @@ struct Op {
     // workspace offsets (bytes); SIZE_MAX = absent
     size_t o_ref = SIZE_MAX, o_cur = SIZE_MAX, o_out = SIZE_MAX, o_wt = SIZE_MAX, o_bias = SIZE_MAX,
            o_taps = SIZE_MAX, o_chg = SIZE_MAX, o_upd = SIZE_MAX, o_pool = SIZE_MAX, o_clist = SIZE_MAX,
-           o_ulist = SIZE_MAX, o_counts = SIZE_MAX, o_groups = SIZE_MAX;
+           o_ulist = SIZE_MAX, o_counts = SIZE_MAX, o_groups = SIZE_MAX, o_halves = SIZE_MAX;
 };
 
 struct Plan {
@@ -100,9 +102,9 @@ cbk::GemmArgs gemm_shape(const Op &op, int streams, int dtype)
     return a;
 }
 
-// Validates the description and lays out the workspace for launches of at most max_grid workgroups.
-// Touches no device.
-int make_plan(const cbinfer_network *net, float threshold, bool need_threshold, Plan &P, int max_grid = kMaxGemmGrid)
+// Validates the description and lays out the workspace for launches of at most max_grid workgroups, with or
+// without room for filter matrices in halves.  Touches no device.
+int make_plan(const cbinfer_network *net, float threshold, bool need_threshold, Plan &P, int max_grid = kMaxGemmGrid, bool halves = true)
 {
     P.compute_units = max_grid;
     if (!net) return fail(CBINFER_EINVAL, "network description is NULL");
@@ -215,6 +217,8 @@ int make_plan(const cbinfer_network *net, float threshold, bool need_threshold, 
             if (l == 0 || ((P.hold || op.dense) && !op.propagate)) op.o_ref = cv.take(in_px * op.pix_words * 4 + 16);
             if (l == 0 && P.hold) op.o_cur = cv.take(in_px * op.pix_words * 4 + 16);
             op.o_wt = cv.take(cbk::gemm_filter_bytes(P.dtype, op.Mpad, op.Kpad));
+            if (halves && cbk::gemm_filter_halves(gemm_shape(op, P.S, P.dtype), max_grid))
+                op.o_halves = cv.take(cbk::gemm_halves_bytes(op.Mpad, op.Kpad));
             op.o_bias = cv.take((size_t)op.Mpad * 4);
             op.o_taps = cv.take((size_t)op.Kpad / eu * sizeof(int2));
         }
@@ -419,9 +423,28 @@ int filter_exponent(float largest, bool tiny)
     return e;
 }
 
+// Whether the halves of a row of n weights carry them: they end at 2^-40 of the layer's largest, so of eight in a row (of
+// consecutive channels) the largest must be at least `least`, 2^-24 of that, or all of them zero.  (Sums to which only
+// smaller weights add would lose bits; of a million normally distributed weights the least is 2^-22 of the largest, but not
+// eight in a row.)
+constexpr int kHalvesTop = 14; // the exponent of the largest weight in halves
+bool row_suits_halves(const float *x, int n, float least)
+{
+    int bound, bad = 0; // bits of magnitudes compare like integers
+    memcpy(&bound, &least, 4);
+    for (int i = 0; i < n; i += 8) { // rows are whole slices of 32
+        int m = 0, u[8];
+        memcpy(u, x + i, 32);
+        for (int e = 0; e < 8; ++e) m = std::max(m, u[e] & 0x7fffffff);
+        bad |= m - 1 < bound - 1 && m > 0;
+    }
+    return !bad;
+}
+
 // Filter matrix K (Section 3) re-laid-out for the gather: row o, column k = (j*kw + i)*Cs + c, as
-// float32 or bfloat16 (round to nearest even), row by row or in fragments.
-void build_filter_matrix(const Op &op, int dtype, const float *w, std::vector<unsigned char> &bytes)
+// float32 or bfloat16 (round to nearest even), row by row or in fragments.  Returns whether its rows suit halves (largest:
+// of the weights).
+bool build_filter_matrix(const Op &op, int dtype, const float *w, std::vector<unsigned char> &bytes, float largest)
 {
     bytes.assign(cbk::gemm_filter_bytes(dtype, op.Mpad, op.Kpad), 0);
     const bool fragments = cbk::gemm_filter_in_fragments(dtype, op.Mpad, op.Kpad);
@@ -434,6 +457,8 @@ void build_filter_matrix(const Op &op, int dtype, const float *w, std::vector<un
     const float scale = std::ldexp(1.0f, op.filter_exp);
     for (size_t v = 0; v < place.size(); ++v)
         place[v] = cbk::gemm_filter_fragment(dtype, op.Mpad, op.Kpad, 0, (int)v * eu);
+    bool suits = op.o_halves != SIZE_MAX && largest > 0.0f;
+    const float least = (float)std::ldexp((double)largest, op.filter_exp - 24);
     for (int o = 0; o < op.M; ++o) {
         for (int c = 0; c < op.C; ++c)
             for (int t = 0; t < area; ++t) row[(size_t)t * op.Cs + c] = w[((size_t)o * op.C + c) * area + t] * scale;
@@ -441,6 +466,7 @@ void build_filter_matrix(const Op &op, int dtype, const float *w, std::vector<un
             memcpy(f + (size_t)o * op.Kpad, row.data(), (size_t)op.Kpad * 4);
             continue;
         }
+        suits = suits && row_suits_halves(row.data(), op.Kpad, least);
         bf16_parts(row.data(), op.Kpad, fragments ? parts : 1, part.data(), part.data() + op.Kpad, part.data() + 2 * (size_t)op.Kpad);
         if (!fragments) {
             memcpy(b + (size_t)o * op.Kpad, part.data(), (size_t)op.Kpad * 2);
@@ -456,6 +482,7 @@ void build_filter_matrix(const Op &op, int dtype, const float *w, std::vector<un
                     memcpy(dst + place[v] + q * cbk::kFilterPartStride, src, 16);
             }
     }
+    return suits;
 }
 
 // One entry per 16-byte unit of a filter-matrix row: where its tap sits relative to the window origin.
@@ -719,6 +746,8 @@ int enqueue_frame(cbinfer_state *s, const float *frame, float *out)
             a.max_pixels = S * No;
             a.tiny_sum = op.tiny_sum;
             a.filter_exp = op.filter_exp;
+            a.wt_halves = op.halves ? s->at<void>(op.o_halves) : nullptr;
+            a.halves_exp = op.halves_exp;
             a.partial = s->at<float>(P.o_partial);
             a.tickets = s->at<int>(P.o_tickets);
             a.grid = op.gemm_grid;
@@ -858,19 +887,25 @@ static cbinfer_state *create_state(const cbinfer_network *net, const Plan &P, ch
             Op &op = s->plan.ops[l];
             if (op.kind != CBINFER_OP_CONV) continue;
             const cbinfer_layer &L = net->layers[l];
+            float largest = 0.0f;
             if (P.dtype == cbk::kF32 && cbk::gemm_filter_in_fragments(P.dtype, op.Mpad, op.Kpad)) {
                 bool tiny = false;
                 const float m = largest_weight(static_cast<const float *>(L.weight), (size_t)op.M * op.C * op.kh * op.kw, tiny);
                 op.tiny_sum = cbk::gemm_tiny_sum(op.K, m);
                 op.filter_exp = filter_exponent(m, tiny);
+                if (m > 0.0f) op.halves_exp = kHalvesTop - std::ilogb(m);
+                largest = m;
             }
-            build_filter_matrix(op, P.dtype, static_cast<const float *>(L.weight), wt);
+            op.halves = build_filter_matrix(op, P.dtype, static_cast<const float *>(L.weight), wt, largest);
             bias.assign(op.Mpad, 0.0f);
             if (L.bias)
                 for (int o = 0; o < op.M; ++o) bias[o] = L.bias[o];
             build_taps(op, P.dtype, taps);
             // the staging vectors are reused for the next layer: wait for the copies first
             HIP_TRY(hipMemcpyAsync(s->at<void>(op.o_wt), wt.data(), wt.size(), hipMemcpyHostToDevice, s->stream));
+            if (op.halves)
+                HIP_TRY(cbk::gemm_make_halves(s->stream, s->at<void>(op.o_wt), s->at<void>(op.o_halves), op.Mpad, op.Kpad,
+                                              op.halves_exp - op.filter_exp));
             HIP_TRY(hipMemcpyAsync(s->at<float>(op.o_bias), bias.data(), bias.size() * 4, hipMemcpyHostToDevice, s->stream));
             HIP_TRY(hipMemcpyAsync(s->at<int2>(op.o_taps), taps.data(), taps.size() * sizeof(int2), hipMemcpyHostToDevice, s->stream));
             HIP_TRY(hipStreamSynchronize(s->stream));
@@ -901,6 +936,9 @@ cbinfer_state *cbinfer_create(const cbinfer_network *net, float threshold)
             fail(CBINFER_EINVAL, "workspace must be %zu-byte aligned", kAlign);
             return nullptr;
         }
+        Plan Q; // one of fewer bytes than asked for may do without halves
+        if (net->workspace_bytes < P.bytes && make_plan(net, threshold, true, Q, kMaxGemmGrid, false) == CBINFER_OK && Q.bytes <= net->workspace_bytes)
+            P = Q;
         if (net->workspace_bytes < P.bytes) {
             fail(CBINFER_ENOMEM, "workspace has %zu bytes, %zu needed", net->workspace_bytes, P.bytes);
             return nullptr;
@@ -927,11 +965,11 @@ cbinfer_state *cbinfer_create_static(const cbinfer_network *net, float threshold
 {
     Plan P;
     if (make_plan(net, threshold, true, P) != CBINFER_OK) return nullptr;
-    // Partial sums take up to 128 KiB per workgroup, half of what fits: a network of large filter matrices runs
-    // with fewer workgroups rather than not at all.
-    for (int grid = kMaxGemmGrid / 2; P.bytes > (size_t)CBINFER_STATIC_WORKSPACE_BYTES && grid >= kMaxGemmGrid / 4; grid /= 2) {
+    // Partial sums take up to 128 KiB per workgroup, half of what fits: a network of large filter matrices runs without
+    // halves, then with fewer workgroups rather than not at all.
+    for (int grid = kMaxGemmGrid; P.bytes > (size_t)CBINFER_STATIC_WORKSPACE_BYTES && grid >= kMaxGemmGrid / 4; grid /= 2) {
         Plan Q;
-        if (make_plan(net, threshold, true, Q, grid) == CBINFER_OK && Q.bytes <= (size_t)CBINFER_STATIC_WORKSPACE_BYTES) P = Q;
+        if (make_plan(net, threshold, true, Q, grid, false) == CBINFER_OK && Q.bytes <= (size_t)CBINFER_STATIC_WORKSPACE_BYTES) P = Q;
     }
     if (P.bytes > (size_t)CBINFER_STATIC_WORKSPACE_BYTES) {
         fail(CBINFER_ENOMEM,

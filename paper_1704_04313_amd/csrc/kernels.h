@@ -255,6 +255,8 @@ struct GemmArgs {
     // themselves (gemm_tiny_sum).  0: none.
     unsigned tiny_sum;
     int filter_exp;     // float32 in parts: the filter matrix holds the weights times 2^filter_exp
+    const void *wt_halves; // null, or (only where gemm_filter_halves()) the filter matrix in float16 halves as well
+    int halves_exp;        // ... of the weights times 2^halves_exp
     float *partial;     // scratch for partial accumulators, gemm_partial_bytes() bytes
     int *tickets;       // gemm_ticket_bytes(grid) bytes, zero before the first launch (each launch
                         // leaves them zero again)
@@ -283,6 +285,12 @@ bool gemm_filter_in_fragments(int dtype, int Mpad, int Kpad);
 size_t gemm_filter_bytes(int dtype, int Mpad, int Kpad);
 size_t gemm_filter_fragment(int dtype, int Mpad, int Kpad, int row, int k);
 constexpr int kFilterPartStride = 512;
+// float32 layers of more than 64 channels and long rows, on maps large enough: the same fragments of two float16 each that
+// add up to the weight times 2^halves_exp to 23 bits.  Needs dtype, Mpad, Kpad and max_pixels; grid: workgroups at most.
+bool gemm_filter_halves(const GemmArgs &a, int grid);
+size_t gemm_halves_bytes(int Mpad, int Kpad);
+// ... from the bfloat16 parts of the weights times 2^(halves_exp - shift).
+hipError_t gemm_make_halves(hipStream_t st, const void *wt, void *wt_halves, int Mpad, int Kpad, int shift);
 // GemmArgs::tiny_sum for rows of K weights of at most that magnitude.  The parts of a pixel value are off by half the
 // smallest bfloat16 at most, 2^-134, and a sum by 2^-134 K times the largest weight: below 2^24 times that
 // it is less exact than float32, so it is formed again.  (A sum that is exactly zero is taken as it is:

@@ -39,6 +39,13 @@
 // once, when the state is created, and lies in memory in the order in which it is read; pixels are split in
 // registers (3.5 instructions per value) in the shadow of the MFMAs.
 //
+// Layers of more than 64 channels whose workgroups sum up long ranges of K (halves_suit) take float16 halves and three
+// products instead, half the matrix time and two thirds of the filter bytes: 64->256 7x7 on 320x180 382 -> 267 us (347
+// TFLOP/s), on 80x60 50.6 -> 38.7, 256->256 3x3 on 160x120 118 -> 87, 512->512 3x3 on 80x60 114 -> 80, two frames of 64 streams of
+// the benchmark network 6.45 -> 5.25 ms, with smaller errors than the parts' there (figures at kHalfRange).  The MFMAs are 45 %
+// of that time now; the rest is vector instructions (split, largest value, sums folded) and fragment reads that do not
+// overlap with them, about 8 % the loads.  Up to 64 channels gain 3 to 5 % only and stay with the parts.
+//
 // Work distribution: one workgroup per compute unit.  Output tiles are dealt out whole as long
 // as every workgroup gets one; the (tiles mod workgroups) left over are cut along K into
 // equal iteration ranges, one per workgroup, so that all compute units finish together whatever
@@ -105,14 +112,36 @@ __host__ __device__ inline int small_tile_factor(int dtype, int bm, int nk)
     return dtype == kF32 && bm == 128 && nk >= 48 ? 4 : 2;
 }
 
+// Whether a launch of that many big tiles (128 channels, 128 pixels) of nk slices multiplies in halves: where the ranges
+// of K that workgroups sum up are kHalfRange slices long on average.  Halves leave off the last of float32's 24 bits in a
+// quarter of the values and the product of both second halves, 7.0e-8 of a sum whatever its length; the bfloat16 parts are
+// exact but are rounded at the magnitude of the whole sum in every slice, 3.4e-8 sqrt(slices / 2).  Error against 64 bits
+// (2-norm, halves / parts): 64->256 7x7 (98 slices) whole 1.43e-7 / 2.62e-7, in three ranges 1.29e-7 / 1.47e-7, in twelve
+// 1.30e-7 / 0.95e-7; 128->128 3x3 (36) whole 1.23e-7 / 1.46e-7; 75 slices in nine ranges 1.22e-7 / 1.10e-7.  So the line
+// is where the errors meet; short ranges are latency, not multiplication (the last two 19.1 / 20.4 and 22.4 / 25.0 us).
+static constexpr int kHalfRange = 24;
+__host__ __device__ inline bool halves_suit(long long tiles, int nk, int grid)
+{
+    if (tiles >= grid) return nk >= kHalfRange; // whole tiles, and a round in which some are cut
+    // where the big tile is used at all: gemm_partial_bytes has no room for its partial sums elsewhere
+    if (tiles < 1 || tiles * small_tile_factor(kF32, 128, nk) < grid) return false;
+    // as make_schedule cuts them: into equal parts, or evenly over all workgroups, which then cross from tile to tile
+    const int parts = grid / (int)tiles;
+    const long long ranges = tiles * parts * 8 >= (long long)grid * 7 ? tiles * parts : grid + tiles;
+    return tiles * nk >= kHalfRange * ranges;
+}
+
 static constexpr int kSelMaxWords = 2048; // largest selection map ranked in-kernel (131072 pixels)
 static constexpr int kSelWordsPerThread = (kSelMaxWords + NT - 1) / NT;
 static constexpr int kSelSlots = kSelMaxWords + kSelWordsPerThread; // LDS words per ranking array
 
 // 16-byte-per-lane fragments that one slice of 16 filter rows consists of: bfloat16 storage two (the two
-// halves of a slice's 64 k), float32 three (the bfloat16 parts of 32 k, see split_fragment).
+// halves of a slice's 64 k), float32 three (the bfloat16 parts of 32 k, see split_fragment) or, in halves, two.
+static constexpr int kF32Halves = 2; // besides kF32 and kBF16: float32 storage, multiplied in halves (split_halves)
 template <int DT>
-static constexpr int kFilterParts = DT == kBF16 ? 2 : 3;
+static constexpr int kFilterParts = DT == kF32 ? 3 : 2;
+template <int DT>
+static constexpr int kStorage = DT == kBF16 ? kBF16 : kF32;
 static constexpr int kFragBytes = 1024; // one fragment: 64 lanes x 16 bytes
 
 // LDS of one tile shape: a ring of STAGES K slices of both operands, then pixel lists.
@@ -123,7 +152,7 @@ struct TileSmem {
     // Pixel lists: of the segment the consumers finish and of those that the slices after it belong to.
     // A segment has a slice at least; of the 64-channel tiles in float32 (rows of five slices or more, the
     // shorter ones are the thin kernel's) at most two can be that short in a row, and LDS has no room for more.
-    static constexpr int lists = DT == kF32 && BM == 64 && BN == 256 ? 3 : STAGES + 1;
+    static constexpr int lists = DT != kBF16 && BM == 64 && BN == 256 ? 3 : STAGES + 1;
     // with a list go the biases of its tile's channels
     static constexpr int list_words = BN + BM;
     static constexpr int tile_bytes = STAGES * (a_floats + b_floats) * 4 + lists * list_words * 4;
@@ -657,7 +686,7 @@ __device__ __forceinline__ void direct_producer(const GemmArgs &a, const int n, 
         walk.next(a, seg);
         kc = seg.kc0;
         const int pt = small_div(seg.tile, mtiles), mt = seg.tile - pt * mtiles;
-        wtile = static_cast<const char *>(a.wt) + (size_t)mt * walk.nk * (FB * kFragBytes);
+        wtile = static_cast<const char *>(DT == kF32Halves ? a.wt_halves : a.wt) + (size_t)mt * walk.nk * (FB * kFragBytes);
         // a lane per row of this wave: eight in each pass (one search of the ranks instead of one per pass)
         static_assert(PA <= 8, "the wave's rows fit its lanes");
         int *rows = sU + list * TileSmem<DT, BM, BN, STAGES>::list_words + pw * 8;
@@ -836,6 +865,56 @@ __device__ __forceinline__ Parts split_fragment(const floatx4 x0, const floatx4 
     return p;
 }
 
+// float32 in halves: a value times a power of two as the sum of two float16 (11 bits each and the sign of the second: all
+// but one of float32's 24), for the three products hi hi, hi lo and lo hi -- half of what the bfloat16 parts take.  An
+// instruction per value for each half: v_fma_mix multiplies, subtracts and rounds at once.  (As a multiplication, two
+// conversions and a difference, 3 a value, 64->256 7x7 at 320x180 took 302 us, now 267: vector instructions add to the
+// MFMAs of a SIMD, see below.)  The compiler does not know what the asm writes to; whoever multiplies the halves at once
+// waits two cycles first.
+// Below 2^-2 of the scaled value the second half ends at the smallest float16, 2^-24: precision is relative to the
+// largest value of a scale, down to 2^-40 of it.
+typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
+struct Halves {
+    uintx4 hi, lo;
+};
+__device__ __forceinline__ Halves split_halves(const floatx4 x0, const floatx4 x1, const float scale)
+{
+    Halves p;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float a = i < 2 ? x0[2 * i] : x1[2 * i - 4], b = i < 2 ? x0[2 * i + 1] : x1[2 * i - 3];
+        unsigned h, l;
+        asm("v_fma_mixlo_f16 %0, %1, %3, 0\n\tv_fma_mixhi_f16 %0, %2, %3, 0" : "=&v"(h) : "v"(a), "v"(b), "s"(scale));
+        asm("v_fma_mixlo_f16 %0, %1, %3, -%4 op_sel_hi:[0,0,1]\n\tv_fma_mixhi_f16 %0, %2, %3, -%4 op_sel:[0,0,1] op_sel_hi:[0,0,1]"
+            : "=&v"(l)
+            : "v"(a), "v"(b), "s"(scale), "v"(h));
+        p.hi[i] = h;
+        p.lo[i] = l;
+    }
+    return p;
+}
+// The largest magnitude of m and eight values (a NaN counts as nothing).
+__device__ __forceinline__ float largest(float m, const floatx4 x0, const floatx4 x1)
+{
+    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(x0[0]), "v"(x0[1]));
+    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(x0[2]), "v"(x0[3]));
+    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(x1[0]), "v"(x1[1]));
+    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(x1[2]), "v"(x1[3]));
+    return m;
+}
+// The largest of the 64 lanes' numbers (bits of magnitudes compare like integers), moved as in wave_inclusive_sum.
+__device__ __forceinline__ unsigned wave_largest(unsigned x)
+{
+    auto with = [](unsigned x, unsigned y) { return x > y ? x : y; };
+    x = with(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false));
+    x = with(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false));
+    x = with(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false));
+    x = with(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false));
+    x = with(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false));
+    x = with(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false));
+    return (unsigned)__builtin_amdgcn_readlane((int)x, 63);
+}
+
 // Where value (row, k) of a filter matrix in fragments lies, in bfloat16 values from its start; float32:
 // its first part.
 template <int DT>
@@ -848,6 +927,11 @@ __host__ __device__ inline size_t filter_fragment(int bm, int nk, int row, int k
     const int part = DT == kF32 ? 0 : kk / 32;
     return ((((size_t)mt * nk + kc) * (bm / 16) + ct) * kFilterParts<DT> + part) * (kFragBytes / 2) + (lk * 16 + row % 16) * 8 + e;
 }
+
+// float32 in halves: the exponent that a scale gives the largest value; slices until leading sums are folded; how far a
+// later slice's values may be above the first ones'; how small a pixel's largest scaled value may be.
+static constexpr int kHalfTop = 13, kHalfChunk = 4, kHalfJump = 16;
+static constexpr float kHalfMost = 0.5f;
 
 // Parts of a shared tile's sum that the finishing wave has under way, by its accumulators.
 template <int ACC>
@@ -975,12 +1059,12 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
     float *Bs = smem + STAGES * ASZ;                      // [STAGES][BM/16][FP] filter fragments
     int *sU = reinterpret_cast<int *>(Bs + STAGES * BSZ); // [lists][BN + BM] pixels of a tile (-1: none), biases
 
-    const int lane = threadIdx.x & 63;
+    int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
     const int mtiles = a.Mpad / BM;
     Walk walk;
-    walk.nk = a.Kpad / (Unit<DT>::N * KU); // K slices
+    walk.nk = a.Kpad / (Unit<kStorage<DT>>::N * KU); // K slices
     walk.W = gridDim.x;
     walk.sch = make_schedule(n, BN, mtiles, walk.nk, a.dGrid);
     const Schedule &sch = walk.sch;
@@ -1014,8 +1098,8 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
 
     const int wpx0 = (wave % WN) * (BN / WN);
     const int wch0 = (wave / WN) * (BM / WM);
-    const int lrow = lane & 15; // row of the 16-row operand tiles this lane feeds
-    const int lk = lane >> 4;   // k slot this lane feeds
+    int lrow = lane & 15; // row of the 16-row operand tiles this lane feeds
+    int lk = lane >> 4;   // k slot this lane feeds
     const int nk = walk.nk;
     int slot = 0; // ring slot of the slice in hand
     const int *list = sU;
@@ -1026,6 +1110,7 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
         const int pt = small_div(seg.tile, mtiles), mt = seg.tile - pt * mtiles;
         const bool partial = (kc1 - kc0) != nk;
         floatx4 acc[TC][TP];
+        bool again = false; // float32 in halves: whether the wave's sums have to be formed again
         {
 #pragma unroll
             for (int j = 0; j < TC; ++j)
@@ -1094,6 +1179,165 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                     slot = nslot;
                     consumer_barrier();
                 }
+            } else if constexpr (DT == kF32Halves) {
+                auto mfma_half = [](const uintx4 w, const uintx4 x, const floatx4 c) {
+                    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(halfx8, w), __builtin_bit_cast(halfx8, x), c,
+                                                                  0, 0, 0);
+                };
+                // float32 in halves: three of the four products, hi hi in the leading sums, the others in sums of their own.  The
+                // matrix unit cuts addends off at 2^-24 of the largest (an error of 4.7e-8 of the sum per instruction, measured,
+                // on float16 products of 22 bits; 3.4e-8 on bfloat16's 16), so the leading sums go to others every kHalfChunk
+                // slices and begin again: their roundings are relative to four slices' sum, not to all.
+                floatx4 lead[TC][TP], cor[TC][TP];
+#pragma unroll
+                for (int j = 0; j < TC; ++j)
+#pragma unroll
+                    for (int i = 0; i < TP; ++i) lead[j][i] = cor[j][i] = (floatx4){0.f, 0.f, 0.f, 0.f};
+                Halves x0[TP], x1[TP]; // pixel fragments of two slices in turn
+                uintx4 w[2][2];
+                auto read_tile = [&](int set, int sl, int j) {
+                    w[set][0] = read_filter(sl, j, 0);
+                    w[set][1] = read_filter(sl, j, 1);
+                };
+                // The power of two that the wave's pixels are multiplied with, from the largest value of the first slice: it
+                // becomes 2^13 to 2^14.  A slice with a value beyond `limit` has the sums so far folded and another
+                // power from then on.
+                int shift;
+                float scale, limit, unscale, most[TP];
+                auto set_scale = [&](unsigned bits) {
+                    const int e = (int)(bits >> 23) - 127;
+                    shift = kHalfTop - e < 126 ? kHalfTop - e : 126;
+                    scale = __uint_as_float((unsigned)(127 + shift) << 23);
+                    limit = __builtin_ldexpf(65504.f, -shift);
+                    unscale = __builtin_ldexpf(1.f, -shift); // the weights' power of two is taken off at the end
+                };
+                auto fold = [&](floatx4(&from)[TC][TP]) {
+#pragma unroll
+                    for (int j = 0; j < TC; ++j)
+#pragma unroll
+                        for (int i = 0; i < TP; ++i) {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) acc[j][i][e] = fmaf(from[j][i][e], unscale, acc[j][i][e]);
+                            from[j][i] = (floatx4){0.f, 0.f, 0.f, 0.f};
+                        }
+                };
+                read_tile(0, slot, 0);
+                {
+                    floatx4 raw[TP][2];
+                    unsigned top = 0;
+#pragma unroll
+                    for (int i = 0; i < TP; ++i) {
+                        raw[i][0] = read_pixels(slot, 0, i);
+                        raw[i][1] = read_pixels(slot, 1, i);
+                        most[i] = 0.f;
+                        most[i] = largest(most[i], raw[i][0], raw[i][1]);
+                        top = max(top, __float_as_uint(most[i]));
+                    }
+                    set_scale(wave_largest(top));
+#pragma unroll
+                    for (int i = 0; i < TP; ++i) x0[i] = split_halves(raw[i][0], raw[i][1], scale);
+                    asm volatile("s_nop 3");
+                }
+                auto step = [&](Halves(&x)[TP], Halves(&nx)[TP], const bool more) {
+                    const int nslot = slot == STAGES - 1 ? 0 : slot + 1;
+                    floatx4 raw[TP][2];
+#pragma unroll
+                    for (int j = 0; j < TC; ++j) {
+                        if (j + 1 < TC)
+                            read_tile((j + 1) & 1, slot, j + 1);
+                        else
+                            read_tile((j + 1) & 1, nslot, 0);
+                        // pixel fragment i of the next slice is read a channel tile before it is split
+#pragma unroll
+                        for (int i = 0; i < TP; ++i) {
+                            if (j == (i < TC - 1 ? i : (TC > 1 ? TC - 2 : 0))) {
+                                raw[i][0] = read_pixels(nslot, 0, i);
+                                raw[i][1] = read_pixels(nslot, 1, i);
+                            }
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                        const uintx4 *wj = w[j & 1];
+#pragma unroll
+                        for (int i = 0; i < TP; ++i) cor[j][i] = mfma_half(wj[1], x[i].hi, cor[j][i]);
+#pragma unroll
+                        for (int i = 0; i < TP; ++i) lead[j][i] = mfma_half(wj[0], x[i].hi, lead[j][i]);
+#pragma unroll
+                        for (int i = 0; i < TP; ++i) cor[j][i] = mfma_half(wj[0], x[i].lo, cor[j][i]);
+                        keep(wj[0]);
+                        keep(wj[1]);
+#pragma unroll
+                        for (int i = 0; i < TP; ++i) {
+                            if (j < TC - 1) continue;
+                            keep(x[i].hi);
+                            keep(x[i].lo);
+                        }
+#pragma unroll
+                        for (int i = 0; i < TP; ++i)
+                            if (j == (i + 1 < TC ? i + 1 : TC - 1)) {
+                                if (more) most[i] = largest(most[i], raw[i][0], raw[i][1]); // else the slot holds nothing of this tile
+                                nx[i] = split_halves(raw[i][0], raw[i][1], scale);
+                            }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if constexpr (TC & 1) {
+                        w[0][0] = w[1][0];
+                        w[0][1] = w[1][1];
+                    }
+                    slot = nslot;
+                    consumer_barrier();
+                };
+                int kc = kc0;
+                for (;;) {
+                    bool over = false;
+#pragma unroll
+                    for (int s = 0; s < kHalfChunk; ++s) {
+                        if (s & 1)
+                            step(x1, x0, kc + 1 < kc1);
+                        else
+                            step(x0, x1, kc + 1 < kc1);
+                        float top = most[0];
+#pragma unroll
+                        for (int i = 1; i < TP; ++i) top = fmaxf(top, most[i]);
+                        over = __any(top > limit);
+                        if (++kc == kc1 || over) break;
+                    }
+                    fold(lead);
+                    if (kc == kc1) break;
+                    if (__builtin_expect(over, 0)) { // the next slice needs another power of two
+                        fold(cor);
+                        unsigned top = __float_as_uint(most[0]);
+#pragma unroll
+                        for (int i = 1; i < TP; ++i) top = max(top, __float_as_uint(most[i]));
+                        const int before = shift;
+                        set_scale(wave_largest(top));
+                        again |= before < 126 && before - shift > kHalfJump; // 126: nothing but zeros so far
+#pragma unroll
+                        for (int i = 0; i < TP; ++i) x0[i] = split_halves(read_pixels(slot, 0, i), read_pixels(slot, 1, i), scale);
+                        asm volatile("s_nop 3");
+                    }
+                }
+                fold(cor);
+#pragma unroll
+                for (int j = 0; j < TC; ++j)
+#pragma unroll
+                    for (int i = 0; i < TP; ++i)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[j][i][e] = __builtin_ldexpf(acc[j][i][e], -a.halves_exp);
+                // A pixel's values below kHalfMost all of them, but not zero, lose bits that float32 has: the wave forms its sums
+                // again.  (So does one that met a jump of 2^kHalfJump: zero weights at the large values leave sums of the others.)
+#pragma unroll
+                for (int i = 0; i < TP; ++i) {
+                    float m = most[i]; // a pixel's values are in lanes 16 apart
+                    m = fmaxf(m, __shfl_xor(m, 16));
+                    m = fmaxf(m, __shfl_xor(m, 32));
+                    if (__any(m > 0.f && m * scale < kHalfMost)) again = true;
+                }
+                // found anew rather than kept across the K loop, which needs all registers
+                unsigned thread = threadIdx.x;
+                asm volatile("" : "+v"(thread));
+                lane = (int)thread & 63;
+                lrow = lane & 15;
+                lk = lane >> 4;
             } else {
                 // float32: six of the nine products of parts, everything down to 2^-24 of the leading one.
                 // Leading products and corrections have accumulators of their own: the corrections are
@@ -1180,7 +1424,7 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
             __builtin_amdgcn_s_setprio(0);
         }
 
-        if constexpr (DT == kF32) {
+        if constexpr (DT != kBF16) {
             // Sums that are not finite, and such small ones that parts below the smallest bfloat16 count
             // (GemmArgs::tiny_sum), are formed again from the values themselves, by each wave for its own K
             // range.  (x * 0 is zero for every finite x.)  A tile with such a sum takes two to five times as long:
@@ -1201,11 +1445,13 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                         z = fmaf(acc[j][i][e], 0.f, z);
                         least = min(least, size(acc[j][i][e]));
                     }
-            if (__builtin_expect(__any(z != 0.f || least < a.tiny_sum), 0)) { // NaN compares unequal
+            if (__builtin_expect(__any(z != 0.f || (DT == kF32 ? least < a.tiny_sum : again)), 0)) { // NaN compares unequal
                 const char *wt = static_cast<const char *>(a.wt) +
                                  (((size_t)mt * nk + kc0) * (BM / 16) + wch0 / 16) * (3 * kFragBytes);
                 // two channel tiles at a time: more would not leave their operands registers
                 constexpr int CJ = TC % 2 == 0 ? 2 : 1;
+                float keep_below = again ? -1.f : __builtin_inff(); // in halves: of magnitudes, those that stay
+                asm("" : "+v"(keep_below)); // a condition on `again` would be a branch per sum
                 static_assert(TC % CJ == 0, "whole steps");
 #pragma unroll 1
                 for (int j0 = 0; j0 < TC; j0 += CJ) {
@@ -1220,7 +1466,8 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                             for (int e = 0; e < 4; ++e) {
                                 float v = acc[j][i][e];
                                 asm("" : "+v"(v)); // compared anew: the results from above would all be kept in registers
-                                if (!(fabsf(v) < __builtin_inff()) || size(v) < a.tiny_sum) acc[j][i][e] = sum[j % CJ][i][e];
+                                if (DT == kF32 ? !(fabsf(v) < __builtin_inff()) || size(v) < a.tiny_sum : !(fabsf(v) < keep_below))
+                                    acc[j][i][e] = sum[j % CJ][i][e];
                             }
                     }
                 }
@@ -1435,10 +1682,74 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((NT + 255) /
         n = a.count ? *a.count : a.max_pixels;
     }
     const long long big_tiles = (long long)((n + BNB - 1) / BNB) * (a.Mpad / BM);
-    if (big_tiles * small_tile_factor(DT, BM, a.dNk.d) >= (long long)gridDim.x)
+    if (big_tiles * small_tile_factor(kStorage<DT>, BM, a.dNk.d) >= (long long)gridDim.x)
         gemm_gather_body<DT, BM, BNB, WMB, WNB, SB>(a, n, smem, sel);
     else
         gemm_gather_body<DT, BM, BNS, WMS, WNS, SS>(a, n, smem, sel);
+}
+
+// The halves of a filter matrix from its bfloat16 parts, once per state: a thread eight values of a fragment, which lie
+// alike.  (On the host this took 2 ms for the 0.8 million weights of 64->256 7x7, as long as all the rest of its creation.)
+__global__ void make_halves_kernel(const uintx4 *__restrict__ wt, uintx4 *__restrict__ out, size_t n, int shift)
+{
+    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const size_t fragment = i >> 6, lane = i & 63;
+    uintx4 part[3], hi, lo;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) part[p] = wt[(fragment * 3 + p) * 64 + lane];
+    typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        halfx2 h, l;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            auto value = [&](int p) { return bf16_value((unsigned short)(part[p][q] >> (16 * e))); };
+            const float v = __builtin_ldexpf(value(0) + (value(1) + value(2)), shift);
+            h[e] = (_Float16)v;
+            l[e] = fabsf(v) < __builtin_inff() ? (_Float16)(v - (float)h[e]) : (_Float16)0.f;
+        }
+        hi[q] = __builtin_bit_cast(unsigned, h);
+        lo[q] = __builtin_bit_cast(unsigned, l);
+    }
+    out[fragment * 128 + lane] = hi;
+    out[fragment * 128 + 64 + lane] = lo;
+}
+
+// float32 layers of more than 64 channels that have their filter matrix in halves too: the big tile in halves where sums
+// are long, else the kernel above.
+static constexpr int kHalfStages = 4;
+template <int BNB, int WMB, int WNB, int SB, int BNS, int WMS, int WNS, int SS>
+struct HalvesSmem {
+    static constexpr int th = TileSmem<kF32Halves, 128, BNB, kHalfStages>::tile_bytes;
+    static constexpr int other = KernelSmem<kF32, 128, BNB, SB, BNS, SS>::sel_offset;
+    static constexpr int sel_offset = ((th > other ? th : other) + 15) / 16 * 16;
+    static constexpr int bytes = sel_offset + kSelSlots * 12 + 64;
+    static_assert(bytes <= 160 * 1024, "a workgroup has 160 KiB of LDS");
+};
+template <int BNB, int WMB, int WNB, int SB, int BNS, int WMS, int WNS, int SS>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((NT + 255) / 256, (NT + 255) / 256))) void gemm_halves_kernel(GemmArgs a)
+{
+    extern __shared__ __align__(16) float smem[];
+    Selection sel = {nullptr, nullptr, 0};
+    int n;
+    if (a.sel_words > 0) {
+        char *base = reinterpret_cast<char *>(smem) + HalvesSmem<BNB, WMB, WNB, SB, BNS, WMS, WNS, SS>::sel_offset;
+        uint64_t *sW = reinterpret_cast<uint64_t *>(base);
+        int *sRank = reinterpret_cast<int *>(base + kSelSlots * 8);
+        n = rank_selection(a, sW, sRank, sRank + kSelSlots, reinterpret_cast<uint64_t *>(smem));
+        sel = make_selection(a, sW, sRank);
+        if (a.sel_dilate && threadIdx.x < 64) write_update_map(a, sW); // a consumer wave: the first slices are awaited
+    } else {
+        n = a.count ? *a.count : a.max_pixels;
+    }
+    const long long big_tiles = (long long)((n + BNB - 1) / BNB) * (a.Mpad / 128);
+    if (big_tiles * small_tile_factor(kF32, 128, a.dNk.d) < (long long)gridDim.x)
+        gemm_gather_body<kF32, 128, BNS, WMS, WNS, SS>(a, n, smem, sel);
+    else if (halves_suit(big_tiles, a.dNk.d, (int)gridDim.x))
+        gemm_gather_body<kF32Halves, 128, BNB, WMB, WNB, kHalfStages>(a, n, smem, sel);
+    else
+        gemm_gather_body<kF32, 128, BNB, WMB, WNB, SB>(a, n, smem, sel);
 }
 
 // ---- layers whose whole reduction fits a wave's registers ----------------------------------
@@ -1795,6 +2106,23 @@ size_t gemm_filter_fragment(int dtype, int Mpad, int Kpad, int row, int k)
 }
 
 // ---- host side --------------------------------------------------------------------------
+bool gemm_filter_halves(const GemmArgs &a, int grid)
+{
+    return a.dtype == kF32 && a.Mpad % 128 == 0 && a.Mpad > 0 &&
+           halves_suit((long long)((a.max_pixels + 127) / 128) * (a.Mpad / 128), a.Kpad / gemm_k_multiple(kF32), grid);
+}
+
+size_t gemm_halves_bytes(int Mpad, int Kpad) { return (size_t)Mpad * Kpad * 4; }
+
+hipError_t gemm_make_halves(hipStream_t st, const void *wt, void *wt_halves, int Mpad, int Kpad, int shift)
+{
+    if (!wt || !wt_halves || Mpad < 128 || Mpad % 128 || Kpad < 1 || Kpad % gemm_k_multiple(kF32)) return hipErrorInvalidValue;
+    const size_t n = (size_t)Mpad * Kpad / 8;
+    make_halves_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st>>>(static_cast<const uintx4 *>(wt), static_cast<uintx4 *>(wt_halves),
+                                                                                n, shift);
+    return hipGetLastError();
+}
+
 unsigned gemm_tiny_sum(int K, float largest_weight)
 {
     const double t = std::ldexp((double)K * largest_weight, -110);
@@ -1909,6 +2237,7 @@ size_t gemm_partial_bytes(const GemmArgs &a, int compute_units)
 }
 
 // storage type; BM; big tile (BN, WM, WN, ring slices); small tile (the same)
+#define CBK_HALVES_SHAPES 128, 1, 8, 3, 64, 2, 4, 4 // of the kernel with halves, as without
 #define CBK_VARIANTS(X)                                  \
     X(kF32, 16, 256, 1, 8, 3, 128, 1, 8, 4)              \
     X(kF32, 32, 256, 1, 8, 3, 64, 2, 4, 4)               \
@@ -1936,6 +2265,9 @@ hipError_t gemm_prepare(void)
             hipFuncAttributeMaxDynamicSharedMemorySize, KernelSmem<DT_, BM_, BNB_, SB_, BNS_, SS_>::bytes);
     CBK_VARIANTS(X)
 #undef X
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_halves_kernel<CBK_HALVES_SHAPES>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                HalvesSmem<CBK_HALVES_SHAPES>::bytes);
 #define T(DT_, MT_)                                                                                                \
     if (e == hipSuccess)                                                                                           \
         e = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_thin_kernel<DT_, MT_>),                       \
@@ -1952,6 +2284,7 @@ hipError_t gemm_gather(hipStream_t st, const GemmArgs &a, const Timing &tm)
     if (a.Mpad % bm != 0 || a.Kpad % gemm_k_multiple(a.dtype) != 0 || a.Ms % eu != 0 || a.pix_words < 1 || !a.partial ||
         !a.tickets || a.grid < 8 || (a.grid & 7) || a.grid > kMaxGrid)
         return hipErrorInvalidValue;
+    if (a.wt_halves && (a.dtype != kF32 || bm != 128)) return hipErrorInvalidValue;
     // the wide 64-channel tile in float32 counts on rows of four slices or more (TileSmem::lists); those it gets have five
     if (a.dtype == kF32 && bm == 64 && bn == 256 && !gemm_is_thin(a) && a.Kpad < 4 * gemm_k_multiple(kF32)) return hipErrorInvalidValue;
     // the divisors must belong to these arguments, and the schedule's 32-bit arithmetic must hold
@@ -1993,6 +2326,10 @@ hipError_t gemm_gather(hipStream_t st, const GemmArgs &a, const Timing &tm)
     }
         T(kF32, 1) T(kF32, 2) T(kF32, 4) T(kBF16, 1) T(kBF16, 2) T(kBF16, 4)
 #undef T
+    }
+    if (a.wt_halves) {
+        launch_kernel(tm, gemm_halves_kernel<CBK_HALVES_SHAPES>, dim3(a.grid), dim3(NT), (HalvesSmem<CBK_HALVES_SHAPES>::bytes), st, a);
+        return hipGetLastError();
     }
 #define X(DT_, BM_, BNB_, WMB_, WNB_, SB_, BNS_, WMS_, WNS_, SS_)                                                        \
     if (a.dtype == DT_ && bm == BM_ && bn == BNB_) {                                                                     \

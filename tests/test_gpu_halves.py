@@ -1,0 +1,99 @@
+"""float32 layers of more than 64 channels whose sums are long are multiplied in float16 halves: sampled positions against 64
+bits, at the shortest rows and ranges that take that path, with values of every scale, scales that change along a sum,
+pixels far darker than their neighbours, values and weights that the halves cannot carry."""
+import numpy as np
+import pytest
+
+import paper_1704_04313_amd as cb
+from workloads.networks import conv, make_weights
+
+from gpu_util import to_dev
+from test_gpu_tile_shapes import _sampled
+
+pytestmark = pytest.mark.gpu
+
+
+def _scaled(x, kind):
+    C, H, W = x.shape
+    if kind == "large":
+        return x * np.float32(2.0 ** 60)
+    if kind == "small":
+        return x * np.float32(2.0 ** -70)
+    if kind == "brighter":  # along every sum that crosses the middle, by eight binades, and from nothing at all at the top
+        x[:, : H // 2] *= np.float32(2.0 ** -8)
+        x[:, : H // 5] = 0
+    if kind == "dim":
+        x[:, H // 4: H // 2, W // 4: W // 2] *= np.float32(2.0 ** -20)
+    if kind == "special":
+        for n, v in enumerate((np.nan, np.inf, -np.inf, 3.4028e38, 1e25, -1e8)):
+            x[(7 * n) % C, (n * H) // 7, (n * W) // 6] = v
+    return x
+
+
+# 24 slices are the fewest of a whole tile, 27 and 37 leave halves of a chunk; 213 to 269 tiles are cut across, below or
+# above a round of 256; 64->256 in three ranges; 100, 130 and 200 channels pad their tiles
+@pytest.mark.parametrize("cin,cout,k,h,w", [
+    (256, 128, 3, 190, 181), (96, 100, 3, 181, 190), (84, 130, 3, 131, 129), (24, 200, 7, 133, 127), (64, 256, 7, 60, 80), (768, 128, 1, 181, 190)])
+@pytest.mark.parametrize("kind", ["plain", "large", "small", "brighter", "dim", "special"])
+def test_against_64_bits(cin, cout, k, h, w, kind):
+    L = conv(cin, cout, k, relu=False)
+    (wt, b), = make_weights([L], cin + cout)
+    b = b * 0
+    if kind == "small":
+        wt = wt * np.float32(2.0 ** -50)
+    r = np.random.default_rng(cin + k)
+    x = _scaled(np.maximum(r.standard_normal((cin, h, w), dtype=np.float32), 0), kind)
+    rows = [slice(0, h // 4 - k), slice(h // 4 + k, h // 2 - k), slice(h // 2 - k, h // 2 + k), slice(h // 2 + k, h)]
+    with np.errstate(all="ignore"):
+        net = cb.CBInfer([L], [(wt, b)], x.shape, 0.02)
+        net.set_mode(True)
+        got = net.process_frame(to_dev(x)).cpu().numpy()[0].astype(np.float64)
+        net.destroy()
+        slices = (cin * k * k + 31) // 32
+        for ys in rows:
+            for xs in (slice(0, w), slice(w // 4 + k, w // 2 - k)):  # all, and where "dim" is
+                yy, xx = np.mgrid[ys, xs]
+                pos = (yy * w + xx).ravel()
+                pos = r.choice(pos, min(250, pos.size), replace=False)
+                want = _sampled(L, wt, b, x, pos)[0].astype(np.float32).astype(np.float64)
+                size = _sampled(L, wt, b, np.where(np.isfinite(x), x, 0), pos)[1]
+                g = got.reshape(cout, -1)[:, pos]
+                np.testing.assert_array_equal(np.isnan(g), np.isnan(want))
+                np.testing.assert_array_equal(np.isinf(g) * np.sign(g), np.isinf(want) * np.sign(want))
+                fine = np.isfinite(want)
+                err = np.abs(np.where(fine, g, 0) - np.where(fine, want, 0))
+                # Formed again with the float32 instruction: a product and an addition per value, half a unit of 2^-23 each.
+                # In halves: 2^-22 for each value's last bit and for what the second halves multiply to, and half a unit per
+                # slice, doubled for what the matrix unit cuts off.
+                per = cin * k * k + 40 if kind in ("dim", "special") else slices + 8
+                assert np.all(err <= per * (2.0 ** -23 * np.where(fine, size, 0) + 2.0 ** -149))
+                if kind in ("plain", "large", "small"):  # roundings of either sign add up like their square root
+                    assert np.linalg.norm(err) <= np.sqrt(slices + 8) * 2.0 ** -24 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("kind", ["some", "channels", "inf", "zero"])
+def test_weights_that_halves_do_not_carry(kind):
+    """Weights far below the layer's largest where nothing else meets the pixels, infinite ones, a layer of zeros."""
+    L = conv(128, 128, 3, relu=False)
+    (wt, b), = make_weights([L], 9)
+    b = b * 0
+    r = np.random.default_rng(5)
+    x = r.random((128, 131, 140), dtype=np.float32)
+    if kind == "some":
+        wt[:64, :64] *= np.float32(2.0 ** -40)
+        x[64:, :, :70] = 0
+    if kind == "channels":
+        wt[5] *= np.float32(2.0 ** -60)
+    if kind == "inf":
+        wt[7, 100, 1, 1] = np.inf
+    if kind == "zero":
+        wt[:] = 0
+    pos = np.concatenate([np.arange(60), r.integers(0, 131 * 140, 600)])
+    want, size = _sampled(L, wt, b, x, pos)
+    net = cb.CBInfer([L], [(wt, b)], x.shape, 0.02)
+    net.set_mode(True)
+    g = net.process_frame(to_dev(x)).cpu().numpy()[0].reshape(128, -1)[:, pos].astype(np.float64)
+    net.destroy()
+    fine = np.isfinite(want)
+    np.testing.assert_array_equal(g[~fine], want[~fine])
+    assert np.all(np.abs(np.where(fine, g, 0) - np.where(fine, want, 0)) <= (128 * 9 + 8) * 2.0 ** -23 * np.where(fine, size, 0))
