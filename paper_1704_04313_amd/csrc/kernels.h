@@ -285,7 +285,7 @@ bool gemm_filter_in_fragments(int dtype, int Mpad, int Kpad);
 size_t gemm_filter_bytes(int dtype, int Mpad, int Kpad);
 size_t gemm_filter_fragment(int dtype, int Mpad, int Kpad, int row, int k);
 constexpr int kFilterPartStride = 512;
-// float32 layers of more than 64 channels and long rows, on maps large enough: the same fragments of two float16 each that
+// float32 layers of more than 32 channels and long rows, on maps large enough: the same fragments of two float16 each that
 // add up to the weight times 2^halves_exp to 23 bits.  Needs dtype, Mpad, Kpad and max_pixels; grid: workgroups at most.
 bool gemm_filter_halves(const GemmArgs &a, int grid);
 size_t gemm_halves_bytes(int Mpad, int Kpad);

@@ -39,12 +39,13 @@
 // once, when the state is created, and lies in memory in the order in which it is read; pixels are split in
 // registers (3.5 instructions per value) in the shadow of the MFMAs.
 //
-// Layers of more than 64 channels whose workgroups sum up long ranges of K (halves_suit) take float16 halves and three
+// Layers of more than 32 channels whose workgroups sum up long ranges of K (halves_suit) take float16 halves and three
 // products instead, half the matrix time and two thirds of the filter bytes: 64->256 7x7 on 320x180 382 -> 267 us (347
-// TFLOP/s), on 80x60 50.6 -> 38.7, 256->256 3x3 on 160x120 118 -> 87, 512->512 3x3 on 80x60 114 -> 80, two frames of 64 streams of
-// the benchmark network 6.45 -> 5.25 ms, with smaller errors than the parts' there (figures at kHalfRange).  The MFMAs are 45 %
-// of that time now; the rest is vector instructions (split, largest value, sums folded) and fragment reads that do not
-// overlap with them, about 8 % the loads.  Up to 64 channels gain 3 to 5 % only and stay with the parts.
+// TFLOP/s), on 80x60 50.6 -> 38.7, 256->256 3x3 on 160x120 118 -> 87, 512->512 3x3 on 80x60 114 -> 80; 16->64 7x7 on 640x360 130 ->
+// 116, 64->64 5x5 on 400x300 126 -> 101, 96->64 3x3 on 640x480 172 -> 139; with smaller errors than the parts' there (figures
+// at kHalfRange).  What bounds the 128-channel tile is the matrix rate the card sustains, as above (347 x 3 = 1 041 of 1 120 to
+// 1 340; without the split of pixels, which feeding it halves would save, 385 x 3); the 64-channel one moves 24 KiB into LDS
+// for half the MFMAs and is bound by that.
 //
 // Work distribution: one workgroup per compute unit.  Output tiles are dealt out whole as long
 // as every workgroup gets one; the (tiles mod workgroups) left over are cut along K into
@@ -112,23 +113,27 @@ __host__ __device__ inline int small_tile_factor(int dtype, int bm, int nk)
     return dtype == kF32 && bm == 128 && nk >= 48 ? 4 : 2;
 }
 
-// Whether a launch of that many big tiles (128 channels, 128 pixels) of nk slices multiplies in halves: where the ranges
-// of K that workgroups sum up are kHalfRange slices long on average.  Halves leave off the last of float32's 24 bits in a
-// quarter of the values and the product of both second halves, 7.0e-8 of a sum whatever its length; the bfloat16 parts are
-// exact but are rounded at the magnitude of the whole sum in every slice, 3.4e-8 sqrt(slices / 2).  Error against 64 bits
-// (2-norm, halves / parts): 64->256 7x7 (98 slices) whole 1.43e-7 / 2.62e-7, in three ranges 1.29e-7 / 1.47e-7, in twelve
-// 1.30e-7 / 0.95e-7; 128->128 3x3 (36) whole 1.23e-7 / 1.46e-7; 75 slices in nine ranges 1.22e-7 / 1.10e-7.  So the line
-// is where the errors meet; short ranges are latency, not multiplication (the last two 19.1 / 20.4 and 22.4 / 25.0 us).
-static constexpr int kHalfRange = 24;
-__host__ __device__ inline bool halves_suit(long long tiles, int nk, int grid)
+// Whether a launch of that many big tiles (channel tile bm) of nk slices multiplies in halves: where the ranges of K that
+// workgroups sum up are kHalfRange slices long in the mean over the tiles.  Halves leave off the last of float32's 24 bits
+// in a quarter of the values and the product of both second halves, 7.0e-8 of a sum whatever its length; the bfloat16 parts
+// are exact but are rounded at the magnitude of the whole sum in every slice, 3.4e-8 sqrt(slices / 2).  Error against 64
+// bits (2-norm, halves / parts): 64->256 7x7 (98 slices) whole 1.43e-7 / 2.62e-7, in three ranges 1.29e-7 / 1.47e-7, in
+// twelve 1.30e-7 / 0.95e-7; 128->128 3x3 (36) whole 1.23e-7 / 1.46e-7; 16->64 7x7 (25) 1.24e-7 / 1.27e-7; 32->60 5x5 (25, half
+// the tiles in ranges of eleven) 1.16e-7 / 1.12e-7; 75 slices in nine ranges 1.22e-7 / 1.10e-7.  So the line is where the
+// errors meet; short ranges are latency, not multiplication (64->256 in twelve 19.1 / 20.4 us, the last 22.4 / 25.0).
+static constexpr int kHalfRange = 22;
+__host__ __device__ inline bool halves_suit(int bm, int tiles, int whole_rounds, int nk, int grid)
 {
-    if (tiles >= grid) return nk >= kHalfRange; // whole tiles, and a round in which some are cut
-    // where the big tile is used at all: gemm_partial_bytes has no room for its partial sums elsewhere
-    if (tiles < 1 || tiles * small_tile_factor(kF32, 128, nk) < grid) return false;
+    // only where the big tile is used at all: gemm_partial_bytes has no room for its partial sums elsewhere
+    if (nk < kHalfRange || tiles < 1 || (long long)tiles * small_tile_factor(kF32, bm, nk) < grid) return false;
+    const int rem = tiles - whole_rounds * grid;
+    if (rem == 0) return true;
     // as make_schedule cuts them: into equal parts, or evenly over all workgroups, which then cross from tile to tile
-    const int parts = grid / (int)tiles;
-    const long long ranges = tiles * parts * 8 >= (long long)grid * 7 ? tiles * parts : grid + tiles;
-    return tiles * nk >= kHalfRange * ranges;
+    const int most = nk / kMinIters > 1 ? nk / kMinIters : 1;
+    int parts = grid / rem;
+    if (parts > most) parts = most;
+    const long long ranges = rem * parts * 8 < grid * 7 && rem * most >= grid ? grid + rem : rem * parts;
+    return (tiles - rem) * (nk * ranges) + (long long)rem * rem * nk >= kHalfRange * ranges * tiles;
 }
 
 static constexpr int kSelMaxWords = 2048; // largest selection map ranked in-kernel (131072 pixels)
@@ -1716,25 +1721,24 @@ __global__ void make_halves_kernel(const uintx4 *__restrict__ wt, uintx4 *__rest
     out[fragment * 128 + 64 + lane] = lo;
 }
 
-// float32 layers of more than 64 channels that have their filter matrix in halves too: the big tile in halves where sums
-// are long, else the kernel above.
-static constexpr int kHalfStages = 4;
-template <int BNB, int WMB, int WNB, int SB, int BNS, int WMS, int WNS, int SS>
+// float32 layers of more than 32 channels that have their filter matrix in halves too: a big tile in halves where sums are
+// long, else as in the kernel above.
+template <int BM, int BNB, int WMB, int WNB, int SB, int BNS, int WMS, int WNS, int SS, int BNH, int SH>
 struct HalvesSmem {
-    static constexpr int th = TileSmem<kF32Halves, 128, BNB, kHalfStages>::tile_bytes;
-    static constexpr int other = KernelSmem<kF32, 128, BNB, SB, BNS, SS>::sel_offset;
+    static constexpr int th = TileSmem<kF32Halves, BM, BNH, SH>::tile_bytes;
+    static constexpr int other = KernelSmem<kF32, BM, BNB, SB, BNS, SS>::sel_offset;
     static constexpr int sel_offset = ((th > other ? th : other) + 15) / 16 * 16;
     static constexpr int bytes = sel_offset + kSelSlots * 12 + 64;
     static_assert(bytes <= 160 * 1024, "a workgroup has 160 KiB of LDS");
 };
-template <int BNB, int WMB, int WNB, int SB, int BNS, int WMS, int WNS, int SS>
+template <int BM, int BNB, int WMB, int WNB, int SB, int BNS, int WMS, int WNS, int SS, int BNH, int SH>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((NT + 255) / 256, (NT + 255) / 256))) void gemm_halves_kernel(GemmArgs a)
 {
     extern __shared__ __align__(16) float smem[];
     Selection sel = {nullptr, nullptr, 0};
     int n;
     if (a.sel_words > 0) {
-        char *base = reinterpret_cast<char *>(smem) + HalvesSmem<BNB, WMB, WNB, SB, BNS, WMS, WNS, SS>::sel_offset;
+        char *base = reinterpret_cast<char *>(smem) + HalvesSmem<BM, BNB, WMB, WNB, SB, BNS, WMS, WNS, SS, BNH, SH>::sel_offset;
         uint64_t *sW = reinterpret_cast<uint64_t *>(base);
         int *sRank = reinterpret_cast<int *>(base + kSelSlots * 8);
         n = rank_selection(a, sW, sRank, sRank + kSelSlots, reinterpret_cast<uint64_t *>(smem));
@@ -1743,13 +1747,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((NT + 255) /
     } else {
         n = a.count ? *a.count : a.max_pixels;
     }
-    const long long big_tiles = (long long)((n + BNB - 1) / BNB) * (a.Mpad / 128);
-    if (big_tiles * small_tile_factor(kF32, 128, a.dNk.d) < (long long)gridDim.x)
-        gemm_gather_body<kF32, 128, BNS, WMS, WNS, SS>(a, n, smem, sel);
-    else if (halves_suit(big_tiles, a.dNk.d, (int)gridDim.x))
-        gemm_gather_body<kF32Halves, 128, BNB, WMB, WNB, kHalfStages>(a, n, smem, sel);
+    const long long big_tiles = (long long)((n + BNB - 1) / BNB) * (a.Mpad / BM);
+    const int half_tiles = (n + BNH - 1) / BNH * (a.Mpad / BM);
+    if (big_tiles * small_tile_factor(kF32, BM, a.dNk.d) < (long long)gridDim.x)
+        gemm_gather_body<kF32, BM, BNS, WMS, WNS, SS>(a, n, smem, sel);
+    else if (halves_suit(BM, half_tiles, fast_div(half_tiles, a.dGrid), a.dNk.d, (int)gridDim.x))
+        gemm_gather_body<kF32Halves, BM, BNH, 1, 8, SH>(a, n, smem, sel);
     else
-        gemm_gather_body<kF32, 128, BNB, WMB, WNB, SB>(a, n, smem, sel);
+        gemm_gather_body<kF32, BM, BNB, WMB, WNB, SB>(a, n, smem, sel);
 }
 
 // ---- layers whose whole reduction fits a wave's registers ----------------------------------
@@ -2108,15 +2113,17 @@ size_t gemm_filter_fragment(int dtype, int Mpad, int Kpad, int row, int k)
 // ---- host side --------------------------------------------------------------------------
 bool gemm_filter_halves(const GemmArgs &a, int grid)
 {
-    return a.dtype == kF32 && a.Mpad % 128 == 0 && a.Mpad > 0 &&
-           halves_suit((long long)((a.max_pixels + 127) / 128) * (a.Mpad / 128), a.Kpad / gemm_k_multiple(kF32), grid);
+    if (a.dtype != kF32 || a.Mpad < 64 || gemm_is_thin(a)) return false;
+    const int bm = gemm_channel_tile(a.M);
+    const int tiles = (a.max_pixels + 127) / 128 * (a.Mpad / bm);
+    return halves_suit(bm, tiles, tiles / grid, a.Kpad / gemm_k_multiple(kF32), grid);
 }
 
 size_t gemm_halves_bytes(int Mpad, int Kpad) { return (size_t)Mpad * Kpad * 4; }
 
 hipError_t gemm_make_halves(hipStream_t st, const void *wt, void *wt_halves, int Mpad, int Kpad, int shift)
 {
-    if (!wt || !wt_halves || Mpad < 128 || Mpad % 128 || Kpad < 1 || Kpad % gemm_k_multiple(kF32)) return hipErrorInvalidValue;
+    if (!wt || !wt_halves || Mpad < 64 || Mpad % 16 || Kpad < 1 || Kpad % gemm_k_multiple(kF32)) return hipErrorInvalidValue;
     const size_t n = (size_t)Mpad * Kpad / 8;
     make_halves_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st>>>(static_cast<const uintx4 *>(wt), static_cast<uintx4 *>(wt_halves),
                                                                                 n, shift);
@@ -2237,7 +2244,12 @@ size_t gemm_partial_bytes(const GemmArgs &a, int compute_units)
 }
 
 // storage type; BM; big tile (BN, WM, WN, ring slices); small tile (the same)
-#define CBK_HALVES_SHAPES 128, 1, 8, 3, 64, 2, 4, 4 // of the kernel with halves, as without
+// float32 with halves: the same, then the tile in halves (BN, ring slices).  Of 64 channels it is 128 pixels on every map:
+// 16->64 7x7 on 1200x1280 613 us, with 256 pixels (26 registers spilled) 737, in parts 701.
+#define CBK_HALVES(X)                                \
+    X(64, 256, 1, 8, 3, 64, 2, 4, 5, 128, 5)         \
+    X(64, 128, 1, 8, 4, 64, 2, 4, 5, 128, 5)         \
+    X(128, 128, 1, 8, 3, 64, 2, 4, 4, 128, 4)
 #define CBK_VARIANTS(X)                                  \
     X(kF32, 16, 256, 1, 8, 3, 128, 1, 8, 4)              \
     X(kF32, 32, 256, 1, 8, 3, 64, 2, 4, 4)               \
@@ -2265,9 +2277,12 @@ hipError_t gemm_prepare(void)
             hipFuncAttributeMaxDynamicSharedMemorySize, KernelSmem<DT_, BM_, BNB_, SB_, BNS_, SS_>::bytes);
     CBK_VARIANTS(X)
 #undef X
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_halves_kernel<CBK_HALVES_SHAPES>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                HalvesSmem<CBK_HALVES_SHAPES>::bytes);
+#define X(...)                                                                                                                      \
+    if (e == hipSuccess)                                                                                                            \
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_halves_kernel<__VA_ARGS__>), hipFuncAttributeMaxDynamicSharedMemorySize, \
+                                HalvesSmem<__VA_ARGS__>::bytes);
+    CBK_HALVES(X)
+#undef X
 #define T(DT_, MT_)                                                                                                \
     if (e == hipSuccess)                                                                                           \
         e = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_thin_kernel<DT_, MT_>),                       \
@@ -2284,7 +2299,7 @@ hipError_t gemm_gather(hipStream_t st, const GemmArgs &a, const Timing &tm)
     if (a.Mpad % bm != 0 || a.Kpad % gemm_k_multiple(a.dtype) != 0 || a.Ms % eu != 0 || a.pix_words < 1 || !a.partial ||
         !a.tickets || a.grid < 8 || (a.grid & 7) || a.grid > kMaxGrid)
         return hipErrorInvalidValue;
-    if (a.wt_halves && (a.dtype != kF32 || bm != 128)) return hipErrorInvalidValue;
+    if (a.wt_halves && (a.dtype != kF32 || bm < 64 || gemm_is_thin(a))) return hipErrorInvalidValue;
     // the wide 64-channel tile in float32 counts on rows of four slices or more (TileSmem::lists); those it gets have five
     if (a.dtype == kF32 && bm == 64 && bn == 256 && !gemm_is_thin(a) && a.Kpad < 4 * gemm_k_multiple(kF32)) return hipErrorInvalidValue;
     // the divisors must belong to these arguments, and the schedule's 32-bit arithmetic must hold
@@ -2328,8 +2343,13 @@ hipError_t gemm_gather(hipStream_t st, const GemmArgs &a, const Timing &tm)
 #undef T
     }
     if (a.wt_halves) {
-        launch_kernel(tm, gemm_halves_kernel<CBK_HALVES_SHAPES>, dim3(a.grid), dim3(NT), (HalvesSmem<CBK_HALVES_SHAPES>::bytes), st, a);
-        return hipGetLastError();
+#define X(BM_, BNB_, ...)                                                                                                         \
+    if (bm == BM_ && bn == BNB_) {                                                                                                \
+        launch_kernel(tm, gemm_halves_kernel<BM_, BNB_, __VA_ARGS__>, dim3(a.grid), dim3(NT), (HalvesSmem<BM_, BNB_, __VA_ARGS__>::bytes), st, a); \
+        return hipGetLastError();                                                                                                 \
+    }
+        CBK_HALVES(X)
+#undef X
     }
 #define X(DT_, BM_, BNB_, WMB_, WNB_, SB_, BNS_, WMS_, WNS_, SS_)                                                        \
     if (a.dtype == DT_ && bm == BM_ && bn == BNB_) {                                                                     \

@@ -1,4 +1,4 @@
-"""float32 layers of more than 64 channels whose sums are long are multiplied in float16 halves: sampled positions against 64
+"""float32 layers of more than 32 channels whose sums are long are multiplied in float16 halves: sampled positions against 64
 bits, at the shortest rows and ranges that take that path, with values of every scale, scales that change along a sum,
 pixels far darker than their neighbours, values and weights that the halves cannot carry."""
 import numpy as np
@@ -31,9 +31,11 @@ def _scaled(x, kind):
 
 
 # 24 slices are the fewest of a whole tile, 27 and 37 leave halves of a chunk; 213 to 269 tiles are cut across, below or
-# above a round of 256; 64->256 in three ranges; 100, 130 and 200 channels pad their tiles
+# above a round of 256; 64->256 in three ranges; 100, 130 and 200 channels pad their tiles; the last three are the 64-channel
+# kernels of either tile in parts
 @pytest.mark.parametrize("cin,cout,k,h,w", [
-    (256, 128, 3, 190, 181), (96, 100, 3, 181, 190), (84, 130, 3, 131, 129), (24, 200, 7, 133, 127), (64, 256, 7, 60, 80), (768, 128, 1, 181, 190)])
+    (256, 128, 3, 190, 181), (96, 100, 3, 181, 190), (84, 130, 3, 131, 129), (24, 200, 7, 133, 127), (64, 256, 7, 60, 80), (768, 128, 1, 181, 190),
+    (16, 64, 7, 260, 257), (23, 50, 7, 365, 357), (96, 64, 3, 727, 725)])
 @pytest.mark.parametrize("kind", ["plain", "large", "small", "brighter", "dim", "special"])
 def test_against_64_bits(cin, cout, k, h, w, kind):
     L = conv(cin, cout, k, relu=False)
