@@ -1773,6 +1773,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((NT + 255) /
 static constexpr int kThinGroups = 16;
 static constexpr int kThinChannels = 64;
 static constexpr int kThinMaxWork = 32;     // groups x channel tiles up to which this kernel is used
+// Tiles of 16 positions per wave from which the taps are kept in registers: 3->16 7x7 on 1280x720 (19 a wave) 89 -> 78 us, on
+// 1800x1600 264 -> 225, 256->16 1x1 on 640x480 71.6 -> 69; fewer do not pay for putting them there (320x240, 1.6 a wave:
+// 12.2 either way).
+static constexpr int kThinManyFactor = 4;
 static constexpr int kThinWholeFactor = 2; // tiles of 16 positions per wave from which a wave takes all channel tiles
 static constexpr int kThinScratchBytes = (kSelMaxWords + 2 * kSelGuard) * 8;                   // front-end scratch
 static constexpr int kThinFilterBytes = kThinChannels * (kThinGroups * 4 + 1) * 16;              // [Mpad][units + 1]
@@ -1786,7 +1790,10 @@ static_assert(kThinSmemBytes <= 160 * 1024, "a workgroup has 160 KiB of LDS");
 // issue the next tile's gathers into the registers the MFMAs have just read, update the outputs of
 // the current tile -- so a tile's gather latency passes during the update before it and the search
 // after it.
-template <int DT, int TC>
+// MANY: launches of several tiles a wave, on maps below 4 GiB with sides up to 16000, keep the taps in registers, packed
+// coordinates and byte offsets: a gather is five vector instructions and a load from a scalar base, instead of a tap from
+// LDS, a dozen instructions and a 64-bit address.
+template <int DT, int TC, bool MANY>
 __device__ __forceinline__ void thin_tiles(const GemmArgs &a, const int n, const Selection &sel, const uintx4 *sB,
                                            const int2 *sTap, const int G, const int pitch)
 {
@@ -1820,10 +1827,34 @@ __device__ __forceinline__ void thin_tiles(const GemmArgs &a, const int n, const
     };
     floatx4 ra[kThinGroups];
     uintx4 replaced[TC];
-    auto gather = [&](const Where &p, int cg) {
+    constexpr int KT = MANY ? kThinGroups : 1;
+    unsigned taps[KT], offsets[KT]; // of this lane's units
+    if constexpr (MANY) {
 #pragma unroll
         for (int gg = 0; gg < kThinGroups; ++gg) {
-            if (gg < G) {
+            const int2 tp = sTap[gg < G ? 4 * gg + lk : lk];
+            taps[gg] = (tp.y >> 16) != 0 ? (unsigned)(tp.y & 0xff) << 16 | (unsigned)(tp.y >> 8 & 0xff) : 0x40004000u;
+            offsets[gg] = (unsigned)tp.x * 4u;
+        }
+    }
+    auto gather = [&](const Where &p, int cg) {
+        if constexpr (MANY) {
+            const unsigned at0 = p.g >= 0 ? (unsigned)p.iy0 << 16 | ((unsigned)p.ix0 & 0xffffu) : 0x80008000u;
+            const unsigned origin = (unsigned)p.base * 4u, zero = (unsigned)a.zero_word * 4u;
+            const ushortx2 last = {(unsigned short)(a.W - 1), (unsigned short)(a.H - 1)};
+#pragma unroll
+            for (int gg = 0; gg < kThinGroups; ++gg) {
+                if (gg < G) {
+                    const ushortx2 at = __builtin_bit_cast(ushortx2, at0) + __builtin_bit_cast(ushortx2, taps[MANY ? gg : 0]);
+                    const bool ok = __builtin_bit_cast(unsigned, __builtin_elementwise_sub_sat(at, last)) == 0u;
+                    const unsigned o = ok ? origin + offsets[MANY ? gg : 0] : zero;
+                    ra[gg] = *reinterpret_cast<const floatx4_a4 *>(reinterpret_cast<const char *>(x) + o);
+                }
+            }
+        }
+#pragma unroll
+        for (int gg = 0; gg < kThinGroups; ++gg) {
+            if (!MANY && gg < G) {
                 const int2 tp = sTap[4 * gg + lk];
                 const int tj = tp.y & 0xff, ti = (tp.y >> 8) & 0xff;
                 const bool ok = (tp.y >> 16) != 0 && (unsigned)(p.iy0 + tj) < (unsigned)a.H && (unsigned)(p.ix0 + ti) < (unsigned)a.W;
@@ -1973,13 +2004,20 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((NT + 255) /
         n = a.count ? *a.count : a.max_pixels;
     }
     __syncthreads();
-    if constexpr (MT > 1) {
-        if (((n + 15) >> 4) >= kThinWholeFactor * (NT / 64) * (int)gridDim.x) {
-            thin_tiles<DT, MT>(a, n, sel, sB, sTap, G, pitch);
+    const int tiles = (n + 15) >> 4, waves = (NT / 64) * (int)gridDim.x;
+    if constexpr (MT == 1) { // wider layers gather less per MFMA: 5x5/2 3->32 on 640x480 33.9 -> 34.5 us, 3x3 16->32 there 40.1 -> 40.7
+        if (tiles >= kThinManyFactor * waves && a.taps_mode != kTapGeneral && a.H <= 16000 && a.W <= 16000) {
+            thin_tiles<DT, 1, true>(a, n, sel, sB, sTap, G, pitch);
             return;
         }
     }
-    thin_tiles<DT, 1>(a, n, sel, sB, sTap, G, pitch);
+    if constexpr (MT > 1) {
+        if (tiles >= kThinWholeFactor * waves) {
+            thin_tiles<DT, MT, false>(a, n, sel, sB, sTap, G, pitch);
+            return;
+        }
+    }
+    thin_tiles<DT, 1, false>(a, n, sel, sB, sTap, G, pitch);
 }
 
 // ---- 1x1 layers on pixels of one or two units ------------------------------------------------
