@@ -1970,8 +1970,9 @@ __device__ __forceinline__ void thin_tiles(const GemmArgs &a, const int n, const
 }
 
 // MT: channel tiles of the layer (Mpad / 16).  A wave takes all of them for its 16 positions when
-// there are enough positions to occupy every wave that way, else one each.
-template <int DT, int MT>
+// there are enough positions to occupy every wave that way, else one each.  MANY: maps on which a launch may have
+// kThinManyFactor tiles a wave; a kernel of its own, for the sake of the small launches' registers and code.
+template <int DT, int MT, bool MANY>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((NT + 255) / 256, (NT + 255) / 256))) void gemm_thin_kernel(GemmArgs a)
 {
     extern __shared__ __align__(16) float smem[];
@@ -2005,8 +2006,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((NT + 255) /
     }
     __syncthreads();
     const int tiles = (n + 15) >> 4, waves = (NT / 64) * (int)gridDim.x;
-    if constexpr (MT == 1) { // wider layers gather less per MFMA: 5x5/2 3->32 on 640x480 33.9 -> 34.5 us, 3x3 16->32 there 40.1 -> 40.7
-        if (tiles >= kThinManyFactor * waves && a.taps_mode != kTapGeneral && a.H <= 16000 && a.W <= 16000) {
+    if constexpr (MANY) {
+        if (tiles >= kThinManyFactor * waves) {
             thin_tiles<DT, 1, true>(a, n, sel, sB, sTap, G, pitch);
             return;
         }
@@ -2305,6 +2306,18 @@ size_t gemm_partial_bytes(const GemmArgs &a, int compute_units)
 CBK_VARIANTS(X)
 #undef X
 
+// One channel tile only: wider layers gather less per MFMA (5x5/2 3->32 on 640x480 33.9 -> 34.5 us, 3x3 16->32 there 40.1 ->
+// 40.7).
+static bool thin_many(const GemmArgs &a)
+{
+    return a.Mpad == 16 && (a.max_pixels + 15) / 16 >= kThinManyFactor * (NT / 64) * a.grid && a.taps_mode != kTapGeneral &&
+           a.H <= 16000 && a.W <= 16000;
+}
+// storage type; channel tiles; many tiles a wave
+#define CBK_THIN(T)                                                      \
+    T(kF32, 1, false) T(kF32, 1, true) T(kF32, 2, false) T(kF32, 4, false) \
+    T(kBF16, 1, false) T(kBF16, 1, true) T(kBF16, 2, false) T(kBF16, 4, false)
+
 hipError_t gemm_prepare(void)
 {
     hipError_t e = hipSuccess;
@@ -2321,11 +2334,11 @@ hipError_t gemm_prepare(void)
                                 HalvesSmem<__VA_ARGS__>::bytes);
     CBK_HALVES(X)
 #undef X
-#define T(DT_, MT_)                                                                                                \
+#define T(DT_, MT_, MANY_)                                                                                         \
     if (e == hipSuccess)                                                                                           \
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_thin_kernel<DT_, MT_>),                       \
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_thin_kernel<DT_, MT_, MANY_>),                \
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kThinSmemBytes);
-    T(kF32, 1) T(kF32, 2) T(kF32, 4) T(kBF16, 1) T(kBF16, 2) T(kBF16, 4)
+    CBK_THIN(T)
 #undef T
     return e;
 }
@@ -2372,12 +2385,13 @@ hipError_t gemm_gather(hipStream_t st, const GemmArgs &a, const Timing &tm)
 #undef P
     }
     if (gemm_is_thin(a)) {
-#define T(DT_, MT_)                                                                                      \
-    if (a.dtype == DT_ && a.Mpad == 16 * MT_) {                                                           \
-        launch_kernel(tm, gemm_thin_kernel<DT_, MT_>, dim3(a.grid), dim3(NT), kThinSmemBytes, st, a);    \
-        return hipGetLastError();                                                                        \
+        const bool many = thin_many(a);
+#define T(DT_, MT_, MANY_)                                                                                    \
+    if (a.dtype == DT_ && a.Mpad == 16 * MT_ && many == MANY_) {                                               \
+        launch_kernel(tm, gemm_thin_kernel<DT_, MT_, MANY_>, dim3(a.grid), dim3(NT), kThinSmemBytes, st, a);  \
+        return hipGetLastError();                                                                             \
     }
-        T(kF32, 1) T(kF32, 2) T(kF32, 4) T(kBF16, 1) T(kBF16, 2) T(kBF16, 4)
+        CBK_THIN(T)
 #undef T
     }
     if (a.wt_halves) {
