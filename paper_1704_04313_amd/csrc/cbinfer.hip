@@ -5,6 +5,7 @@
 #include "../../include/cbinfer.h"
 #include "kernels.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -54,7 +55,8 @@ struct Op {
     int gemm_grid = 0;
     unsigned tiny_sum = 0;     // CONV: GemmArgs::tiny_sum, ...
     int filter_exp = 0;        // ... filter_exp
-    int halves_exp = 0;        // ... and halves_exp
+    int halves_exp = 0;        // ... halves_exp ...
+    float halves_least = 0;    // ... and halves_least
     bool halves = false;       // CONV: the weights are multiplied in halves where sums are long (o_halves exists)
     bool select = false; // CONV: maps small enough for the GEMM (and the pooling after it) to pick their
                          // positions from the update maps themselves; index lists are then only
@@ -441,11 +443,24 @@ bool row_suits_halves(const float *x, int n, float least)
     return !bad;
 }
 
+// The sum of the magnitudes of a row of n values.
+double magnitudes(const float *x, int n)
+{
+    float sum[16] = {}; // rows are whole slices of 32
+    for (int i = 0; i < n; i += 16)
+        for (int e = 0; e < 16; ++e) sum[e] += std::fabs(x[i + e]);
+    double all = 0;
+    for (float v : sum) all += v;
+    return all;
+}
+
 // Filter matrix K (Section 3) re-laid-out for the gather: row o, column k = (j*kw + i)*Cs + c, as
 // float32 or bfloat16 (round to nearest even), row by row or in fragments.  Returns whether its rows suit halves (largest:
-// of the weights).
-bool build_filter_matrix(const Op &op, int dtype, const float *w, std::vector<unsigned char> &bytes, float largest)
+// of the weights); then rows_least holds gemm_halves_least() of each.
+bool build_filter_matrix(const Op &op, int dtype, const float *w, std::vector<unsigned char> &bytes, float largest,
+                         std::vector<float> &rows_least)
 {
+    rows_least.assign(op.Mpad, 0.0f);
     bytes.assign(cbk::gemm_filter_bytes(dtype, op.Mpad, op.Kpad), 0);
     const bool fragments = cbk::gemm_filter_in_fragments(dtype, op.Mpad, op.Kpad);
     unsigned short *b = reinterpret_cast<unsigned short *>(bytes.data());
@@ -467,6 +482,7 @@ bool build_filter_matrix(const Op &op, int dtype, const float *w, std::vector<un
             continue;
         }
         suits = suits && row_suits_halves(row.data(), op.Kpad, least);
+        if (suits) rows_least[o] = cbk::gemm_halves_least(std::ldexp(magnitudes(row.data(), op.Kpad), op.halves_exp - op.filter_exp));
         bf16_parts(row.data(), op.Kpad, fragments ? parts : 1, part.data(), part.data() + op.Kpad, part.data() + 2 * (size_t)op.Kpad);
         if (!fragments) {
             memcpy(b + (size_t)o * op.Kpad, part.data(), (size_t)op.Kpad * 2);
@@ -748,6 +764,7 @@ int enqueue_frame(cbinfer_state *s, const float *frame, float *out)
             a.filter_exp = op.filter_exp;
             a.wt_halves = op.halves ? s->at<void>(op.o_halves) : nullptr;
             a.halves_exp = op.halves_exp;
+            a.halves_least = op.halves_least;
             a.partial = s->at<float>(P.o_partial);
             a.tickets = s->at<int>(P.o_tickets);
             a.grid = op.gemm_grid;
@@ -881,7 +898,7 @@ static cbinfer_state *create_state(const cbinfer_network *net, const Plan &P, ch
         // (the static workspace keeps whatever the state before this one left in it)
         HIP_TRY(hipMemsetAsync(s->ws, 0, P.bytes, s->stream));
         std::vector<unsigned char> wt;
-        std::vector<float> bias;
+        std::vector<float> bias, rows_least;
         std::vector<int2> taps;
         for (size_t l = 0; l < P.ops.size(); ++l) {
             Op &op = s->plan.ops[l];
@@ -896,16 +913,20 @@ static cbinfer_state *create_state(const cbinfer_network *net, const Plan &P, ch
                 if (m > 0.0f) op.halves_exp = kHalvesTop - std::ilogb(m);
                 largest = m;
             }
-            op.halves = build_filter_matrix(op, P.dtype, static_cast<const float *>(L.weight), wt, largest);
+            op.halves = build_filter_matrix(op, P.dtype, static_cast<const float *>(L.weight), wt, largest, rows_least);
             bias.assign(op.Mpad, 0.0f);
             if (L.bias)
                 for (int o = 0; o < op.M; ++o) bias[o] = L.bias[o];
             build_taps(op, P.dtype, taps);
             // the staging vectors are reused for the next layer: wait for the copies first
             HIP_TRY(hipMemcpyAsync(s->at<void>(op.o_wt), wt.data(), wt.size(), hipMemcpyHostToDevice, s->stream));
-            if (op.halves)
+            if (op.halves) {
                 HIP_TRY(cbk::gemm_make_halves(s->stream, s->at<void>(op.o_wt), s->at<void>(op.o_halves), op.Mpad, op.Kpad,
                                               op.halves_exp - op.filter_exp));
+                op.halves_least = *std::max_element(rows_least.begin(), rows_least.end());
+                HIP_TRY(hipMemcpyAsync(s->at<float>(op.o_halves) + (size_t)op.Mpad * op.Kpad, rows_least.data(), rows_least.size() * 4,
+                                       hipMemcpyHostToDevice, s->stream));
+            }
             HIP_TRY(hipMemcpyAsync(s->at<float>(op.o_bias), bias.data(), bias.size() * 4, hipMemcpyHostToDevice, s->stream));
             HIP_TRY(hipMemcpyAsync(s->at<int2>(op.o_taps), taps.data(), taps.size() * sizeof(int2), hipMemcpyHostToDevice, s->stream));
             HIP_TRY(hipStreamSynchronize(s->stream));

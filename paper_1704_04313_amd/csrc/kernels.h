@@ -256,7 +256,9 @@ struct GemmArgs {
     unsigned tiny_sum;
     int filter_exp;     // float32 in parts: the filter matrix holds the weights times 2^filter_exp
     const void *wt_halves; // null, or (only where gemm_filter_halves()) the filter matrix in float16 halves as well
-    int halves_exp;        // ... of the weights times 2^halves_exp
+    int halves_exp;        // ... of the weights times 2^halves_exp, and behind it
+                           // gemm_halves_least() for each of the Mpad rows
+    float halves_least;    // the largest of these
     float *partial;     // scratch for partial accumulators, gemm_partial_bytes() bytes
     int *tickets;       // gemm_ticket_bytes(grid) bytes, zero before the first launch (each launch
                         // leaves them zero again)
@@ -289,6 +291,11 @@ constexpr int kFilterPartStride = 512;
 // add up to the weight times 2^halves_exp to 23 bits.  Needs dtype, Mpad, Kpad and max_pixels; grid: workgroups at most.
 bool gemm_filter_halves(const GemmArgs &a, int grid);
 size_t gemm_halves_bytes(int Mpad, int Kpad);
+// Sums in halves whose magnitude is below this are formed again, in units of a weight's halves (2^-halves_exp) times those of a
+// pixel's; magnitudes: of a row's weights, added up, in the former.  A pixel's halves are off by 2^-37 at most beyond what is relative
+// to the value, and the product of second halves that is left out by as much, so a sum is off by at most 2^-36 times the
+// magnitudes, whatever the pixels are.
+float gemm_halves_least(double magnitudes);
 // ... from the bfloat16 parts of the weights times 2^(halves_exp - shift).
 hipError_t gemm_make_halves(hipStream_t st, const void *wt, void *wt_halves, int Mpad, int Kpad, int shift);
 // GemmArgs::tiny_sum for rows of K weights of at most that magnitude.  The parts of a pixel value are off by half the

@@ -871,28 +871,31 @@ __device__ __forceinline__ Parts split_fragment(const floatx4 x0, const floatx4 
 }
 
 // float32 in halves: a value times a power of two as the sum of two float16 (11 bits each and the sign of the second: all
-// but one of float32's 24), for the three products hi hi, hi lo and lo hi -- half of what the bfloat16 parts take.  An
-// instruction per value for each half: v_fma_mix multiplies, subtracts and rounds at once.  (As a multiplication, two
-// conversions and a difference, 3 a value, 64->256 7x7 at 320x180 took 302 us, now 267: vector instructions add to the
-// MFMAs of a SIMD, see below.)  The compiler does not know what the asm writes to; whoever multiplies the halves at once
-// waits two cycles first.
-// Below 2^-2 of the scaled value the second half ends at the smallest float16, 2^-24: precision is relative to the
-// largest value of a scale, down to 2^-40 of it.
+// but one of float32's 24), for the three products hi hi, hi lo and lo hi -- half of what the bfloat16 parts take.  The
+// second is held times 2^kHalfLift, so that it does not end at the smallest float16, 2^-24, but at 2^-36 of where
+// the first does: of a largest value between 2^13 and 2^15, values down to 2^-14 have all their bits, and what lies below is
+// off by 2^-37 at most.  (Without the lift values below 2^-2 lost bits: a channel 2^-20 of its brightest neighbour,
+// which its filter does not see, came out 4.4e-6 off, one of 2^-40 as zero.)  Three instructions per value: the scale, and
+// v_fma_mix, which multiplies, subtracts and rounds at once, for each half.  The compiler does not know what the asm writes to;
+// whoever multiplies the halves at once waits two cycles first.
+static constexpr int kHalfLift = 12;
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 struct Halves {
     uintx4 hi, lo;
 };
+// scale: the power of two, times 2^kHalfLift
 __device__ __forceinline__ Halves split_halves(const floatx4 x0, const floatx4 x1, const float scale)
 {
+    const float up = 1 << kHalfLift, down = 1.0f / (1 << kHalfLift);
     Halves p;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const float a = i < 2 ? x0[2 * i] : x1[2 * i - 4], b = i < 2 ? x0[2 * i + 1] : x1[2 * i - 3];
+        const float a = (i < 2 ? x0[2 * i] : x1[2 * i - 4]) * scale, b = (i < 2 ? x0[2 * i + 1] : x1[2 * i - 3]) * scale;
         unsigned h, l;
-        asm("v_fma_mixlo_f16 %0, %1, %3, 0\n\tv_fma_mixhi_f16 %0, %2, %3, 0" : "=&v"(h) : "v"(a), "v"(b), "s"(scale));
-        asm("v_fma_mixlo_f16 %0, %1, %3, -%4 op_sel_hi:[0,0,1]\n\tv_fma_mixhi_f16 %0, %2, %3, -%4 op_sel:[0,0,1] op_sel_hi:[0,0,1]"
+        asm("v_fma_mixlo_f16 %0, %1, %3, 0\n\tv_fma_mixhi_f16 %0, %2, %3, 0" : "=&v"(h) : "v"(a), "v"(b), "s"(down));
+        asm("v_fma_mixlo_f16 %0, -%4, %3, %1 op_sel_hi:[1,0,0]\n\tv_fma_mixhi_f16 %0, -%4, %3, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]"
             : "=&v"(l)
-            : "v"(a), "v"(b), "s"(scale), "v"(h));
+            : "v"(a), "v"(b), "s"(up), "v"(h));
         p.hi[i] = h;
         p.lo[i] = l;
     }
@@ -907,17 +910,11 @@ __device__ __forceinline__ float largest(float m, const floatx4 x0, const floatx
     asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(x1[2]), "v"(x1[3]));
     return m;
 }
-// The largest of the 64 lanes' numbers (bits of magnitudes compare like integers), moved as in wave_inclusive_sum.
-__device__ __forceinline__ unsigned wave_largest(unsigned x)
+// A pixel's values are in lanes 16 apart: the largest of theirs.
+__device__ __forceinline__ float pixel_largest(float m)
 {
-    auto with = [](unsigned x, unsigned y) { return x > y ? x : y; };
-    x = with(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false));
-    x = with(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false));
-    x = with(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false));
-    x = with(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false));
-    x = with(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false));
-    x = with(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false));
-    return (unsigned)__builtin_amdgcn_readlane((int)x, 63);
+    m = fmaxf(m, __shfl_xor(m, 16));
+    return fmaxf(m, __shfl_xor(m, 32));
 }
 
 // Where value (row, k) of a filter matrix in fragments lies, in bfloat16 values from its start; float32:
@@ -933,10 +930,13 @@ __host__ __device__ inline size_t filter_fragment(int bm, int nk, int row, int k
     return ((((size_t)mt * nk + kc) * (bm / 16) + ct) * kFilterParts<DT> + part) * (kFragBytes / 2) + (lk * 16 + row % 16) * 8 + e;
 }
 
-// float32 in halves: the exponent that a scale gives the largest value; slices until leading sums are folded; how far a
-// later slice's values may be above the first ones'; how small a pixel's largest scaled value may be.
-static constexpr int kHalfTop = 13, kHalfChunk = 4, kHalfJump = 16;
-static constexpr float kHalfMost = 0.5f;
+// float32 in halves: the exponent that a scale gives the largest value; the largest scale; the exponent of the largest value that
+// it can have (half a unit of the last place of the first half is then 2^3, 2^15 when lifted); slices until leading sums are folded.
+static constexpr int kHalfTop = 13, kHalfMostShift = 126 - kHalfLift, kHalfLimit = 15, kHalfChunk = 4;
+// Sums that the halves' absolute errors may reach beyond 2^-kHalfBits of are formed again (gemm_halves_least).  That is if all of
+// them have one sign; of either sign, they are a twentieth of it.  Of pixels of one scale it is one sum in several millions: with 2^-18
+// and 2^-20 64->256 7x7 on 320x180 takes 288 us, without any 290, with 2^-21 292.
+static constexpr int kHalfBits = 20;
 
 // Parts of a shared tile's sum that the finishing wave has under way, by its accumulators.
 template <int ACC>
@@ -950,7 +950,9 @@ static constexpr int kPartsUnderWay = ACC <= 4 ? 4 : 2;
 // together from their parts; channels behind the last one of a packed pixel count as zero.  Bound by putting the
 // filter values together, vector instructions that add to the MFMAs, so a value serves all pixels of the sub-tile,
 // and by the loads, which are issued one group ahead; see the figures where it is called.
-template <int BM, int TP, int TC>
+// FOLD: the products of two slices are added up before they join the sums, whose roundings are then as few as those of the
+// halves that they replace.
+template <int BM, int TP, int TC, bool FOLD>
 __device__ __forceinline__ void plain_sums(const GemmArgs &a, int kc0, int kc1, const char *wt, const int *list, floatx4 (&sum)[TC][TP])
 {
     int lane = threadIdx.x & 63;
@@ -971,6 +973,30 @@ __device__ __forceinline__ void plain_sums(const GemmArgs &a, int kc0, int kc1, 
     for (int j = 0; j < TC; ++j)
 #pragma unroll
         for (int i = 0; i < TP; ++i) sum[j][i] = (floatx4){0.f, 0.f, 0.f, 0.f};
+    floatx4 part[FOLD ? TC : 1][TP];
+    auto &to = [&]() -> floatx4(&)[TC][TP] {
+        if constexpr (FOLD)
+            return part;
+        else
+            return sum;
+    }();
+    auto fold = [&] {
+        if constexpr (FOLD) {
+#pragma unroll
+            for (int j = 0; j < TC; ++j)
+#pragma unroll
+                for (int i = 0; i < TP; ++i) {
+                    sum[j][i] += part[j][i];
+                    part[j][i] = (floatx4){0.f, 0.f, 0.f, 0.f};
+                }
+        }
+    };
+    if constexpr (FOLD) {
+#pragma unroll
+        for (int j = 0; j < TC; ++j)
+#pragma unroll
+            for (int i = 0; i < TP; ++i) part[j][i] = (floatx4){0.f, 0.f, 0.f, 0.f};
+    }
     // G groups of four units are loaded together: a slice, as wide as loads come, or half of one where two tiles of
     // pixels would not leave two of channels their registers (with whole slices and one tile of channels 16->64
     // 7x7 on 640 x 900 positions that are all NaN 1190 us, now 1024; 64->32 5x5 on 320 x 240 197 and 167, with one NaN
@@ -1006,14 +1032,14 @@ __device__ __forceinline__ void plain_sums(const GemmArgs &a, int kc0, int kc1, 
     auto multiply = [&](const Slice &v) {
 #pragma unroll
         for (int e = 0; e < 4 * G; ++e) {
-            auto part = [&](int j, int p) { return bf16_value((unsigned short)((&v.w[j][p].x)[e >> 1] >> (e & 1 ? 16 : 0))); };
+            auto value = [&](int j, int p) { return bf16_value((unsigned short)((&v.w[j][p].x)[e >> 1] >> (e & 1 ? 16 : 0))); };
 #pragma unroll
             for (int j = 0; j < TC; ++j)
 #pragma unroll
                 for (int i = 0; i < TP; ++i)
-                    sum[j][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                        __builtin_ldexpf(part(j, 0) + (part(j, 1) + part(j, 2)), -a.filter_exp),
-                        v.c[e >> 2] + (e & 3) < a.pix_words ? v.px[e >> 2][i][e & 3] : 0.f, sum[j][i], 0, 0, 0);
+                    to[j][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                        __builtin_ldexpf(value(j, 0) + (value(j, 1) + value(j, 2)), -a.filter_exp),
+                        v.c[e >> 2] + (e & 3) < a.pix_words ? v.px[e >> 2][i][e & 3] : 0.f, to[j][i], 0, 0, 0);
         }
     };
     Slice v0, v1;
@@ -1026,9 +1052,47 @@ __device__ __forceinline__ void plain_sums(const GemmArgs &a, int kc0, int kc1, 
         multiply(v0);
         load(v0, kc + 2 < end ? kc + 2 : kc);
         multiply(v1);
+        fold();
     }
     if (kc < end) multiply(v0);
+    fold();
 }
+
+// One such sum, of output position g and a row of the filter matrix (from its beginning, wt), by the whole wave: a unit per lane and
+// step, in ascending order, the lanes' sums by halving.  (64->256 7x7 on 80x60 with one of them in the launch 44 us, without 42,
+// by plain_sums 62.)
+template <int BM>
+__device__ __forceinline__ float plain_sum(const GemmArgs &a, int kc0, int kc1, const char *wt, int g, int row)
+{
+    const int lane = threadIdx.x & 63, nk = a.dNk.d;
+    const float *x = static_cast<const float *>(a.x);
+    const int st = fast_div(g < 0 ? 0 : g, a.dNo), q = g < 0 ? 0 : g - st * a.No, qy = fast_div(q, a.dWo), qx = q - qy * a.Wo;
+    const int iy0 = g < 0 ? -(1 << 28) : qy * a.stride - a.pad, ix0 = qx * a.stride - a.pad;
+    const int base = g < 0 ? 0 : ((st * a.H + iy0) * a.W + ix0) * a.pix_words;
+    float sum = 0.f;
+#pragma unroll 4
+    for (int unit = kc0 * KU + lane; unit < kc1 * KU; unit += 64) {
+        const int tap = fast_div(unit, a.dVin), cu = unit - tap * a.dVin.d;
+        const int tj = fast_div(tap, a.dKw), ti = tap - tj * a.kw;
+        const bool ok = tj < a.kh && (unsigned)(iy0 + tj) < (unsigned)a.H && (unsigned)(ix0 + ti) < (unsigned)a.W;
+        const floatx4 px = *reinterpret_cast<const floatx4_a4 *>(
+            x + (ok ? (unsigned)(base + (tj * a.W + ti) * a.pix_words + cu * 4) : (unsigned)a.zero_word));
+        uint2 w[3];
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+            w[p] = *reinterpret_cast<const uint2 *>(wt + filter_fragment<kF32>(BM, nk, row, unit * 4) * 2 + p * kFragBytes);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            auto value = [&](int p) { return bf16_value((unsigned short)((&w[p].x)[e >> 1] >> (e & 1 ? 16 : 0))); };
+            sum = fmaf(__builtin_ldexpf(value(0) + (value(1) + value(2)), -a.filter_exp), cu * 4 + e < a.pix_words ? px[e] : 0.f, sum);
+        }
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d);
+    return sum;
+}
+// Sums of two channel tiles of a wave up to which they are formed one by one.
+static constexpr int kFewSums = 16;
 
 // BM x BN workgroup tile; the consumer waves are arranged WM (channels) x WN (pixels).
 //
@@ -1115,7 +1179,7 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
         const int pt = small_div(seg.tile, mtiles), mt = seg.tile - pt * mtiles;
         const bool partial = (kc1 - kc0) != nk;
         floatx4 acc[TC][TP];
-        bool again = false; // float32 in halves: whether the wave's sums have to be formed again
+        float unit[TP]; // float32 in halves: what a unit of scaled pixel values is, 0 for pixels of zeros
         {
 #pragma unroll
             for (int j = 0; j < TC; ++j)
@@ -1204,43 +1268,42 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                     w[set][0] = read_filter(sl, j, 0);
                     w[set][1] = read_filter(sl, j, 1);
                 };
-                // The power of two that the wave's pixels are multiplied with, from the largest value of the first slice: it
-                // becomes 2^13 to 2^14.  A slice with a value beyond `limit` has the sums so far folded and another
-                // power from then on.
-                int shift;
-                float scale, limit, unscale, most[TP];
-                auto set_scale = [&](unsigned bits) {
-                    const int e = (int)(bits >> 23) - 127;
-                    shift = kHalfTop - e < 126 ? kHalfTop - e : 126;
-                    scale = __uint_as_float((unsigned)(127 + shift) << 23);
-                    limit = __builtin_ldexpf(65504.f, -shift);
-                    unscale = __builtin_ldexpf(1.f, -shift); // the weights' power of two is taken off at the end
+                // The power of two that a pixel's values are multiplied with, from the largest in its first slice: that becomes
+                // 2^kHalfTop to twice as much.  A slice with a value beyond 2^kHalfLimit has the sums so far folded and another
+                // power from then on.  A power for each pixel: how bright its neighbours are is nothing to it.
+                float scale[TP], most[TP]; // a power of two, with kHalfLift; the largest of this lane's values
+                auto set_scale = [&] {
+#pragma unroll
+                    for (int i = 0; i < TP; ++i) {
+                        const int shift = kHalfTop + 127 - (int)(__float_as_uint(pixel_largest(most[i])) >> 23);
+                        scale[i] = __uint_as_float((unsigned)(127 + kHalfLift + (shift < kHalfMostShift ? shift : kHalfMostShift)) << 23);
+                    }
                 };
-                auto fold = [&](floatx4(&from)[TC][TP]) {
+                auto unscale = [&](int i, int lift) { // one through the power of two, and through 2^lift
+                    return __uint_as_float(((unsigned)(254 + kHalfLift - lift) << 23) - __float_as_uint(scale[i]));
+                };
+                auto fold = [&](floatx4(&from)[TC][TP], int lift) {
 #pragma unroll
                     for (int j = 0; j < TC; ++j)
 #pragma unroll
                         for (int i = 0; i < TP; ++i) {
 #pragma unroll
-                            for (int e = 0; e < 4; ++e) acc[j][i][e] = fmaf(from[j][i][e], unscale, acc[j][i][e]);
+                            for (int e = 0; e < 4; ++e) acc[j][i][e] = fmaf(from[j][i][e], unscale(i, lift), acc[j][i][e]);
                             from[j][i] = (floatx4){0.f, 0.f, 0.f, 0.f};
                         }
                 };
                 read_tile(0, slot, 0);
                 {
                     floatx4 raw[TP][2];
-                    unsigned top = 0;
 #pragma unroll
                     for (int i = 0; i < TP; ++i) {
                         raw[i][0] = read_pixels(slot, 0, i);
                         raw[i][1] = read_pixels(slot, 1, i);
-                        most[i] = 0.f;
-                        most[i] = largest(most[i], raw[i][0], raw[i][1]);
-                        top = max(top, __float_as_uint(most[i]));
+                        most[i] = largest(0.f, raw[i][0], raw[i][1]);
                     }
-                    set_scale(wave_largest(top));
+                    set_scale();
 #pragma unroll
-                    for (int i = 0; i < TP; ++i) x0[i] = split_halves(raw[i][0], raw[i][1], scale);
+                    for (int i = 0; i < TP; ++i) x0[i] = split_halves(raw[i][0], raw[i][1], scale[i]);
                     asm volatile("s_nop 3");
                 }
                 auto step = [&](Halves(&x)[TP], Halves(&nx)[TP], const bool more) {
@@ -1280,7 +1343,7 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                         for (int i = 0; i < TP; ++i)
                             if (j == (i + 1 < TC ? i + 1 : TC - 1)) {
                                 if (more) most[i] = largest(most[i], raw[i][0], raw[i][1]); // else the slot holds nothing of this tile
-                                nx[i] = split_halves(raw[i][0], raw[i][1], scale);
+                                nx[i] = split_halves(raw[i][0], raw[i][1], scale[i]);
                             }
                         __builtin_amdgcn_sched_barrier(0);
                     }
@@ -1300,43 +1363,31 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                             step(x1, x0, kc + 1 < kc1);
                         else
                             step(x0, x1, kc + 1 < kc1);
-                        float top = most[0];
+                        bool beyond = false;
 #pragma unroll
-                        for (int i = 1; i < TP; ++i) top = fmaxf(top, most[i]);
-                        over = __any(top > limit);
+                        for (int i = 0; i < TP; ++i) beyond |= most[i] * scale[i] > (float)(1 << (kHalfLimit + kHalfLift));
+                        over = __any(beyond);
                         if (++kc == kc1 || over) break;
                     }
-                    fold(lead);
+                    fold(lead, 0);
                     if (kc == kc1) break;
                     if (__builtin_expect(over, 0)) { // the next slice needs another power of two
-                        fold(cor);
-                        unsigned top = __float_as_uint(most[0]);
+                        fold(cor, kHalfLift);
+                        set_scale();
 #pragma unroll
-                        for (int i = 1; i < TP; ++i) top = max(top, __float_as_uint(most[i]));
-                        const int before = shift;
-                        set_scale(wave_largest(top));
-                        again |= before < 126 && before - shift > kHalfJump; // 126: nothing but zeros so far
-#pragma unroll
-                        for (int i = 0; i < TP; ++i) x0[i] = split_halves(read_pixels(slot, 0, i), read_pixels(slot, 1, i), scale);
+                        for (int i = 0; i < TP; ++i) x0[i] = split_halves(read_pixels(slot, 0, i), read_pixels(slot, 1, i), scale[i]);
                         asm volatile("s_nop 3");
                     }
                 }
-                fold(cor);
+                fold(cor, kHalfLift);
 #pragma unroll
                 for (int j = 0; j < TC; ++j)
 #pragma unroll
                     for (int i = 0; i < TP; ++i)
 #pragma unroll
                         for (int e = 0; e < 4; ++e) acc[j][i][e] = __builtin_ldexpf(acc[j][i][e], -a.halves_exp);
-                // A pixel's values below kHalfMost all of them, but not zero, lose bits that float32 has: the wave forms its sums
-                // again.  (So does one that met a jump of 2^kHalfJump: zero weights at the large values leave sums of the others.)
 #pragma unroll
-                for (int i = 0; i < TP; ++i) {
-                    float m = most[i]; // a pixel's values are in lanes 16 apart
-                    m = fmaxf(m, __shfl_xor(m, 16));
-                    m = fmaxf(m, __shfl_xor(m, 32));
-                    if (__any(m > 0.f && m * scale < kHalfMost)) again = true;
-                }
+                for (int i = 0; i < TP; ++i) unit[i] = pixel_largest(most[i]) > 0.f ? unscale(i, 0) : 0.f;
                 // found anew rather than kept across the K loop, which needs all registers
                 unsigned thread = threadIdx.x;
                 asm volatile("" : "+v"(thread));
@@ -1438,30 +1489,79 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
             // 11 150 us for that one NaN, 25 700 for the full map).  The 128-channel tile in a 2 x 4 arrangement of waves
             // took 428 us for the map of nothing else, as a filter value put together served two tiles of pixels, and 120
             // and 425 for the others.
+            // In halves these are, of pixels that are not all zero, the sums below GemmArgs::halves_least or, looked at more
+            // closely, what is stored behind the halves for their rows.
             float z = 0.f;
             unsigned least = ~0u;
             auto size = [](float v) { return (__float_as_uint(v) << 1) - 1u; }; // grows with |v|; largest for zero
+            bool again = false;
 #pragma unroll
-            for (int j = 0; j < TC; ++j)
+            for (int i = 0; i < TP; ++i) {
+                float lowest = __builtin_inff();
 #pragma unroll
-                for (int i = 0; i < TP; ++i)
+                for (int j = 0; j < TC; ++j)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         z = fmaf(acc[j][i][e], 0.f, z);
-                        least = min(least, size(acc[j][i][e]));
+                        if constexpr (DT == kF32)
+                            least = min(least, size(acc[j][i][e]));
+                        else
+                            lowest = fminf(lowest, fabsf(acc[j][i][e]));
                     }
-            if (__builtin_expect(__any(z != 0.f || (DT == kF32 ? least < a.tiny_sum : again)), 0)) { // NaN compares unequal
+                if constexpr (DT == kF32Halves) again |= lowest < __builtin_ldexpf(a.halves_least * unit[i], -a.halves_exp);
+            }
+            if constexpr (DT == kF32) again = least < a.tiny_sum;
+            if (__builtin_expect(__any(z != 0.f || again), 0)) { // NaN compares unequal
                 const char *wt = static_cast<const char *>(a.wt) +
                                  (((size_t)mt * nk + kc0) * (BM / 16) + wch0 / 16) * (3 * kFragBytes);
                 // two channel tiles at a time: more would not leave their operands registers
                 constexpr int CJ = TC % 2 == 0 ? 2 : 1;
-                float keep_below = again ? -1.f : __builtin_inff(); // in halves: of magnitudes, those that stay
-                asm("" : "+v"(keep_below)); // a condition on `again` would be a branch per sum
                 static_assert(TC % CJ == 0, "whole steps");
 #pragma unroll 1
                 for (int j0 = 0; j0 < TC; j0 += CJ) {
+                    float4 row_least[CJ]; // of this lane's rows
+                    // whether a sum does not stand
+                    auto fails = [&](float v, int j, int i, int e) {
+                        if constexpr (DT == kF32) return !(fabsf(v) < __builtin_inff()) || size(v) < a.tiny_sum;
+                        const float t = __builtin_ldexpf((&row_least[j % CJ].x)[e] * unit[i], -a.halves_exp);
+                        return !(fabsf(v) < __builtin_inff()) || fabsf(v) < t;
+                    };
+                    if constexpr (DT == kF32Halves) { // most often it is one sum of the tile
+                        const float *row = static_cast<const float *>(a.wt_halves) + (size_t)a.Mpad * a.Kpad + mt * BM + wch0 + j0 * 16 + lk * 4;
+#pragma unroll
+                        for (int j = 0; j < CJ; ++j) row_least[j] = *reinterpret_cast<const float4 *>(row + j * 16);
+                        static_assert(TP == 1, "sums are numbered by channel tile and channel");
+                        unsigned failed = 0;
+#pragma unroll
+                        for (int j = 0; j < TC; ++j) {
+                            if (j / CJ != j0 / CJ) continue;
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) failed |= fails(acc[j][0][e], j, 0, e) ? 1u << (j % CJ * 4 + e) : 0u;
+                        }
+                        int count = 0;
+#pragma unroll
+                        for (int bit = 0; bit < CJ * 4; ++bit) count += __builtin_popcountll(__ballot(failed >> bit & 1));
+                        if (count <= kFewSums) {
+                            for (uint64_t lanes; (lanes = __ballot(failed != 0)) != 0;) {
+                                const int from = __builtin_ctzll(lanes);
+                                const int bit = __builtin_ctz(__builtin_amdgcn_readlane((int)failed, from));
+                                const int g = __builtin_amdgcn_readfirstlane(list[wpx0 + (from & 15)]);
+                                const float v = plain_sum<BM>(a, kc0, kc1, static_cast<const char *>(a.wt), g,
+                                                              mt * BM + wch0 + (j0 + (bit >> 2)) * 16 + (from >> 4) * 4 + (bit & 3));
+#pragma unroll
+                                for (int j = 0; j < TC; ++j) {
+                                    if (j / CJ != j0 / CJ) continue;
+#pragma unroll
+                                    for (int e = 0; e < 4; ++e)
+                                        if (bit == j % CJ * 4 + e && lane == from) acc[j][0][e] = v;
+                                }
+                                if (lane == from) failed &= failed - 1;
+                            }
+                            continue;
+                        }
+                    }
                     floatx4 sum[CJ][TP];
-                    plain_sums<BM, TP, CJ>(a, kc0, kc1, wt + j0 * (3 * kFragBytes), list + wpx0, sum);
+                    plain_sums<BM, TP, CJ, DT == kF32Halves>(a, kc0, kc1, wt + j0 * (3 * kFragBytes), list + wpx0, sum);
 #pragma unroll
                     for (int j = 0; j < TC; ++j) {
                         if (j / CJ != j0 / CJ) continue;
@@ -1471,8 +1571,7 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
                             for (int e = 0; e < 4; ++e) {
                                 float v = acc[j][i][e];
                                 asm("" : "+v"(v)); // compared anew: the results from above would all be kept in registers
-                                if (DT == kF32 ? !(fabsf(v) < __builtin_inff()) || size(v) < a.tiny_sum : !(fabsf(v) < keep_below))
-                                    acc[j][i][e] = sum[j % CJ][i][e];
+                                if (fails(v, j, i, e)) acc[j][i][e] = sum[j % CJ][i][e];
                             }
                     }
                 }
@@ -1565,7 +1664,8 @@ __device__ __forceinline__ void gemm_gather_body(const GemmArgs &a, const int n,
             // stores of those accumulators (the compiler cannot move a load across a store to the
             // same map, and one round trip to memory per accumulator would line up at the very end
             // of the kernel).  Accumulator q covers channels of block q / TP at the positions of block q % TP.
-            constexpr int CH = TC * TP < kEpiChunk ? TC * TP : kEpiChunk;
+            // (Eight accumulators in halves: two at a time, as four spill.)
+            constexpr int CH = DT == kF32Halves && TC > 4 ? 2 : TC * TP < kEpiChunk ? TC * TP : kEpiChunk;
             static_assert((TC * TP) % CH == 0, "whole chunks");
 #pragma unroll
             for (int q0 = 0; q0 < TC * TP; q0 += CH) {
@@ -1712,7 +1812,7 @@ __global__ void make_halves_kernel(const uintx4 *__restrict__ wt, uintx4 *__rest
             auto value = [&](int p) { return bf16_value((unsigned short)(part[p][q] >> (16 * e))); };
             const float v = __builtin_ldexpf(value(0) + (value(1) + value(2)), shift);
             h[e] = (_Float16)v;
-            l[e] = fabsf(v) < __builtin_inff() ? (_Float16)(v - (float)h[e]) : (_Float16)0.f;
+            l[e] = (_Float16)((v - (float)h[e]) * (1 << kHalfLift));
         }
         hi[q] = __builtin_bit_cast(unsigned, h);
         lo[q] = __builtin_bit_cast(unsigned, l);
@@ -2158,7 +2258,9 @@ bool gemm_filter_halves(const GemmArgs &a, int grid)
     return halves_suit(bm, tiles, tiles / grid, a.Kpad / gemm_k_multiple(kF32), grid);
 }
 
-size_t gemm_halves_bytes(int Mpad, int Kpad) { return (size_t)Mpad * Kpad * 4; }
+size_t gemm_halves_bytes(int Mpad, int Kpad) { return (size_t)Mpad * Kpad * 4 + (size_t)Mpad * 4; }
+
+float gemm_halves_least(double magnitudes) { return (float)std::ldexp(magnitudes, kHalfBits - 36); }
 
 hipError_t gemm_make_halves(hipStream_t st, const void *wt, void *wt_halves, int Mpad, int Kpad, int shift)
 {
