@@ -425,33 +425,32 @@ int filter_exponent(float largest, bool tiny)
     return e;
 }
 
-// Whether the halves of a row of n weights carry them: they end at 2^-40 of the layer's largest, so of eight in a row (of
-// consecutive channels) the largest must be at least `least`, 2^-24 of that, or all of them zero.  (Sums to which only
-// smaller weights add would lose bits; of a million normally distributed weights the least is 2^-22 of the largest, but not
-// eight in a row.)
 constexpr int kHalvesTop = 14; // the exponent of the largest weight in halves
-bool row_suits_halves(const float *x, int n, float least)
+// Of a row of n weights: the sum of their magnitudes, and how many are not zero but below `whole`.
+struct RowScale {
+    double magnitudes = 0;
+    int small = 0;
+};
+RowScale row_scale(const float *x, int n, float whole)
 {
-    int bound, bad = 0; // bits of magnitudes compare like integers
-    memcpy(&bound, &least, 4);
-    for (int i = 0; i < n; i += 8) { // rows are whole slices of 32
-        int m = 0, u[8];
-        memcpy(u, x + i, 32);
-        for (int e = 0; e < 8; ++e) m = std::max(m, u[e] & 0x7fffffff);
-        bad |= m - 1 < bound - 1 && m > 0;
+    constexpr int B = 16; // rows are whole slices of 32
+    float sum[B] = {};
+    int small[B] = {}, bound; // bits of magnitudes compare like integers
+    memcpy(&bound, &whole, 4);
+    for (int i = 0; i < n; i += B) {
+        int u[B];
+        memcpy(u, x + i, sizeof u);
+        for (int e = 0; e < B; ++e) {
+            sum[e] += std::fabs(x[i + e]);
+            small[e] += (u[e] & 0x7fffffff) != 0 && (u[e] & 0x7fffffff) < bound;
+        }
     }
-    return !bad;
-}
-
-// The sum of the magnitudes of a row of n values.
-double magnitudes(const float *x, int n)
-{
-    float sum[16] = {}; // rows are whole slices of 32
-    for (int i = 0; i < n; i += 16)
-        for (int e = 0; e < 16; ++e) sum[e] += std::fabs(x[i + e]);
-    double all = 0;
-    for (float v : sum) all += v;
-    return all;
+    RowScale r;
+    for (int e = 0; e < B; ++e) {
+        r.magnitudes += sum[e];
+        r.small += small[e];
+    }
+    return r;
 }
 
 // Filter matrix K (Section 3) re-laid-out for the gather: row o, column k = (j*kw + i)*Cs + c, as
@@ -473,7 +472,7 @@ bool build_filter_matrix(const Op &op, int dtype, const float *w, std::vector<un
     for (size_t v = 0; v < place.size(); ++v)
         place[v] = cbk::gemm_filter_fragment(dtype, op.Mpad, op.Kpad, 0, (int)v * eu);
     bool suits = op.o_halves != SIZE_MAX && largest > 0.0f;
-    const float least = (float)std::ldexp((double)largest, op.filter_exp - 24);
+    const float whole = (float)std::ldexp(1.0, cbk::kHalvesWhole - op.halves_exp + op.filter_exp);
     for (int o = 0; o < op.M; ++o) {
         for (int c = 0; c < op.C; ++c)
             for (int t = 0; t < area; ++t) row[(size_t)t * op.Cs + c] = w[((size_t)o * op.C + c) * area + t] * scale;
@@ -481,8 +480,15 @@ bool build_filter_matrix(const Op &op, int dtype, const float *w, std::vector<un
             memcpy(f + (size_t)o * op.Kpad, row.data(), (size_t)op.Kpad * 4);
             continue;
         }
-        suits = suits && row_suits_halves(row.data(), op.Kpad, least);
-        if (suits) rows_least[o] = cbk::gemm_halves_least(std::ldexp(magnitudes(row.data(), op.Kpad), op.halves_exp - op.filter_exp));
+        if (suits) {
+            // A row keeps the parts (and with it the layer) if its small weights are as much of a reason to form sums again as its
+            // pixels are.  Normally distributed weights, 2^-29 of the largest of which is needed for it, never come near that in
+            // rows that reach 2^-10 of the layer's largest.
+            const RowScale r = row_scale(row.data(), op.Kpad, whole);
+            const double m = std::ldexp(r.magnitudes, op.halves_exp - op.filter_exp);
+            rows_least[o] = cbk::gemm_halves_least(m, r.small);
+            suits = rows_least[o] <= 2 * cbk::gemm_halves_least(m, 0);
+        }
         bf16_parts(row.data(), op.Kpad, fragments ? parts : 1, part.data(), part.data() + op.Kpad, part.data() + 2 * (size_t)op.Kpad);
         if (!fragments) {
             memcpy(b + (size_t)o * op.Kpad, part.data(), (size_t)op.Kpad * 2);

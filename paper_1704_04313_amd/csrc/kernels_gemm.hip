@@ -2260,7 +2260,10 @@ bool gemm_filter_halves(const GemmArgs &a, int grid)
 
 size_t gemm_halves_bytes(int Mpad, int Kpad) { return (size_t)Mpad * Kpad * 4 + (size_t)Mpad * 4; }
 
-float gemm_halves_least(double magnitudes) { return (float)std::ldexp(magnitudes, kHalfBits - 36); }
+float gemm_halves_least(double magnitudes, int small)
+{
+    return (float)std::ldexp(magnitudes + std::ldexp((double)small, kHalfLimit), kHalfBits - 36);
+}
 
 hipError_t gemm_make_halves(hipStream_t st, const void *wt, void *wt_halves, int Mpad, int Kpad, int shift)
 {

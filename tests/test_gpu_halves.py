@@ -207,3 +207,37 @@ def test_halves_are_used(run):
     (ws, _), = make_weights([short], 25)
     with pytest.raises(cb.CBInferError, match="needed"):
         run(short, ws, x[:48], False)
+
+
+@pytest.mark.parametrize("b", [-10, -12, -14, -16, -18, -20, -22, -24, -30])
+def test_rows_of_small_weights(run, b):
+    """Some output channels whose weights are all 2^b of the layer's largest."""
+    L = conv(128, 128, 3, relu=False)
+    (wt, _), = make_weights([L], 26)
+    wt[64:] *= np.float32(2.0 ** b)
+    x = np.maximum(np.random.default_rng(8).standard_normal((128,) + _MAP, dtype=np.float32), 0)
+    _compare(run, L, wt, x, [slice(0, 64), slice(64, 128)])
+
+
+@pytest.mark.parametrize("kind", ["outlier", "one of eight", "one of eight in small rows", "one per row"])
+@pytest.mark.parametrize("b", [-10, -14, -16, -20, -24, -40])
+def test_small_weights_beside_large_ones(run, kind, b):
+    """One weight beside which all others are small; seven of eight consecutive channels with small weights, whose large one meets
+    zeros; the same in rows that are small themselves, and with one large weight per row."""
+    L = conv(128, 128, 3, relu=False)
+    (wt, _), = make_weights([L], 27)
+    x = np.maximum(np.random.default_rng(9).standard_normal((128,) + _MAP, dtype=np.float32), 0)
+    if kind == "outlier":
+        wt[3, 3, 1, 1] = np.float32(2.0 ** -b)
+    elif kind != "one per row":
+        small = np.arange(128) % 8 != 3
+        wt[:, small] *= np.float32(2.0 ** b)
+        wt[:, ~small] = np.copysign(np.float32(0.05), wt[:, ~small])
+        if kind == "one of eight in small rows":
+            wt[4:] *= np.float32(2.0 ** -16)
+        x[~small] = 0
+    else:
+        wt *= np.float32(2.0 ** b)
+        wt[:, 3, 1, 1] = 1
+        x[3] = 0
+    _compare(run, L, wt, x, [slice(0, 3), slice(4, 128)])
