@@ -481,13 +481,13 @@ bool build_filter_matrix(const Op &op, int dtype, const float *w, std::vector<un
             continue;
         }
         if (suits) {
-            // A row keeps the parts (and with it the layer) if its small weights are as much of a reason to form sums again as its
-            // pixels are.  Normally distributed weights, 2^-29 of the largest of which is needed for it, never come near that in
+            // A row keeps the parts (and with it the layer) if a weight is not finite, as all of its sums would be formed again, or if
+            // its small weights are as much of a reason to form sums again as its pixels are.  Normally distributed weights, 2^-29 of the largest of which is needed for it, never come near that in
             // rows that reach 2^-10 of the layer's largest.
             const RowScale r = row_scale(row.data(), op.Kpad, whole);
             const double m = std::ldexp(r.magnitudes, op.halves_exp - op.filter_exp);
             rows_least[o] = cbk::gemm_halves_least(m, r.small);
-            suits = rows_least[o] <= 2 * cbk::gemm_halves_least(m, 0);
+            suits = std::isfinite(m) && rows_least[o] <= 2 * cbk::gemm_halves_least(m, 0);
         }
         bf16_parts(row.data(), op.Kpad, fragments ? parts : 1, part.data(), part.data() + op.Kpad, part.data() + 2 * (size_t)op.Kpad);
         if (!fragments) {

@@ -288,17 +288,18 @@ size_t gemm_filter_bytes(int dtype, int Mpad, int Kpad);
 size_t gemm_filter_fragment(int dtype, int Mpad, int Kpad, int row, int k);
 constexpr int kFilterPartStride = 512;
 // float32 layers of more than 32 channels and long rows, on maps large enough: the same fragments of two float16 each that
-// add up to the weight times 2^halves_exp, to 23 bits where that is 2^kHalvesWhole at least.  Needs dtype, Mpad, Kpad and max_pixels; grid: workgroups at most.
+// add up to the weight times 2^halves_exp, to 23 bits where that is 2^kHalvesWhole at least.  Needs dtype, Mpad, Kpad and
+// max_pixels; grid: workgroups at most.
 bool gemm_filter_halves(const GemmArgs &a, int grid);
 size_t gemm_halves_bytes(int Mpad, int Kpad);
+// ... from the bfloat16 parts of the weights times 2^(halves_exp - shift).
+hipError_t gemm_make_halves(hipStream_t st, const void *wt, void *wt_halves, int Mpad, int Kpad, int shift);
 // Sums in halves whose magnitude is below this are formed again, in units of a weight's halves (2^-halves_exp) times those of a
 // pixel's; of a row's weights, magnitudes: added up, in the former, small: how many are not zero but below 2^kHalvesWhole there.  The
 // halves of values below that are off by 2^-37 at most, and the product of second halves that is left out by as much, so a sum
 // is off by at most 2^-36 times the magnitudes plus, as pixels end at 2^15, 2^-21 for each small weight, whatever the pixels are.
 constexpr int kHalvesWhole = -14;
 float gemm_halves_least(double magnitudes, int small);
-// ... from the bfloat16 parts of the weights times 2^(halves_exp - shift).
-hipError_t gemm_make_halves(hipStream_t st, const void *wt, void *wt_halves, int Mpad, int Kpad, int shift);
 // GemmArgs::tiny_sum for rows of K weights of at most that magnitude.  The parts of a pixel value are off by half the
 // smallest bfloat16 at most, 2^-134, and a sum by 2^-134 K times the largest weight: below 2^24 times that
 // it is less exact than float32, so it is formed again.  (A sum that is exactly zero is taken as it is:

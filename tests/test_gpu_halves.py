@@ -198,11 +198,16 @@ def test_one_tap(run, k2):
 
 
 def test_halves_are_used(run):
-    """Different bits with and without room for the halves; a layer whose length keeps the parts takes no room for them."""
+    """Different bits with and without room for the halves; a layer whose length keeps the parts takes no room for them, one
+    with weights that are not finite leaves it alone."""
     L = conv(128, 128, 3, relu=False)
     (wt, _), = make_weights([L], 24)
     x = np.random.default_rng(7).random((128,) + _MAP, dtype=np.float32)
     assert not np.array_equal(run(L, wt, x), run(L, wt, x, False))
+    for w in (np.inf, -np.inf, np.nan):
+        odd = wt.copy()
+        odd[5, 100, 1, 1] = w
+        np.testing.assert_array_equal(run(L, odd, x), run(L, odd, x, False))
     short = conv(48, 128, 3, relu=False)
     (ws, _), = make_weights([short], 25)
     with pytest.raises(cb.CBInferError, match="needed"):
