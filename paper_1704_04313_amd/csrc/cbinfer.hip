@@ -56,7 +56,8 @@ struct Op {
     unsigned tiny_sum = 0;     // CONV: GemmArgs::tiny_sum, ...
     int filter_exp = 0;        // ... filter_exp
     int halves_exp = 0;        // ... halves_exp ...
-    float halves_least = 0;    // ... and halves_least
+    float halves_least = 0;    // ... halves_least ...
+    int halves_range = 0;      // ... and halves_range
     bool halves = false;       // CONV: the weights are multiplied in halves where sums are long (o_halves exists)
     bool select = false; // CONV: maps small enough for the GEMM (and the pooling after it) to pick their
                          // positions from the update maps themselves; index lists are then only
@@ -101,6 +102,7 @@ cbk::GemmArgs gemm_shape(const Op &op, int streams, int dtype)
     a.dtype = dtype;
     a.M = op.M; a.Mpad = op.Mpad; a.Kpad = op.Kpad;
     a.max_pixels = streams * op.Ho * op.Wo;
+    a.halves_range = op.halves_range;
     return a;
 }
 
@@ -172,6 +174,7 @@ int make_plan(const cbinfer_network *net, float threshold, bool need_threshold, 
             op.Wo = (w + 2 * L.pad - L.kw) / L.stride + 1;
             op.K = L.kh * L.kw * op.Cs;
             op.Kpad = round_up(op.K, cbk::gemm_k_multiple(P.dtype));
+            op.halves_range = cbk::gemm_halves_range(op.Kpad, L.kh * L.kw * op.C);
             // A large camera frame of a float32 network with 1, 2, 3, 5, 6 or 7 channels is stored without
             // padding channels: the detection pass then moves only what the method needs.
             op.pix_words = (l == 0 && cbk::detect_frame_packs(P.dtype, op.C, (long long)P.S * h * w)) ? op.C
@@ -426,38 +429,39 @@ int filter_exponent(float largest, bool tiny)
 }
 
 constexpr int kHalvesTop = 14; // the exponent of the largest weight in halves
-// Of a row of n weights: the sum of their magnitudes, and how many are not zero but below `whole`.
+// Of a row of n weights: the sum of their magnitudes, how many are not zero, and how many of these are below `whole`.
 struct RowScale {
     double magnitudes = 0;
-    int small = 0;
+    int nonzero = 0, small = 0;
 };
 RowScale row_scale(const float *x, int n, float whole)
 {
     constexpr int B = 16; // rows are whole slices of 32
     float sum[B] = {};
-    int small[B] = {}, bound; // bits of magnitudes compare like integers
+    int nonzero[B] = {}, small[B] = {}, bound; // bits of magnitudes compare like integers
     memcpy(&bound, &whole, 4);
     for (int i = 0; i < n; i += B) {
         int u[B];
         memcpy(u, x + i, sizeof u);
         for (int e = 0; e < B; ++e) {
             sum[e] += std::fabs(x[i + e]);
+            nonzero[e] += (u[e] & 0x7fffffff) != 0;
             small[e] += (u[e] & 0x7fffffff) != 0 && (u[e] & 0x7fffffff) < bound;
         }
     }
     RowScale r;
     for (int e = 0; e < B; ++e) {
         r.magnitudes += sum[e];
+        r.nonzero += nonzero[e];
         r.small += small[e];
     }
     return r;
 }
 
 // Filter matrix K (Section 3) re-laid-out for the gather: row o, column k = (j*kw + i)*Cs + c, as
-// float32 or bfloat16 (round to nearest even), row by row or in fragments.  Returns whether its rows suit halves (largest:
-// of the weights); then rows_least holds gemm_halves_least() of each.
-bool build_filter_matrix(const Op &op, int dtype, const float *w, std::vector<unsigned char> &bytes, float largest,
-                         std::vector<float> &rows_least)
+// float32 or bfloat16 (round to nearest even), row by row or in fragments.  Finds out whether its rows suit halves
+// (op.halves) and from which length on (op.halves_range); rows_least: gemm_halves_least() of each.
+void build_filter_matrix(Op &op, int dtype, const float *w, std::vector<unsigned char> &bytes, std::vector<float> &rows_least)
 {
     rows_least.assign(op.Mpad, 0.0f);
     bytes.assign(cbk::gemm_filter_bytes(dtype, op.Mpad, op.Kpad), 0);
@@ -471,7 +475,8 @@ bool build_filter_matrix(const Op &op, int dtype, const float *w, std::vector<un
     const float scale = std::ldexp(1.0f, op.filter_exp);
     for (size_t v = 0; v < place.size(); ++v)
         place[v] = cbk::gemm_filter_fragment(dtype, op.Mpad, op.Kpad, 0, (int)v * eu);
-    bool suits = op.o_halves != SIZE_MAX && largest > 0.0f;
+    bool suits = op.o_halves != SIZE_MAX;
+    int sparsest = op.C * area; // weights that are not zero, of the rows that have any
     const float whole = (float)std::ldexp(1.0, cbk::kHalvesWhole - op.halves_exp + op.filter_exp);
     for (int o = 0; o < op.M; ++o) {
         for (int c = 0; c < op.C; ++c)
@@ -488,6 +493,7 @@ bool build_filter_matrix(const Op &op, int dtype, const float *w, std::vector<un
             const double m = std::ldexp(r.magnitudes, op.halves_exp - op.filter_exp);
             rows_least[o] = cbk::gemm_halves_least(m, r.small);
             suits = std::isfinite(m) && rows_least[o] <= 2 * cbk::gemm_halves_least(m, 0);
+            if (r.nonzero) sparsest = std::min(sparsest, r.nonzero);
         }
         bf16_parts(row.data(), op.Kpad, fragments ? parts : 1, part.data(), part.data() + op.Kpad, part.data() + 2 * (size_t)op.Kpad);
         if (!fragments) {
@@ -504,7 +510,8 @@ bool build_filter_matrix(const Op &op, int dtype, const float *w, std::vector<un
                     memcpy(dst + place[v] + q * cbk::kFilterPartStride, src, 16);
             }
     }
-    return suits;
+    op.halves_range = cbk::gemm_halves_range(op.Kpad, sparsest);
+    op.halves = suits && op.halves_range <= op.Kpad / cbk::gemm_k_multiple(dtype);
 }
 
 // One entry per 16-byte unit of a filter-matrix row: where its tap sits relative to the window origin.
@@ -771,6 +778,7 @@ int enqueue_frame(cbinfer_state *s, const float *frame, float *out)
             a.wt_halves = op.halves ? s->at<void>(op.o_halves) : nullptr;
             a.halves_exp = op.halves_exp;
             a.halves_least = op.halves_least;
+            a.halves_range = op.halves_range;
             a.partial = s->at<float>(P.o_partial);
             a.tickets = s->at<int>(P.o_tickets);
             a.grid = op.gemm_grid;
@@ -910,16 +918,14 @@ static cbinfer_state *create_state(const cbinfer_network *net, const Plan &P, ch
             Op &op = s->plan.ops[l];
             if (op.kind != CBINFER_OP_CONV) continue;
             const cbinfer_layer &L = net->layers[l];
-            float largest = 0.0f;
             if (P.dtype == cbk::kF32 && cbk::gemm_filter_in_fragments(P.dtype, op.Mpad, op.Kpad)) {
                 bool tiny = false;
                 const float m = largest_weight(static_cast<const float *>(L.weight), (size_t)op.M * op.C * op.kh * op.kw, tiny);
                 op.tiny_sum = cbk::gemm_tiny_sum(op.K, m);
                 op.filter_exp = filter_exponent(m, tiny);
                 if (m > 0.0f) op.halves_exp = kHalvesTop - std::ilogb(m);
-                largest = m;
             }
-            op.halves = build_filter_matrix(op, P.dtype, static_cast<const float *>(L.weight), wt, largest, rows_least);
+            build_filter_matrix(op, P.dtype, static_cast<const float *>(L.weight), wt, rows_least);
             bias.assign(op.Mpad, 0.0f);
             if (L.bias)
                 for (int o = 0; o < op.M; ++o) bias[o] = L.bias[o];

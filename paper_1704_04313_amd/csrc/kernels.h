@@ -259,6 +259,7 @@ struct GemmArgs {
     int halves_exp;        // ... of the weights times 2^halves_exp, and behind it
                            // gemm_halves_least() for each of the Mpad rows
     float halves_least;    // the largest of these
+    int halves_range;      // used by launches whose ranges of K are that many slices long in the mean (gemm_halves_range)
     float *partial;     // scratch for partial accumulators, gemm_partial_bytes() bytes
     int *tickets;       // gemm_ticket_bytes(grid) bytes, zero before the first launch (each launch
                         // leaves them zero again)
@@ -287,9 +288,12 @@ bool gemm_filter_in_fragments(int dtype, int Mpad, int Kpad);
 size_t gemm_filter_bytes(int dtype, int Mpad, int Kpad);
 size_t gemm_filter_fragment(int dtype, int Mpad, int Kpad, int row, int k);
 constexpr int kFilterPartStride = 512;
+// GemmArgs::halves_range of a layer whose sparsest row has so many weights that are not zero: kHalfRange slices full of them.
+constexpr int kHalfRange = 24;
+inline int gemm_halves_range(int Kpad, int nonzero) { return (int)(((long long)kHalfRange * Kpad + nonzero / 2) / nonzero); }
 // float32 layers of more than 32 channels and long rows, on maps large enough: the same fragments of two float16 each that
-// add up to the weight times 2^halves_exp, to 23 bits where that is 2^kHalvesWhole at least.  Needs dtype, Mpad, Kpad and
-// max_pixels; grid: workgroups at most.
+// add up to the weight times 2^halves_exp, to 23 bits where that is 2^kHalvesWhole at least.  Needs dtype, Mpad, Kpad,
+// max_pixels and halves_range; grid: workgroups at most.
 bool gemm_filter_halves(const GemmArgs &a, int grid);
 size_t gemm_halves_bytes(int Mpad, int Kpad);
 // ... from the bfloat16 parts of the weights times 2^(halves_exp - shift).

@@ -114,18 +114,19 @@ __host__ __device__ inline int small_tile_factor(int dtype, int bm, int nk)
 }
 
 // Whether a launch of that many big tiles (channel tile bm) of nk slices multiplies in halves: where the ranges of K that
-// workgroups sum up are kHalfRange slices long in the mean over the tiles.  Halves leave off the last of float32's 24 bits
+// workgroups sum up are `range` slices long in the mean over the tiles.  Halves leave off the last of float32's 24 bits
 // in a quarter of the values and the product of both second halves, 7.0e-8 of a sum whatever its length; the bfloat16 parts
 // are exact but are rounded at the magnitude of the whole sum in every slice, 3.4e-8 sqrt(slices / 2).  Error against 64
-// bits (2-norm, halves / parts): 64->256 7x7 (98 slices) whole 1.43e-7 / 2.62e-7, in three ranges 1.29e-7 / 1.47e-7, in
-// twelve 1.30e-7 / 0.95e-7; 128->128 3x3 (36) whole 1.23e-7 / 1.46e-7; 16->64 7x7 (25) 1.24e-7 / 1.27e-7; 32->60 5x5 (25, half
-// the tiles in ranges of eleven) 1.16e-7 / 1.12e-7; 75 slices in nine ranges 1.22e-7 / 1.10e-7.  So the line is where the
-// errors meet; short ranges are latency, not multiplication (64->256 in twelve 19.1 / 20.4 us, the last 22.4 / 25.0).
-static constexpr int kHalfRange = 22;
-__host__ __device__ inline bool halves_suit(int bm, int tiles, int whole_rounds, int nk, int grid)
+// bits (2-norm, halves / parts, pixels of which half are zero): whole ranges of 20 slices 1.17e-7 / 1.10e-7, 22 1.18e-7 / 1.15e-7,
+// 23 1.20e-7 / 1.20e-7, 24 1.23e-7 / 1.24e-7, 28 1.23e-7 / 1.36e-7, 36 1.20e-7 / 1.51e-7; 16->64 7x7 (24.5, eight sets of
+// weights and pixels) 1.22e-7 / 1.23e-7; 64->256 7x7 (98) 1.43e-7 / 2.62e-7, in three ranges 1.27e-7 / 1.47e-7, in twelve
+// 1.30e-7 / 0.95e-7.  So the line is where the errors meet; short ranges are latency, not multiplication (64->256 in
+// twelve 19.1 / 20.4 us, the last 22.4 / 25.0).  Zero weights round nothing, so ranges are counted in the nonzero weights
+// of the layer's sparsest row (64->256 7x7 with a quarter of them 1.32e-7 / 1.27e-7, with an eighth 1.30e-7 / 0.91e-7).
+__host__ __device__ inline bool halves_suit(int bm, int tiles, int whole_rounds, int nk, int grid, int range)
 {
     // only where the big tile is used at all: gemm_partial_bytes has no room for its partial sums elsewhere
-    if (nk < kHalfRange || tiles < 1 || (long long)tiles * small_tile_factor(kF32, bm, nk) < grid) return false;
+    if (nk < range || tiles < 1 || (long long)tiles * small_tile_factor(kF32, bm, nk) < grid) return false;
     const int rem = tiles - whole_rounds * grid;
     if (rem == 0) return true;
     // as make_schedule cuts them: into equal parts, or evenly over all workgroups, which then cross from tile to tile
@@ -133,7 +134,7 @@ __host__ __device__ inline bool halves_suit(int bm, int tiles, int whole_rounds,
     int parts = grid / rem;
     if (parts > most) parts = most;
     const long long ranges = rem * parts * 8 < grid * 7 && rem * most >= grid ? grid + rem : rem * parts;
-    return (tiles - rem) * (nk * ranges) + (long long)rem * rem * nk >= kHalfRange * ranges * tiles;
+    return (tiles - rem) * (nk * ranges) + (long long)rem * rem * nk >= range * ranges * tiles;
 }
 
 static constexpr int kSelMaxWords = 2048; // largest selection map ranked in-kernel (131072 pixels)
@@ -1851,7 +1852,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu((NT + 255) /
     const int half_tiles = (n + BNH - 1) / BNH * (a.Mpad / BM);
     if (big_tiles * small_tile_factor(kF32, BM, a.dNk.d) < (long long)gridDim.x)
         gemm_gather_body<kF32, BM, BNS, WMS, WNS, SS>(a, n, smem, sel);
-    else if (halves_suit(BM, half_tiles, fast_div(half_tiles, a.dGrid), a.dNk.d, (int)gridDim.x))
+    else if (halves_suit(BM, half_tiles, fast_div(half_tiles, a.dGrid), a.dNk.d, (int)gridDim.x, a.halves_range))
         gemm_gather_body<kF32Halves, BM, BNH, 1, 8, SH>(a, n, smem, sel);
     else
         gemm_gather_body<kF32, BM, BNB, WMB, WNB, SB>(a, n, smem, sel);
@@ -2255,7 +2256,7 @@ bool gemm_filter_halves(const GemmArgs &a, int grid)
     if (a.dtype != kF32 || a.Mpad < 64 || gemm_is_thin(a)) return false;
     const int bm = gemm_channel_tile(a.M);
     const int tiles = (a.max_pixels + 127) / 128 * (a.Mpad / bm);
-    return halves_suit(bm, tiles, tiles / grid, a.Kpad / gemm_k_multiple(kF32), grid);
+    return halves_suit(bm, tiles, tiles / grid, a.Kpad / gemm_k_multiple(kF32), grid, a.halves_range);
 }
 
 size_t gemm_halves_bytes(int Mpad, int Kpad) { return (size_t)Mpad * Kpad * 4 + (size_t)Mpad * 4; }

@@ -149,6 +149,7 @@ def _compare(run, L, wt, x, rows, columns=1):
             errors = [np.linalg.norm((g[s] - want[s])[:, at]) / np.linalg.norm(want[s][:, at]) for g in both]
             # what the parts are held to (test_gpu_float32_parts.py), and the halves like them
             assert max(errors) <= np.sqrt(slices + 8) * 2.0 ** -24, errors
+    return errors
 
 
 _MAP = (181, 190)  # 269 tiles of 128 positions on 256 workgroups
@@ -170,7 +171,7 @@ def test_one_channel_brighter(run, bright, b, weights):
     _compare(run, L, wt, x, [slice(None)])
 
 
-@pytest.mark.parametrize("cin,cout,k,h,w", [(128, 128, 3) + _MAP, (16, 64, 7, 260, 257)])
+@pytest.mark.parametrize("cin,cout,k,h,w", [(256, 128, 3) + _MAP, (64, 64, 5, 260, 257)])
 @pytest.mark.parametrize("k2", [-40, -30, -24, -20, -16, -12, 16, 24, 40])
 def test_two_groups(run, cin, cout, k, h, w, k2):
     """Filters of two groups, each of which sees half of the channels: the second half's values are 2^k2 of the first one's."""
@@ -184,14 +185,14 @@ def test_two_groups(run, cin, cout, k, h, w, k2):
 
 
 @pytest.mark.parametrize("k2", [-16, -20, -30, -40])
-def test_one_tap(run, k2):
-    """Filters of one tap on a map of bright, dim and dark columns: every sum is of one kind only, whatever lies under the other
-    taps; from dark to bright it is two steps, none of which is large."""
-    L = conv(128, 128, 3, relu=False)
+def test_one_column_of_taps(run, k2):
+    """Filters of one column of taps on a map of bright, dim and dark columns: every sum is of one kind only, whatever lies under the
+    other taps; from dark to bright it is two steps, none of which is large."""
+    L = conv(192, 128, 5, relu=False)
     (wt, _), = make_weights([L], 23)
-    keep = np.zeros((3, 3), np.float32)
-    keep[1, 1] = 1
-    x = np.maximum(np.random.default_rng(6).standard_normal((128,) + _MAP, dtype=np.float32), 0)
+    keep = np.zeros((5, 5), np.float32)
+    keep[:, 2] = 1
+    x = np.maximum(np.random.default_rng(6).standard_normal((192,) + _MAP, dtype=np.float32), 0)
     x[:, :, 1::3] *= np.float32(2.0 ** (k2 // 2))
     x[:, :, 0::3] *= np.float32(2.0 ** k2)
     _compare(run, L, wt * keep, x, [slice(None)], columns=3)
@@ -199,7 +200,7 @@ def test_one_tap(run, k2):
 
 def test_halves_are_used(run):
     """Different bits with and without room for the halves; a layer whose length keeps the parts takes no room for them, one
-    with weights that are not finite leaves it alone."""
+    with weights that are not finite or mostly zero leaves it alone."""
     L = conv(128, 128, 3, relu=False)
     (wt, _), = make_weights([L], 24)
     x = np.random.default_rng(7).random((128,) + _MAP, dtype=np.float32)
@@ -208,10 +209,29 @@ def test_halves_are_used(run):
         odd = wt.copy()
         odd[5, 100, 1, 1] = w
         np.testing.assert_array_equal(run(L, odd, x), run(L, odd, x, False))
+    few = wt.copy()
+    few[7, 80:] = 0  # 720 weights of one row
+    np.testing.assert_array_equal(run(L, few, x), run(L, few, x, False))
+    few[7, 80:86] = wt[7, 80:86]  # 774
+    assert not np.array_equal(run(L, few, x[:, :128, :128].repeat(2, 2)), run(L, few, x[:, :128, :128].repeat(2, 2), False))
     short = conv(48, 128, 3, relu=False)
     (ws, _), = make_weights([short], 25)
     with pytest.raises(cb.CBInferError, match="needed"):
         run(short, ws, x[:48], False)
+
+
+@pytest.mark.parametrize("cin,cout,k,h,w", [(768, 128, 1, 128, 256), (768, 64, 1, 128, 256), (16, 64, 7, 256, 256)])
+def test_shortest_ranges(run, cin, cout, k, h, w):
+    """Where halves begin, 24 slices in whole tiles, they are as exact as the parts (within the spread from one set of weights to
+    another, 5 % each way)."""
+    L = conv(cin, cout, k, relu=False)
+    (wt, _), = make_weights([L], 28)
+    x = np.maximum(np.random.default_rng(10).standard_normal((cin, h, w), dtype=np.float32), 0)
+    halves, parts = _compare(run, L, wt, x, [slice(None)])
+    assert halves <= 1.05 * parts
+    shorter = conv(cin * 23 // 24, cout, k, relu=False)
+    with pytest.raises(cb.CBInferError, match="needed"):  # no room that it could do without
+        run(shorter, wt[:, : cin * 23 // 24], x[: cin * 23 // 24], False)
 
 
 @pytest.mark.parametrize("b", [-10, -12, -14, -16, -18, -20, -22, -24, -30])
