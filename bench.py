@@ -140,33 +140,48 @@ def timed_blocks(net, frames_dev, out, n_frames, warmup, steps, blocks):
             for b in range(blocks)]
 
 
-def in_halves(L, positions, workgroups=256):
-    """Whether a float32 launch that recomputes that many positions multiplies in float16 halves (three products a value): layers
-    of more than 32 outputs where the ranges of K that workgroups sum up are 22 slices long in the mean over the tiles."""
-    bm, nk = (64 if L.cout <= 64 else 128), -(-L.kh * L.kw * ((L.cin + 3) // 4) // 8)
-    tiles = -(-int(positions) // 128) * -(-L.cout // bm)
-    if L.cout <= 32 or nk < 22 or tiles < 1 or tiles * (4 if bm == 128 and nk >= 48 else 2) < workgroups:
+def in_halves(L, positions, outputs):
+    """Whether a float32 launch that recomputes that many positions of a map of `outputs` multiplies in float16 halves (three products
+    a value): layers of more than 32 outputs, none of whose weights is zero, where the ranges of K that workgroups sum up are 24
+    slices full of weights long in the mean over the tiles, and would be if the whole map were recomputed."""
+    bm, units = (64 if L.cout <= 64 else 128), L.kh * L.kw * ((L.cin + 3) // 4)
+    nk, weights, mtiles = -(-units // 8), L.kh * L.kw * L.cin, -(-L.cout // bm)
+    if L.cout <= 32:
         return False
-    rem, most = tiles % workgroups, max(nk // 8, 1)
-    if rem == 0:
-        return True
-    parts = min(workgroups // rem, most)
-    uneven = rem * parts * 8 < workgroups * 7 and rem * most >= workgroups
-    ranges = workgroups + rem if uneven else rem * parts
-    return (tiles - rem) * nk * ranges + rem * rem * nk >= 22 * ranges * tiles
+    least = (24 * nk * 32 + weights // 2) // weights
+    wide = 256 if bm == 64 and outputs > 1 << 19 else 128
+    factor = 4 if bm == 128 and nk >= 48 else 2
+    big = -(-outputs // wide) * mtiles
+    tiles = big if big * factor >= 256 else -(-outputs // 64) * mtiles
+    workgroups = 256 if tiles >= 256 else min(256, max(8, (tiles * max(nk // 8, 1) + 7) // 8 * 8))
+
+    def long_ranges(n):
+        tiles = -(-n // 128) * mtiles
+        if nk < least or tiles < 1 or tiles * factor < workgroups:
+            return False
+        rem, most = tiles % workgroups, max(nk // 8, 1)
+        if rem == 0:
+            return True
+        parts = min(workgroups // rem, most)
+        uneven = rem * parts * 8 < workgroups * 7 and rem * most >= workgroups
+        ranges = workgroups + rem if uneven else rem * parts
+        return (tiles - rem) * nk * ranges + rem * rem * nk >= least * ranges * tiles
+
+    n = int(positions)
+    return long_ranges(outputs) and -(-n // wide) * mtiles * factor >= workgroups and long_ranges(n)
 
 
-def matrix_peak(L, bf16, positions=0):
+def matrix_peak(L, bf16, positions=0, outputs=0):
     """Rate in TFLOP/s that bounds a convolution layer's multiplication by the instruction it uses.  float32
     layers of short filter rows (at most 64 units of four channels, 64 outputs, and 32 groups of four units times
     tiles of 16 outputs) run on the float32 instruction, all others on bfloat16 parts or, where a launch's `positions`
-    make for long sums, on float16 halves."""
+    of `outputs` make for long sums, on float16 halves."""
     if bf16:
         return MI355X_BF16_MFMA_TFLOPS
     units = (L.kh * L.kw * ((L.cin + 3) // 4) + 7) // 8 * 8
     tiles = 1 if L.cout <= 16 else 2 if L.cout <= 32 else 4
     short = L.cout <= 64 and units <= 64 and units // 4 * tiles <= 32
-    if not short and in_halves(L, positions):
+    if not short and in_halves(L, positions, outputs):
         return MI355X_BF16_MFMA_TFLOPS / 3
     return MI355X_FP32_TFLOPS if short else MI355X_FP32_PARTS_TFLOPS
 
@@ -229,7 +244,7 @@ def kernel_entries(cfg, net, prof, sums, P, in_shape, propagate=False, detect_wr
                         by += S * (esz + 4.0) * c_last * h_last * w_last
             elif name == "gemm":
                 fl = 2.0 * L.cout * L.cin * L.kh * L.kw * n_u
-                peak = matrix_peak(L, bf16, n_u)
+                peak = matrix_peak(L, bf16, n_u, S * h_out * w_out)
                 e.update(flops=fl, TFLOPs=fl / (ms * 1e-3) / 1e12, peak_TFLOPs=peak, frac_mfma=fl / (ms * 1e-3) / 1e12 / peak)
                 # the least it has to move: the filters, the input values under the updated outputs'
                 # receptive fields (each once, never more than the whole map), a list entry and the

@@ -295,6 +295,8 @@ inline int gemm_halves_range(int Kpad, int nonzero) { return (int)(((long long)k
 // add up to the weight times 2^halves_exp, to 23 bits where that is 2^kHalvesWhole at least.  Needs dtype, Mpad, Kpad,
 // max_pixels and halves_range; grid: workgroups at most.
 bool gemm_filter_halves(const GemmArgs &a, int grid);
+// Whether a launch of such a layer (a.grid workgroups) on a list of n positions takes them.
+bool gemm_takes_halves(const GemmArgs &a, int n);
 size_t gemm_halves_bytes(int Mpad, int Kpad);
 // ... from the bfloat16 parts of the weights times 2^(halves_exp - shift).
 hipError_t gemm_make_halves(hipStream_t st, const void *wt, void *wt_halves, int Mpad, int Kpad, int shift);

@@ -2374,6 +2374,14 @@ int gemm_grid(const GemmArgs &a, int compute_units)
     return (int)(need < W ? need : W);
 }
 
+bool gemm_takes_halves(const GemmArgs &a, int n) // as gemm_halves_kernel
+{
+    const int bm = gemm_channel_tile(a.M), bn = pixel_tile(bm, a.max_pixels, a.dtype), nk = a.Kpad / gemm_k_multiple(kF32), mtiles = a.Mpad / bm;
+    const int half_tiles = (n + 127) / 128 * mtiles;
+    return gemm_filter_halves(a, a.grid) && (long long)((n + bn - 1) / bn) * mtiles * small_tile_factor(kF32, bm, nk) >= a.grid &&
+           halves_suit(bm, half_tiles, half_tiles / a.grid, nk, a.grid, a.halves_range);
+}
+
 // Two slabs of partial sums per workgroup, of the tile shape that the launch uses.  That is the big one only if
 // its tiles of the longest list come to the launch's workgroups / small_tile_factor, which on a map of few
 // positions they do in launches of few workgroups alone.  (Fewer compute units never make for more workgroups.)
