@@ -45,3 +45,32 @@ def test_same_bits_as_on_a_piece(cin, cout, k, stride, h, w, bf16):
         want, size = _sampled(L, *params[0], x, pos)
         # a product and an addition per value, half a unit each
         assert np.all(np.abs(got.reshape(cout, -1)[:, pos] - want) <= (cin * k * k + 2) * 2.0 ** -23 * size)
+
+
+# lists of 196 608 positions and more, ragged ones of them, and short lists by the same kernel; one stream and two; a layer of the
+# same kernel behind the first, which takes its changes from it
+@pytest.mark.parametrize("streams,h,w", [(1, 515, 513), (2, 371, 359)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_lists_give_the_bits_of_dense_frames(streams, h, w, bf16):
+    """With a threshold of zero a frame's output does not depend on what was kept from the frames before it."""
+    layers = [conv(3, 16, 7), conv(16, 16, 3, relu=False)]
+    params = make_weights(layers, 31)
+    r = np.random.default_rng(h)
+    frames = [r.random((streams, 3, h, w), dtype=np.float32)]
+    most = frames[0].copy()
+    most[:, :, : h * 9 // 10] += r.random(most[:, :, : h * 9 // 10].shape, dtype=np.float32)
+    few = most.copy()
+    few[-1, :, h // 2: h // 2 + 3, w // 3: w // 2] += np.float32(0.25)
+    frames += [most, few, frames[0]]
+    dtype = cb.BF16 if bf16 else cb.F32
+    lists, dense = [cb.CBInfer(layers, params, (3, h, w), 0.0, n_streams=streams, dtype=dtype) for _ in range(2)]
+    dense.set_mode(True)
+    for t, f in enumerate(frames):
+        got, want = [net.process_frame(to_dev(f)).cpu().numpy() for net in (lists, dense)]
+        np.testing.assert_array_equal(got, want, err_msg="frame %d" % t)
+        if t == 1:
+            assert 4 * 12 * 256 * 16 <= lists.layer_counts(0)[1] < streams * h * w
+        if t == 2:
+            assert 0 < lists.layer_counts(0)[1] < 4 * 12 * 256 * 16
+    lists.destroy()
+    dense.destroy()
