@@ -149,6 +149,10 @@ def _compare(run, L, wt, x, rows, columns=1):
             errors = [np.linalg.norm((g[s] - want[s])[:, at]) / np.linalg.norm(want[s][:, at]) for g in both]
             # what the parts are held to (test_gpu_float32_parts.py), and the halves like them
             assert max(errors) <= np.sqrt(slices + 8) * 2.0 ** -24, errors
+            # Halves: 7.0e-8 for what they leave off, 4.7e-8 for each of four slices relative to their sum (measured for single
+            # instructions), 2^-25 for each time that four are added up, 50 times at most here and half as large in the mean: as
+            # squares 1.6e-7.
+            assert errors[0] <= 2.0 ** -22.5, errors
     return errors
 
 
@@ -232,6 +236,37 @@ def test_shortest_ranges(run, cin, cout, k, h, w):
     shorter = conv(cin * 23 // 24, cout, k, relu=False)
     with pytest.raises(cb.CBInferError, match="needed"):  # no room that it could do without
         run(shorter, wt[:, : cin * 23 // 24], x[: cin * 23 // 24], False)
+
+
+@pytest.mark.parametrize("streams", [1, 2])
+def test_lists_in_front_of_another_layer(streams):
+    """Frames of changes in two layers whose sums are long, each of which flags the next one's: with a threshold of zero they
+    are those of dense frames, up to roundings."""
+    layers = [conv(64, 128, 5), conv(128, 64, 3), conv(64, 8, 1, relu=False)]
+    params = make_weights(layers, 33)
+    r = np.random.default_rng(streams)
+    frames = [np.maximum(r.standard_normal((streams, 64) + _MAP, dtype=np.float32), 0)]
+    most = frames[0].copy()
+    most[:, :, : 170] += r.random(most[:, :, : 170].shape, dtype=np.float32)
+    few = most.copy()
+    few[-1, :, 90:94, 60:80] *= np.float32(2.0 ** -20)
+    frames += [most, few, frames[0]]
+    lists, dense = [cb.CBInfer(layers, params, (64,) + _MAP, 0.0, n_streams=streams) for _ in range(2)]
+    dense.set_mode(True)
+    for t, f in enumerate(frames):
+        lists.process_frame(to_dev(f))
+        dense.process_frame(to_dev(f))
+        for l in range(3):
+            got, want = [net.read_map(l, cb.MAP_OUTPUT).astype(np.float64) for net in (lists, dense)]
+            # each side within what the parts are held to, layer by layer (50, 36 and 4 slices)
+            bound = 2 * sum(np.sqrt(s + 8) for s in (50, 36, 4)[: l + 1]) * 2.0 ** -24
+            assert np.linalg.norm(got - want) <= bound * np.linalg.norm(want), (t, l)
+            # no position is left as it was: 2^-20 of a value that is typical
+            assert np.abs(got - want).max() <= 2.0 ** -18 * np.sqrt((want ** 2).mean()), (t, l)
+        if t == 2:
+            assert 0 < lists.layer_counts(1)[1] < 1000
+    lists.destroy()
+    dense.destroy()
 
 
 @pytest.mark.parametrize("b", [-10, -12, -14, -16, -18, -20, -22, -24, -30])
