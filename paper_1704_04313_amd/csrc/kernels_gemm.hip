@@ -40,12 +40,13 @@
 // registers (3.5 instructions per value) in the shadow of the MFMAs.
 //
 // Layers of more than 32 channels whose workgroups sum up long ranges of K (halves_suit) take float16 halves and three
-// products instead, half the matrix time and two thirds of the filter bytes: 64->256 7x7 on 320x180 382 -> 267 us (347
-// TFLOP/s), on 80x60 50.6 -> 38.7, 256->256 3x3 on 160x120 118 -> 87, 512->512 3x3 on 80x60 114 -> 80; 16->64 7x7 on 640x360 130 ->
-// 116, 64->64 5x5 on 400x300 126 -> 101, 96->64 3x3 on 640x480 172 -> 139; with smaller errors than the parts' there (figures
-// at kHalfRange).  What bounds the 128-channel tile is the matrix rate the card sustains, as above (347 x 3 = 1 041 of 1 120 to
-// 1 340; without the split of pixels, which feeding it halves would save, 385 x 3); the 64-channel one moves 24 KiB into LDS
-// for half the MFMAs and is bound by that.
+// products instead, half the matrix time and two thirds of the filter bytes: 64->256 7x7 on 320x180 407 -> 300 us (308
+// TFLOP/s), on 80x60 50.6 -> 44.1, 256->256 3x3 on 160x120 122 -> 96, 512->512 3x3 on 80x60 117 -> 88; 16->64 7x7 on 640x360 131 ->
+// 120, 64->64 5x5 on 400x300 133 -> 110, 96->64 3x3 on 640x480 181 -> 154; on pixels of one scale with errors no larger than the
+// parts' (figures at kHalfRange), on others by the check of every sum (kHalfBits).  What bounds them is the split of the pixels, 3.5
+// vector instructions a value that add to the MFMAs (one instruction less, without the scale: 5 % faster, and wrong for pixels far
+// below their brightest neighbours), and the card's clock: on 64 streams the matrix unit is busy 48 % of the time in the
+// 128-channel tile, at 1.9 GHz, and 27 % in the 64-channel one, which splits as much for half the MFMAs.
 //
 // Work distribution: one workgroup per compute unit.  Output tiles are dealt out whole as long
 // as every workgroup gets one; the (tiles mod workgroups) left over are cut along K into
@@ -935,7 +936,7 @@ __host__ __device__ inline size_t filter_fragment(int bm, int nk, int row, int k
 // it can have (half a unit of the last place of the first half is then 2^3, 2^15 when lifted); slices until leading sums are folded.
 static constexpr int kHalfTop = 13, kHalfMostShift = 126 - kHalfLift, kHalfLimit = 15, kHalfChunk = 4;
 // Sums that the halves' absolute errors may reach beyond 2^-kHalfBits of are formed again (gemm_halves_least).  That is if all of
-// them have one sign; of either sign, they are a twentieth of it.  Of pixels of one scale it is one sum in several millions: with 2^-18
+// them have one sign; of either sign, they are a fiftieth of it or less.  Of pixels of one scale it is one sum in several millions: with 2^-18
 // and 2^-20 64->256 7x7 on 320x180 takes 288 us, without any 290, with 2^-21 292.
 static constexpr int kHalfBits = 20;
 
@@ -1875,8 +1876,8 @@ static constexpr int kThinGroups = 16;
 static constexpr int kThinChannels = 64;
 static constexpr int kThinMaxWork = 32;     // groups x channel tiles up to which this kernel is used
 // Tiles of 16 positions per wave from which the taps are kept in registers: 3->16 7x7 on 1280x720 (19 a wave) 89 -> 78 us, on
-// 1800x1600 264 -> 225, 256->16 1x1 on 640x480 71.6 -> 69; fewer do not pay for putting them there (320x240, 1.6 a wave:
-// 12.2 either way).
+// 1800x1600 264 -> 225, 256->16 1x1 on 640x480 71.6 -> 69; in bfloat16 49.9 -> 41, 151 -> 124 and 28.9 -> 29.7, 12->16 3x3 there 14.6 ->
+// 13.5; fewer do not pay for putting them there (320x240, 1.6 a wave: 12.2 either way).
 static constexpr int kThinManyFactor = 4;
 static constexpr int kThinWholeFactor = 2; // tiles of 16 positions per wave from which a wave takes all channel tiles
 static constexpr int kThinScratchBytes = (kSelMaxWords + 2 * kSelGuard) * 8;                   // front-end scratch
@@ -2398,7 +2399,8 @@ size_t gemm_partial_bytes(const GemmArgs &a, int compute_units)
 
 // storage type; BM; big tile (BN, WM, WN, ring slices); small tile (the same)
 // float32 with halves: the same, then the tile in halves (BN, ring slices).  Of 64 channels it is 128 pixels on every map:
-// 16->64 7x7 on 1200x1280 613 us, with 256 pixels (26 registers spilled) 737, in parts 701.
+// 16->64 7x7 on 1200x1280 662 us, in parts 773; with 256 pixels 26 registers spilled (737 us where 128 took 613, before a pixel had
+// a scale of its own).
 #define CBK_HALVES(X)                                \
     X(64, 256, 1, 8, 3, 64, 2, 4, 5, 128, 5)         \
     X(64, 128, 1, 8, 4, 64, 2, 4, 5, 128, 5)         \
